@@ -184,37 +184,46 @@ __global__ void k_center_sums(int64_t C, const uint32_t *__restrict__ order, con
     cscan[c] = (int32_t)(key % (uint64_t)n_scans);
 }
 
+// Row e of the tile that holds cluster i (ten component rows), and its id.
+template <class T>
+__device__ __forceinline__ T *tile_at(char *tiles, int64_t i) {
+    return reinterpret_cast<T *>(tiles + (i >> 6) * Tile<T>::BYTES) + (i & 63);
+}
+template <class T>
+__device__ __forceinline__ int32_t *tile_id(char *tiles, int64_t i) {
+    return reinterpret_cast<int32_t *>(tiles + (i >> 6) * Tile<T>::BYTES + Tile<T>::IDS) + (i & 63);
+}
+
 // Scatter centred clusters into the voxel-major wave-interleaved layout.
-__global__ void k_scatter_vox(int64_t C, const int64_t *__restrict__ dst, int64_t c_pad,
-                              const double *__restrict__ cN, const double *__restrict__ cmu,
-                              const double *__restrict__ cS, const int32_t *__restrict__ cscan,
-                              double *__restrict__ vN, double *__restrict__ vmu, double *__restrict__ vS,
-                              int32_t *__restrict__ vpose) {
+__global__ void k_scatter_vox(int64_t C, const int64_t *__restrict__ dst, const double *__restrict__ cN,
+                              const double *__restrict__ cmu, const double *__restrict__ cS,
+                              const int32_t *__restrict__ cscan, char *__restrict__ tiles) {
     int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= C) return;
-    int64_t d = dst[c];
-    vN[d] = cN[c];
-    vpose[d] = cscan[c];
+    const int64_t d = dst[c];
+    double *o = tile_at<double>(tiles, d);
+    o[0] = cN[c];
+    *tile_id<double>(tiles, d) = cscan[c];
 #pragma unroll
-    for (int k = 0; k < 3; k++) vmu[k * c_pad + d] = cmu[3 * c + k];
+    for (int k = 0; k < 3; k++) o[64 * (1 + k)] = cmu[3 * c + k];
 #pragma unroll
-    for (int k = 0; k < 6; k++) vS[k * c_pad + d] = cS[6 * c + k];
+    for (int k = 0; k < 6; k++) o[64 * (4 + k)] = cS[6 * c + k];
 }
 
 // Gather centred clusters into the pose-major layout.
 __global__ void k_gather_pose(int64_t C, const int32_t *__restrict__ order, const int32_t *__restrict__ slot_of,
                               const double *__restrict__ cN, const double *__restrict__ cmu,
-                              const double *__restrict__ cS, double *__restrict__ pN, double *__restrict__ pmu,
-                              double *__restrict__ pS, int32_t *__restrict__ pslot) {
+                              const double *__restrict__ cS, char *__restrict__ tiles) {
     int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= C) return;
     int64_t c = order[q];
-    pN[q] = cN[c];
-    pslot[q] = slot_of[c];
+    double *o = tile_at<double>(tiles, q);
+    o[0] = cN[c];
+    *tile_id<double>(tiles, q) = slot_of[c];
 #pragma unroll
-    for (int k = 0; k < 3; k++) pmu[k * C + q] = cmu[3 * c + k];
+    for (int k = 0; k < 3; k++) o[64 * (1 + k)] = cmu[3 * c + k];
 #pragma unroll
-    for (int k = 0; k < 6; k++) pS[k * C + q] = cS[6 * c + k];
+    for (int k = 0; k < 6; k++) o[64 * (4 + k)] = cS[6 * c + k];
 }
 
 static inline unsigned nblk(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
@@ -239,12 +248,9 @@ __device__ __forceinline__ void ref_frame_f32(const Pose &P0, const double *c, c
 
 // One thread per slot; padding slots get a zero reference (their clusters are
 // never read).  err: 1 = non-finite reference, 2 = a count >= 2^24.
-__global__ void k_vox_ref_f32(int64_t n_slots, const GroupDesc *__restrict__ groups, int64_t c_pad,
-                              const double *__restrict__ vN, const double *__restrict__ vmu,
-                              const double *__restrict__ vS, const int32_t *__restrict__ vpose,
+__global__ void k_vox_ref_f32(int64_t n_slots, const GroupDesc *__restrict__ groups, char *__restrict__ tiles64,
                               const double *__restrict__ ref_poses, double *__restrict__ vref,
-                              float *__restrict__ vN32, float *__restrict__ vmu32, float *__restrict__ vS32,
-                              int32_t *__restrict__ err) {
+                              char *__restrict__ tiles32, int32_t *__restrict__ err) {
     const int64_t sl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (sl >= n_slots) return;
     const GroupDesc g = groups[sl >> 6];
@@ -257,12 +263,13 @@ __global__ void k_vox_ref_f32(int64_t n_slots, const GroupDesc *__restrict__ gro
     double n = 0.0, c[3] = {0.0, 0.0, 0.0};
     for (int k = 0; k < g.m; k++) {
         const int64_t idx = g.cbase + 64LL * k + lane;
+        const double *v = tile_at<double>(tiles64, idx);
         Pose P0;
-        load_pose(ref_poses, vpose[idx], P0);
-        const double mu[3] = {vmu[idx], vmu[c_pad + idx], vmu[2 * c_pad + idx]};
+        load_pose(ref_poses, *tile_id<double>(tiles64, idx), P0);
+        const double mu[3] = {v[64], v[128], v[192]};
         double y[3];
         rot(P0.r, mu, y);
-        const double nk = vN[idx];
+        const double nk = v[0];
         n += nk;
 #pragma unroll
         for (int q = 0; q < 3; q++) c[q] = fma(nk, y[q] + P0.t[q], c[q]);
@@ -274,21 +281,25 @@ __global__ void k_vox_ref_f32(int64_t n_slots, const GroupDesc *__restrict__ gro
     ref[0] = c[0]; ref[1] = c[1]; ref[2] = c[2]; ref[3] = 0.0;
     for (int k = 0; k < g.m; k++) {
         const int64_t idx = g.cbase + 64LL * k + lane;
+        const double *v = tile_at<double>(tiles64, idx);
+        const int32_t j = *tile_id<double>(tiles64, idx);
         Pose P0;
-        load_pose(ref_poses, vpose[idx], P0);
-        const double mu[3] = {vmu[idx], vmu[c_pad + idx], vmu[2 * c_pad + idx]};
+        load_pose(ref_poses, j, P0);
+        const double mu[3] = {v[64], v[128], v[192]};
         double S[6];
 #pragma unroll
-        for (int e = 0; e < 6; e++) S[e] = vS[e * c_pad + idx];
+        for (int e = 0; e < 6; e++) S[e] = v[64 * (4 + e)];
         float m32[3], S32[6];
         ref_frame_f32(P0, c, mu, S, m32, S32);
+        float *o = tile_at<float>(tiles32, idx);
 #pragma unroll
-        for (int e = 0; e < 3; e++) vmu32[e * c_pad + idx] = m32[e];
+        for (int e = 0; e < 3; e++) o[64 * (1 + e)] = m32[e];
 #pragma unroll
-        for (int e = 0; e < 6; e++) vS32[e * c_pad + idx] = S32[e];
-        const double nk = vN[idx];
+        for (int e = 0; e < 6; e++) o[64 * (4 + e)] = S32[e];
+        const double nk = v[0];
         if (nk >= 16777216.0) bad |= 2;
-        vN32[idx] = (float)nk;
+        o[0] = (float)nk;
+        *tile_id<float>(tiles32, idx) = j;
     }
     if (bad) atomicOr(err, bad);
 }
@@ -298,8 +309,7 @@ __global__ void k_gather_pose_f32(int64_t C, const int32_t *__restrict__ order, 
                                   const int32_t *__restrict__ cscan, const double *__restrict__ cN,
                                   const double *__restrict__ cmu, const double *__restrict__ cS,
                                   const double *__restrict__ vref, const double *__restrict__ ref_poses,
-                                  float *__restrict__ pN, float *__restrict__ pmu, float *__restrict__ pS,
-                                  int32_t *__restrict__ pslot) {
+                                  char *__restrict__ tiles) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= C) return;
     const int64_t c = order[q];
@@ -312,12 +322,13 @@ __global__ void k_gather_pose_f32(int64_t C, const int32_t *__restrict__ order, 
     for (int k = 0; k < 6; k++) S[k] = cS[6 * c + k];
     float m32[3], S32[6];
     ref_frame_f32(P0, vref + 4LL * sl, mu, S, m32, S32);
+    float *o = tile_at<float>(tiles, q);
 #pragma unroll
-    for (int k = 0; k < 3; k++) pmu[k * C + q] = m32[k];
+    for (int k = 0; k < 3; k++) o[64 * (1 + k)] = m32[k];
 #pragma unroll
-    for (int k = 0; k < 6; k++) pS[k * C + q] = S32[k];
-    pN[q] = (float)cN[c];
-    pslot[q] = sl;
+    for (int k = 0; k < 6; k++) o[64 * (4 + k)] = S32[k];
+    o[0] = (float)cN[c];
+    *tile_id<float>(tiles, q) = sl;
 }
 
 __global__ void k_validate_poses(int64_t n, const double *__restrict__ poses, int32_t *__restrict__ err) {
@@ -536,11 +547,9 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &cvox, const s
     // voxel-major copy is a build temporary and no FP64 pose-major copy exists
     const bool f32 = P->prec == BA_PREC_F32;
     DevArena f64tmp;
-    DevArena &iter = f32 ? f64tmp : keep;
-    BA_TRY(iter.alloc(&P->v_mu, 3 * CP));
-    BA_TRY(iter.alloc(&P->v_S, 6 * CP));
-    BA_TRY(iter.alloc(&P->v_N, CP));
-    BA_TRY(keep.alloc(&P->v_pose, CP));
+    char *v64 = nullptr;
+    const int64_t vt = tiles_of(CP), pt = tiles_of(C);
+    BA_TRY((f32 ? f64tmp : keep).alloc(&v64, vt * Tile<double>::BYTES));
     BA_TRY(keep.alloc(&P->groups, std::max<int64_t>(P->n_groups, 1)));
     BA_TRY(keep.alloc(&P->vblocks, std::max<int64_t>(P->n_vblocks, 1)));
     BA_TRY(keep.alloc(&P->vblocks_mix, std::max<int64_t>(P->n_vblocks_mix, 1)));
@@ -548,20 +557,14 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &cvox, const s
     BA_TRY(keep.alloc(&P->vstate, 2 * std::max<int64_t>(NS, 1) * VSTATE));
     BA_TRY(keep.alloc(&P->wave_cost, std::max<int64_t>(P->n_groups, 1)));
     if (f32) {
-        BA_TRY(keep.alloc(&P->v_mu32, 3 * CP));
-        BA_TRY(keep.alloc(&P->v_S32, 6 * CP));
-        BA_TRY(keep.alloc(&P->v_N32, CP));
-        BA_TRY(keep.alloc(&P->p_mu32, 3 * C));
-        BA_TRY(keep.alloc(&P->p_S32, 6 * C));
-        BA_TRY(keep.alloc(&P->p_N32, C));
+        BA_TRY(keep.alloc(&P->v_tiles, vt * Tile<float>::BYTES));
+        BA_TRY(keep.alloc(&P->p_tiles, pt * Tile<float>::BYTES));
         BA_TRY(keep.alloc(&P->v_ref, 4 * std::max<int64_t>(NS, 1)));
         BA_TRY(keep.alloc(&P->pdelta, 16LL * N));
     } else {
-        BA_TRY(keep.alloc(&P->p_mu, 3 * C));
-        BA_TRY(keep.alloc(&P->p_S, 6 * C));
-        BA_TRY(keep.alloc(&P->p_N, C));
+        P->v_tiles = v64;
+        BA_TRY(keep.alloc(&P->p_tiles, pt * Tile<double>::BYTES));
     }
-    BA_TRY(keep.alloc(&P->p_slot, C));
     BA_TRY(keep.alloc(&P->p_cidx, C));
     BA_TRY(keep.alloc(&P->chunks, P->chunk_cap));
     BA_TRY(keep.alloc(&P->chunk_ptr, N + 1));
@@ -579,10 +582,7 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &cvox, const s
     P->h_win_pose_ptr = new int32_t[W + 1];
     std::memcpy(P->h_win_pose_ptr, win_pose_ptr.data(), sizeof(int32_t) * (W + 1));
 
-    BA_HIP(hipMemsetAsync(P->v_mu, 0, sizeof(double) * 3 * CP, s));
-    BA_HIP(hipMemsetAsync(P->v_S, 0, sizeof(double) * 6 * CP, s));
-    BA_HIP(hipMemsetAsync(P->v_N, 0, sizeof(double) * CP, s));
-    BA_HIP(hipMemsetAsync(P->v_pose, 0, sizeof(int32_t) * CP, s));
+    BA_HIP(hipMemsetAsync(v64, 0, vt * Tile<double>::BYTES, s));
     BA_HIP(hipMemsetAsync(P->vstate, 0, sizeof(double) * 2 * std::max<int64_t>(NS, 1) * VSTATE, s));
     BA_HIP(hipMemcpyAsync(P->groups, groups.data(), sizeof(GroupDesc) * groups.size(), hipMemcpyHostToDevice, s));
     BA_HIP(hipMemcpyAsync(P->vblocks, vblocks.data(), sizeof(VoxBlock) * vblocks.size(), hipMemcpyHostToDevice, s));
@@ -608,29 +608,26 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &cvox, const s
     BA_HIP(hipMemcpyAsync(d_slot_of, slot_of.data(), sizeof(int32_t) * C, hipMemcpyHostToDevice, s));
     BA_HIP(hipMemcpyAsync(d_porder, porder.data(), sizeof(int32_t) * C, hipMemcpyHostToDevice, s));
     BA_HIP(hipMemcpyAsync(P->p_cidx, porder.data(), sizeof(int32_t) * C, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_scatter_vox, dim3(nblk(C)), dim3(256), 0, s, C, d_dst, CP, P->c_N, P->c_mu, P->c_S,
-                       P->c_scan, P->v_N, P->v_mu, P->v_S, P->v_pose);
+    hipLaunchKernelGGL(k_scatter_vox, dim3(nblk(C)), dim3(256), 0, s, C, d_dst, P->c_N, P->c_mu, P->c_S,
+                       P->c_scan, v64);
     if (!f32) {
         hipLaunchKernelGGL(k_gather_pose, dim3(nblk(C)), dim3(256), 0, s, C, d_porder, d_slot_of, P->c_N, P->c_mu,
-                           P->c_S, P->p_N, P->p_mu, P->p_S, P->p_slot);
+                           P->c_S, P->p_tiles);
         BA_HIP(hipGetLastError());
         BA_HIP(hipStreamSynchronize(s));
         return BA_OK;
     }
     BA_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
-    BA_HIP(hipMemsetAsync(P->v_mu32, 0, sizeof(float) * 3 * CP, s));
-    BA_HIP(hipMemsetAsync(P->v_S32, 0, sizeof(float) * 6 * CP, s));
-    BA_HIP(hipMemsetAsync(P->v_N32, 0, sizeof(float) * CP, s));
+    BA_HIP(hipMemsetAsync(P->v_tiles, 0, vt * Tile<float>::BYTES, s));
     if (NS > 0)
-        hipLaunchKernelGGL(k_vox_ref_f32, dim3(nblk(NS)), dim3(256), 0, s, NS, P->groups, CP, P->v_N, P->v_mu, P->v_S,
-                           P->v_pose, P->ref_poses, P->v_ref, P->v_N32, P->v_mu32, P->v_S32, d_err);
+        hipLaunchKernelGGL(k_vox_ref_f32, dim3(nblk(NS)), dim3(256), 0, s, NS, P->groups, v64, P->ref_poses,
+                           P->v_ref, P->v_tiles, d_err);
     hipLaunchKernelGGL(k_gather_pose_f32, dim3(nblk(C)), dim3(256), 0, s, C, d_porder, d_slot_of, P->c_scan,
-                       P->c_N, P->c_mu, P->c_S, P->v_ref, P->ref_poses, P->p_N32, P->p_mu32, P->p_S32, P->p_slot);
+                       P->c_N, P->c_mu, P->c_S, P->v_ref, P->ref_poses, P->p_tiles);
     BA_HIP(hipGetLastError());
     int32_t herr = 0;
     BA_HIP(hipMemcpyAsync(&herr, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     BA_HIP(hipStreamSynchronize(s));
-    P->v_mu = P->v_S = P->v_N = nullptr;   // released with f64tmp
     if (herr & 2) {
         set_error("precision form: a cluster holds 2^24 points or more (its count is not exact in FP32)");
         return BA_E_UNSUPPORTED;

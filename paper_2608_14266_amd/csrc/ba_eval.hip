@@ -53,16 +53,28 @@ struct VoxSums {
 // S' = R0 S R0^T, in the world frame of the scan's reference pose T0 and
 // relative to the voxel's reference point c_i (`ref`, per slot).
 struct SrcF64 {
-    const double *N, *mu, *S;
+    using T = double;
+    const char *tiles;
 };
 struct SrcF32 {
-    const float *N, *mu, *S;
+    using T = float;
+    const char *tiles;
     const double *ref_poses;   // [n_poses][12]
     const double *ref;         // [slots][4]
     const double *pdelta;      // [n_poses][16] pose changes of the evaluated poses: E (9), w (3) (residual pass)
     const int32_t *cidx;       // [C] (voxel, scan)-order index of each pose-major cluster
     double *h;                 // [C][6] coupled pair vectors, written when not null
 };
+
+// Cluster i of a copy: component e at c[64 e] (N, mu, S), and its id.
+template <class T>
+__device__ __forceinline__ const T *tile_at(const char *tiles, int64_t i) {
+    return reinterpret_cast<const T *>(tiles + (i >> 6) * Tile<T>::BYTES) + (i & 63);
+}
+template <class T>
+__device__ __forceinline__ int32_t tile_id(const char *tiles, int64_t i) {
+    return reinterpret_cast<const int32_t *>(tiles + (i >> 6) * Tile<T>::BYTES + Tile<T>::IDS)[i & 63];
+}
 
 // Pose change of every scan for the precision form's residual pass:
 // E = R R0^T - I and w = dt - E t0 with dt = t - t0 (one thread per pose),
@@ -144,31 +156,32 @@ __device__ __forceinline__ void vox_stage(const GroupDesc *__restrict__ groups, 
 // FP64: the reference is the centroid of the lane's first cluster.  srow:
 // the group's staged scan rows in LDS, or null (gathers from `poses`).
 __device__ __forceinline__ void vox_accumulate(const GroupDesc &g, int64_t slot, int lane, int k0, int kstep,
-                                               int64_t c_pad, const SrcF64 &src, const int32_t *__restrict__ vpose,
-                                               const double *__restrict__ poses, const double *__restrict__ srow,
+                                               const SrcF64 &src, const double *__restrict__ poses, const double *__restrict__ srow,
                                                VoxSums &a) {
     vox_zero(a);
     {
         const int64_t idx = g.cbase + lane;
-        const double mu[3] = {src.mu[idx], src.mu[c_pad + idx], src.mu[2 * c_pad + idx]};
+        const double *cl = tile_at<double>(src.tiles, idx);
+        const double mu[3] = {cl[64], cl[128], cl[192]};
         Pose P;
-        load_pose(poses, vpose[idx], P);
+        load_pose(poses, tile_id<double>(src.tiles, idx), P);
         rot(P.r, mu, a.r);
         a.r[0] += P.t[0]; a.r[1] += P.t[1]; a.r[2] += P.t[2];
     }
     // the scan id of the next cluster is loaded one iteration ahead, so the
     // pose gather does not wait for a dependent round trip
-    int j_next = (k0 < g.m) ? vpose[g.cbase + 64LL * k0 + lane] : 0;
+    int j_next = (k0 < g.m) ? tile_id<double>(src.tiles, g.cbase + 64LL * k0 + lane) : 0;
 #pragma unroll 2
     for (int k = k0; k < g.m; k += kstep) {
         const int64_t idx = g.cbase + 64LL * k + lane;
         const int j = j_next;
-        if (k + kstep < g.m) j_next = vpose[idx + 64LL * kstep];
-        const double nk = src.N[idx];
-        const double mu[3] = {src.mu[idx], src.mu[c_pad + idx], src.mu[2 * c_pad + idx]};
+        if (k + kstep < g.m) j_next = tile_id<double>(src.tiles, idx + 64LL * kstep);
+        const double *cl = tile_at<double>(src.tiles, idx);
+        const double nk = cl[0];
+        const double mu[3] = {cl[64], cl[128], cl[192]};
         double S[6];
 #pragma unroll
-        for (int q = 0; q < 6; q++) S[q] = src.S[q * c_pad + idx];
+        for (int q = 0; q < 6; q++) S[q] = cl[64 * (4 + q)];
         Pose P;
         if (srow) {
             const double *q = srow + VOX_ROW * (j - g.scan0);
@@ -195,23 +208,23 @@ __device__ __forceinline__ void vox_accumulate(const GroupDesc &g, int64_t slot,
 // differences reach 1e-12 relative near convergence, below the noise of any
 // FP32 product here; E c and E t0 round at about 1e-16 |E| |c|.
 __device__ __forceinline__ void vox_accumulate(const GroupDesc &g, int64_t slot, int lane, int k0, int kstep,
-                                               int64_t c_pad, const SrcF32 &src, const int32_t *__restrict__ vpose,
-                                               const double *__restrict__ poses, const double *__restrict__ srow,
+                                               const SrcF32 &src, const double *__restrict__ poses, const double *__restrict__ srow,
                                                VoxSums &a) {
     vox_zero(a);
     const double *c = src.ref + 4 * slot;
     a.r[0] = c[0]; a.r[1] = c[1]; a.r[2] = c[2];
-    int j_next = (k0 < g.m) ? vpose[g.cbase + 64LL * k0 + lane] : 0;
+    int j_next = (k0 < g.m) ? tile_id<float>(src.tiles, g.cbase + 64LL * k0 + lane) : 0;
 #pragma unroll 1
     for (int k = k0; k < g.m; k += kstep) {
         const int64_t idx = g.cbase + 64LL * k + lane;
         const int j = j_next;
-        if (k + kstep < g.m) j_next = vpose[idx + 64LL * kstep];
-        const double nk = (double)src.N[idx];
-        const double mu[3] = {(double)src.mu[idx], (double)src.mu[c_pad + idx], (double)src.mu[2 * c_pad + idx]};
+        if (k + kstep < g.m) j_next = tile_id<float>(src.tiles, idx + 64LL * kstep);
+        const float *cl = tile_at<float>(src.tiles, idx);
+        const double nk = (double)cl[0];
+        const double mu[3] = {(double)cl[64], (double)cl[128], (double)cl[192]};
         double S[6];
 #pragma unroll
-        for (int q = 0; q < 6; q++) S[q] = (double)src.S[q * c_pad + idx];
+        for (int q = 0; q < 6; q++) S[q] = (double)cl[64 * (4 + q)];
         // pose change of scan j, formed once per evaluation (k_pose_delta)
         double E[9], w[3];
         if (srow) {
@@ -271,8 +284,8 @@ __device__ __forceinline__ void store_records(const double *R, double *__restric
 
 template <class Src, int SPLIT>
 __device__ __forceinline__ void vox_item(int bi, const VoxBlock *__restrict__ blocks,
-                                         const GroupDesc *__restrict__ groups, int64_t c_pad, const Src &src,
-                                         const int32_t *__restrict__ vpose, const double *__restrict__ poses,
+                                         const GroupDesc *__restrict__ groups, const Src &src,
+                                         const double *__restrict__ poses,
                                          double *__restrict__ vstate, int64_t n_slots,
                                          const LMState *__restrict__ lm, int trial,
                                          double *__restrict__ group_cost, double (*part)[10][64],
@@ -296,7 +309,7 @@ __device__ __forceinline__ void vox_item(int bi, const VoxBlock *__restrict__ bl
     VoxSums a;
     vox_zero(a);
     if (active && w < g.m)
-        vox_accumulate(g, (int64_t)gi * 64 + lane, lane, w, SPLIT, c_pad, src, vpose, poses, srow, a);
+        vox_accumulate(g, (int64_t)gi * 64 + lane, lane, w, SPLIT, src, poses, srow, a);
     if (SPLIT > 1 && w > 0) {
         double *pp = &part[w - 1][0][0];
         pp[lane] = a.n;
@@ -338,19 +351,18 @@ __device__ __forceinline__ void vox_item(int bi, const VoxBlock *__restrict__ bl
 // which writes back the XCD-private L2.)
 template <class Src, int SPLIT, bool PERSIST>
 __global__ __launch_bounds__(64 * SPLIT) void k_vox(const VoxBlock *__restrict__ blocks, int32_t n_blocks,
-                                                    const GroupDesc *__restrict__ groups, int64_t c_pad, Src src,
-                                                    const int32_t *__restrict__ vpose,
+                                                    const GroupDesc *__restrict__ groups, Src src,
                                                     const double *__restrict__ poses, double *__restrict__ vstate,
                                                     int64_t n_slots, const LMState *__restrict__ lm, int trial,
                                                     double *__restrict__ group_cost) {
     __shared__ double part[SPLIT > 1 ? SPLIT - 1 : 1][10][64];
     __shared__ double rows[VOX_STAGE * VOX_ROW];
     if constexpr (!PERSIST) {
-        vox_item<Src, SPLIT>((int)blockIdx.x, blocks, groups, c_pad, src, vpose, poses, vstate, n_slots, lm, trial,
+        vox_item<Src, SPLIT>((int)blockIdx.x, blocks, groups, src, poses, vstate, n_slots, lm, trial,
                              group_cost, part, rows);
     } else {
         for (int bi = blockIdx.x; bi < n_blocks; bi += gridDim.x) {
-            vox_item<Src, SPLIT>(bi, blocks, groups, c_pad, src, vpose, poses, vstate, n_slots, lm, trial,
+            vox_item<Src, SPLIT>(bi, blocks, groups, src, poses, vstate, n_slots, lm, trial,
                                  group_cost, part, rows);
             __syncthreads();   // part[] and rows[] are reused by the next item
         }
@@ -364,8 +376,7 @@ __global__ __launch_bounds__(64 * SPLIT) void k_vox(const VoxBlock *__restrict__
 // finishes the voxels.  Every wave reaches the one barrier.
 template <class Src, bool PERSIST>
 __global__ __launch_bounds__(256) void k_vox_mixed(const VoxBlock *__restrict__ blocks, int32_t n_blocks,
-                                                   const GroupDesc *__restrict__ groups, int64_t c_pad, Src src,
-                                                   const int32_t *__restrict__ vpose,
+                                                   const GroupDesc *__restrict__ groups, Src src,
                                                    const double *__restrict__ poses, double *__restrict__ vstate,
                                                    int64_t n_slots, const LMState *__restrict__ lm, int trial,
                                                    double *__restrict__ group_cost) {
@@ -394,7 +405,7 @@ __global__ __launch_bounds__(256) void k_vox_mixed(const VoxBlock *__restrict__ 
         VoxSums a;
         vox_zero(a);
         if (active && pt < g.m)
-            vox_accumulate(g, (int64_t)gi * 64 + lane, lane, pt, sp, c_pad, src, vpose, poses, srow, a);
+            vox_accumulate(g, (int64_t)gi * 64 + lane, lane, pt, sp, src, poses, srow, a);
         if (pt > 0) {
             double *pp = &part[w][0][0];
             pp[lane] = a.n;
@@ -497,13 +508,9 @@ struct PoseCtx {
     float E[9];
 };
 
-__device__ __forceinline__ void pose_cluster(const SrcF64 &src, const PoseCtx &cx, int64_t q, int64_t C,
-                                             const double *st, int32_t slot, double *acc) {
-    const double n = src.N[q];
-    const double mu[3] = {src.mu[q], src.mu[C + q], src.mu[2 * C + q]};
-    double S[6];
-#pragma unroll
-    for (int k = 0; k < 6; k++) S[k] = src.S[k * C + q];
+__device__ __forceinline__ void pose_cluster(const PoseCtx &cx, const double *cv, const double *st, double *acc) {
+    const double n = cv[0];
+    const double *mu = cv + 1, *S = cv + 4;
     const double u[3] = {st[0], st[1], st[2]};
     double y[3], St[6];
     rot(cx.P.r, mu, y);
@@ -517,14 +524,11 @@ __device__ __forceinline__ void pose_cluster(const SrcF64 &src, const PoseCtx &c
 // y, the plane offset e = u^T d and the gradient terms in FP64 from the FP32
 // cluster; D(E, S') and the Hessian terms in FP32 (FP64 in the coupled form).
 template <bool HESS64>
-__device__ __forceinline__ void pose_cluster(const SrcF32 &src, const PoseCtx &cx, int64_t q, int64_t C,
-                                             const double *st, int32_t slot, double *acc, float *hacc) {
-    const float n = src.N[q];
-    const double mu[3] = {(double)src.mu[q], (double)src.mu[C + q], (double)src.mu[2 * C + q]};
-    float S[6];
-#pragma unroll
-    for (int k = 0; k < 6; k++) S[k] = src.S[k * C + q];
-    const double *c = src.ref + 4LL * slot;
+__device__ __forceinline__ void pose_cluster(const SrcF32 &src, const PoseCtx &cx, int64_t q, const float *cv,
+                                             const double *st, const double *c, double *acc, float *hacc) {
+    const float n = cv[0];
+    const double mu[3] = {(double)cv[1], (double)cv[2], (double)cv[3]};
+    const float *S = cv + 4;
     const double qv[3] = {c[0] - cx.P0.t[0], c[1] - cx.P0.t[1], c[2] - cx.P0.t[2]};
     // FP64: G mu' = mu' + E mu', the lever arm y = G mu' + G q and the plane
     // offset e = u^T (G mu' + E q + dt + c - mbar)
@@ -608,11 +612,12 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
 // With a persistent grid each wave walks the chunk list with a stride of the
 // number of waves.
 template <class Src, bool PERSIST, bool HESS64>
-__global__ __launch_bounds__(256) void k_pose(const ChunkDesc *__restrict__ chunks, int32_t n_chunks, int64_t C,
-                                              Src src, const int32_t *__restrict__ pslot,
+__global__ __launch_bounds__(256) void k_pose(const ChunkDesc *__restrict__ chunks, int32_t n_chunks, Src src,
                                               const double *__restrict__ poses, const double *__restrict__ vstate,
                                               int64_t n_slots, const int32_t *__restrict__ pose_window,
                                               const LMState *__restrict__ lm, double *__restrict__ partials) {
+    using T = typename Src::T;
+    constexpr bool F32 = sizeof(T) == 4;
     const int lane = threadIdx.x & 63;
     const int n_waves = (int)((gridDim.x * blockDim.x) >> 6);
     const int blk = xcd_block((int)blockIdx.x, (int)gridDim.x);
@@ -627,7 +632,7 @@ __global__ __launch_bounds__(256) void k_pose(const ChunkDesc *__restrict__ chun
         }
         PoseCtx cx;
         load_pose(poses, ch.pose, cx.P);
-        if constexpr (sizeof(*src.N) == 4) {
+        if constexpr (F32) {
             load_pose(src.ref_poses, ch.pose, cx.P0);
             pose_delta(cx.P, cx.P0, cx.D);
 #pragma unroll
@@ -643,16 +648,33 @@ __global__ __launch_bounds__(256) void k_pose(const ChunkDesc *__restrict__ chun
         float hacc[NPART - 6];
 #pragma unroll
         for (int q = 0; q < NPART - 6; q++) hacc[q] = 0.0f;
+        // every lane loads a cluster and its voxel's row, those past the chunk's
+        // end the last one's, so that the loads need no branch and are all in
+        // flight at once
 #pragma unroll 1
-        for (int i = lane; i < ch.count; i += 64) {
-            const int64_t q = ch.start + i;
-            const int32_t slot = pslot[q];
-            if constexpr (sizeof(*src.N) == 4)
-                pose_cluster<HESS64>(src, cx, q, C, vs + (int64_t)slot * VSTATE, slot, acc, hacc);
-            else
-                pose_cluster(src, cx, q, C, vs + (int64_t)slot * VSTATE, slot, acc);
+        for (int i0 = 0; i0 < ch.count; i0 += 64) {
+            const int i = i0 + lane;
+            const int64_t q = ch.start + min(i, ch.count - 1);
+            const int32_t slot = tile_id<T>(src.tiles, q);
+            const T *cl = tile_at<T>(src.tiles, q);
+            T cv[10];
+#pragma unroll
+            for (int e = 0; e < 10; e++) cv[e] = cl[64 * e];
+            double st[VSTATE - 1], c[3];
+#pragma unroll
+            for (int e = 0; e < VSTATE - 1; e++) st[e] = vs[(int64_t)slot * VSTATE + e];
+            if constexpr (F32) {
+#pragma unroll
+                for (int e = 0; e < 3; e++) c[e] = src.ref[4LL * slot + e];
+            }
+            if (i < ch.count) {
+                if constexpr (F32)
+                    pose_cluster<HESS64>(src, cx, q, cv, st, c, acc, hacc);
+                else
+                    pose_cluster(cx, cv, st, acc);
+            }
         }
-        if constexpr (sizeof(*src.N) == 4 && !HESS64) {
+        if constexpr (F32 && !HESS64) {
 #pragma unroll
             for (int q = 0; q < NPART - 6; q++) acc[6 + q] = (double)hacc[q];
         }
@@ -730,11 +752,11 @@ __global__ void k_voxel_eig(int64_t n_slots, const int32_t *__restrict__ slot_vo
 static inline unsigned nblk(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
 static SrcF64 src64(Problem *P, bool vox, bool = false) {
-    return vox ? SrcF64{P->v_N, P->v_mu, P->v_S} : SrcF64{P->p_N, P->p_mu, P->p_S};
+    return SrcF64{vox ? P->v_tiles : P->p_tiles};
 }
 static SrcF32 src32(Problem *P, bool vox, bool hvec = false) {
-    return vox ? SrcF32{P->v_N32, P->v_mu32, P->v_S32, P->ref_poses, P->v_ref, P->pdelta, nullptr, nullptr}
-               : SrcF32{P->p_N32, P->p_mu32, P->p_S32, P->ref_poses, P->v_ref, nullptr, P->p_cidx,
+    return vox ? SrcF32{P->v_tiles, P->ref_poses, P->v_ref, P->pdelta, nullptr, nullptr}
+               : SrcF32{P->p_tiles, P->ref_poses, P->v_ref, nullptr, P->p_cidx,
                         hvec ? dense_hvec(P) : nullptr};
 }
 
@@ -761,11 +783,11 @@ void launch_vox(Problem *P, const double *poses, bool use_lm, bool trial, hipStr
     do {                                                                                                           \
         if (pers)                                                                                                  \
             hipLaunchKernelGGL((k_vox<SRC, SPL, true>), grid, dim3(64 * SPL), 0, s, P->vblocks, P->n_vblocks,      \
-                               P->groups, P->c_pad, MK(P, true), P->v_pose, poses, P->vstate, ns, lm, t,           \
+                               P->groups, MK(P, true), poses, P->vstate, ns, lm, t,           \
                                P->wave_cost);                                                                      \
         else                                                                                                       \
             hipLaunchKernelGGL((k_vox<SRC, SPL, false>), grid, dim3(64 * SPL), 0, s, P->vblocks, P->n_vblocks,     \
-                               P->groups, P->c_pad, MK(P, true), P->v_pose, poses, P->vstate, ns, lm, t,           \
+                               P->groups, MK(P, true), poses, P->vstate, ns, lm, t,           \
                                P->wave_cost);                                                                      \
     } while (0)
 #define BA_VOX_MIX(SRC, MK)                                                                                       \
@@ -773,11 +795,11 @@ void launch_vox(Problem *P, const double *poses, bool use_lm, bool trial, hipStr
         const dim3 gm(pass_grid(P->n_vblocks_mix, 1, P->tune.vox_grid, P->n_cu));                                   \
         if (pers)                                                                                                  \
             hipLaunchKernelGGL((k_vox_mixed<SRC, true>), gm, dim3(256), 0, s, P->vblocks_mix, P->n_vblocks_mix,    \
-                               P->groups, P->c_pad, MK(P, true), P->v_pose, poses, P->vstate, ns, lm, t,           \
+                               P->groups, MK(P, true), poses, P->vstate, ns, lm, t,           \
                                P->wave_cost);                                                                      \
         else                                                                                                       \
             hipLaunchKernelGGL((k_vox_mixed<SRC, false>), gm, dim3(256), 0, s, P->vblocks_mix, P->n_vblocks_mix,   \
-                               P->groups, P->c_pad, MK(P, true), P->v_pose, poses, P->vstate, ns, lm, t,           \
+                               P->groups, MK(P, true), poses, P->vstate, ns, lm, t,           \
                                P->wave_cost);                                                                      \
     } while (0)
     if (P->tune.vox_split == 0) {
@@ -808,8 +830,8 @@ void launch_pose_chunks(Problem *P, const double *poses, bool use_lm, hipStream_
     const dim3 grid(pass_grid(P->n_chunks, 4, P->tune.pose_grid, P->n_cu));
     const bool pers = P->tune.pose_grid > 0;
 #define BA_POSE(SRC, PER, H64, MK)                                                                                 \
-    hipLaunchKernelGGL((k_pose<SRC, PER, H64>), grid, dim3(256), 0, s, P->chunks, P->n_chunks, P->n_clusters,     \
-                       MK(P, false, H64), P->p_slot, poses, P->vstate, ns, P->pose_window, lm, P->partials)
+    hipLaunchKernelGGL((k_pose<SRC, PER, H64>), grid, dim3(256), 0, s, P->chunks, P->n_chunks,                    \
+                       MK(P, false, H64), poses, P->vstate, ns, P->pose_window, lm, P->partials)
     if (P->prec == BA_PREC_F32) {
         if (hess64) {
             if (pers) BA_POSE(SrcF32, true, true, src32);
