@@ -487,6 +487,17 @@ ba_status ba_voxel_map_export(const ba_voxel_map *m, int32_t *voxel, int32_t *sc
 ba_status ba_voxel_map_destroy(ba_voxel_map *m);
 
 /*
+ * Memory kept between calls: builds, voxelizations and destroyed problems and
+ * maps return their device memory to a list that later calls take from (a
+ * release and a new allocation of such sizes cost this driver milliseconds,
+ * at times far more).  At most 1/32 of the device's memory is kept, nothing
+ * while less than 1/8 of it is free, and all of it is returned when an
+ * allocation of the library fails.  This call returns it to the driver now
+ * (e.g. before another library needs the memory).  Any thread.
+ */
+ba_status ba_release_cached_memory(void);
+
+/*
  * Kernel timing (instrumentation, not part of the method): when enabled,
  * later calls record a pair of HIP events on their stream around each launch
  * of the residual kernel ("k_vox"), the derivative kernel ("k_pose"), the

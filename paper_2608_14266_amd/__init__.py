@@ -30,6 +30,7 @@ from ._lib import (  # noqa: F401
     profile_reset,
     problem_get_tuning,
     problem_set_tuning,
+    release_cached_memory,
     request_footprint,
     solve_increment,
     solve_increment_noalloc,

@@ -181,6 +181,8 @@ def load():
     L.ba_voxel_map_export.argtypes = [P, P, P, P, P, P, P, P, P]
     L.ba_voxel_map_destroy.restype = i32
     L.ba_voxel_map_destroy.argtypes = [P]
+    L.ba_release_cached_memory.restype = i32
+    L.ba_release_cached_memory.argtypes = []
     _lib = L
     return L
 
@@ -398,6 +400,12 @@ def iterate(problem: Problem, poses, mode: int = MODE_MM, max_iters: int = 10, m
     _check(load().ba_iterate(problem.handle, _ptr(poses), ct.byref(o), reps, trp, _stream()))
     out = [{k: getattr(r, k) for k, _ in _LMReport._fields_} for r in reps]
     return out, (tr[: int(max_iters)] if trace else None)
+
+
+def release_cached_memory():
+    """ba_release_cached_memory: return the device and pinned memory the library
+    keeps between calls to the driver."""
+    _check(load().ba_release_cached_memory())
 
 
 def profile_enable(on: bool = True):

@@ -309,6 +309,8 @@ ba_status ba_build_clusters_from_sums(const ba_cluster_sums *cs, const ba_build_
 ba_status ba_problem_destroy(ba_problem *p) {
     if (!p) return BA_OK;
     (void)hipDeviceSynchronize();
+    int dev = -1;
+    p->P.mem.drained = hipGetDevice(&dev) == hipSuccess && dev == p->P.device;
     delete p;
     return BA_OK;
 }

@@ -615,6 +615,7 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &cvox, const s
                            P->c_S, P->p_tiles);
         BA_HIP(hipGetLastError());
         BA_HIP(hipStreamSynchronize(s));
+        tmp.drained = true;
         return BA_OK;
     }
     BA_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
@@ -628,6 +629,7 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &cvox, const s
     int32_t herr = 0;
     BA_HIP(hipMemcpyAsync(&herr, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     BA_HIP(hipStreamSynchronize(s));
+    tmp.drained = f64tmp.drained = true;
     if (herr & 2) {
         set_error("precision form: a cluster holds 2^24 points or more (its count is not exact in FP32)");
         return BA_E_UNSUPPORTED;
@@ -685,6 +687,7 @@ static ba_status finish_build(Problem *P, DevArena &keep, const ba_build_options
         int32_t herr = 0;
         BA_HIP(hipMemcpyAsync(&herr, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         BA_HIP(hipStreamSynchronize(s));
+        tmp.drained = true;
         if (herr) {
             set_error("ref_poses holds non-finite values");
             return BA_E_ARG;
@@ -757,7 +760,9 @@ ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, P
     hipLaunchKernelGGL(k_cluster_stats, dim3(nblk(C * 64)), dim3(256), 0, s, C, starts, xs, ys, zs, keys,
                        pts->n_scans, P->c_N, P->c_mu, P->c_S, P->c_vox, P->c_scan);
     BA_HIP(hipGetLastError());
-    return finish_build(P, keep, opt, s);
+    BA_TRY(finish_build(P, keep, opt, s));
+    tmp.drained = true;   // the plan's last step waits for the stream
+    return BA_OK;
 }
 
 ba_status build_from_sums(const ba_cluster_sums *cs, const ba_build_options *opt, Problem *P, DevArena &keep,
@@ -808,7 +813,9 @@ ba_status build_from_sums(const ba_cluster_sums *cs, const ba_build_options *opt
     hipLaunchKernelGGL(k_center_sums, dim3(nblk(n)), dim3(256), 0, s, n, vals, keys, cs->count, cs->sum, cs->sumsq,
                        cs->n_scans, P->c_N, P->c_mu, P->c_S, P->c_vox, P->c_scan);
     BA_HIP(hipGetLastError());
-    return finish_build(P, keep, opt, s);
+    BA_TRY(finish_build(P, keep, opt, s));
+    tmp.drained = true;   // the plan's last step waits for the stream
+    return BA_OK;
 }
 
 }  // namespace ba

@@ -2023,6 +2023,7 @@ struct DenseState {
 static DenseState *dense_state(Problem *P) { return (DenseState *)P->dense_state; }
 
 void dense_release(Problem *P) {
+    if (P->dense_state && P->mem.drained) dense_state(P)->mem.drained = true;
     delete dense_state(P);
     P->dense_state = nullptr;
 }
@@ -2178,6 +2179,7 @@ ba_status dense_prepare(Problem *P) {
         hipLaunchKernelGGL(k_seg_emit, dim3(nblk(E)), dim3(256), 0, s, E, keys, head, bits_b, D->segs);
         hipLaunchKernelGGL(k_seg_count, dim3(nblk(n_seg)), dim3(256), 0, s, n_seg, E, D->segs);
         BA_HIP(hipStreamSynchronize(s));   // before the temporaries go
+        tmp.drained = true;
     } else {
         BA_TRY(D->mem.alloc(&D->segs, 1));
     }

@@ -45,25 +45,43 @@ struct SlotArena {
 };
 extern thread_local SlotArena *tl_slot_arena;
 
+// Blocks kept between calls (ba_mem.hip).
+struct DevBlock {
+    void *p;
+    size_t bytes;
+    int device;
+};
+hipError_t pool_alloc(void **p, size_t nb, size_t *bytes);
+void pool_free(const std::vector<DevBlock> &blocks);
+hipError_t pinned_alloc(void **p, size_t nb, size_t *bytes);
+void pinned_free(void *p, size_t bytes);
+void pool_trim();
+hipError_t stream_take(hipStream_t *s, int device);   // a non-blocking stream of the current device
+void stream_put(hipStream_t s, int device);           // idle
+
 // A set of device allocations released together (memory carved from an
-// installed slot arena is returned by the arena's owner, not here).
+// installed slot arena is returned by the arena's owner, not here).  Small
+// allocations share slabs.  A released block may be taken by any thread and
+// stream at once, so release waits for the device unless the owner has set
+// `drained`: every stream that used the arena has been synchronised.
 struct DevArena {
-    std::vector<void *> ptrs;
+    static constexpr size_t SLAB = (size_t)2 << 20, SMALL = SLAB / 8;
+    std::vector<DevBlock> ptrs;
+    char *slab = nullptr;
+    size_t slab_left = 0;
     size_t bytes = 0;
+    bool drained = false;
     DevArena() = default;
     DevArena(const DevArena &) = delete;
     DevArena &operator=(const DevArena &) = delete;
     ~DevArena() { release(); }
-    void release() {
-        for (void *p : ptrs) (void)hipFree(p);
-        ptrs.clear();
-        bytes = 0;
-    }
+    void release();
+    ba_status alloc_block(void **p, size_t nb);
     template <class T>
     ba_status alloc(T **p, int64_t count) {
-        size_t nb = sizeof(T) * (size_t)(count > 0 ? count : 1);
+        const size_t nb = sizeof(T) * (size_t)(count > 0 ? count : 1);
+        const size_t nba = (nb + 255) / 256 * 256;
         if (SlotArena *a = tl_slot_arena) {
-            const size_t nba = (nb + 255) / 256 * 256;
             if (a->off + nba <= a->cap) {
                 *p = (T *)(a->base + a->off);
                 a->off += nba;
@@ -72,13 +90,18 @@ struct DevArena {
             }
         }
         void *q = nullptr;
-        hipError_t e = hipMalloc(&q, nb);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            set_error("device allocation of %zu bytes failed: %s", nb, hipGetErrorString(e));
-            return BA_E_NOMEM;
+        if (nba <= SMALL) {
+            if (nba > slab_left) {
+                BA_TRY(alloc_block(&q, SLAB));
+                slab = (char *)q;
+                slab_left = SLAB;
+            }
+            q = slab;
+            slab += nba;
+            slab_left -= nba;
+        } else {
+            BA_TRY(alloc_block(&q, nb));
         }
-        ptrs.push_back(q);
         bytes += nb;
         *p = (T *)q;
         return BA_OK;

@@ -199,7 +199,7 @@ static ba_status run_request(Server *S, Request &R, hipStream_t stream, bool &ca
             st = BA_E_HIP;
         }
     }
-    (void)hipStreamSynchronize(stream);
+    in.drained = p->P.mem.drained = hipStreamSynchronize(stream) == hipSuccess && st == BA_OK;
     return st;
 }
 
@@ -372,7 +372,7 @@ static ba_status run_batch(Server *S, std::vector<std::shared_ptr<Request>> &B, 
         }
         left -= o.max_iters;
     }
-    (void)hipStreamSynchronize(stream);
+    in.drained = p->P.mem.drained = hipStreamSynchronize(stream) == hipSuccess;
     return BA_OK;
 }
 
