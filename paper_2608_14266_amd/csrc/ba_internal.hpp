@@ -138,6 +138,7 @@ struct Problem {
     // pose-major copy: tiles of the n_clusters clusters sorted by (scan, slot), with their slots
     char *p_tiles = nullptr;
     int32_t *p_cidx = nullptr;  // [C] (voxel, scan)-order index of each pose-major cluster
+    int64_t *pose_start = nullptr; // [n_poses+1] device copy of h_pose_start
     ChunkDesc *chunks = nullptr;
     int32_t *chunk_ptr = nullptr; // [n_poses+1]
     double *partials = nullptr; // [n_chunks][NPART]
@@ -187,6 +188,11 @@ ba_status build_from_sums(const ba_cluster_sums *cs, const ba_build_options *opt
 // primitives
 size_t scan_workspace_bytes(int64_t n);
 hipError_t exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, int64_t *total, void *ws, hipStream_t s);
+template <class K>
+hipError_t segment_count(const K *keys, int64_t n, int shift, int64_t *total, void *ws, hipStream_t s);
+template <class K>
+hipError_t segment_write(const K *keys, int64_t n, int shift, int64_t n_seg, int64_t *starts, int32_t *ids, void *ws,
+                         hipStream_t s);
 size_t radix_sort_workspace_bytes(int64_t n);
 hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int bits, void *ws, hipStream_t s);
 

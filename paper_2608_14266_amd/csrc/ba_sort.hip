@@ -126,6 +126,89 @@ hipError_t exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, int64_
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- segments
+// Runs of equal (key >> shift) in a sorted key array, without a flag array:
+// the heads are counted per tile from the keys, the tile counts scanned, and
+// a second pass over the keys writes every run's first position (and, if
+// asked for, every element's run number).  Two reads of the keys (16 bytes an
+// element of 8-byte keys) where flags, their scan and the scatter moved 72.
+template <class K>
+__device__ __forceinline__ int seg_heads(const K *__restrict__ keys, int64_t base, int64_t n, int shift, unsigned &bits) {
+    bits = 0;
+    int c = 0;
+    K prev = (base > 0 && base < n) ? keys[base - 1] : K(0);
+#pragma unroll
+    for (int k = 0; k < SCAN_IPT; k++) {
+        const int64_t i = base + k;
+        if (i < n) {
+            const K cur = keys[i];
+            if (i == 0 || (cur >> shift) != (prev >> shift)) {
+                bits |= 1u << k;
+                c++;
+            }
+            prev = cur;
+        }
+    }
+    return c;
+}
+
+template <class K>
+__global__ __launch_bounds__(SCAN_THREADS) void k_seg_reduce(const K *__restrict__ keys, int64_t n, int shift,
+                                                             int64_t *__restrict__ bsum) {
+    __shared__ int64_t lw[SCAN_THREADS / 64];
+    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_IPT;
+    unsigned bits;
+    int64_t tot;
+    block_excl_scan(seg_heads(keys, base, n, shift, bits), lw, tot);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+}
+
+template <class K>
+__global__ __launch_bounds__(SCAN_THREADS) void k_seg_write(const K *__restrict__ keys, int64_t n, int shift,
+                                                            const int64_t *__restrict__ boff, int64_t n_seg,
+                                                            int64_t *__restrict__ starts, int32_t *__restrict__ ids) {
+    __shared__ int64_t lw[SCAN_THREADS / 64];
+    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_IPT;
+    unsigned bits;
+    int64_t tot;
+    const int c = seg_heads(keys, base, n, shift, bits);
+    int64_t r = boff[blockIdx.x] + block_excl_scan(c, lw, tot);
+#pragma unroll
+    for (int k = 0; k < SCAN_IPT; k++) {
+        const int64_t i = base + k;
+        if (i >= n) break;
+        if (bits & (1u << k)) starts[r++] = i;
+        if (ids) ids[i] = (int32_t)(r - 1);
+    }
+    if (base == 0) starts[n_seg] = n;
+}
+
+// total (device) receives the number of runs; ws as for a scan of n values.
+template <class K>
+hipError_t segment_count(const K *keys, int64_t n, int shift, int64_t *total, void *ws, hipStream_t s) {
+    const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
+    hipLaunchKernelGGL(k_seg_reduce<K>, dim3((unsigned)nb), dim3(SCAN_THREADS), 0, s, keys, n, shift, (int64_t *)ws);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_THREADS), 0, s, (int64_t *)ws, nb, total);
+    return hipGetLastError();
+}
+
+// starts[0 .. n_seg] (after segment_count with the same arguments and ws)
+template <class K>
+hipError_t segment_write(const K *keys, int64_t n, int shift, int64_t n_seg, int64_t *starts, int32_t *ids, void *ws,
+                         hipStream_t s) {
+    const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
+    hipLaunchKernelGGL(k_seg_write<K>, dim3((unsigned)nb), dim3(SCAN_THREADS), 0, s, keys, n, shift,
+                       (const int64_t *)ws, n_seg, starts, ids);
+    return hipGetLastError();
+}
+
+template hipError_t segment_count<uint64_t>(const uint64_t *, int64_t, int, int64_t *, void *, hipStream_t);
+template hipError_t segment_write<uint64_t>(const uint64_t *, int64_t, int, int64_t, int64_t *, int32_t *, void *,
+                                            hipStream_t);
+template hipError_t segment_count<int32_t>(const int32_t *, int64_t, int, int64_t *, void *, hipStream_t);
+template hipError_t segment_write<int32_t>(const int32_t *, int64_t, int, int64_t, int64_t *, int32_t *, void *,
+                                           hipStream_t);
+
 // ---------------------------------------------------------------- radix sort
 static constexpr int RS_THREADS = 256;
 static constexpr int RS_WAVES = RS_THREADS / 64;
