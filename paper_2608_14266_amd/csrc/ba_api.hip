@@ -346,9 +346,7 @@ ba_status ba_problem_export_clusters(const ba_problem *p, int32_t *voxel, int32_
     const int64_t C = P.n_clusters;
     if (voxel) BA_HIP(hipMemcpyAsync(voxel, P.c_vox, sizeof(int32_t) * C, hipMemcpyDeviceToDevice, stream));
     if (scan) BA_HIP(hipMemcpyAsync(scan, P.c_scan, sizeof(int32_t) * C, hipMemcpyDeviceToDevice, stream));
-    if (count) BA_HIP(hipMemcpyAsync(count, P.c_N, sizeof(double) * C, hipMemcpyDeviceToDevice, stream));
-    if (mu) BA_HIP(hipMemcpyAsync(mu, P.c_mu, sizeof(double) * 3 * C, hipMemcpyDeviceToDevice, stream));
-    if (S) BA_HIP(hipMemcpyAsync(S, P.c_S, sizeof(double) * 6 * C, hipMemcpyDeviceToDevice, stream));
+    if (count || mu || S) BA_HIP(export_records(&P, count, mu, S, stream));
     return BA_OK;
 }
 

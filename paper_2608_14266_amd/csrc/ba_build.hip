@@ -27,51 +27,74 @@
 namespace ba {
 
 // ---------------------------------------------------------------- kernels
-__global__ void k_validate_points(int64_t n, const double *__restrict__ x, const double *__restrict__ y,
-                                  const double *__restrict__ z, const int32_t *__restrict__ scan,
-                                  const int32_t *__restrict__ voxel, int32_t n_scans, int32_t n_voxels,
-                                  int32_t *__restrict__ err) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+static inline unsigned nblk(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
+
+// Sort keys (voxel << sbits | scan) and what the input's own order lacks:
+// order[0] is set where a scan falls below its predecessor's, order[1] where a
+// key does.  Points in scan order (a log) need a stable sort by voxel alone,
+// and clusters in (voxel, scan) order (a voxel map's export) none.  The blocks
+// walk the list, so that a block stores its findings once: with one atomic per
+// wave on the flag word the 3.99M keys of a city took 171 us instead of 16.
+static constexpr unsigned KEY_BLOCKS = 8192;
+
+struct KeyOrder {
+    bool scans = false, keys = false;
+};
+
+__device__ __forceinline__ void make_key(int64_t i, const int32_t *__restrict__ scan,
+                                         const int32_t *__restrict__ voxel, int sbits, uint64_t *__restrict__ keys,
+                                         KeyOrder &o) {
+    const int32_t sc = scan[i], vx = voxel[i];
+    const uint64_t k = (uint64_t)vx << sbits | (uint64_t)sc;
+    keys[i] = k;
+    if (i > 0) {
+        const int32_t ps = scan[i - 1], pv = voxel[i - 1];
+        o.scans |= sc < ps;
+        o.keys |= k < ((uint64_t)pv << sbits | (uint64_t)ps);
+    }
+}
+
+__device__ __forceinline__ void store_order(const KeyOrder &o, int32_t *__restrict__ order) {
+    const int s = __syncthreads_or(o.scans), k = __syncthreads_or(o.keys);
+    if (threadIdx.x == 0) {
+        if (s) order[0] = 1;
+        if (k) order[1] = 1;
+    }
+}
+
+// Checks and sort key of every point.
+__global__ __launch_bounds__(256) void k_point_keys(int64_t n, const double *__restrict__ x,
+                                                    const double *__restrict__ y, const double *__restrict__ z,
+                                                    const int32_t *__restrict__ scan,
+                                                    const int32_t *__restrict__ voxel, int32_t n_scans,
+                                                    int32_t n_voxels, int sbits, uint64_t *__restrict__ keys,
+                                                    int32_t *__restrict__ err) {
+    KeyOrder o;
     int bad = 0;
-    if (!(isfinite(x[i]) && isfinite(y[i]) && isfinite(z[i]))) bad |= 1;
-    if (scan[i] < 0 || scan[i] >= n_scans) bad |= 2;
-    if (voxel[i] < 0 || voxel[i] >= n_voxels) bad |= 4;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        if (!(isfinite(x[i]) && isfinite(y[i]) && isfinite(z[i]))) bad |= 1;
+        if (scan[i] < 0 || scan[i] >= n_scans) bad |= 2;
+        if (voxel[i] < 0 || voxel[i] >= n_voxels) bad |= 4;
+        make_key(i, scan, voxel, sbits, keys, o);
+    }
     if (bad) atomicOr(err, bad);
+    store_order(o, err + 1);
 }
 
-__global__ void k_make_keys(int64_t n, const int32_t *__restrict__ scan, const int32_t *__restrict__ voxel,
-                            int32_t n_scans, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    keys[i] = (uint64_t)voxel[i] * (uint64_t)n_scans + (uint64_t)scan[i];
-    vals[i] = (uint32_t)i;
+__global__ __launch_bounds__(256) void k_sum_keys(int64_t n, const int32_t *__restrict__ scan,
+                                                  const int32_t *__restrict__ voxel, int sbits,
+                                                  uint64_t *__restrict__ keys, int32_t *__restrict__ order) {
+    KeyOrder o;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        make_key(i, scan, voxel, sbits, keys, o);
+    store_order(o, order);
 }
 
-__global__ void k_head_flags(int64_t n, const uint64_t *__restrict__ keys, int64_t *__restrict__ flags) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    flags[i] = (i == 0 || keys[i] != keys[i - 1]) ? 1 : 0;
-}
-
-// after an exclusive scan of the head flags: starts[cid] = i for every head
-__global__ void k_segment_starts(int64_t n, const uint64_t *__restrict__ keys, const int64_t *__restrict__ excl,
-                                 int64_t *__restrict__ starts, int64_t n_seg) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (i == 0 || keys[i] != keys[i - 1]) starts[excl[i]] = i;
-    if (i == 0) starts[n_seg] = n;
-}
-
-__global__ void k_gather_xyz(int64_t n, const uint32_t *__restrict__ idx, const double *__restrict__ x,
-                             const double *__restrict__ y, const double *__restrict__ z, double *__restrict__ xs,
-                             double *__restrict__ ys, double *__restrict__ zs) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    uint32_t j = idx[i];
-    xs[i] = x[j];
-    ys[i] = y[j];
-    zs[i] = z[j];
+// Sort of the keys by what their order lacks (see k_make_keys).
+static hipError_t sort_keys(SortBuf &b, int64_t n, int vbits, int sbits, const int32_t order[2], hipStream_t s) {
+    if (!order[1]) return radix_sort_pairs(b, n, 0, 0, true, s);
+    if (!order[0]) return radix_sort_pairs(b, n, sbits, vbits, true, s);
+    return radix_sort_pairs(b, n, 0, vbits + sbits, true, s);
 }
 
 __device__ __forceinline__ double dd_div_int(double hi, double lo, double n) {
@@ -80,23 +103,51 @@ __device__ __forceinline__ double dd_div_int(double hi, double lo, double n) {
     return q + r / n;
 }
 
-// One wavefront per cluster: compensated centroid, then centred scatter.
+// One wavefront per cluster: compensated centroid, then centred scatter.  Lane
+// l takes the cluster's points l, l + 64, ... through the sorted index and
+// keeps the first STATS_KEEP of them in registers for the second pass, so a
+// cluster of up to 64 STATS_KEEP points is read once.  Bound by the latency of
+// start -> index -> point with the waves that fit.  199k clusters of 29.6M
+// points: 363 us; 421 us keeping 8 points a lane (5 waves per SIMD instead of
+// 6), 469 us with 16 lanes per cluster, 632 us with a gathered copy of the
+// points in between, read by both passes.
+static constexpr int STATS_KEEP = 4;
 __global__ __launch_bounds__(256) void k_cluster_stats(int64_t C, const int64_t *__restrict__ starts,
-                                                       const double *__restrict__ xs, const double *__restrict__ ys,
-                                                       const double *__restrict__ zs,
-                                                       const uint64_t *__restrict__ skeys, int32_t n_scans,
-                                                       double *__restrict__ cN, double *__restrict__ cmu,
-                                                       double *__restrict__ cS, int32_t *__restrict__ cvox,
+                                                       const uint32_t *__restrict__ idx,
+                                                       const double *__restrict__ x, const double *__restrict__ y,
+                                                       const double *__restrict__ z,
+                                                       const uint64_t *__restrict__ skeys, int sbits,
+                                                       double *__restrict__ crec, int32_t *__restrict__ cvox,
                                                        int32_t *__restrict__ cscan) {
     int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     int lane = threadIdx.x & 63;
     if (c >= C) return;
     int64_t a = starts[c], b = starts[c + 1];
+    const uint64_t key = skeys[a];
+    double px[STATS_KEEP], py[STATS_KEEP], pz[STATS_KEEP];
+#pragma unroll
+    for (int k = 0; k < STATS_KEEP; k++) {
+        const int64_t i = a + 64 * k + lane;
+        if (i < b) {
+            const uint32_t j = idx[i];
+            px[k] = x[j];
+            py[k] = y[j];
+            pz[k] = z[j];
+        }
+    }
     double hx = 0, lx = 0, hy = 0, ly = 0, hz = 0, lz = 0;
-    for (int64_t i = a + lane; i < b; i += 64) {
-        dd_add(hx, lx, xs[i]);
-        dd_add(hy, ly, ys[i]);
-        dd_add(hz, lz, zs[i]);
+#pragma unroll
+    for (int k = 0; k < STATS_KEEP; k++)
+        if (a + 64 * k + lane < b) {
+            dd_add(hx, lx, px[k]);
+            dd_add(hy, ly, py[k]);
+            dd_add(hz, lz, pz[k]);
+        }
+    for (int64_t i = a + 64 * STATS_KEEP + lane; i < b; i += 64) {
+        const uint32_t j = idx[i];
+        dd_add(hx, lx, x[j]);
+        dd_add(hy, ly, y[j]);
+        dd_add(hz, lz, z[j]);
     }
     wave_dd_sum(hx, lx);
     wave_dd_sum(hy, ly);
@@ -104,21 +155,29 @@ __global__ __launch_bounds__(256) void k_cluster_stats(int64_t C, const int64_t 
     double n = (double)(b - a);
     double mx = dd_div_int(hx, lx, n), my = dd_div_int(hy, ly, n), mz = dd_div_int(hz, lz, n);
     double sxx = 0, sxy = 0, sxz = 0, syy = 0, syz = 0, szz = 0;
-    for (int64_t i = a + lane; i < b; i += 64) {
-        double dx = xs[i] - mx, dy = ys[i] - my, dz = zs[i] - mz;
+    auto add = [&](double qx, double qy, double qz) {
+        double dx = qx - mx, dy = qy - my, dz = qz - mz;
         sxx = fma(dx, dx, sxx); sxy = fma(dx, dy, sxy); sxz = fma(dx, dz, sxz);
         syy = fma(dy, dy, syy); syz = fma(dy, dz, syz); szz = fma(dz, dz, szz);
+    };
+#pragma unroll
+    for (int k = 0; k < STATS_KEEP; k++)
+        if (a + 64 * k + lane < b) add(px[k], py[k], pz[k]);
+    for (int64_t i = a + 64 * STATS_KEEP + lane; i < b; i += 64) {
+        const uint32_t j = idx[i];
+        add(x[j], y[j], z[j]);
     }
     sxx = wave_sum(sxx); sxy = wave_sum(sxy); sxz = wave_sum(sxz);
     syy = wave_sum(syy); syz = wave_sum(syz); szz = wave_sum(szz);
     if (lane == 0) {
-        uint64_t key = skeys[a];
-        cN[c] = n;
-        cmu[3 * c + 0] = mx; cmu[3 * c + 1] = my; cmu[3 * c + 2] = mz;
-        cS[6 * c + 0] = sxx; cS[6 * c + 1] = sxy; cS[6 * c + 2] = sxz;
-        cS[6 * c + 3] = syy; cS[6 * c + 4] = syz; cS[6 * c + 5] = szz;
-        cvox[c] = (int32_t)(key / (uint64_t)n_scans);
-        cscan[c] = (int32_t)(key % (uint64_t)n_scans);
+        double2 *o = reinterpret_cast<double2 *>(crec + CREC * c);
+        o[0] = {n, mx};
+        o[1] = {my, mz};
+        o[2] = {sxx, sxy};
+        o[3] = {sxz, syy};
+        o[4] = {syz, szz};
+        cvox[c] = (int32_t)(key >> sbits);
+        cscan[c] = (int32_t)(key & (((uint64_t)1 << sbits) - 1));
     }
 }
 
@@ -155,32 +214,50 @@ __device__ __forceinline__ double centre_entry(double q, double sa, double sb, d
     return s + (e - ql);
 }
 
-__global__ void k_center_sums(int64_t C, const uint32_t *__restrict__ order, const uint64_t *__restrict__ skeys,
-                              const int64_t *__restrict__ count, const double *__restrict__ s1,
-                              const double *__restrict__ s2, int32_t n_scans, double *__restrict__ cN,
-                              double *__restrict__ cmu, double *__restrict__ cS, int32_t *__restrict__ cvox,
-                              int32_t *__restrict__ cscan) {
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    uint32_t j = order[c];
-    double n = (double)count[j];
-    double s[3] = {s1[3 * (int64_t)j], s1[3 * (int64_t)j + 1], s1[3 * (int64_t)j + 2]};
-    for (int k = 0; k < 3; k++) {
-        double q = s[k] / n;
-        double r = fma(-q, n, s[k]);
-        cmu[3 * c + k] = q + r / n;
+// A block centres 256 clusters: their sums come and their records go through
+// LDS in whole lines (thread by thread, the 24- and 48-byte rows in and the
+// 80-byte records out took 192 us for 3.99M clusters; so: 135).
+__global__ __launch_bounds__(256) void k_center_sums(int64_t C, const uint32_t *__restrict__ order,
+                                                     const uint64_t *__restrict__ skeys,
+                                                     const int64_t *__restrict__ count,
+                                                     const double *__restrict__ s1, const double *__restrict__ s2,
+                                                     int sbits, double *__restrict__ crec,
+                                                     int32_t *__restrict__ cvox, int32_t *__restrict__ cscan) {
+    __shared__ __attribute__((aligned(16))) double row[256 * CREC];
+    __shared__ uint32_t from[256];
+    const int64_t c_first = (int64_t)blockIdx.x * 256;
+    const int t = threadIdx.x, nb = (int)min((int64_t)256, C - c_first);
+    if (t < nb) from[t] = order[c_first + t];
+    __syncthreads();
+    for (int e = t; e < 3 * nb; e += 256) row[CREC * (e / 3) + 1 + e % 3] = s1[3 * (int64_t)from[e / 3] + e % 3];
+    for (int e = t; e < 6 * nb; e += 256) row[CREC * (e / 6) + 4 + e % 6] = s2[6 * (int64_t)from[e / 6] + e % 6];
+    __syncthreads();
+    if (t < nb) {
+        const int64_t c = c_first + t;
+        double *v = row + CREC * t;
+        const double n = (double)count[from[t]];
+        const double s[3] = {v[1], v[2], v[3]};
+        const double Q[6] = {v[4], v[5], v[6], v[7], v[8], v[9]};
+        v[0] = n;
+        for (int k = 0; k < 3; k++) {
+            double q = s[k] / n;
+            double r = fma(-q, n, s[k]);
+            v[1 + k] = q + r / n;
+        }
+        v[4] = centre_entry(Q[0], s[0], s[0], n);
+        v[5] = centre_entry(Q[1], s[0], s[1], n);
+        v[6] = centre_entry(Q[2], s[0], s[2], n);
+        v[7] = centre_entry(Q[3], s[1], s[1], n);
+        v[8] = centre_entry(Q[4], s[1], s[2], n);
+        v[9] = centre_entry(Q[5], s[2], s[2], n);
+        const uint64_t key = skeys[c];
+        cvox[c] = (int32_t)(key >> sbits);
+        cscan[c] = (int32_t)(key & (((uint64_t)1 << sbits) - 1));
     }
-    const double *Q = s2 + 6 * (int64_t)j;
-    cS[6 * c + 0] = centre_entry(Q[0], s[0], s[0], n);
-    cS[6 * c + 1] = centre_entry(Q[1], s[0], s[1], n);
-    cS[6 * c + 2] = centre_entry(Q[2], s[0], s[2], n);
-    cS[6 * c + 3] = centre_entry(Q[3], s[1], s[1], n);
-    cS[6 * c + 4] = centre_entry(Q[4], s[1], s[2], n);
-    cS[6 * c + 5] = centre_entry(Q[5], s[2], s[2], n);
-    cN[c] = n;
-    uint64_t key = skeys[c];
-    cvox[c] = (int32_t)(key / (uint64_t)n_scans);
-    cscan[c] = (int32_t)(key % (uint64_t)n_scans);
+    __syncthreads();
+    double2 *o = reinterpret_cast<double2 *>(crec + CREC * c_first);
+    const double2 *r2 = reinterpret_cast<const double2 *>(row);
+    for (int e = t; e < CREC / 2 * nb; e += 256) o[e] = r2[e];
 }
 
 // Row e of the tile that holds cluster i (ten component rows), and its id.
@@ -193,50 +270,87 @@ __device__ __forceinline__ int32_t *tile_id(char *tiles, int64_t i) {
     return reinterpret_cast<int32_t *>(tiles + (i >> 6) * Tile<T>::BYTES + Tile<T>::IDS) + (i & 63);
 }
 
+__device__ __forceinline__ void load_record(const double *__restrict__ crec, int64_t c, double (&v)[CREC]) {
+    const double2 *p = reinterpret_cast<const double2 *>(crec + CREC * c);
+#pragma unroll
+    for (int k = 0; k < CREC / 2; k++) {
+        const double2 d = p[k];
+        v[2 * k] = d.x;
+        v[2 * k + 1] = d.y;
+    }
+}
+
 // Voxel-major copy, one thread per slot: the voxel's clusters lie together in
-// the centred arrays, so a thread reads its rows in turn and the 64 lanes of a
-// group write whole tile rows.  Padding lanes hold zeros.
+// the centred records, so a thread reads its records in turn and the 64 lanes
+// of a group write whole tile rows.  Padding lanes hold zeros.  Bound by the
+// record loads, 64 lines an instruction: five of 16 bytes a record, where ten
+// loads from three arrays took 59 us for 199k clusters (now 32) and, in the
+// FP32 form with two passes over them, 618 us for 3.99M (now 237).
 __global__ __launch_bounds__(256) void k_fill_vox(int64_t n_slots, const GroupDesc *__restrict__ groups,
                                                   const int64_t *__restrict__ slot_start,
-                                                  const double *__restrict__ cN, const double *__restrict__ cmu,
-                                                  const double *__restrict__ cS, const int32_t *__restrict__ cscan,
+                                                  const double *__restrict__ crec, const int32_t *__restrict__ cscan,
                                                   char *__restrict__ tiles) {
     const int64_t sl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (sl >= n_slots) return;
     const GroupDesc g = groups[sl >> 6];
     const int lane = (int)(sl & 63);
     const bool used = lane < g.nvox;
-    const int64_t c0 = used ? slot_start[sl] : 0;
+    const int64_t c0 = slot_start[sl];
+#pragma unroll 2
     for (int k = 0; k < g.m; k++) {
-        const int64_t d = g.cbase + 64LL * k + lane, c = c0 + k;
+        const int64_t d = g.cbase + 64LL * k + lane;
+        double v[CREC];
+#pragma unroll
+        for (int e = 0; e < CREC; e++) v[e] = 0.0;
+        int32_t j = 0;
+        if (used) {
+            load_record(crec, c0 + k, v);
+            j = cscan[c0 + k];
+        }
         double *o = tile_at<double>(tiles, d);
-        o[0] = used ? cN[c] : 0.0;
-        *tile_id<double>(tiles, d) = used ? cscan[c] : 0;
 #pragma unroll
-        for (int e = 0; e < 3; e++) o[64 * (1 + e)] = used ? cmu[3 * c + e] : 0.0;
-#pragma unroll
-        for (int e = 0; e < 6; e++) o[64 * (4 + e)] = used ? cS[6 * c + e] : 0.0;
+        for (int e = 0; e < CREC; e++) o[64 * e] = v[e];
+        *tile_id<double>(tiles, d) = j;
     }
 }
 
 // Gather centred clusters into the pose-major layout.
 __global__ void k_gather_pose(int64_t C, const uint32_t *__restrict__ order, const int32_t *__restrict__ slot_of,
-                              const double *__restrict__ cN, const double *__restrict__ cmu,
-                              const double *__restrict__ cS, char *__restrict__ tiles, int32_t *__restrict__ cidx) {
+                              const double *__restrict__ crec, char *__restrict__ tiles,
+                              int32_t *__restrict__ cidx) {
     int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= C) return;
     int64_t c = order[q];
     cidx[q] = (int32_t)c;
+    double v[CREC];
+    load_record(crec, c, v);
     double *o = tile_at<double>(tiles, q);
-    o[0] = cN[c];
+#pragma unroll
+    for (int e = 0; e < CREC; e++) o[64 * e] = v[e];
     *tile_id<double>(tiles, q) = slot_of[c];
-#pragma unroll
-    for (int k = 0; k < 3; k++) o[64 * (1 + k)] = cmu[3 * c + k];
-#pragma unroll
-    for (int k = 0; k < 6; k++) o[64 * (4 + k)] = cS[6 * c + k];
 }
 
-static inline unsigned nblk(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
+__global__ void k_export_records(int64_t C, const double *__restrict__ crec, double *__restrict__ count,
+                                 double *__restrict__ mu, double *__restrict__ S) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= CREC * C) return;
+    const int64_t c = t / CREC;
+    const int e = (int)(t - CREC * c);
+    const double v = crec[t];
+    if (e == 0) {
+        if (count) count[c] = v;
+    } else if (e < 4) {
+        if (mu) mu[3 * c + e - 1] = v;
+    } else if (S) {
+        S[6 * c + e - 4] = v;
+    }
+}
+
+hipError_t export_records(const Problem *P, double *count, double *mu, double *S, hipStream_t s) {
+    const int64_t C = P->n_clusters;
+    hipLaunchKernelGGL(k_export_records, dim3(nblk(CREC * C)), dim3(256), 0, s, C, P->c_rec, count, mu, S);
+    return hipGetLastError();
+}
 
 // ---------------------------------------------------------------- precision form
 // Reference point of each voxel slot: the FP64 centroid c_i of the voxel's
@@ -259,15 +373,24 @@ __device__ __forceinline__ void ref_frame_f32(const Pose &P0, const double *c, c
 // One thread per slot, as k_fill_vox: the voxel's reference point, then its
 // clusters in the reference frame.  Padding slots get a zero reference and
 // zero clusters.  err: 1 = non-finite reference, 2 = a count >= 2^24.
+// A wave's group observes a short run of scans, whose reference poses it stages
+// in LDS when they are at most FILL_STAGE (they would be half of the loads).
+static constexpr int FILL_STAGE = 32, FILL_KEEP = 8;
 __global__ __launch_bounds__(256) void k_fill_vox_f32(
-    int64_t n_slots, const GroupDesc *__restrict__ groups, const int64_t *__restrict__ slot_start,
-    const double *__restrict__ cN, const double *__restrict__ cmu, const double *__restrict__ cS,
-    const int32_t *__restrict__ cscan, const double *__restrict__ ref_poses, double *__restrict__ vref,
-    char *__restrict__ tiles, int32_t *__restrict__ err) {
-    const int64_t sl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (sl >= n_slots) return;
-    const GroupDesc g = groups[sl >> 6];
-    const int lane = (int)(sl & 63);
+    int32_t n_groups, const GroupDesc *__restrict__ groups, const int64_t *__restrict__ slot_start,
+    const double *__restrict__ crec, const int32_t *__restrict__ cscan, const double *__restrict__ ref_poses,
+    double *__restrict__ vref, char *__restrict__ tiles, int32_t *__restrict__ err) {
+    __shared__ double rows[4][FILL_STAGE * 12];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int32_t gi = (int32_t)(blockIdx.x * 4 + w);
+    const bool has = gi < n_groups;
+    const GroupDesc g = groups[has ? gi : 0];
+    const bool staged = g.nscan <= FILL_STAGE;
+    if (staged)
+        for (int e = lane; e < 12 * g.nscan; e += 64) rows[w][e] = ref_poses[12LL * g.scan0 + e];
+    __syncthreads();
+    if (!has) return;
+    const int64_t sl = 64LL * gi + lane;
     double *ref = vref + 4 * sl;
     if (lane >= g.nvox) {
         ref[0] = ref[1] = ref[2] = ref[3] = 0.0;
@@ -275,52 +398,87 @@ __global__ __launch_bounds__(256) void k_fill_vox_f32(
             const int64_t idx = g.cbase + 64LL * k + lane;
             float *o = tile_at<float>(tiles, idx);
 #pragma unroll
-            for (int e = 0; e < 10; e++) o[64 * e] = 0.0f;
+            for (int e = 0; e < CREC; e++) o[64 * e] = 0.0f;
             *tile_id<float>(tiles, idx) = 0;
         }
         return;
     }
     const int64_t c0 = slot_start[sl];
-    double n = 0.0, c[3] = {0.0, 0.0, 0.0};
-    for (int k = 0; k < g.m; k++) {
-        Pose P0;
-        load_pose(ref_poses, cscan[c0 + k], P0);
-        double y[3];
-        rot(P0.r, cmu + 3 * (c0 + k), y);
-        const double nk = cN[c0 + k];
-        n += nk;
+    auto pose_of = [&](int32_t j, Pose &P0) {
+        if (staged) {
+            const double *q = rows[w] + 12 * (j - g.scan0);
 #pragma unroll
-        for (int q = 0; q < 3; q++) c[q] = fma(nk, y[q] + P0.t[q], c[q]);
+            for (int e = 0; e < 9; e++) P0.r[e] = q[e];
+#pragma unroll
+            for (int e = 0; e < 3; e++) P0.t[e] = q[9 + e];
+        } else {
+            load_pose(ref_poses, j, P0);
+        }
+    };
+    // one pass over the records: the reference point needs every cluster's
+    // placed centroid first, so the first FILL_KEEP of them wait in registers
+    // and only longer voxels read theirs again
+    double n = 0.0, c[3] = {0.0, 0.0, 0.0}, held[FILL_KEEP][3];
+    int bad = 0;
+    auto first = [&](int k, double *p) {
+        const int64_t idx = g.cbase + 64LL * k + lane;
+        const int32_t j = cscan[c0 + k];
+        double v[CREC];
+        load_record(crec, c0 + k, v);
+        Pose P0;
+        pose_of(j, P0);
+        double y[3], St[6];
+        rot(P0.r, v + 1, y);
+        n += v[0];
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            p[q] = y[q] + P0.t[q];
+            c[q] = fma(v[0], p[q], c[q]);
+        }
+        rot_sym(P0.r, v + 4, St);
+        float *o = tile_at<float>(tiles, idx);
+        if (v[0] >= 16777216.0) bad |= 2;
+        o[0] = (float)v[0];
+#pragma unroll
+        for (int e = 0; e < 6; e++) o[64 * (4 + e)] = (float)St[e];
+        *tile_id<float>(tiles, idx) = j;
+    };
+#pragma unroll
+    for (int k = 0; k < FILL_KEEP; k++)
+        if (k < g.m) first(k, held[k]);
+    for (int k = FILL_KEEP; k < g.m; k++) {
+        double p[3];
+        first(k, p);
     }
 #pragma unroll
     for (int q = 0; q < 3; q++) c[q] /= n;
-    int bad = 0;
     if (!(isfinite(c[0]) && isfinite(c[1]) && isfinite(c[2]))) bad |= 1;
     ref[0] = c[0]; ref[1] = c[1]; ref[2] = c[2]; ref[3] = 0.0;
-    for (int k = 0; k < g.m; k++) {
-        const int64_t idx = g.cbase + 64LL * k + lane;
-        const int32_t j = cscan[c0 + k];
+    auto second = [&](int k, const double *p) {
+        float *o = tile_at<float>(tiles, g.cbase + 64LL * k + lane);
+#pragma unroll
+        for (int e = 0; e < 3; e++) o[64 * (1 + e)] = (float)(p[e] - c[e]);
+    };
+#pragma unroll
+    for (int k = 0; k < FILL_KEEP; k++)
+        if (k < g.m) second(k, held[k]);
+    for (int k = FILL_KEEP; k < g.m; k++) {
+        const double2 *p = reinterpret_cast<const double2 *>(crec + CREC * (c0 + k));
+        const double2 p0 = p[0], p1 = p[1];
+        const double mu[3] = {p0.y, p1.x, p1.y};
         Pose P0;
-        load_pose(ref_poses, j, P0);
-        float m32[3], S32[6];
-        ref_frame_f32(P0, c, cmu + 3 * (c0 + k), cS + 6 * (c0 + k), m32, S32);
-        float *o = tile_at<float>(tiles, idx);
-#pragma unroll
-        for (int e = 0; e < 3; e++) o[64 * (1 + e)] = m32[e];
-#pragma unroll
-        for (int e = 0; e < 6; e++) o[64 * (4 + e)] = S32[e];
-        const double nk = cN[c0 + k];
-        if (nk >= 16777216.0) bad |= 2;
-        o[0] = (float)nk;
-        *tile_id<float>(tiles, idx) = j;
+        pose_of(cscan[c0 + k], P0);
+        double y[3];
+        rot(P0.r, mu, y);
+        const double q[3] = {y[0] + P0.t[0], y[1] + P0.t[1], y[2] + P0.t[2]};
+        second(k, q);
     }
     if (bad) atomicOr(err, bad);
 }
 
 // Pose-major FP32 copy in the same reference frames.
-__global__ void k_gather_pose_f32(int64_t C, const uint32_t *__restrict__ order, const int32_t *__restrict__ slot_of,
-                                  const int32_t *__restrict__ cscan, const double *__restrict__ cN,
-                                  const double *__restrict__ cmu, const double *__restrict__ cS,
+__global__ void k_gather_pose_f32(int64_t C, const uint32_t *__restrict__ order, const uint64_t *__restrict__ scan_of,
+                                  const int32_t *__restrict__ slot_of, const double *__restrict__ crec,
                                   const double *__restrict__ vref, const double *__restrict__ ref_poses,
                                   char *__restrict__ tiles, int32_t *__restrict__ cidx) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -328,20 +486,21 @@ __global__ void k_gather_pose_f32(int64_t C, const uint32_t *__restrict__ order,
     const int64_t c = order[q];
     cidx[q] = (int32_t)c;
     const int32_t sl = slot_of[c];
+    double v[CREC];
+    load_record(crec, c, v);
     Pose P0;
-    load_pose(ref_poses, cscan[c], P0);
-    const double mu[3] = {cmu[3 * c], cmu[3 * c + 1], cmu[3 * c + 2]};
-    double S[6];
-#pragma unroll
-    for (int k = 0; k < 6; k++) S[k] = cS[6 * c + k];
+    load_pose(ref_poses, (int)scan_of[q], P0);
+    const double2 *rp = reinterpret_cast<const double2 *>(vref + 4LL * sl);
+    const double2 r0 = rp[0], r1 = rp[1];
+    const double ref[3] = {r0.x, r0.y, r1.x};
     float m32[3], S32[6];
-    ref_frame_f32(P0, vref + 4LL * sl, mu, S, m32, S32);
+    ref_frame_f32(P0, ref, v + 1, v + 4, m32, S32);
     float *o = tile_at<float>(tiles, q);
 #pragma unroll
     for (int k = 0; k < 3; k++) o[64 * (1 + k)] = m32[k];
 #pragma unroll
     for (int k = 0; k < 6; k++) o[64 * (4 + k)] = S32[k];
-    o[0] = (float)cN[c];
+    o[0] = (float)v[0];
     *tile_id<float>(tiles, q) = sl;
 }
 
@@ -350,6 +509,12 @@ __global__ void k_validate_poses(int64_t n, const double *__restrict__ poses, in
     if (i < n && !isfinite(poses[i])) atomicOr(err, 1);
 }
 
+
+static ba_status read_count(int64_t *dst, const int64_t *src, hipStream_t s) {
+    BA_HIP(hipMemcpyAsync(dst, src, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+    BA_HIP(hipStreamSynchronize(s));
+    return BA_OK;
+}
 
 static int bit_length(uint64_t v) {
     int b = 0;
@@ -412,34 +577,34 @@ ba_status replan_chunks(Problem *P, int32_t chunk_len, hipStream_t s) {
 // tables up, the plan took 104 ms of a 107 ms build of 4M clusters, which now
 // takes 2.7 ms.)
 
-// One thread per voxel: the largest cluster count, and the first voxel that
+// The largest cluster count of a voxel (one atomic per block: blocks walk the
+// voxels), and the first voxel that
 // is observed from more than one window (err, or INT32_MAX).
 __global__ __launch_bounds__(256) void k_plan_check(int32_t V, const int64_t *__restrict__ vstart,
                                                     const int32_t *__restrict__ cscan,
                                                     const int32_t *__restrict__ pose_window, int32_t W,
                                                     int32_t *__restrict__ max_m, int32_t *__restrict__ err) {
-    const int32_t v = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
     int32_t m = 0;
-    if (v < V) {
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += (int64_t)gridDim.x * blockDim.x) {
         const int64_t a = vstart[v], b = vstart[v + 1];
-        m = (int32_t)(b - a);
+        m = max(m, (int32_t)(b - a));
         // the scans rise, and so do their windows
-        if (W > 1 && pose_window[cscan[b - 1]] != pose_window[cscan[a]]) atomicMin(err, v);
+        if (W > 1 && pose_window[cscan[b - 1]] != pose_window[cscan[a]]) atomicMin(err, (int32_t)v);
     }
-    m = -wave_min_i(-m);
-    if ((threadIdx.x & 63) == 0) atomicMax(max_m, m);
+    __shared__ int red[4];
+    m = -block_min_i<4>(-m, red);
+    if (threadIdx.x == 0) atomicMax(max_m, m);
 }
 
 // Sort key (window, m, first observing scan) of every voxel.
 __global__ void k_plan_keys(int32_t V, const int64_t *__restrict__ vstart, const int32_t *__restrict__ cscan,
                             const int32_t *__restrict__ pose_window, int mbits, int sbits,
-                            uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
+                            uint64_t *__restrict__ keys) {
     const int32_t v = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
     if (v >= V) return;
     const int64_t a = vstart[v];
     const uint64_t m = (uint64_t)(vstart[v + 1] - a), j = (uint64_t)cscan[a];
     keys[v] = (((uint64_t)pose_window[j] << mbits | m) << sbits) | j;
-    vals[v] = (uint32_t)v;
 }
 
 __global__ void k_run_keys(int64_t R, const int64_t *__restrict__ starts, const uint64_t *__restrict__ keys,
@@ -492,21 +657,28 @@ __global__ __launch_bounds__(256) void k_plan_groups(int32_t G, int32_t R, const
     const int32_t nvox = (int32_t)min((int64_t)64, r.len - v0);
     const int64_t sl = 64LL * gi + lane;
     int32_t s0 = INT32_MAX, s1 = INT32_MAX;   // lowest scan, minus the highest
+    int64_t a = 0;
     if (lane < nvox) {
-        const int64_t a = vstart[order[r.first + v0 + lane]];
+        a = vstart[order[r.first + v0 + lane]];
         s0 = cscan[a];
         s1 = -cscan[a + r.m - 1];
         slot_vox[sl] = cvox[a];
         slot_start[sl] = a;
-        const int64_t u = r.ubase + r.m * (v0 + lane);
-        for (int32_t k = 0; k < r.m; k++) {
-            c_slot[a + k] = (int32_t)sl;
-            keys[u + k] = (uint64_t)cscan[a + k];
-            vals[u + k] = (uint32_t)(a + k);
-        }
     } else {
         slot_vox[sl] = -1;
         slot_start[sl] = 0;
+    }
+    // the group's clusters voxel by voxel, 64 at a time: the list is written in
+    // whole lines and the clusters are read in runs of m
+    const int64_t u = r.ubase + r.m * v0;
+    for (int32_t e0 = 0; e0 < nvox * r.m; e0 += 64) {
+        const int32_t e = e0 + lane, l = min(e / r.m, 63);
+        const int64_t c = __shfl(a, l, BA_WAVE) + (e - l * r.m);
+        if (e < nvox * r.m) {
+            c_slot[c] = 64 * gi + l;
+            keys[u + e] = (uint64_t)cscan[c];
+            vals[u + e] = (uint32_t)c;
+        }
     }
     s0 = wave_min_i(s0);
     s1 = -wave_min_i(s1);
@@ -566,21 +738,7 @@ __global__ void k_pose_starts(int64_t C, int32_t N, const uint64_t *__restrict__
         for (int64_t t = j + 1; t <= N; t++) start[t] = C;
 }
 
-// Sort buffers of the build, at least as long as the cluster list.
-struct BuildWork {
-    uint64_t *keys;
-    uint32_t *vals;
-    char *ws;
-    int64_t *total;   // device: one count
-};
-
-static ba_status read_count(int64_t *dst, const int64_t *src, hipStream_t s) {
-    BA_HIP(hipMemcpyAsync(dst, src, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    BA_HIP(hipStreamSynchronize(s));
-    return BA_OK;
-}
-
-static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, const BuildWork &bw, DevArena &keep,
+static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, SortBuf &bw, DevArena &keep,
                            hipStream_t s) {
     const int64_t C = P->n_clusters;
     const int32_t N = P->n_poses;
@@ -607,10 +765,10 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     int32_t *d_chk;
     BA_TRY(tmp.alloc(&vstart, (int64_t)V + 1));
     BA_TRY(tmp.alloc(&d_chk, 2));
-    BA_HIP(segment_write(P->c_vox, C, 0, (int64_t)V, vstart, (int32_t *)nullptr, bw.ws, s));
+    BA_HIP(segment_write(P->c_vox, C, 0, (int64_t)V, vstart, bw.ws, s));
     int32_t chk[2] = {0, INT32_MAX};   // largest m, first offending voxel
     BA_HIP(hipMemcpyAsync(d_chk, chk, sizeof(chk), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_plan_check, dim3(nblk(V)), dim3(256), 0, s, V, vstart, P->c_scan, P->pose_window, W, d_chk,
+    hipLaunchKernelGGL(k_plan_check, dim3(std::min(nblk(V), 512u)), dim3(256), 0, s, V, vstart, P->c_scan, P->pose_window, W, d_chk,
                        d_chk + 1);
     BA_HIP(hipGetLastError());
     BA_HIP(hipMemcpyAsync(chk, d_chk, sizeof(chk), hipMemcpyDeviceToHost, s));
@@ -630,8 +788,8 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     // then its runs of one window and one m
     const int sbits = bit_length((uint64_t)(N - 1)), mbits = bit_length((uint64_t)P->max_m);
     hipLaunchKernelGGL(k_plan_keys, dim3(nblk(V)), dim3(256), 0, s, V, vstart, P->c_scan, P->pose_window, mbits,
-                       sbits, bw.keys, bw.vals);
-    BA_HIP(radix_sort_pairs(bw.keys, bw.vals, V, sbits + mbits + bit_length((uint64_t)(W - 1)), bw.ws, s));
+                       sbits, bw.keys);
+    BA_HIP(radix_sort_pairs(bw, V, 0, sbits + mbits + bit_length((uint64_t)(W - 1)), true, s));
     int64_t R = 0;
     BA_HIP(segment_count((const uint64_t *)bw.keys, (int64_t)V, sbits, bw.total, bw.ws, s));
     BA_TRY(read_count(&R, bw.total, s));
@@ -643,7 +801,7 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     BA_TRY(tmp.alloc(&d_rk, R));
     BA_TRY(tmp.alloc(&order, V));
     BA_TRY(tmp.alloc(&d_runs, R));
-    BA_HIP(segment_write((const uint64_t *)bw.keys, (int64_t)V, sbits, R, d_rs, (int32_t *)nullptr, bw.ws, s));
+    BA_HIP(segment_write((const uint64_t *)bw.keys, (int64_t)V, sbits, R, d_rs, bw.ws, s));
     hipLaunchKernelGGL(k_run_keys, dim3(nblk(R)), dim3(256), 0, s, R, d_rs, bw.keys, sbits, d_rk);
     BA_HIP(hipGetLastError());
     BA_HIP(hipMemcpyAsync(order, bw.vals, sizeof(uint32_t) * V, hipMemcpyDeviceToDevice, s));
@@ -737,17 +895,17 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     hipLaunchKernelGGL(k_plan_mix, dim3(nblk(n_mix)), dim3(256), 0, s, n_mix, W, d_mix, P->vblocks_mix);
     // pose-major order (scan, slot): a stable sort by scan of that list (a
     // voxel's clusters have distinct scans)
-    BA_HIP(radix_sort_pairs(bw.keys, bw.vals, C, sbits, bw.ws, s));
+    BA_HIP(radix_sort_pairs(bw, C, 0, sbits, false, s));
     hipLaunchKernelGGL(k_pose_starts, dim3(nblk(C)), dim3(256), 0, s, C, N, bw.keys, P->pose_start);
     BA_HIP(hipGetLastError());
     P->h_pose_start.resize(N + 1);
     BA_HIP(hipMemcpyAsync(P->h_pose_start.data(), P->pose_start, sizeof(int64_t) * (N + 1), hipMemcpyDeviceToHost, s));
     // the two copies of the clusters
     if (!f32) {
-        hipLaunchKernelGGL(k_fill_vox, dim3(nblk(NS)), dim3(256), 0, s, NS, P->groups, slot_start, P->c_N, P->c_mu,
-                           P->c_S, P->c_scan, P->v_tiles);
-        hipLaunchKernelGGL(k_gather_pose, dim3(nblk(C)), dim3(256), 0, s, C, bw.vals, P->c_slot, P->c_N, P->c_mu,
-                           P->c_S, P->p_tiles, P->p_cidx);
+        hipLaunchKernelGGL(k_fill_vox, dim3(nblk(NS)), dim3(256), 0, s, NS, P->groups, slot_start, P->c_rec,
+                           P->c_scan, P->v_tiles);
+        hipLaunchKernelGGL(k_gather_pose, dim3(nblk(C)), dim3(256), 0, s, C, bw.vals, P->c_slot, P->c_rec,
+                           P->p_tiles, P->p_cidx);
         BA_HIP(hipGetLastError());
         BA_HIP(hipStreamSynchronize(s));
         BA_TRY(replan_chunks(P, P->chunk_len, s));
@@ -755,10 +913,10 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
         return BA_OK;
     }
     BA_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
-    hipLaunchKernelGGL(k_fill_vox_f32, dim3(nblk(NS)), dim3(256), 0, s, NS, P->groups, slot_start, P->c_N, P->c_mu,
-                       P->c_S, P->c_scan, P->ref_poses, P->v_ref, P->v_tiles, d_err);
-    hipLaunchKernelGGL(k_gather_pose_f32, dim3(nblk(C)), dim3(256), 0, s, C, bw.vals, P->c_slot, P->c_scan, P->c_N,
-                       P->c_mu, P->c_S, P->v_ref, P->ref_poses, P->p_tiles, P->p_cidx);
+    hipLaunchKernelGGL(k_fill_vox_f32, dim3(nblk(NS)), dim3(256), 0, s, P->n_groups, P->groups, slot_start, P->c_rec,
+                       P->c_scan, P->ref_poses, P->v_ref, P->v_tiles, d_err);
+    hipLaunchKernelGGL(k_gather_pose_f32, dim3(nblk(C)), dim3(256), 0, s, C, bw.vals, bw.keys, P->c_slot, P->c_rec,
+                       P->v_ref, P->ref_poses, P->p_tiles, P->p_cidx);
     BA_HIP(hipGetLastError());
     int32_t herr = 0;
     BA_HIP(hipMemcpyAsync(&herr, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -776,7 +934,7 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     return BA_OK;
 }
 
-static ba_status finish_build(Problem *P, DevArena &keep, const ba_build_options *opt, const BuildWork &bw,
+static ba_status finish_build(Problem *P, DevArena &keep, const ba_build_options *opt, SortBuf &bw,
                               hipStream_t s) {
     std::vector<int32_t> scan_window(P->n_poses, 0);
     int32_t W = 1;
@@ -843,55 +1001,36 @@ ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, P
     P->chunk_len = (opt && opt->chunk_len > 0) ? opt->chunk_len : 256;
     DevArena tmp;
     int32_t *err;
-    uint64_t *keys;
-    uint32_t *vals;
-    int64_t *flags, *total;
-    BA_TRY(tmp.alloc(&err, 1));
-    BA_TRY(tmp.alloc(&keys, n));
-    BA_TRY(tmp.alloc(&vals, n));
-    BA_TRY(tmp.alloc(&flags, n + 1));
-    BA_TRY(tmp.alloc(&total, 1));
-    size_t ws_bytes = std::max(radix_sort_workspace_bytes(n), scan_workspace_bytes(n));
-    char *ws;
-    BA_TRY(tmp.alloc(&ws, (int64_t)ws_bytes));
-    BA_HIP(hipMemsetAsync(err, 0, sizeof(int32_t), s));
-    hipLaunchKernelGGL(k_validate_points, dim3(nblk(n)), dim3(256), 0, s, n, pts->x, pts->y, pts->z, pts->scan,
-                       pts->voxel, pts->n_scans, pts->n_voxels, err);
-    hipLaunchKernelGGL(k_make_keys, dim3(nblk(n)), dim3(256), 0, s, n, pts->scan, pts->voxel, pts->n_scans, keys,
-                       vals);
+    SortBuf b;
+    BA_TRY(tmp.alloc(&err, 3));   // error flags, then the order's two
+    BA_TRY(b.alloc(tmp, n));
+    BA_HIP(hipMemsetAsync(err, 0, 3 * sizeof(int32_t), s));
+    const int sbits = bit_length((uint64_t)(pts->n_scans - 1)), vbits = bit_length((uint64_t)(pts->n_voxels - 1));
+    hipLaunchKernelGGL(k_point_keys, dim3(std::min(nblk(n), KEY_BLOCKS)), dim3(256), 0, s, n, pts->x, pts->y, pts->z, pts->scan, pts->voxel,
+                       pts->n_scans, pts->n_voxels, sbits, b.keys, err);
     BA_HIP(hipGetLastError());
-    int32_t herr = 0;
-    BA_HIP(hipMemcpyAsync(&herr, err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    int32_t flags[3] = {0, 0, 0};
+    BA_HIP(hipMemcpyAsync(flags, err, sizeof(flags), hipMemcpyDeviceToHost, s));
     BA_HIP(hipStreamSynchronize(s));
-    if (herr) {
-        set_error("invalid points (flags 0x%x: 1 non-finite, 2 scan out of range, 4 voxel out of range)", herr);
+    if (flags[0]) {
+        set_error("invalid points (flags 0x%x: 1 non-finite, 2 scan out of range, 4 voxel out of range)", flags[0]);
         return BA_E_ARG;
     }
-    int bits = bit_length((uint64_t)pts->n_voxels * (uint64_t)pts->n_scans - 1);
-    BA_HIP(radix_sort_pairs(keys, vals, n, bits, ws, s));
-    hipLaunchKernelGGL(k_head_flags, dim3(nblk(n)), dim3(256), 0, s, n, keys, flags);
-    BA_HIP(exclusive_scan_i64(flags, flags, n, total, ws, s));
+    BA_HIP(sort_keys(b, n, vbits, sbits, flags + 1, s));
     int64_t C = 0;
-    BA_HIP(hipMemcpyAsync(&C, total, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    BA_HIP(hipStreamSynchronize(s));
+    BA_HIP(segment_count((const uint64_t *)b.keys, n, 0, b.total, b.ws, s));
+    BA_TRY(read_count(&C, b.total, s));
     P->n_clusters = C;
     int64_t *starts;
-    double *xs, *ys, *zs;
     BA_TRY(tmp.alloc(&starts, C + 1));
-    BA_TRY(tmp.alloc(&xs, n));
-    BA_TRY(tmp.alloc(&ys, n));
-    BA_TRY(tmp.alloc(&zs, n));
-    hipLaunchKernelGGL(k_segment_starts, dim3(nblk(n)), dim3(256), 0, s, n, keys, flags, starts, C);
-    hipLaunchKernelGGL(k_gather_xyz, dim3(nblk(n)), dim3(256), 0, s, n, vals, pts->x, pts->y, pts->z, xs, ys, zs);
-    BA_TRY(keep.alloc(&P->c_N, C));
-    BA_TRY(keep.alloc(&P->c_mu, 3 * C));
-    BA_TRY(keep.alloc(&P->c_S, 6 * C));
+    BA_HIP(segment_write((const uint64_t *)b.keys, n, 0, C, starts, b.ws, s));
+    BA_TRY(keep.alloc(&P->c_rec, CREC * C));
     BA_TRY(keep.alloc(&P->c_vox, C));
     BA_TRY(keep.alloc(&P->c_scan, C));
-    hipLaunchKernelGGL(k_cluster_stats, dim3(nblk(C * 64)), dim3(256), 0, s, C, starts, xs, ys, zs, keys,
-                       pts->n_scans, P->c_N, P->c_mu, P->c_S, P->c_vox, P->c_scan);
+    hipLaunchKernelGGL(k_cluster_stats, dim3(nblk(C * 64)), dim3(256), 0, s, C, starts, b.vals, pts->x, pts->y,
+                       pts->z, b.keys, sbits, P->c_rec, P->c_vox, P->c_scan);
     BA_HIP(hipGetLastError());
-    BA_TRY(finish_build(P, keep, opt, BuildWork{keys, vals, ws, total}, s));
+    BA_TRY(finish_build(P, keep, opt, b, s));
     tmp.drained = true;   // the plan's last step waits for the stream
     return BA_OK;
 }
@@ -912,22 +1051,20 @@ ba_status build_from_sums(const ba_cluster_sums *cs, const ba_build_options *opt
     P->chunk_len = (opt && opt->chunk_len > 0) ? opt->chunk_len : 256;
     DevArena tmp;
     int32_t *err;
-    uint64_t *keys;
-    uint32_t *vals;
-    BA_TRY(tmp.alloc(&err, 1));
-    BA_TRY(tmp.alloc(&keys, n));
-    BA_TRY(tmp.alloc(&vals, n));
-    char *ws;
-    int64_t *total;
-    BA_TRY(tmp.alloc(&ws, (int64_t)std::max(radix_sort_workspace_bytes(n), scan_workspace_bytes(n))));
-    BA_TRY(tmp.alloc(&total, 1));
-    BA_HIP(hipMemsetAsync(err, 0, sizeof(int32_t), s));
+    SortBuf b;
+    BA_TRY(tmp.alloc(&err, 3));   // error flags, then the order's two
+    BA_TRY(b.alloc(tmp, n));
+    BA_HIP(hipMemsetAsync(err, 0, 3 * sizeof(int32_t), s));
+    const int sbits = bit_length((uint64_t)(cs->n_scans - 1)), vbits = bit_length((uint64_t)(cs->n_voxels - 1));
     hipLaunchKernelGGL(k_validate_sums, dim3(nblk(n)), dim3(256), 0, s, n, cs->voxel, cs->scan, cs->count, cs->sum,
                        cs->sumsq, cs->n_scans, cs->n_voxels, err);
-    hipLaunchKernelGGL(k_make_keys, dim3(nblk(n)), dim3(256), 0, s, n, cs->scan, cs->voxel, cs->n_scans, keys, vals);
-    int bits = bit_length((uint64_t)cs->n_voxels * (uint64_t)cs->n_scans - 1);
-    BA_HIP(radix_sort_pairs(keys, vals, n, bits, ws, s));
-    hipLaunchKernelGGL(k_dup_keys, dim3(nblk(n)), dim3(256), 0, s, n, keys, err);
+    hipLaunchKernelGGL(k_sum_keys, dim3(std::min(nblk(n), KEY_BLOCKS)), dim3(256), 0, s, n, cs->scan, cs->voxel, sbits, b.keys, err + 1);
+    BA_HIP(hipGetLastError());
+    int32_t lacks[2] = {0, 0};
+    BA_HIP(hipMemcpyAsync(lacks, err + 1, sizeof(lacks), hipMemcpyDeviceToHost, s));
+    BA_HIP(hipStreamSynchronize(s));
+    BA_HIP(sort_keys(b, n, vbits, sbits, lacks, s));
+    hipLaunchKernelGGL(k_dup_keys, dim3(nblk(n)), dim3(256), 0, s, n, b.keys, err);
     BA_HIP(hipGetLastError());
     int32_t herr = 0;
     BA_HIP(hipMemcpyAsync(&herr, err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -938,15 +1075,13 @@ ba_status build_from_sums(const ba_cluster_sums *cs, const ba_build_options *opt
         return BA_E_ARG;
     }
     P->n_clusters = n;
-    BA_TRY(keep.alloc(&P->c_N, n));
-    BA_TRY(keep.alloc(&P->c_mu, 3 * n));
-    BA_TRY(keep.alloc(&P->c_S, 6 * n));
+    BA_TRY(keep.alloc(&P->c_rec, CREC * n));
     BA_TRY(keep.alloc(&P->c_vox, n));
     BA_TRY(keep.alloc(&P->c_scan, n));
-    hipLaunchKernelGGL(k_center_sums, dim3(nblk(n)), dim3(256), 0, s, n, vals, keys, cs->count, cs->sum, cs->sumsq,
-                       cs->n_scans, P->c_N, P->c_mu, P->c_S, P->c_vox, P->c_scan);
+    hipLaunchKernelGGL(k_center_sums, dim3(nblk(n)), dim3(256), 0, s, n, b.vals, b.keys, cs->count, cs->sum, cs->sumsq,
+                       sbits, P->c_rec, P->c_vox, P->c_scan);
     BA_HIP(hipGetLastError());
-    BA_TRY(finish_build(P, keep, opt, BuildWork{keys, vals, ws, total}, s));
+    BA_TRY(finish_build(P, keep, opt, b, s));
     tmp.drained = true;   // the plan's last step waits for the stream
     return BA_OK;
 }

@@ -54,7 +54,7 @@ struct DenseParam {
 
 // ---------------------------------------------------------------- assembly
 // h_c = (N_c / N_i) [ (R mu_c) x u ; u ] for every cluster (voxel-major order)
-__global__ void k_hvec(int64_t C, const double *__restrict__ cN, const double *__restrict__ cmu,
+__global__ void k_hvec(int64_t C, const double *__restrict__ crec,
                        const int32_t *__restrict__ cscan, const int32_t *__restrict__ cslot,
                        const double *__restrict__ poses, const double *__restrict__ vstate, int64_t n_slots,
                        const int32_t *__restrict__ pose_window, const LMState *__restrict__ lm,
@@ -70,10 +70,11 @@ __global__ void k_hvec(int64_t C, const double *__restrict__ cN, const double *_
     }
     const double *st = vstate + ((int64_t)buf * n_slots + cslot[c]) * VSTATE;
     const double u[3] = {st[0], st[1], st[2]};
-    const double f = cN[c] * (0.5 * st[6]);
+    const double *cl = crec + CREC * c;
+    const double f = cl[0] * (0.5 * st[6]);
     Pose P;
     load_pose(poses, j, P);
-    const double mu[3] = {cmu[3 * c], cmu[3 * c + 1], cmu[3 * c + 2]};
+    const double mu[3] = {cl[1], cl[2], cl[3]};
     double y[3], a[3];
     rot(P.r, mu, y);
     cross(y, u, a);
@@ -153,8 +154,7 @@ __global__ __launch_bounds__(256) void k_pairs(int32_t n_seg, const PairSeg *__r
 // -sum_k v_k,a v_k,b^T.  Terms of a gap l_l - l0 <= 1e-12 l2 are dropped.
 // One thread per voxel recomputes the voxel covariance at the poses and its
 // full eigen-decomposition from the centred clusters (voxel-major order).
-__global__ void k_exact_vecs(int32_t n_vx, const int64_t *__restrict__ vptr, const double *__restrict__ cN,
-                             const double *__restrict__ cmu, const double *__restrict__ cS,
+__global__ void k_exact_vecs(int32_t n_vx, const int64_t *__restrict__ vptr, const double *__restrict__ crec,
                              const int32_t *__restrict__ cscan, const double *__restrict__ poses,
                              double *__restrict__ ev) {
     const int v = blockIdx.x * blockDim.x + threadIdx.x;
@@ -164,9 +164,9 @@ __global__ void k_exact_vecs(int32_t n_vx, const int64_t *__restrict__ vptr, con
     for (int64_t c = a; c < b; c++) {
         Pose P;
         load_pose(poses, cscan[c], P);
-        const double n = cN[c];
+        const double n = crec[CREC * c];
         double y[3];
-        rot(P.r, cmu + 3 * c, y);
+        rot(P.r, crec + CREC * c + 1, y);
 #pragma unroll
         for (int r = 0; r < 3; r++) mb[r] += n * (y[r] + P.t[r]);
         Nv += n;
@@ -177,10 +177,10 @@ __global__ void k_exact_vecs(int32_t n_vx, const int64_t *__restrict__ vptr, con
     for (int64_t c = a; c < b; c++) {
         Pose P;
         load_pose(poses, cscan[c], P);
-        const double n = cN[c];
+        const double n = crec[CREC * c];
         double y[3], St[6], d[3];
-        rot(P.r, cmu + 3 * c, y);
-        rot_sym(P.r, cS + 6 * c, St);
+        rot(P.r, crec + CREC * c + 1, y);
+        rot_sym(P.r, crec + CREC * c + 4, St);
 #pragma unroll
         for (int r = 0; r < 3; r++) d[r] = y[r] + P.t[r] - mb[r];
         A[0] += St[0] + n * d[0] * d[0];
@@ -204,10 +204,10 @@ __global__ void k_exact_vecs(int32_t n_vx, const int64_t *__restrict__ vptr, con
     for (int64_t c = a; c < b; c++) {
         Pose P;
         load_pose(poses, cscan[c], P);
-        const double n = cN[c];
+        const double n = crec[CREC * c];
         double y[3], St[6], d[3], w0[3], su[3], ya[3];
-        rot(P.r, cmu + 3 * c, y);
-        rot_sym(P.r, cS + 6 * c, St);
+        rot(P.r, crec + CREC * c + 1, y);
+        rot_sym(P.r, crec + CREC * c + 4, St);
 #pragma unroll
         for (int r = 0; r < 3; r++) d[r] = y[r] + P.t[r] - mb[r];
         const double e0 = dot(u0, d);
@@ -2043,7 +2043,7 @@ double *dense_hvec(Problem *P) {
 // this order.
 __global__ void k_pair_emit(int32_t n_vx, const int64_t *__restrict__ vptr, const int64_t *__restrict__ poff,
                             const int32_t *__restrict__ cscan, int bits_b, uint64_t *__restrict__ keys,
-                            uint32_t *__restrict__ vals, int32_t *__restrict__ ea, int32_t *__restrict__ eb) {
+                            int32_t *__restrict__ ea, int32_t *__restrict__ eb) {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n_vx) return;
     const int64_t a = vptr[v], b = vptr[v + 1];
@@ -2052,7 +2052,6 @@ __global__ void k_pair_emit(int32_t n_vx, const int64_t *__restrict__ vptr, cons
         const uint64_t ki = (uint64_t)cscan[i] << bits_b;
         for (int64_t j = i; j < b; j++, q++) {
             keys[q] = ki | (uint64_t)cscan[j];
-            vals[q] = (uint32_t)q;
             ea[q] = (int32_t)i;
             eb[q] = (int32_t)j;
         }
@@ -2146,37 +2145,32 @@ ba_status dense_prepare(Problem *P) {
         while (bits_b < 31 && (int64_t(1) << bits_b) < NP) bits_b++;
         DevArena tmp;
         int64_t *d_poff, *head, *d_total;
-        uint64_t *keys;
-        uint32_t *vals;
+        SortBuf sb;
         int32_t *ea, *eb, *qc = nullptr;
-        char *ws;
-        const size_t ws_bytes = std::max(radix_sort_workspace_bytes(E), scan_workspace_bytes(E));
         BA_TRY(tmp.alloc(&d_poff, (int64_t)poff.size()));
-        BA_TRY(tmp.alloc(&keys, E));
-        BA_TRY(tmp.alloc(&vals, E));
+        BA_TRY(sb.alloc(tmp, E));
         BA_TRY(tmp.alloc(&ea, E));
         BA_TRY(tmp.alloc(&eb, E));
         BA_TRY(tmp.alloc(&head, E));
         BA_TRY(tmp.alloc(&d_total, 1));
-        BA_TRY(tmp.alloc(&ws, (int64_t)ws_bytes));
         BA_HIP(hipMemcpy(d_poff, poff.data(), sizeof(int64_t) * poff.size(), hipMemcpyHostToDevice));
         hipLaunchKernelGGL(k_pair_emit, dim3(nblk(D->n_vx)), dim3(256), 0, s, D->n_vx, D->vptr, d_poff, P->c_scan,
-                           bits_b, keys, vals, ea, eb);
-        BA_HIP(radix_sort_pairs(keys, vals, E, 2 * bits_b, ws, s));
+                           bits_b, sb.keys, ea, eb);
+        BA_HIP(radix_sort_pairs(sb, E, 0, 2 * bits_b, true, s));
         // the precision form keeps h in the order of its derivative pass's
         // cluster copy: the pair lists then index that order
         if (P->prec == BA_PREC_F32) {
             BA_TRY(tmp.alloc(&qc, C));
             hipLaunchKernelGGL(k_inv_perm, dim3(nblk(C)), dim3(256), 0, s, C, P->p_cidx, qc);
         }
-        hipLaunchKernelGGL(k_pair_out, dim3(nblk(E)), dim3(256), 0, s, E, keys, vals, ea, eb, qc, D->pa, D->pb,
+        hipLaunchKernelGGL(k_pair_out, dim3(nblk(E)), dim3(256), 0, s, E, sb.keys, sb.vals, ea, eb, qc, D->pa, D->pb,
                            head);
-        BA_HIP(exclusive_scan_i64(head, head, E, d_total, ws, s));
+        BA_HIP(exclusive_scan_i64(head, head, E, d_total, sb.ws, s));
         int64_t n_seg = 0;
         BA_HIP(hipMemcpy(&n_seg, d_total, sizeof(int64_t), hipMemcpyDeviceToHost));
         D->n_seg = (int32_t)n_seg;
         BA_TRY(D->mem.alloc(&D->segs, std::max<int64_t>(n_seg, 1)));
-        hipLaunchKernelGGL(k_seg_emit, dim3(nblk(E)), dim3(256), 0, s, E, keys, head, bits_b, D->segs);
+        hipLaunchKernelGGL(k_seg_emit, dim3(nblk(E)), dim3(256), 0, s, E, sb.keys, head, bits_b, D->segs);
         hipLaunchKernelGGL(k_seg_count, dim3(nblk(n_seg)), dim3(256), 0, s, n_seg, E, D->segs);
         BA_HIP(hipStreamSynchronize(s));   // before the temporaries go
         tmp.drained = true;
@@ -2306,7 +2300,7 @@ ba_status dense_assemble(Problem *P, const double *poses, double *hess_out, bool
     // clusters as the per-pose blocks, so the pair blocks cancel the diagonal
     // blocks exactly along the translation gauge)
     if (P->prec != BA_PREC_F32)
-        hipLaunchKernelGGL(k_hvec, dim3(nblk(C)), dim3(256), 0, s, C, P->c_N, P->c_mu, P->c_scan, P->c_slot, poses,
+        hipLaunchKernelGGL(k_hvec, dim3(nblk(C)), dim3(256), 0, s, C, P->c_rec, P->c_scan, P->c_slot, poses,
                            P->vstate, (int64_t)P->n_groups * 64, P->pose_window, lm, D->h);
     // windows whose derivatives are stale are rebuilt whole; the others keep their matrix
     if (!use_lm) {
@@ -2338,8 +2332,8 @@ ba_status dense_assemble_exact(Problem *P, const double *poses, double *hess_out
     if (!D->ev) BA_TRY(D->mem.alloc(&D->ev, 18 * std::max<int64_t>(P->n_clusters, 1)));
     double *dst = hess_out ? hess_out : P->dense;
     const LMState *lm = use_lm ? P->lm : nullptr;
-    hipLaunchKernelGGL(k_exact_vecs, dim3(nblk(D->n_vx)), dim3(256), 0, s, D->n_vx, D->vptr, P->c_N, P->c_mu,
-                       P->c_S, P->c_scan, poses, D->ev);
+    hipLaunchKernelGGL(k_exact_vecs, dim3(nblk(D->n_vx)), dim3(256), 0, s, D->n_vx, D->vptr, P->c_rec,
+                       P->c_scan, poses, D->ev);
     if (!use_lm) {
         const int64_t tot = P->dense_total;
         hipLaunchKernelGGL(k_fill, dim3(nblk(tot)), dim3(256), 0, s, tot, dst, 0.0);

@@ -86,6 +86,7 @@ struct DecideArgs {
 };
 
 static constexpr int VSTATE = 8;    // doubles per voxel slot: u[3] mbar[3] 2/N lam0
+static constexpr int CREC = 10;     // doubles per centred cluster: N mu[3] S[6]
 static constexpr int NPART = 27;    // g[6] + Hpp[6] + Hpt[9] + Htt[6]
 
 // Launch choices of the two evaluation passes (ba_tuning).
@@ -143,8 +144,9 @@ struct Problem {
     int32_t *chunk_ptr = nullptr; // [n_poses+1]
     double *partials = nullptr; // [n_chunks][NPART]
 
-    // centred clusters in (voxel, scan) order, kept for export
-    double *c_mu = nullptr, *c_S = nullptr, *c_N = nullptr; // [C][3], [C][6], [C]
+    // centred clusters in (voxel, scan) order, kept for export: [C][CREC] N, mu[3], S[6],
+    // so that a cluster is 80 consecutive bytes in five 16-byte loads
+    double *c_rec = nullptr;
     int32_t *c_vox = nullptr, *c_scan = nullptr;
     int32_t *c_slot = nullptr;                 // residual-pass slot of each cluster
 
@@ -177,6 +179,7 @@ struct Problem {
 };
 
 ba_status replan_chunks(Problem *P, int32_t chunk_len, hipStream_t s);
+hipError_t export_records(const Problem *P, double *count, double *mu, double *S, hipStream_t s);
 int64_t dense_device_bytes(const Problem *P);
 ba_status dense_prepare(Problem *P);
 double *dense_hvec(Problem *P);   // [C][6] pair vectors of the coupled form
@@ -191,10 +194,18 @@ hipError_t exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, int64_
 template <class K>
 hipError_t segment_count(const K *keys, int64_t n, int shift, int64_t *total, void *ws, hipStream_t s);
 template <class K>
-hipError_t segment_write(const K *keys, int64_t n, int shift, int64_t n_seg, int64_t *starts, int32_t *ids, void *ws,
+hipError_t segment_write(const K *keys, int64_t n, int shift, int64_t n_seg, int64_t *starts, void *ws,
                          hipStream_t s);
 size_t radix_sort_workspace_bytes(int64_t n);
-hipError_t radix_sort_pairs(uint64_t *keys, uint32_t *vals, int64_t n, int bits, void *ws, hipStream_t s);
+// Buffers of the radix sort (and of scans of up to cap values, in ws).
+struct SortBuf {
+    uint64_t *keys = nullptr, *keys2 = nullptr;
+    uint32_t *vals = nullptr, *vals2 = nullptr;
+    char *ws = nullptr;
+    int64_t *total = nullptr;   // device: one count
+    ba_status alloc(DevArena &a, int64_t cap);
+};
+hipError_t radix_sort_pairs(SortBuf &b, int64_t n, int lo, int bits, bool iota, hipStream_t s);
 
 }  // namespace ba
 

@@ -93,6 +93,7 @@ __device__ __forceinline__ void vx_unpack(const CellLayout &L, uint64_t k, int64
 
 // error flags of the cloud
 static constexpr int VX_ERR_FINITE = 1, VX_ERR_SCAN = 2, VX_ERR_RANGE = 4;
+static constexpr int VX_UNSORTED = 8;   // no error: a scan id falls somewhere in the input
 
 __global__ __launch_bounds__(VX_THREADS) void k_vx_cells(int64_t n, const double *__restrict__ x,
                                                          const double *__restrict__ y, const double *__restrict__ z,
@@ -108,6 +109,7 @@ __global__ __launch_bounds__(VX_THREADS) void k_vx_cells(int64_t n, const double
     int err = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int32_t s = scan[i];
+        if (i > 0 && s < scan[i - 1]) err |= VX_UNSORTED;
         if (s < 0 || s >= n_scans) {
             err |= VX_ERR_SCAN;
             continue;
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(VX_THREADS) void k_vx_cells(int64_t n, const double
     // OR of the flags, one bit at a time (a bit is set if some thread's is)
     int orr = 0;
 #pragma unroll
-    for (int bit = 0; bit < 3; bit++) orr |= (block_min_i<NW>((err >> bit) & 1 ? 0 : 1, red) == 0) ? (1 << bit) : 0;
+    for (int bit = 0; bit < 4; bit++) orr |= (block_min_i<NW>((err >> bit) & 1 ? 0 : 1, red) == 0) ? (1 << bit) : 0;
     if (threadIdx.x == 0) out[6] = orr;
 }
 
@@ -170,43 +172,26 @@ __global__ __launch_bounds__(VX_THREADS) void k_vx_bbox(int nb, const int32_t *_
     }
     int orr = 0;
 #pragma unroll
-    for (int bit = 0; bit < 3; bit++) orr |= (block_min_i<NW>((flags >> bit) & 1 ? 0 : 1, red) == 0) ? (1 << bit) : 0;
+    for (int bit = 0; bit < 4; bit++) orr |= (block_min_i<NW>((flags >> bit) & 1 ? 0 : 1, red) == 0) ? (1 << bit) : 0;
     if (threadIdx.x == 0) box[6] = orr;
 }
 
 __global__ void k_vx_keys_points(int64_t n, const int32_t *__restrict__ cell, const int32_t *__restrict__ scan,
-                                 CellLayout L, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
+                                 CellLayout L, uint64_t *__restrict__ keys) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     keys[i] = vx_pack(L, cell[i], cell[n + i], cell[2 * n + i], scan[i]);
-    vals[i] = (uint32_t)i;
 }
 
 // key of the parent cell (Eq. 5: floor of half the index) of each cluster
 __global__ void k_vx_keys_up(int64_t C, const uint64_t *__restrict__ ckey, CellLayout Lc, CellLayout Lp,
-                             uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
+                             uint64_t *__restrict__ keys) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= C) return;
     int64_t c[3];
     int32_t s;
     vx_unpack(Lc, ckey[i], c, s);
     keys[i] = vx_pack(Lp, c[0] >> 1, c[1] >> 1, c[2] >> 1, s);
-    vals[i] = (uint32_t)i;
-}
-
-// head flag where (key >> shift) changes
-__global__ void k_vx_heads(int64_t n, const uint64_t *__restrict__ keys, int shift, int64_t *__restrict__ flags) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    flags[i] = (i == 0 || (keys[i] >> shift) != (keys[i - 1] >> shift)) ? 1 : 0;
-}
-
-__global__ void k_vx_starts(int64_t n, const uint64_t *__restrict__ keys, int shift, const int64_t *__restrict__ excl,
-                            int64_t *__restrict__ starts, int64_t n_seg) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (i == 0 || (keys[i] >> shift) != (keys[i - 1] >> shift)) starts[excl[i]] = i;
-    if (i == 0) starts[n_seg] = n;
 }
 
 // raw sums of one level-1 cluster: VX_SUM_LANES lanes per cluster, lane g
@@ -428,11 +413,10 @@ __global__ __launch_bounds__(VX_THREADS) void k_vx_cell_box(int64_t C, const int
 }
 
 __global__ void k_vx_keys_cells(int64_t C, const int32_t *__restrict__ cell, const int32_t *__restrict__ cscan,
-                                CellLayout L, uint64_t *__restrict__ keys, uint32_t *__restrict__ vals) {
+                                CellLayout L, uint64_t *__restrict__ keys) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= C) return;
     keys[c] = vx_pack(L, cell[3 * c], cell[3 * c + 1], cell[3 * c + 2], cscan[c]);
-    vals[c] = (uint32_t)c;
 }
 
 // one level's clusters (keys in (cell, scan) order) and its selection
@@ -445,14 +429,6 @@ struct VxLevel {
     int64_t *vstart = nullptr, *keep = nullptr, *vrank = nullptr, *coff = nullptr;
 };
 
-// sort and scan buffers for up to cap entries
-struct VxWork {
-    uint64_t *keys = nullptr;
-    uint32_t *vals = nullptr;
-    int64_t *flags = nullptr, *total = nullptr;
-    char *ws = nullptr;
-    int64_t cap = 0;
-};
 
 }  // namespace ba
 
@@ -475,27 +451,14 @@ static ba_status sync_read(void *dst, const void *src, size_t bytes, hipStream_t
     return BA_OK;
 }
 
-static ba_status work_alloc(DevArena &a, VxWork &w, int64_t cap) {
-    w.cap = cap;
-    BA_TRY(a.alloc(&w.keys, cap));
-    BA_TRY(a.alloc(&w.vals, cap));
-    BA_TRY(a.alloc(&w.flags, cap + 1));
-    BA_TRY(a.alloc(&w.total, 1));
-    BA_TRY(a.alloc(&w.ws, (int64_t)std::max(radix_sort_workspace_bytes(cap), scan_workspace_bytes(cap))));
-    return BA_OK;
-}
-
 // segments of sorted keys that agree above bit `shift`: their number and
 // their starts (length n_seg + 1)
-static ba_status vx_segments(DevArena &tmp, VxWork &w, const uint64_t *keys, int64_t n, int shift,
+static ba_status vx_segments(DevArena &tmp, SortBuf &w, const uint64_t *keys, int64_t n, int shift,
                              int64_t **starts, int64_t *n_seg, hipStream_t s) {
-    hipLaunchKernelGGL(k_vx_heads, dim3(vx_nblk(n)), dim3(VX_THREADS), 0, s, n, keys, shift, w.flags);
-    BA_HIP(exclusive_scan_i64(w.flags, w.flags, n, w.total, w.ws, s));
+    BA_HIP(segment_count(keys, n, shift, w.total, w.ws, s));
     BA_TRY(sync_read(n_seg, w.total, sizeof(int64_t), s));
     BA_TRY(tmp.alloc(starts, *n_seg + 1));
-    hipLaunchKernelGGL(k_vx_starts, dim3(vx_nblk(n)), dim3(VX_THREADS), 0, s, n, keys, shift, w.flags, *starts,
-                       *n_seg);
-    BA_HIP(hipGetLastError());
+    BA_HIP(segment_write(keys, n, shift, *n_seg, *starts, w.ws, s));
     return BA_OK;
 }
 
@@ -508,11 +471,14 @@ static ba_status check_layout(const CellLayout &L) {
 }
 
 // Sort the m keys in w (layout cur.L) and form cur's clusters: raw sums of
-// points (x non-null) or of the child clusters.
-static ba_status vx_form_level(DevArena &tmp, VxWork &w, int64_t m, const double *x, const double *y,
+// points (x non-null) or of the child clusters.  by_scan: the keys come in
+// scan order (a scan log), so that a stable sort by cell alone, without the
+// scan bits, leaves the same order.
+static ba_status vx_form_level(DevArena &tmp, SortBuf &w, int64_t m, bool by_scan, const double *x, const double *y,
                                const double *z, const int64_t *ccount, const double *cs1, const double *cs2,
                                VxLevel &cur, hipStream_t s) {
-    BA_HIP(radix_sort_pairs(w.keys, w.vals, m, cur.L.total, w.ws, s));
+    const int lo = by_scan ? cur.L.sbits : 0;
+    BA_HIP(radix_sort_pairs(w, m, lo, cur.L.total - lo, true, s));
     int64_t *starts;
     BA_TRY(vx_segments(tmp, w, w.keys, m, 0, &starts, &cur.C, s));
     BA_TRY(tmp.alloc(&cur.ckey, cur.C));
@@ -545,9 +511,11 @@ static ba_status vx_cells_launch(DevArena &tmp, const double *x, const double *y
     return BA_OK;
 }
 
-static ba_status vx_cells_layout(const int32_t *box, int32_t n_scans, CellLayout *L, hipStream_t s) {
+static ba_status vx_cells_layout(const int32_t *box, int32_t n_scans, CellLayout *L, bool *by_scan, hipStream_t s) {
     int32_t hb[7];
     BA_TRY(sync_read(hb, box, sizeof(hb), s));
+    *by_scan = !(hb[6] & VX_UNSORTED);
+    hb[6] &= ~VX_UNSORTED;
     if (hb[6]) {
         set_error("invalid points (flags 0x%x: 1 non-finite world point, 2 scan out of range, 4 cell index beyond "
                   "2^30 at edge d)",
@@ -560,7 +528,7 @@ static ba_status vx_cells_layout(const int32_t *box, int32_t n_scans, CellLayout
 }
 
 // Planarity decisions of one level and its kept counts.
-static ba_status vx_select_level(DevArena &tmp, VxWork &w, VxLevel &cur, const double *poses,
+static ba_status vx_select_level(DevArena &tmp, SortBuf &w, VxLevel &cur, const double *poses,
                                  const ba_voxelize_options *opt, hipStream_t s) {
     // cells of this level: segments of the cluster keys without the scan bits
     BA_TRY(vx_segments(tmp, w, cur.ckey, cur.C, cur.L.sbits, &cur.vstart, &cur.V, s));
@@ -580,7 +548,7 @@ static ba_status vx_select_level(DevArena &tmp, VxWork &w, VxLevel &cur, const d
 
 // From the level-1 clusters in lv[0]: levels 2..L (Eq. 5), the selection of
 // every level and the concatenated output.
-static ba_status vx_finish(DevArena &tmp, VxWork &w, std::vector<VxLevel> &lv, int32_t n_scans,
+static ba_status vx_finish(DevArena &tmp, SortBuf &w, std::vector<VxLevel> &lv, int32_t n_scans,
                            const double *poses, const ba_voxelize_options *opt, ba_voxel_map *M, hipStream_t s) {
     const int levels = (int)lv.size();
     BA_TRY(vx_select_level(tmp, w, lv[0], poses, opt, s));
@@ -594,9 +562,9 @@ static ba_status vx_finish(DevArena &tmp, VxWork &w, std::vector<VxLevel> &lv, i
         }
         cur.L = make_layout(plo, phi, n_scans);
         hipLaunchKernelGGL(k_vx_keys_up, dim3(vx_nblk(prev.C)), dim3(VX_THREADS), 0, s, prev.C, prev.ckey, prev.L,
-                           cur.L, w.keys, w.vals);
+                           cur.L, w.keys);
         BA_HIP(hipGetLastError());
-        BA_TRY(vx_form_level(tmp, w, prev.C, nullptr, nullptr, nullptr, prev.count, prev.s1, prev.s2, cur, s));
+        BA_TRY(vx_form_level(tmp, w, prev.C, false, nullptr, nullptr, nullptr, prev.count, prev.s1, prev.s2, cur, s));
         BA_TRY(vx_select_level(tmp, w, cur, poses, opt, s));
     }
     int64_t Vout = 0, Cout = 0;
@@ -646,13 +614,13 @@ static ba_status voxelize(const double *x, const double *y, const double *z, con
     std::vector<VxLevel> lv(opt->levels);
     int32_t *box;
     BA_TRY(vx_cells_launch(tmp, x, y, z, scan, n, n_scans, poses, opt->d, cell, &box, s));
-    BA_TRY(vx_cells_layout(box, n_scans, &lv[0].L, s));
-    VxWork w;
-    BA_TRY(work_alloc(tmp, w, n));   // the points are the largest level
-    hipLaunchKernelGGL(k_vx_keys_points, dim3(vx_nblk(n)), dim3(VX_THREADS), 0, s, n, cell, scan, lv[0].L, w.keys,
-                       w.vals);
+    bool by_scan;
+    BA_TRY(vx_cells_layout(box, n_scans, &lv[0].L, &by_scan, s));
+    SortBuf w;
+    BA_TRY(w.alloc(tmp, n));   // the points are the largest level
+    hipLaunchKernelGGL(k_vx_keys_points, dim3(vx_nblk(n)), dim3(VX_THREADS), 0, s, n, cell, scan, lv[0].L, w.keys);
     BA_HIP(hipGetLastError());
-    BA_TRY(vx_form_level(tmp, w, n, x, y, z, nullptr, nullptr, nullptr, lv[0], s));
+    BA_TRY(vx_form_level(tmp, w, n, by_scan, x, y, z, nullptr, nullptr, nullptr, lv[0], s));
     BA_TRY(vx_finish(tmp, w, lv, n_scans, poses, opt, M, s));
     tmp.drained = true;
     M->n_points = n;
@@ -782,8 +750,8 @@ static ba_status voxelize_host(const double *hx, const double *hy, const double 
         BA_TRY(tmp.alloc(&ds[k], B));
     }
     BA_TRY(tmp.alloc(&cell, 3 * B));
-    VxWork w;
-    BA_TRY(work_alloc(tmp, w, B));
+    SortBuf w;
+    BA_TRY(w.alloc(tmp, B));
     const int64_t nbat = (n + B - 1) / B;
     std::vector<VxBatch> bat(nbat);
     // start the transfer of batch b (pageable input: by the staging threads,
@@ -825,11 +793,11 @@ static ba_status voxelize_host(const double *hx, const double *hy, const double 
         BA_TRY(vx_cells_launch(tmp, dx[k], dy[k], dz[k], ds[k], m, n_scans, poses, opt->d, cell, &box, s));
         // the next batch is staged and its transfer queued while this one is clustered
         if (b + 1 < nbat) BA_TRY(start_copy(b + 1));
-        BA_TRY(vx_cells_layout(box, n_scans, &l1.L, s));
-        hipLaunchKernelGGL(k_vx_keys_points, dim3(vx_nblk(m)), dim3(VX_THREADS), 0, s, m, cell, ds[k], l1.L, w.keys,
-                           w.vals);
+        bool by_scan;
+        BA_TRY(vx_cells_layout(box, n_scans, &l1.L, &by_scan, s));
+        hipLaunchKernelGGL(k_vx_keys_points, dim3(vx_nblk(m)), dim3(VX_THREADS), 0, s, m, cell, ds[k], l1.L, w.keys);
         BA_HIP(hipGetLastError());
-        BA_TRY(vx_form_level(tmp, w, m, dx[k], dy[k], dz[k], nullptr, nullptr, nullptr, l1, s));
+        BA_TRY(vx_form_level(tmp, w, m, by_scan, dx[k], dy[k], dz[k], nullptr, nullptr, nullptr, l1, s));
         VxBatch &o = bat[b];
         o.C = l1.C;
         BA_TRY(tmp.alloc(&o.cell, 3 * o.C));
@@ -875,12 +843,11 @@ static ba_status voxelize_host(const double *hx, const double *hy, const double 
     int64_t lo[3] = {hb[0], hb[1], hb[2]}, hi[3] = {-(int64_t)hb[3], -(int64_t)hb[4], -(int64_t)hb[5]};
     lv[0].L = make_layout(lo, hi, n_scans);
     BA_TRY(check_layout(lv[0].L));
-    VxWork wm;
-    BA_TRY(work_alloc(tmp, wm, C));
-    hipLaunchKernelGGL(k_vx_keys_cells, dim3(vx_nblk(C)), dim3(VX_THREADS), 0, s, C, acell, ascan, lv[0].L, wm.keys,
-                       wm.vals);
+    SortBuf wm;
+    BA_TRY(wm.alloc(tmp, C));
+    hipLaunchKernelGGL(k_vx_keys_cells, dim3(vx_nblk(C)), dim3(VX_THREADS), 0, s, C, acell, ascan, lv[0].L, wm.keys);
     BA_HIP(hipGetLastError());
-    BA_TRY(vx_form_level(tmp, wm, C, nullptr, nullptr, nullptr, acount, as1, as2, lv[0], s));
+    BA_TRY(vx_form_level(tmp, wm, C, false, nullptr, nullptr, nullptr, acount, as1, as2, lv[0], s));
     BA_TRY(vx_finish(tmp, wm, lv, n_scans, poses, opt, M, s));
     tmp.drained = true;   // s has waited for every transfer
     M->n_points = n;

@@ -150,3 +150,33 @@ def test_voxel_across_windows_is_refused(ba):
         ba.build_clusters_from_sums(t([3, 3, 7, 7, 9, 9], torch.int32), t([0, 1, 1, 2, 0, 3], torch.int32),
                                     t(pay[0], torch.int64), t(pay[1], torch.float64), t(pay[2], torch.float64), 4, 12,
                                     n_windows=2, scan_window=[0, 0, 1, 1])
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 2047, 2048, 2049, 4095, 4096, 4097, 20000])
+def test_input_order_routes_agree(ba, n):
+    """Points in log order, in (voxel, scan) order and in no order take different sorts (by voxel alone, none, by
+    both); a cluster's own points keep their order in all three, so every output is bitwise the same."""
+    import torch
+    rng = np.random.default_rng(n)
+    n_scans, V = 17, 300
+    scan, vox = rng.integers(0, n_scans, n).astype(np.int32), rng.integers(0, V, n).astype(np.int32)
+    xyz = rng.uniform(-30, 30, (3, n))
+    P = _poses(rng, n_scans)
+    t = lambda a, dt: torch.as_tensor(np.ascontiguousarray(a), dtype=dt, device="cuda")
+    print(f"[gpu-case] input orders, {n} points", flush=True)
+    builds, maps = [], []
+    for order in (np.arange(n), np.argsort(scan, kind="stable"), np.lexsort((scan, vox))):
+        x, y, z = (t(a[order], torch.float64) for a in xyz)
+        sc, vx = t(scan[order], torch.int32), t(vox[order], torch.int32)
+        prob = ba.build_clusters(x, y, z, sc, vx, n_scans, V)
+        builds.append([a.cpu().numpy() for a in prob.export_clusters()])
+        m = ba.voxelize(x, y, z, sc, t(P, torch.float64), 2.0, 3, 5.0)
+        maps.append((m.info()["level_clusters"], {k: v.cpu().numpy() for k, v in m.export().items()}))
+    key = np.unique(vox.astype(np.int64) * n_scans + scan, return_counts=True)
+    assert np.array_equal(builds[0][0].astype(np.int64) * n_scans + builds[0][1], key[0])
+    assert np.array_equal(builds[0][2], key[1].astype(np.float64))
+    for b in builds[1:]:
+        assert all(np.array_equal(a, c) for a, c in zip(builds[0], b))
+    # log order against no order: a cell holds points of several voxels, in (voxel) order in the third
+    assert maps[0][0] == maps[1][0] == maps[2][0]
+    assert all(np.array_equal(maps[0][1][k], maps[1][1][k]) for k in maps[0][1])
