@@ -834,6 +834,125 @@ __global__ __launch_bounds__(256) void k_syrk(const DenseDesc *__restrict__ desc
             }
 }
 
+// The same trailing update by 128 x 128 tiles, a 64 x 64 quadrant per wave (16
+// accumulators of v_mfma_f64_16x16x4f64), two blocks per compute unit.  Half
+// the operand bytes per product of the 64 x 64 tiles above; two k stages in
+// LDS, one barrier a stage.  On the first update of 12000 rows (K = 256) the
+// matrix cores are busy 64% of the time against 56%, 50 against 44 TF/s; the
+// factorization's updates together 16.4 -> 14.5 ms.  (32 k values staged once
+// instead of 16 twice: 15.2; squares of 4 x 4 or 8 x 8 tiles per XCD instead
+// of 2 x 2: 14.8, 15.6.)
+typedef double v2d __attribute__((ext_vector_type(2)));   // (HIP's double2 arrays stay in memory here)
+static constexpr int WT = 128;        // tile edge
+static constexpr int WK = 16;         // k values staged at a time
+static constexpr int WLD = WK + 2;    // LDS row stride: 16-byte reads of 16 rows fall into distinct banks
+static constexpr int WSUP = 2;        // tiles are dealt to the XCDs in WSUP x WSUP squares, which share operands in L2
+
+__device__ __forceinline__ void wide_load(v2d (&v)[WK / 4], const double *__restrict__ A, int64_t ld, int64_t r0,
+                                          int64_t k0, int64_t n) {
+#pragma unroll
+    for (int e = 0; e < WK / 4; e++) {
+        const int idx = threadIdx.x + 256 * e;
+        // rows past the end repeat the last one: they only feed elements that are not stored
+        const int64_t row = std::min<int64_t>(r0 + (idx / (WK / 2)), n - 1);
+        v[e] = *reinterpret_cast<const v2d *>(A + row * ld + k0 + 2 * (idx % (WK / 2)));
+    }
+}
+
+__device__ __forceinline__ void wide_store(double *__restrict__ lds, const v2d (&v)[WK / 4]) {
+#pragma unroll
+    for (int e = 0; e < WK / 4; e++) {
+        const int idx = threadIdx.x + 256 * e;
+        *reinterpret_cast<v2d *>(lds + (idx / (WK / 2)) * WLD + 2 * (idx % (WK / 2))) = v[e];
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void k_syrk_wide(const DenseDesc *__restrict__ desc,
+                                                      const DenseParam *__restrict__ prm, double *__restrict__ work,
+                                                      int kstep, int kw, int tstep) {
+    __shared__ __attribute__((aligned(16))) double sm[2][2][WT * WLD];
+    const int m = blockIdx.y;
+    const DenseDesc d = desc[m];
+    if (!prm[m].active || prm[m].info) return;
+    const int64_t k0 = (int64_t)TB * kstep, T0 = (int64_t)TB * tstep;
+    if (T0 >= d.n) return;
+    const int nt = (int)((d.n - T0 + WT - 1) / WT);
+    // block -> (square of the lower triangle, tile in it); a square's tiles go to one XCD
+    const int b = (int)blockIdx.x;
+    constexpr int PER = WSUP * WSUP;
+    const int sq = (b / (8 * PER)) * 8 + (b & 7), in = (b >> 3) % PER;
+    int SI = (int)((sqrt(8.0 * (double)sq + 1.0) - 1.0) * 0.5);
+    while (SI * (SI + 1) / 2 > sq) SI--;
+    while ((SI + 1) * (SI + 2) / 2 <= sq) SI++;
+    const int I = SI * WSUP + in / WSUP, J = (sq - SI * (SI + 1) / 2) * WSUP + in % WSUP;
+    if (I >= nt || J > I) return;
+    const int64_t ri = T0 + (int64_t)WT * I, rj = T0 + (int64_t)WT * J;
+    double *A = work + d.a_off;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int wr = 64 * (w >> 1), wc = 64 * (w & 1);
+    const int li = lane & 15, lk = lane >> 4;
+    d4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+    v2d va[WK / 4], vb[WK / 4];
+    wide_load(va, A, d.n, ri, k0, d.n);
+    wide_load(vb, A, d.n, rj, k0, d.n);
+    const int steps = kw / WK;
+#pragma unroll 1
+    for (int st = 0; st < steps; st++) {
+        double *Sa = sm[st & 1][0], *Sb = sm[st & 1][1];
+        wide_store(Sa, va);
+        wide_store(Sb, vb);
+        __syncthreads();   // one barrier a step: the other stage is rewritten only after the next one
+        // the next step's operands (the last step loads its own again)
+        const int64_t kn = k0 + WK * std::min(st + 1, steps - 1);
+        wide_load(va, A, d.n, ri, kn, d.n);
+        wide_load(vb, A, d.n, rj, kn, d.n);
+        const double *As = Sa + (wr + li) * WLD + 2 * lk, *Bs = Sb + (wc + li) * WLD + 2 * lk;
+#pragma unroll
+        for (int kk = 0; kk < WK; kk += 8) {
+            // lane group lk holds k = kk + 2 lk (first product) and kk + 2 lk + 1 (second)
+            v2d a[4], bb[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                a[i] = *reinterpret_cast<const v2d *>(As + 16 * i * WLD + kk);
+                bb[i] = *reinterpret_cast<const v2d *>(Bs + 16 * i * WLD + kk);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, bb[j].x, acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, bb[j].y, acc[i][j], 0, 0, 0);
+        }
+    }
+    if (I == J && wc > wr) return;   // the quadrant above the diagonal is not needed
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        double c[4][4];
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int64_t row = ri + wr + 16 * i + lk + 4 * r, col = rj + wc + 16 * j + li;
+                c[j][r] = (row < d.n && col < d.n) ? A[row * d.n + col] : 0.0;
+            }
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int64_t row = ri + wr + 16 * i + lk + 4 * r, col = rj + wc + 16 * j + li;
+                if (row < d.n && col < d.n) A[row * d.n + col] = c[j][r] - acc[i][j][r];
+            }
+    }
+}
+
 // Backward substitution, R block rows per launch: rows k, k-1, ..., k-R+1
 // (those >= 0 that the matrix has; k = `step`).  Every workgroup forms the
 // rows' solutions in order, x_r = L_rr^-T (y_r - sum of L_r'r^T x_r' over the
@@ -2376,8 +2495,35 @@ static void launch_flow_factor(DenseState *D, const double *H, const int64_t *h_
 // 64-wide steps; a step updates the rest of its panel, each panel then the
 // trailing matrix with K = the panel's width (one read and write of the
 // trailing matrix per panel instead of per step).
+// A panel is PANEL tile columns: the trailing matrix is read and written once
+// per panel, so a longer one saves that traffic (the wide update is near it)
+// and costs more small updates inside the panel.  12000 rows: 20.4 ms with 8,
+// 22.0 with 4.  The wide kernel from 256 tiles of its own on (two thirds of
+// them in flight at once); at 6600 rows, where the two meet, both take 6.8 ms.
+// Measured and dropped: the part of an update that the next panel does not
+// need on a second stream beside that panel's factorization (20.2 ms; the
+// panel's kernels then take 1.3 to 2.4 times as long), and the same with that
+// stream held to 192-240 compute units by a mask (27.7-29.3 ms).
+static constexpr int PANEL = 8;
+static constexpr int64_t WIDE_TILES = 256;
+
+// Trailing update by panel [p, pe).
+static void launch_trailing(DenseState *D, int32_t nmat, int nsteps, int p, int pe, hipStream_t s) {
+    const int64_t rest = nsteps - pe;
+    if (rest <= 0) return;
+    const int64_t wide = (rest + 1) / 2;   // 128-wide tile rows
+    ProfScope prof("k_syrk", s);
+    if (wide * (wide + 1) / 2 >= WIDE_TILES) {
+        const int64_t sup = (wide + WSUP - 1) / WSUP, squares = sup * (sup + 1) / 2;
+        hipLaunchKernelGGL(k_syrk_wide, dim3((unsigned)((squares + 7) / 8 * 8 * WSUP * WSUP), nmat), dim3(256), 0, s,
+                           D->desc, D->prm, D->work, p, TB * (pe - p), pe);
+    } else {
+        hipLaunchKernelGGL(k_syrk, dim3((unsigned)(rest * (rest + 1) / 2), nmat), dim3(256), 0, s, D->desc, D->prm,
+                           D->work, p, TB * (pe - p), pe, nsteps);
+    }
+}
+
 static void launch_blocked_factor(DenseState *D, int32_t nmat, int nsteps, hipStream_t s) {
-    constexpr int PANEL = 4;
     for (int p = 0; p < nsteps; p += PANEL) {
         const int pe = std::min(p + PANEL, nsteps);
         for (int st = p; st < pe; st++) {
@@ -2401,12 +2547,7 @@ static void launch_blocked_factor(DenseState *D, int32_t nmat, int nsteps, hipSt
                 }
             }
         }
-        const int64_t rest = nsteps - pe;
-        if (rest > 0) {
-            ProfScope prof("k_syrk", s);
-            hipLaunchKernelGGL(k_syrk, dim3((unsigned)(rest * (rest + 1) / 2), nmat), dim3(256), 0, s, D->desc,
-                               D->prm, D->work, p, TB * (pe - p), pe, nsteps);
-        }
+        launch_trailing(D, nmat, nsteps, p, pe, s);
     }
 }
 

@@ -1,0 +1,37 @@
+"""The trailing update by 128 x 128 tiles (dense systems over 6144 rows) at
+its edges: an odd number of 64-row tiles under a panel, a last tile of a few
+rows, and the sizes where the update passes from wide to narrow tiles."""
+import numpy as np
+import pytest
+
+from helpers import dense_backward_error
+
+pytestmark = [pytest.mark.gpu, pytest.mark.timeout(300)]
+
+
+@pytest.mark.parametrize("n", [6150, 6336, 6402, 7170])
+def test_wide_updates_against_lapack(n):
+    """Backward error within 16 times LAPACK's own on the same system; a
+    non-positive pivot under a wide update is reported at its place."""
+    import torch
+    import paper_2608_14266_amd as ba
+    dev = torch.device("cuda:0")
+    print(f"[gpu-case] wide update n={n}", flush=True)
+    g = torch.Generator(device=dev).manual_seed(n)
+    A = torch.randn(n, n, generator=g, dtype=torch.float64, device=dev)
+    H = A @ A.T / n
+    del A
+    H.diagonal().add_(0.5 + torch.rand(n, generator=g, dtype=torch.float64, device=dev))
+    H = (H + H.T) / 2
+    b = torch.randn(n, generator=g, dtype=torch.float64, device=dev)
+    dx, info = ba.solve_increment(ba.MODE_COUPLED, H, b, 0.0)
+    assert info.item() == 0
+    Hn, bn = H.cpu().numpy(), b.cpu().numpy()
+    ref = np.linalg.solve(Hn, -bn)
+    e_ref, e = dense_backward_error(Hn, ref, -bn), dense_backward_error(Hn, dx.cpu().numpy().ravel(), -bn)
+    print(f"[gpu-case] backward error {e:.2e}, LAPACK {e_ref:.2e}", flush=True)
+    assert e <= 16 * e_ref
+    bad = n - 700
+    H[bad, bad] = -1.0
+    dx, info = ba.solve_increment(ba.MODE_COUPLED, H, b, 0.0)
+    assert info.item() == bad + 1 and not dx.any().item()
