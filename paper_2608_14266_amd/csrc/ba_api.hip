@@ -366,16 +366,17 @@ ba_status ba_eval_residual_grad_hessian(ba_problem *p, const double *poses, int3
     }
     Problem *P = &p->P;
     launch_vox(P, poses, false, false, stream);
-    launch_window_cost(P, cost, stream);
+    if (!grad) launch_window_cost(P, cost, stream);
     if (voxel_eig) launch_voxel_eig(P, voxel_eig, stream);
     if (grad) {
         double *Hmm = (mode == BA_MODE_MM) ? hess : P->H;
         if (mode == BA_MODE_EXACT && P->prec != BA_PREC_F64) {
+            launch_window_cost(P, cost, stream);
             set_error("the exact Hessian is built for FP64 problems only");
             return BA_E_UNSUPPORTED;
         }
         if (mode != BA_MODE_MM) BA_TRY(dense_prepare(P));   // the derivative pass may fill its h vectors
-        launch_pose_derivs(P, poses, false, grad, Hmm, stream, mode == BA_MODE_COUPLED);
+        launch_pose_derivs(P, poses, false, grad, Hmm, stream, mode == BA_MODE_COUPLED, cost);
         if (mode == BA_MODE_COUPLED) BA_TRY(dense_assemble(P, poses, hess, false, stream));
         if (mode == BA_MODE_EXACT) BA_TRY(dense_assemble_exact(P, poses, hess, false, 0.0, stream));
     }

@@ -52,37 +52,6 @@ struct DenseParam {
     int32_t info;
 };
 
-// ---------------------------------------------------------------- assembly
-// h_c = (N_c / N_i) [ (R mu_c) x u ; u ] for every cluster (voxel-major order)
-__global__ void k_hvec(int64_t C, const double *__restrict__ crec,
-                       const int32_t *__restrict__ cscan, const int32_t *__restrict__ cslot,
-                       const double *__restrict__ poses, const double *__restrict__ vstate, int64_t n_slots,
-                       const int32_t *__restrict__ pose_window, const LMState *__restrict__ lm,
-                       double *__restrict__ h) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    const int j = cscan[c];
-    int buf = 0;
-    if (lm) {
-        const LMState &st = lm[pose_window[j]];
-        if (st.done || !st.need_eval) return;
-        buf = st.cur;
-    }
-    const double *st = vstate + ((int64_t)buf * n_slots + cslot[c]) * VSTATE;
-    const double u[3] = {st[0], st[1], st[2]};
-    const double *cl = crec + CREC * c;
-    const double f = cl[0] * (0.5 * st[6]);
-    Pose P;
-    load_pose(poses, j, P);
-    const double mu[3] = {cl[1], cl[2], cl[3]};
-    double y[3], a[3];
-    rot(P.r, mu, y);
-    cross(y, u, a);
-    double *o = h + 6 * c;
-    o[0] = f * a[0]; o[1] = f * a[1]; o[2] = f * a[2];
-    o[3] = f * u[0]; o[4] = f * u[1]; o[5] = f * u[2];
-}
-
 __global__ void k_fill(int64_t n, double *__restrict__ p, double v) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -155,8 +124,8 @@ __global__ __launch_bounds__(256) void k_pairs(int32_t n_seg, const PairSeg *__r
 // One thread per voxel recomputes the voxel covariance at the poses and its
 // full eigen-decomposition from the centred clusters (voxel-major order).
 __global__ void k_exact_vecs(int32_t n_vx, const int64_t *__restrict__ vptr, const double *__restrict__ crec,
-                             const int32_t *__restrict__ cscan, const double *__restrict__ poses,
-                             double *__restrict__ ev) {
+                             const int32_t *__restrict__ cscan, const int32_t *__restrict__ qc,
+                             const double *__restrict__ poses, double *__restrict__ ev) {
     const int v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n_vx) return;
     const int64_t a = vptr[v], b = vptr[v + 1];
@@ -214,7 +183,7 @@ __global__ void k_exact_vecs(int32_t n_vx, const int64_t *__restrict__ vptr, con
         sym_mv(St, u0, su);
 #pragma unroll
         for (int r = 0; r < 3; r++) w0[r] = n * e0 * y[r] + su[r];
-        double *o = ev + 18 * c;
+        double *o = ev + 18LL * qc[c];
         cross(y, u0, ya);
 #pragma unroll
         for (int r = 0; r < 3; r++) {
@@ -2039,7 +2008,8 @@ __global__ void k_dense_finish(int32_t n_poses, const int32_t *__restrict__ pose
                                const double *__restrict__ g, const double *__restrict__ hdx,
                                const double *__restrict__ poses, double *__restrict__ dx,
                                double *__restrict__ pose_q, int32_t *__restrict__ pose_info,
-                               double *__restrict__ poses_trial) {
+                               double *__restrict__ poses_trial, const double *__restrict__ ref_poses,
+                               double *__restrict__ pdelta) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n_poses) return;
     const int w = pose_window[j];
@@ -2061,20 +2031,7 @@ __global__ void k_dense_finish(int32_t n_poses, const int32_t *__restrict__ pose
         pose_q[j] = -(gdx + 0.5 * dhd);
         pose_info[j] = 0;
     }
-    pose_plus(poses + 12LL * j, xj, poses_trial + 12LL * j);
-}
-
-// Zero the dense matrices of windows whose derivatives are being re-evaluated.
-__global__ void k_dense_zero_stale(int32_t W, const DenseDesc *__restrict__ desc, const int64_t *__restrict__ h_off,
-                                   const LMState *__restrict__ lm, double *__restrict__ dense) {
-    for (int w = 0; w < W; w++) {
-        const LMState &st = lm[w];
-        if (st.done || !st.need_eval) continue;
-        const int64_t a = h_off[w], b = h_off[w + 1];
-        for (int64_t i = a + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < b;
-             i += (int64_t)gridDim.x * blockDim.x)
-            dense[i] = 0.0;
-    }
+    store_trial_pose(poses + 12LL * j, xj, j, poses_trial, ref_poses, pdelta);
 }
 
 // ---------------------------------------------------------------- host side
@@ -2107,8 +2064,9 @@ struct DenseState {
     int32_t n_seg = 0;
     PairSeg *segs = nullptr;
     int32_t *pa = nullptr, *pb = nullptr;
-    double *h = nullptr;
-    // exact form: voxel ranges of the voxel-major clusters, 3 vectors per cluster
+    double *h = nullptr;         // pair vectors, pose-major
+    int32_t *qc = nullptr;       // pose-major place of each (voxel, scan)-order cluster
+    // exact form: voxel ranges of the voxel-major clusters, 3 vectors per cluster (pose-major)
     int32_t n_vx = 0;
     int64_t *vptr = nullptr;
     double *ev = nullptr;
@@ -2182,8 +2140,7 @@ __global__ void k_inv_perm(int64_t C, const int32_t *__restrict__ perm, int32_t 
     if (q < C) inv[perm[q]] = (int32_t)q;
 }
 
-// Sorted pairs: their clusters in the order h is kept in (qc maps a
-// voxel-major cluster to it; null: voxel-major) and a 1 at each new key.
+// Sorted pairs: their clusters in pose-major order (qc) and a 1 at each new key.
 __global__ void k_pair_out(int64_t E, const uint64_t *__restrict__ keys, const uint32_t *__restrict__ vals,
                            const int32_t *__restrict__ ea, const int32_t *__restrict__ eb,
                            const int32_t *__restrict__ qc, int32_t *__restrict__ spa, int32_t *__restrict__ spb,
@@ -2192,8 +2149,8 @@ __global__ void k_pair_out(int64_t E, const uint64_t *__restrict__ keys, const u
     if (r >= E) return;
     const uint32_t o = vals[r];
     const int32_t a = ea[o], b = eb[o];
-    spa[r] = qc ? qc[a] : a;
-    spb[r] = qc ? qc[b] : b;
+    spa[r] = qc[a];
+    spb[r] = qc[b];
     head[r] = (r == 0 || keys[r] != keys[r - 1]) ? 1 : 0;
 }
 
@@ -2257,6 +2214,8 @@ ba_status dense_prepare(Problem *P) {
     BA_TRY(D->mem.alloc(&D->pa, std::max<int64_t>(E, 1)));
     BA_TRY(D->mem.alloc(&D->pb, std::max<int64_t>(E, 1)));
     BA_TRY(D->mem.alloc(&D->h, 6 * std::max<int64_t>(C, 1)));
+    BA_TRY(D->mem.alloc(&D->qc, std::max<int64_t>(C, 1)));
+    hipLaunchKernelGGL(k_inv_perm, dim3(nblk(C)), dim3(256), 0, s, C, P->p_cidx, D->qc);
     D->n_seg = 0;
     if (E > 0) {
         const int32_t NP = P->n_poses;
@@ -2265,7 +2224,7 @@ ba_status dense_prepare(Problem *P) {
         DevArena tmp;
         int64_t *d_poff, *head, *d_total;
         SortBuf sb;
-        int32_t *ea, *eb, *qc = nullptr;
+        int32_t *ea, *eb;
         BA_TRY(tmp.alloc(&d_poff, (int64_t)poff.size()));
         BA_TRY(sb.alloc(tmp, E));
         BA_TRY(tmp.alloc(&ea, E));
@@ -2276,13 +2235,9 @@ ba_status dense_prepare(Problem *P) {
         hipLaunchKernelGGL(k_pair_emit, dim3(nblk(D->n_vx)), dim3(256), 0, s, D->n_vx, D->vptr, d_poff, P->c_scan,
                            bits_b, sb.keys, ea, eb);
         BA_HIP(radix_sort_pairs(sb, E, 0, 2 * bits_b, true, s));
-        // the precision form keeps h in the order of its derivative pass's
-        // cluster copy: the pair lists then index that order
-        if (P->prec == BA_PREC_F32) {
-            BA_TRY(tmp.alloc(&qc, C));
-            hipLaunchKernelGGL(k_inv_perm, dim3(nblk(C)), dim3(256), 0, s, C, P->p_cidx, qc);
-        }
-        hipLaunchKernelGGL(k_pair_out, dim3(nblk(E)), dim3(256), 0, s, E, sb.keys, sb.vals, ea, eb, qc, D->pa, D->pb,
+        // the pair vectors are kept in the order of the derivative pass's
+        // cluster copy, which the pair lists index
+        hipLaunchKernelGGL(k_pair_out, dim3(nblk(E)), dim3(256), 0, s, E, sb.keys, sb.vals, ea, eb, D->qc, D->pa, D->pb,
                            head);
         BA_HIP(exclusive_scan_i64(head, head, E, d_total, sb.ws, s));
         int64_t n_seg = 0;
@@ -2325,6 +2280,9 @@ ba_status dense_prepare(Problem *P) {
     BA_TRY(D->mem.alloc(&D->hdx, 6LL * P->n_poses));
     BA_TRY(D->mem.alloc(&P->dense, std::max<int64_t>(h_tot, 1)));
     P->dense_total = h_tot;
+    // zero once: an assembly rewrites the same pair blocks and nothing else
+    hipLaunchKernelGGL(k_fill, dim3(nblk(std::max<int64_t>(h_tot, 1))), dim3(256), 0, s, std::max<int64_t>(h_tot, 1),
+                       P->dense, 0.0);
     for (int32_t w = 0; w < W; w++) {
         desc[w].linv_off += a_tot;
         desc[w].v_off += a_tot + l_tot;
@@ -2403,6 +2361,7 @@ ba_status dense_prepare(Problem *P) {
             BA_HIP(hipMemcpy(D->bs_tasks, bs.data(), sizeof(BsTask) * bs.size(), hipMemcpyHostToDevice));
         BA_HIP(hipMemcpy(D->bs_bo, bo.data(), sizeof(int64_t) * W, hipMemcpyHostToDevice));
     }
+    BA_HIP(hipStreamSynchronize(s));   // the callers' streams need not wait for this one
     D->ready = true;
     return BA_OK;
 }
@@ -2414,20 +2373,16 @@ ba_status dense_assemble(Problem *P, const double *poses, double *hess_out, bool
     DenseState *D = dense_state(P);
     double *dst = hess_out ? hess_out : P->dense;
     const LMState *lm = use_lm ? P->lm : nullptr;
-    const int64_t C = P->n_clusters;
-    // the precision form takes h from the derivative pass (the same FP32
-    // clusters as the per-pose blocks, so the pair blocks cancel the diagonal
-    // blocks exactly along the translation gauge)
-    if (P->prec != BA_PREC_F32)
-        hipLaunchKernelGGL(k_hvec, dim3(nblk(C)), dim3(256), 0, s, C, P->c_rec, P->c_scan, P->c_slot, poses,
-                           P->vstate, (int64_t)P->n_groups * 64, P->pose_window, lm, D->h);
-    // windows whose derivatives are stale are rebuilt whole; the others keep their matrix
+    // h comes from the derivative pass (the same clusters as the per-pose
+    // blocks, so the pair blocks cancel the diagonal blocks exactly along the
+    // translation gauge).  The pair blocks cover the same entries every time
+    // and the problem's own matrices are zero elsewhere from the start
+    // (dense_prepare), so only a caller's matrix is cleared here; clearing
+    // the stale windows' every iteration and a pass of its own over h took
+    // 26 us of 1390 us an iteration at 500 poses.
     if (!use_lm) {
         const int64_t tot = P->dense_total;
         hipLaunchKernelGGL(k_fill, dim3(nblk(tot)), dim3(256), 0, s, tot, dst, 0.0);
-    } else {
-        hipLaunchKernelGGL(k_dense_zero_stale, dim3(2048), dim3(256), 0, s, P->n_windows, D->desc, D->h_off, lm,
-                           dst);
     }
     if (D->n_seg)
         hipLaunchKernelGGL(k_pairs, dim3(nblk((int64_t)D->n_seg * 64)), dim3(256), 0, s, D->n_seg, D->segs, D->pa,
@@ -2452,13 +2407,10 @@ ba_status dense_assemble_exact(Problem *P, const double *poses, double *hess_out
     double *dst = hess_out ? hess_out : P->dense;
     const LMState *lm = use_lm ? P->lm : nullptr;
     hipLaunchKernelGGL(k_exact_vecs, dim3(nblk(D->n_vx)), dim3(256), 0, s, D->n_vx, D->vptr, P->c_rec,
-                       P->c_scan, poses, D->ev);
+                       P->c_scan, D->qc, poses, D->ev);
     if (!use_lm) {
         const int64_t tot = P->dense_total;
         hipLaunchKernelGGL(k_fill, dim3(nblk(tot)), dim3(256), 0, s, tot, dst, 0.0);
-    } else {
-        hipLaunchKernelGGL(k_dense_zero_stale, dim3(2048), dim3(256), 0, s, P->n_windows, D->desc, D->h_off, lm,
-                           dst);
     }
     if (D->n_seg)
         hipLaunchKernelGGL(k_pairs_x, dim3(nblk((int64_t)D->n_seg * 64)), dim3(256), 0, s, D->n_seg, D->segs, D->pa,
@@ -2600,7 +2552,7 @@ ba_status dense_lm_step(Problem *P, const double *poses, double tol_g, hipStream
                        P->dense, D->h_off, P->dx, D->hdx);
     hipLaunchKernelGGL(k_dense_finish, dim3(nblk(P->n_poses)), dim3(256), 0, s, P->n_poses, P->pose_window,
                        P->win_pose_ptr, D->prm, P->g, D->hdx, poses, P->dx, P->pose_q, P->pose_info,
-                       P->poses_trial);
+                       P->poses_trial, P->ref_poses, P->pdelta);
     BA_HIP(hipGetLastError());
     return BA_OK;
 }

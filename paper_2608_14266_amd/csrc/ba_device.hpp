@@ -241,6 +241,25 @@ __device__ __forceinline__ void pose_delta(const Pose &P, const Pose &P0, PoseDe
     for (int k = 0; k < 3; k++) D.dt[k] = P.t[k] - P0.t[k];
 }
 
+// Pose change of scan j from its reference pose as the precision form's
+// residual pass takes it: E (9) and w = dt - E t0 (3) in a row of 16, so that
+// a cluster's offset from its voxel's reference point c is d = mu' + E (mu' + c) + w.
+__device__ __forceinline__ void store_pose_delta(const Pose &P, const double *__restrict__ ref_poses, int j,
+                                                 double *__restrict__ pdelta) {
+    Pose P0;
+    load_pose(ref_poses, j, P0);
+    PoseDelta D;
+    pose_delta(P, P0, D);
+    double *o = pdelta + 16LL * j;
+#pragma unroll
+    for (int e = 0; e < 9; e++) o[e] = D.E[e];
+#pragma unroll
+    for (int e = 0; e < 3; e++)
+        o[9 + e] = D.dt[e] - fma(D.E[3 * e], P0.t[0], fma(D.E[3 * e + 1], P0.t[1], D.E[3 * e + 2] * P0.t[2]));
+#pragma unroll
+    for (int e = 12; e < 16; e++) o[e] = 0.0;
+}
+
 // D = E S + S E^T + E S E^T for symmetric S (6 unique), so that
 // (I + E) S (I + E)^T = S + D with D of the size of E.
 template <typename T>
@@ -546,6 +565,23 @@ __device__ __forceinline__ void pose_plus(const double *T, const double *x, doub
     out[9] = T[9] + x[3];
     out[10] = T[10] + x[4];
     out[11] = T[11] + x[5];
+}
+
+// The trial pose of scan j, and in the precision form (pdelta not null) its
+// change from the reference pose, which the trial residual pass reads: a
+// launch of its own over all poses took 4.8 us an iteration.
+__device__ __forceinline__ void store_trial_pose(const double *T, const double *x, int j, double *poses_trial,
+                                                 const double *__restrict__ ref_poses, double *__restrict__ pdelta) {
+    Pose P;
+    double o[12];
+    pose_plus(T, x, o);
+#pragma unroll
+    for (int e = 0; e < 9; e++) P.r[e] = o[e];
+#pragma unroll
+    for (int e = 0; e < 3; e++) P.t[e] = o[9 + e];
+#pragma unroll
+    for (int e = 0; e < 12; e++) poses_trial[12LL * j + e] = o[e];
+    if (pdelta) store_pose_delta(P, ref_poses, j, pdelta);
 }
 
 }  // namespace ba

@@ -55,6 +55,7 @@ struct VoxSums {
 struct SrcF64 {
     using T = double;
     const char *tiles;
+    double *h;                 // [C][6] coupled pair vectors, written when not null
 };
 struct SrcF32 {
     using T = float;
@@ -76,28 +77,15 @@ __device__ __forceinline__ int32_t tile_id(const char *tiles, int64_t i) {
     return reinterpret_cast<const int32_t *>(tiles + (i >> 6) * Tile<T>::BYTES + Tile<T>::IDS)[i & 63];
 }
 
-// Pose change of every scan for the precision form's residual pass:
-// E = R R0^T - I and w = dt - E t0 with dt = t - t0 (one thread per pose),
-// so that a cluster's offset from its voxel's reference point c is
-// d = mu' + E (mu' + c) + w.
+// Pose change of every scan for the precision form's residual pass (one
+// thread per pose; trial poses get theirs where they are formed).
 __global__ void k_pose_delta(int32_t n, const double *__restrict__ poses, const double *__restrict__ ref_poses,
                              double *__restrict__ pdelta) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
-    Pose P, P0;
+    Pose P;
     load_pose(poses, j, P);
-    load_pose(ref_poses, j, P0);
-    PoseDelta D;
-    pose_delta(P, P0, D);
-    double Et0[3];
-    rot(D.E, P0.t, Et0);
-    double *o = pdelta + 16LL * j;
-#pragma unroll
-    for (int e = 0; e < 9; e++) o[e] = D.E[e];
-#pragma unroll
-    for (int e = 0; e < 3; e++) o[9 + e] = D.dt[e] - Et0[e];
-#pragma unroll
-    for (int e = 12; e < 16; e++) o[e] = 0.0;
+    store_pose_delta(P, ref_poses, j, pdelta);
 }
 
 template <typename T>
@@ -508,12 +496,28 @@ struct PoseCtx {
     float E[9];
 };
 
-__device__ __forceinline__ void pose_cluster(const PoseCtx &cx, const double *cv, const double *st, double *acc) {
+// Pair vector of the coupled form, h = (N_ij / N_i) [y x u ; u], of cluster q
+// in pose-major order (the pair plan indexes it so).
+__device__ __forceinline__ void store_pair_vector(double *__restrict__ h, int64_t q, double n, const double *y,
+                                                  const double *u, double sc) {
+    const double f = n * (0.5 * sc);
+    double a[3];
+    cross(y, u, a);
+    double *o = h + 6 * q;
+    o[0] = f * a[0]; o[1] = f * a[1]; o[2] = f * a[2];
+    o[3] = f * u[0]; o[4] = f * u[1]; o[5] = f * u[2];
+}
+
+template <bool HVEC>
+__device__ __forceinline__ void pose_cluster(const SrcF64 &src, const PoseCtx &cx, int64_t q, const double *cv,
+                                             const double *st, double *acc) {
     const double n = cv[0];
     const double *mu = cv + 1, *S = cv + 4;
     const double u[3] = {st[0], st[1], st[2]};
     double y[3], St[6];
     rot(cx.P.r, mu, y);
+    if constexpr (HVEC)
+        if (src.h) store_pair_vector(src.h, q, n, y, u, st[6]);
     rot_sym(cx.P.r, S, St);
     const double d[3] = {y[0] + cx.P.t[0] - st[3], y[1] + cx.P.t[1] - st[4], y[2] + cx.P.t[2] - st[5]};
     pose_terms(n, y, dot(u, d), St, u, st[6], acc, acc + 6);
@@ -544,15 +548,7 @@ __device__ __forceinline__ void pose_cluster(const SrcF32 &src, const PoseCtx &c
     }
     const double u64[3] = {st[0], st[1], st[2]};
     if constexpr (HESS64) {
-        if (src.h) {
-            // h = (N_ij / N_i) [y x u ; u] of the coupled form
-            const double f = (double)n * (0.5 * st[6]);
-            double a[3];
-            cross(y64, u64, a);
-            double *o = src.h + 6 * q;   // pose-major order (the pair plan indexes it so)
-            o[0] = f * a[0]; o[1] = f * a[1]; o[2] = f * a[2];
-            o[3] = f * u64[0]; o[4] = f * u64[1]; o[5] = f * u64[2];
-        }
+        if (src.h) store_pair_vector(src.h, q, (double)n, y64, u64, st[6]);
         double Sd[6], Dl64[6], S64[6];
 #pragma unroll
         for (int k = 0; k < 6; k++) Sd[k] = (double)S[k];
@@ -671,7 +667,7 @@ __global__ __launch_bounds__(256) void k_pose(const ChunkDesc *__restrict__ chun
                 if constexpr (F32)
                     pose_cluster<HESS64>(src, cx, q, cv, st, c, acc, hacc);
                 else
-                    pose_cluster(cx, cv, st, acc);
+                    pose_cluster<HESS64>(src, cx, q, cv, st, acc);
             }
         }
         if constexpr (F32 && !HESS64) {
@@ -688,9 +684,21 @@ __global__ __launch_bounds__(256) void k_pose(const ChunkDesc *__restrict__ chun
 }
 
 // One thread per (pose, component): fixed-order sum over the pose's chunks.
-__global__ void k_reduce_partials(int32_t n_poses, const int32_t *__restrict__ chunk_ptr,
-                                  const double *__restrict__ partials, const int32_t *__restrict__ pose_window,
-                                  const LMState *__restrict__ lm, double *__restrict__ g, double *__restrict__ H) {
+// The blocks from n_red on, one per window, sum the window's residual instead
+// (an evaluation outside the LM loop: its own launch took 3.3-5 us, a fifth of
+// the evaluation of a ten-scan window: 22.2 -> 18.2 us).
+__global__ __launch_bounds__(DECIDE_THREADS) void k_reduce_partials(
+    int32_t n_poses, const int32_t *__restrict__ chunk_ptr, const double *__restrict__ partials,
+    const int32_t *__restrict__ pose_window, const LMState *__restrict__ lm, double *__restrict__ g,
+    double *__restrict__ H, int32_t n_red, const int32_t *__restrict__ win_group_ptr,
+    const double *__restrict__ group_cost, double *__restrict__ cost) {
+    if ((int)blockIdx.x >= n_red) {
+        __shared__ double red[DECIDE_THREADS / 64];
+        const int w = (int)blockIdx.x - n_red;
+        const double c = window_cost_sum(win_group_ptr[w], win_group_ptr[w + 1], group_cost, red);
+        if (threadIdx.x == 0) cost[w] = c;
+        return;
+    }
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (tid >= (int64_t)n_poses * NPART) return;
     const int j = (int)(tid / NPART), k = (int)(tid % NPART);
@@ -751,8 +759,8 @@ __global__ void k_voxel_eig(int64_t n_slots, const int32_t *__restrict__ slot_vo
 
 static inline unsigned nblk(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
-static SrcF64 src64(Problem *P, bool vox, bool = false) {
-    return SrcF64{vox ? P->v_tiles : P->p_tiles};
+static SrcF64 src64(Problem *P, bool vox, bool hvec = false) {
+    return SrcF64{vox ? P->v_tiles : P->p_tiles, hvec && !vox ? dense_hvec(P) : nullptr};
 }
 static SrcF32 src32(Problem *P, bool vox, bool hvec = false) {
     return vox ? SrcF32{P->v_tiles, P->ref_poses, P->v_ref, P->pdelta, nullptr, nullptr}
@@ -775,7 +783,8 @@ void launch_vox(Problem *P, const double *poses, bool use_lm, bool trial, hipStr
     const LMState *lm = use_lm ? P->lm : nullptr;
     const dim3 grid(pass_grid(P->n_vblocks, 1, P->tune.vox_grid, P->n_cu));
     const int t = trial ? 1 : 0;
-    if (P->prec == BA_PREC_F32)
+    // the pose changes of trial poses come from the kernel that formed the poses
+    if (P->prec == BA_PREC_F32 && !trial)
         hipLaunchKernelGGL(k_pose_delta, dim3(nblk(P->n_poses)), dim3(256), 0, s, P->n_poses, poses, P->ref_poses,
                            P->pdelta);
     const bool pers = P->tune.vox_grid > 0;
@@ -840,6 +849,9 @@ void launch_pose_chunks(Problem *P, const double *poses, bool use_lm, hipStream_
             if (pers) BA_POSE(SrcF32, true, false, src32);
             else BA_POSE(SrcF32, false, false, src32);
         }
+    } else if (hess64) {
+        if (pers) BA_POSE(SrcF64, true, true, src64);
+        else BA_POSE(SrcF64, false, true, src64);
     } else {
         if (pers) BA_POSE(SrcF64, true, false, src64);
         else BA_POSE(SrcF64, false, false, src64);
@@ -848,10 +860,15 @@ void launch_pose_chunks(Problem *P, const double *poses, bool use_lm, hipStream_
 }
 
 void launch_pose_derivs(Problem *P, const double *poses, bool use_lm, double *g, double *H, hipStream_t s,
-                        bool hess64) {
+                        bool hess64, double *cost) {
     launch_pose_chunks(P, poses, use_lm, s, hess64);
-    hipLaunchKernelGGL(k_reduce_partials, dim3(nblk((int64_t)P->n_poses * NPART)), dim3(256), 0, s, P->n_poses,
-                       P->chunk_ptr, P->partials, P->pose_window, use_lm ? P->lm : nullptr, g, H);
+    // blocks of 256 threads unless the window sums ride along, which take the
+    // decision kernel's block (in the LM loop the larger ones took 1 us longer)
+    const int t = cost ? DECIDE_THREADS : 256;
+    const unsigned n_red = nblk((int64_t)P->n_poses * NPART, t);
+    hipLaunchKernelGGL(k_reduce_partials, dim3(n_red + (cost ? P->n_windows : 0)), dim3(t), 0, s, P->n_poses,
+                       P->chunk_ptr, P->partials, P->pose_window, use_lm ? P->lm : nullptr, g, H, (int32_t)n_red,
+                       P->win_group_ptr, P->wave_cost, cost);
 }
 
 void launch_voxel_eig(Problem *P, double *out, hipStream_t s) {

@@ -65,7 +65,7 @@ void stream_put(hipStream_t s, int device);           // idle
 // stream at once, so release waits for the device unless the owner has set
 // `drained`: every stream that used the arena has been synchronised.
 struct DevArena {
-    static constexpr size_t SLAB = (size_t)2 << 20, SMALL = SLAB / 8;
+    static constexpr size_t SLAB = (size_t)2 << 20, SMALL = SLAB / 8, PAGE = 4096;
     std::vector<DevBlock> ptrs;
     char *slab = nullptr;
     size_t slab_left = 0;
@@ -91,14 +91,15 @@ struct DevArena {
         }
         void *q = nullptr;
         if (nba <= SMALL) {
-            if (nba > slab_left) {
+            const size_t take = (nb + PAGE - 1) / PAGE * PAGE;
+            if (take > slab_left) {
                 BA_TRY(alloc_block(&q, SLAB));
                 slab = (char *)q;
                 slab_left = SLAB;
             }
             q = slab;
-            slab += nba;
-            slab_left -= nba;
+            slab += take;
+            slab_left -= take;
         } else {
             BA_TRY(alloc_block(&q, nb));
         }

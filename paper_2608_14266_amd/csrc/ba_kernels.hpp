@@ -9,10 +9,11 @@ namespace ba {
 // evaluation (ba_eval.hip)
 void launch_vox(Problem *P, const double *poses, bool use_lm, bool trial, hipStream_t s);
 void launch_window_cost(Problem *P, double *out, hipStream_t s);
-// hess64: FP64 Hessian terms also in the precision form (the coupled form needs them)
+// hess64: the coupled form's pass: FP64 Hessian terms also in the precision form, and the pair vectors
 void launch_pose_chunks(Problem *P, const double *poses, bool use_lm, hipStream_t s, bool hess64 = false);
+// cost: NULL, or the windows' residuals at the same poses, summed in the same launch
 void launch_pose_derivs(Problem *P, const double *poses, bool use_lm, double *g, double *H, hipStream_t s,
-                        bool hess64 = false);
+                        bool hess64 = false, double *cost = nullptr);
 void launch_voxel_eig(Problem *P, double *out, hipStream_t s);
 
 // LM (ba_lm.hip)

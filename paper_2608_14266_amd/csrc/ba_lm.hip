@@ -129,7 +129,8 @@ __global__ void k_solve_mm_lm(int32_t n_poses, const int32_t *__restrict__ pose_
                               const int32_t *__restrict__ win_pose_ptr, const LMState *__restrict__ lm,
                               const double *__restrict__ H, const double *__restrict__ g,
                               const double *__restrict__ poses, double *__restrict__ dx, double *__restrict__ pose_q,
-                              int32_t *__restrict__ pose_info, double *__restrict__ poses_trial) {
+                              int32_t *__restrict__ pose_info, double *__restrict__ poses_trial,
+                              const double *__restrict__ ref_poses, double *__restrict__ pdelta) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n_poses) return;
     const int w = pose_window[j];
@@ -139,7 +140,7 @@ __global__ void k_solve_mm_lm(int32_t n_poses, const int32_t *__restrict__ pose_
     const int info = solve_pose(H + 36LL * j, g + 6LL * j, st.mu, 1e-12 * st.maxdiag, dx + 6LL * j, q);
     pose_q[j] = q;
     pose_info[j] = info ? 6 * (j - win_pose_ptr[w]) + info : 0;
-    pose_plus(poses + 12LL * j, dx + 6LL * j, poses_trial + 12LL * j);
+    store_trial_pose(poses + 12LL * j, dx + 6LL * j, j, poses_trial, ref_poses, pdelta);
 }
 
 // block per window: predicted reduction, trial cost, gain ratio, damping update.
@@ -242,7 +243,8 @@ __device__ __forceinline__ bool record_stats(LMState &st, double gs, double mx, 
 __global__ __launch_bounds__(WSOLVE_BLOCK) void k_window_solve_mm(
     int32_t W, const int32_t *__restrict__ win_pose_ptr, LMState *__restrict__ lm, const double *__restrict__ g,
     const double *__restrict__ H, const double *__restrict__ poses, double *__restrict__ dx,
-    double *__restrict__ pose_q, int32_t *__restrict__ pose_info, double *__restrict__ poses_trial, double tol_g) {
+    double *__restrict__ pose_q, int32_t *__restrict__ pose_info, double *__restrict__ poses_trial, double tol_g,
+    const double *__restrict__ ref_poses, double *__restrict__ pdelta) {
     __shared__ double red[2 * (WSTAT_THREADS / 64)];
     __shared__ int s_done;
     const int w = blockIdx.x;
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(WSOLVE_BLOCK) void k_window_solve_mm(
     const int info = solve_pose(H + 36LL * j, g + 6LL * j, mu, fl, dx + 6LL * j, q);
     pose_q[j] = q;
     pose_info[j] = info ? 6 * (j - p0) + info : 0;
-    pose_plus(poses + 12LL * j, dx + 6LL * j, poses_trial + 12LL * j);
+    store_trial_pose(poses + 12LL * j, dx + 6LL * j, j, poses_trial, ref_poses, pdelta);
 }
 
 __global__ __launch_bounds__(WSTAT_THREADS) void k_window_stats_mm(int32_t W,
@@ -303,13 +305,13 @@ void launch_window_solve_mm(Problem *P, const double *poses, double tol_g, hipSt
                            P->win_pose_ptr, P->lm, P->g, P->H, tol_g);
         hipLaunchKernelGGL(k_solve_mm_lm, dim3((unsigned)((P->n_poses + 255) / 256)), dim3(256), 0, s, P->n_poses,
                            P->pose_window, P->win_pose_ptr, P->lm, P->H, P->g, poses, P->dx, P->pose_q, P->pose_info,
-                           P->poses_trial);
+                           P->poses_trial, P->ref_poses, P->pdelta);
         return;
     }
     const unsigned nb = (unsigned)std::max(1, (widest + WSOLVE_BLOCK - 1) / WSOLVE_BLOCK);
     hipLaunchKernelGGL(k_window_solve_mm, dim3(P->n_windows, nb), dim3(WSOLVE_BLOCK), 0, s, P->n_windows,
                        P->win_pose_ptr, P->lm, P->g, P->H, poses, P->dx, P->pose_q, P->pose_info, P->poses_trial,
-                       tol_g);
+                       tol_g, P->ref_poses, P->pdelta);
 }
 
 // ---------------------------------------------------------------- standalone MM solve
