@@ -369,11 +369,11 @@ __global__ void k_damp_copy(const DenseDesc *__restrict__ desc, const DenseParam
     if (t < d.n) work[d.v_off + t] = -g[6LL * d.pose0 + t];
 }
 
-// Broadcast lane `src` (wave-uniform) of a wave-wide double to every lane.
-__device__ __forceinline__ double bcast(double v, int src) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
-    return __hiloint2double(hi, lo);
+// Broadcast lane J of every row of 16 lanes to that row.
+template <int J>
+__device__ __forceinline__ double row_bcast(double v) {
+    return __longlong_as_double(
+        __builtin_amdgcn_mov_dpp(__double_as_longlong(v), 0x150 + J /* row_newbcast:J */, 0xf, 0xf, true));
 }
 
 // 1/sqrt(p): the hardware estimate (about 23 bits) refined by one third-order
@@ -394,118 +394,183 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Workgroup barrier that orders LDS accesses only: global stores in flight are
+// not waited for, and global accesses may move across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 static constexpr int LTS = TB + 1;   // padded LDS row stride of the tile and the inverse
 static constexpr int PB = 16;        // panel / block width inside the diagonal block
 static constexpr int NPB = TB / PB;  // panels per diagonal block
 
-// One 16 x 16 x 16 product on matrix cores for the calling wave:
-// acc0 + acc1 += sgn * A B with A and B 16 x 16 blocks (row stride LTS) in
-// LDS, the K steps alternating between the two accumulators so that two
-// product chains are in flight; accumulator register r holds row lane/16 + 4r,
-// column lane%16 (the v_mfma_f64_16x16x4f64 layout).
-__device__ __forceinline__ void mma16(const double *__restrict__ Ab, const double *__restrict__ Bb, double sgn,
-                                      d4 &acc0, d4 &acc1) {
+// A 16 x 16 block as operand of v_mfma_f64_16x16x4f64: lane (lane%16, lane/16)
+// holds entries (lane%16, lane/16 + 4 r).  The accumulator of a product holds
+// entries (lane/16 + 4 r, lane%16), so the accumulator of a transposed product
+// is itself an operand.
+__device__ __forceinline__ d4 block_rows(const double *__restrict__ B) {
     const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
+    d4 v;
 #pragma unroll
-    for (int kk = 0; kk < PB; kk += 8) {
-        const double a0 = sgn * Ab[li * LTS + kk + lk], b0 = Bb[(kk + lk) * LTS + li];
-        const double a1 = sgn * Ab[li * LTS + kk + 4 + lk], b1 = Bb[(kk + 4 + lk) * LTS + li];
-        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc1, 0, 0, 0);
-    }
+    for (int r = 0; r < 4; r++) v[r] = B[li * LTS + lk + 4 * r];
+    return v;
 }
 
-// The same with B given transposed: acc0 + acc1 += sgn * A C^T for 16 x 16
-// blocks A and C (row stride LTS) in LDS.
-__device__ __forceinline__ void mma16_nt(const double *__restrict__ Ab, const double *__restrict__ Cb, double sgn,
-                                         d4 &acc0, d4 &acc1) {
+// The same of a block stored transposed, or of the right operand of a product.
+__device__ __forceinline__ d4 block_cols(const double *__restrict__ B) {
     const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
+    d4 v;
 #pragma unroll
-    for (int kk = 0; kk < PB; kk += 8) {
-        const double a0 = sgn * Ab[li * LTS + kk + lk], b0 = Cb[li * LTS + kk + lk];
-        const double a1 = sgn * Ab[li * LTS + kk + 4 + lk], b1 = Cb[li * LTS + kk + 4 + lk];
-        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc1, 0, 0, 0);
-    }
+    for (int r = 0; r < 4; r++) v[r] = B[(lk + 4 * r) * LTS + li];
+    return v;
 }
 
-// X_qq = L_qq^-1 for the 16 x 16 diagonal block q of the factor in T, by one
-// wave: lane c < 16 solves L_qq x = e_c by forward substitution, taking
-// 1/L_rr from rd; the entries of column r + 1 are read from LDS while column
-// r is applied.
-__device__ __forceinline__ void inverse_diag_block(const double *__restrict__ T, double *__restrict__ X,
-                                                   const double *__restrict__ rd, int q) {
-    const int l = threadIdx.x & 63, c = l & 15;
-    const int b0 = PB * q;
-    double rdv[PB];
+__device__ __forceinline__ void put_cols(double *__restrict__ B, const d4 v) {
+    const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
 #pragma unroll
-    for (int r = 0; r < PB; r++) rdv[r] = rd[b0 + r];
-    double x[PB];
+    for (int r = 0; r < 4; r++) B[(lk + 4 * r) * LTS + li] = v[r];
+}
+
+// c + a b for operands a and b, in two chains of products.
+__device__ __forceinline__ d4 mma16(const d4 a, const d4 b, d4 c) {
+    d4 c1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int r = 0; r < PB; r++) x[r] = (r == c) ? 1.0 : 0.0;
-    double lc[PB];
-#pragma unroll
-    for (int s = 1; s < PB; s++) lc[s] = T[(b0 + s) * LTS + b0];
-#pragma unroll
-    for (int r = 0; r < PB; r++) {
-        double ln[PB];
-        if (r + 1 < PB) {
-#pragma unroll
-            for (int s = r + 2; s < PB; s++) ln[s] = T[(b0 + s) * LTS + b0 + r + 1];
-        }
-        x[r] *= rdv[r];
-#pragma unroll
-        for (int s = r + 1; s < PB; s++) x[s] = fma(-lc[s], x[r], x[s]);
-        if (r + 1 < PB) {
-#pragma unroll
-            for (int s = r + 2; s < PB; s++) lc[s] = ln[s];
-        }
+    for (int r = 0; r < 4; r += 2) {
+        c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], b[r], c, 0, 0, 0);
+        c1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r + 1], b[r + 1], c1, 0, 0, 0);
     }
+    return c + c1;
+}
+
+// x += w * (x of lane J of the row of 16 lanes), eight values at a time: the
+// FP64 multiply-add takes the DPP row broadcast as an operand, which the
+// compiler does not form.  The leading wait covers the two wait states between
+// a vector write and a DPP read of it (the compiler does not look into the
+// block); no value depends on another, and x0 to x5 may be read by DPP right
+// after.
+template <int J>
+__device__ __forceinline__ void row_fmac8(double &x0, double &x1, double &x2, double &x3, double &x4, double &x5,
+                                          double &x6, double &x7, double w) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %0, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %1, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %2, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %3, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %4, %4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %5, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %6, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %7, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3), "+v"(x4), "+v"(x5), "+v"(x6), "+v"(x7)
+        : "v"(w), "n"(J));
+}
+
+// Pivot J (value pv, in every lane) of a 16 x 16 block held one row per lane
+// (a: row li, b: its right-hand side), four copies in the four rows of 16
+// lanes.  The elimination runs on [block | identity] in place: column J, once
+// eliminated, becomes column J of the identity's side (whose unit diagonal is
+// left out), so every pivot updates the 15 other columns.  The next pivot is
+// formed from broadcast values, ahead of the updates.  own: this lane's pivot.
+template <int J>
+__device__ __forceinline__ void block_pivots(double (&a)[PB], double &b, double pv, double &own, int li) {
+    constexpr int N = (J + 1) % PB;
+    const double s = row_bcast<J>(a[N]), dn = row_bcast<N>(a[N]);
+    const double rj = rsq_refined(pv);
+    const double pv_next = fma(-(s * rj) * rj, s, dn);
+    const double nw = li > J ? -(a[J] * rj) * rj : 0.0;
+    a[J] = nw;
+    own = li == J ? pv : own;
+    row_fmac8<J>(a[(J + 2) % PB], a[(J + 1) % PB], a[(J + 3) % PB], a[(J + 4) % PB], a[(J + 5) % PB],
+                 a[(J + 6) % PB], a[(J + 7) % PB], a[(J + 8) % PB], nw);
+    row_fmac8<J>(a[(J + 9) % PB], a[(J + 10) % PB], a[(J + 11) % PB], a[(J + 12) % PB], a[(J + 13) % PB],
+                 a[(J + 14) % PB], a[(J + 15) % PB], b, nw);
+    if constexpr (J + 1 < PB) block_pivots<J + 1>(a, b, pv_next, own, li);
+}
+
+// Diagonal block p of the tile in T (both triangles, layout of
+// put_diag_elem) with right-hand side b (row li of the block in lane li of
+// each row of lanes), by one wave: X_pp = L_pp^-1 into X and y_p = X_pp b_p
+// into yv.  Returns 0, or the 1-based index within the block of the first
+// pivot that is not a positive normal number.
+__device__ __forceinline__ int factor_block(const double *__restrict__ T, double *__restrict__ X,
+                                            double *__restrict__ yv, int p, double b) {
+    const int l = threadIdx.x & 63, li = l & 15, c0 = PB * p;
+    double a[PB], own = 0.0;
+#pragma unroll
+    for (int k = 0; k < PB; k++) a[k] = T[(c0 + li) * LTS + c0 + k];
+    block_pivots<0>(a, b, row_bcast<0>(a[0]), own, li);
+    const unsigned long long bad = __ballot(!(own >= 2.2250738585072014e-308 && own <= 1.7976931348623157e308));
+    const double rs = rsq_refined(own);
     if (l < PB) {
+        double *Xr = X + (c0 + l) * LTS + c0;
 #pragma unroll
-        for (int r = 0; r < PB; r++) X[(b0 + r) * LTS + b0 + l] = x[r];
+        for (int k = 0; k < PB; k++) Xr[k] = a[k] * rs;
+        Xr[l] = rs;
+        yv[c0 + l] = b * rs;
     }
+    return bad ? __builtin_ctzll(bad) + 1 : 0;
 }
 
-// X_qj = -X_qq sum_{k=j}^{q-1} L_qk X_kj for the column blocks j in [jb, je)
-// of row block q, by one wave on matrix cores (X_qq and the row blocks of X
-// above q must be complete).
-__device__ __forceinline__ void inverse_off_blocks(const double *__restrict__ T, double *__restrict__ X, int q,
-                                                   int jb, int je) {
-    const int l = threadIdx.x & 63, li = l & 15, lk = l >> 4;
-    const int b0 = PB * q;
-    for (int j = jb; j < je; j++) {
-        d4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = s0;
-        for (int k = j; k < q; k++) mma16(T + b0 * LTS + PB * k, X + PB * k * LTS + PB * j, 1.0, s0, s1);
-        // the accumulator of S is already in the B operand layout
-        const d4 s = s0 + s1;
-        d4 o0 = {0.0, 0.0, 0.0, 0.0}, o1 = o0;
-#pragma unroll
-        for (int r = 0; r < 4; r += 2) {
-            const double a0 = -X[(b0 + li) * LTS + b0 + 4 * r + lk];
-            const double a1 = -X[(b0 + li) * LTS + b0 + 4 * r + 4 + lk];
-            o0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, s[r], o0, 0, 0, 0);
-            o1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, s[r + 1], o1, 0, 0, 0);
-        }
-        const d4 o = o0 + o1;
-#pragma unroll
-        for (int r = 0; r < 4; r++) X[(b0 + lk + 4 * r) * LTS + PB * j + li] = o[r];
-    }
+// L_Ip = A_Ip X_pp^T (row block I > p) as an operand, by one wave.
+__device__ __forceinline__ d4 panel_block(const double *__restrict__ T, const double *__restrict__ X, int I, int p) {
+    return mma16(block_rows(X + PB * p * LTS + PB * p), block_rows(T + PB * I * LTS + PB * p),
+                 d4{0.0, 0.0, 0.0, 0.0});
 }
 
-// Store, by one wave, the panel's rows of the forward result and (store_L)
-// the finished columns of panel pp (the lower triangle of the nb x nb block
-// within them).
-__device__ __forceinline__ void write_panel_L(const double *__restrict__ T, const double *__restrict__ yv,
-                                              double *__restrict__ A, double *__restrict__ y, int64_t n, int64_t k0,
-                                              int nb, int pp, int lane, bool store_L) {
-    const int c = PB * pp + (lane & 15);
-    if (store_L) {
-#pragma unroll 4
-        for (int r = PB * pp + (lane >> 4); r < nb; r += 4)
-            if (c <= r) A[(k0 + r) * n + k0 + c] = T[r * LTS + c];
-    }
-    if (lane < PB && PB * pp + lane < nb) y[PB * pp + lane] = yv[PB * pp + lane];
+// Block (p, I) of T, above the diagonal, keeps L_Ip^T.
+__device__ __forceinline__ void keep_panel(double *__restrict__ T, int I, int p, const d4 L) {
+    put_cols(T + PB * p * LTS + PB * I, L);
+}
+
+// A_IJ -= L_Ip L_Jp^T in T, by one wave.
+__device__ __forceinline__ void trailing_block(double *__restrict__ T, int I, int J, const d4 LI, const d4 LJ) {
+    double *B = T + PB * I * LTS + PB * J;
+    put_cols(B, mma16(-LI, LJ, block_cols(B)));
+}
+
+// Sum over the four lanes of equal lane%16, in every lane: the exchanges of
+// rows of 16 and of halves that gfx950 has in vector registers.
+__device__ __forceinline__ double rows_sum(double s) {
+    unsigned lo = __double2loint(s), hi = __double2hiint(s);
+    auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    s = __hiloint2double(b[0], a[0]) + __hiloint2double(b[1], a[1]);
+    lo = __double2loint(s), hi = __double2hiint(s);
+    a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return __hiloint2double(b[0], a[0]) + __hiloint2double(b[1], a[1]);
+}
+
+// Row lane%16 of L_Ip y_p, in every lane.
+__device__ __forceinline__ double panel_rhs(const d4 L, const double *__restrict__ y) {
+    const int lk = (threadIdx.x & 63) >> 4;
+    double s = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; r++) s = fma(L[r], y[lk + 4 * r], s);
+    return rows_sum(s);
+}
+
+// Block (q, j) of the inverse, X_qj = -X_qq S_qj with S_qj = sum_{k=j}^{q-1}
+// L_qk X_kj, by one wave: the part j <= k < kend of the sum (as the right
+// operand of a product), and the block.
+__device__ __forceinline__ d4 inverse_sum(const double *__restrict__ T, const double *__restrict__ X, int q, int j,
+                                          int kend) {
+    d4 s = {0.0, 0.0, 0.0, 0.0};
+    for (int k = j; k < kend; k++)
+        s = mma16(block_cols(T + PB * k * LTS + PB * q), block_cols(X + PB * k * LTS + PB * j), s);
+    return s;
+}
+
+__device__ __forceinline__ void inverse_block(double *__restrict__ X, int q, int j, const d4 s) {
+    put_cols(X + PB * q * LTS + PB * j, mma16(-block_rows(X + PB * q * LTS + PB * q), s, d4{0.0, 0.0, 0.0, 0.0}));
+}
+
+// Store through the caches to agent scope, so that the releases that publish
+// tiles find nothing to write back (a release took up to 6 us while other
+// workgroups of the XCD had stores in its L2; 3000 rows 1.02 -> 0.95 ms).
+__device__ __forceinline__ void store_through(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Store, by one wave, row block q of the inverse (64 columns, zero above the
@@ -514,7 +579,7 @@ __device__ __forceinline__ void write_inverse_rows(const double *__restrict__ X,
                                                    int lane) {
 #pragma unroll
     for (int r = PB * q; r < PB * (q + 1); r++)
-        linv[r * TB + lane] = (lane < PB * (q + 1)) ? X[r * LTS + lane] : 0.0;
+        store_through(linv + r * TB + lane, (lane < PB * (q + 1)) ? X[r * LTS + lane] : 0.0);
 }
 
 // Element (r, c) of a diagonal tile into the LDS layout the factor expects:
@@ -531,142 +596,119 @@ __device__ __forceinline__ void put_diag_elem(double *__restrict__ T, int r, int
 // Factor one 64 x 64 diagonal block (A_kk = L L^T), forward-substitute its
 // slice of the right-hand side (y = L^-1 b) and invert the factor
 // (X = L^-1), with four wavefronts and the tile held in LDS, blocked by
-// 16 x 16 blocks:
-//  - factorization, right-looking by 16-column panels.  Wave 0 factors a
-//    panel with lane r holding row r's 16 panel entries in registers.  The
-//    pivot's column is taken from row pr of lane pr (the panel's diagonal
-//    block is read symmetrically from the lower triangle), broadcast through
-//    scalar registers in one batch per pivot, and the next pivot is formed
-//    from broadcast values as soon as 1/sqrt of the current one is known.  The
-//    update of a row uses w_r = L_r,pr / L_pr,pr against the unscaled pivot
-//    row (one fma per entry); the right-hand side is carried the same way and
-//    scaled once at the end of the panel.  Then the panel's rank-16 update of
-//    the trailing blocks runs on matrix cores (one 16 x 16 block per wave at a
-//    time);
-//  - inverse, by 16 x 16 blocks, one and two panels behind the factorization:
-//    while wave 0 factors panel p, wave 1 inverts diagonal block p - 1 and
-//    wave 2 forms the off-diagonal blocks of row block p - 2 on matrix cores
-//    (X_qj = -X_qq sum_k L_qk X_kj); what is left follows the last panel;
-//  - finished panels, right-hand side rows and inverse row blocks are stored
-//    by wave 3 while the factorization goes on.
+// 16 x 16 blocks.  What bounds it is the serial chain of 64 pivots, so only
+// the 16 x 16 diagonal blocks are eliminated pivot by pivot (factor_block: one
+// row per lane, the pivot row broadcast by the DPP row broadcast that the
+// gfx950 FP64 moves have, in vector registers throughout); the same pass leaves
+// the block's inverse, and all the rest is products on matrix cores:
+//  - wave 0 does nothing but the critical chain: block p is factored, then
+//    L_p+1,p = A_p+1,p X_pp^T and the update of diagonal block p + 1 follow in
+//    its registers and it goes on with that block, one barrier per block;
+//  - the other waves meanwhile form the L_Ip that they need (some of them
+//    twice, rather than behind another barrier), the other updates, the row
+//    blocks of the inverse above, and store what is finished.
+// Carrying all 64 rows through the pivots in scalar broadcasts, with the
+// inverse by substitution beside it, took 15.0 us per block; this takes 10.8 us
+// with the tile's last terms included (the dataflow's `pre`, 1.6 us).
 // Only the lower triangle of the tile is read; the 16 x 16 diagonal blocks are
-// mirrored in LDS and kept in both triangles by the trailing updates, so a
-// panel reads its rows straight from the tile.
-// The block is held in T (layout of put_diag_elem) with the right-hand side
-// slice in yv; X, rdiag, pvs and sfail are LDS work space (sfail zero on
-// entry).  The caller has synchronised after filling them.  Writes y to
-// y[0..nb), L^-1 (64 x 64, zero above the diagonal) to linv and, with
-// store_L, the lower triangle of L to the block at A[k0.., k0..] (row stride
-// n; no later step reads it: the solves use L^-1).  Returns 0,
-// or the 1-based row index of a pivot that is not a positive normal number:
-// the factorization stops there (the caller records it as prm.info; the
-// panels stored before it are left in the work buffer, which no later kernel
-// reads once info is set).
+// mirrored in LDS and kept in both triangles by the trailing updates.
+// The block is held in T (layout of put_diag_elem; the blocks above the
+// diagonal are work space) with the right-hand side slice in yv; X and sfail
+// are LDS work space (sfail zero on entry).  `pre` is run by each wave first:
+// wave 0 fills block (0, 0) and yv[0..16), the others the rest but blocks (2, 2),
+// (3, 2) and (3, 3), which `late` fills in waves 1, 2 and 3 a block later (or
+// the caller has filled all and synchronised).  Writes y to y[0..nb) and L^-1
+// (64 x 64, zero above the diagonal) to linv; L itself is not stored (the
+// later steps and the solves use L^-1).  Returns 0, or the 1-based row index
+// of a pivot that is not a positive normal number: the factorization stops
+// there (the caller records it as prm.info; what was stored before it is left
+// in the work buffer, which no later kernel reads once info is set).
+// Only waves 1 to 3 store; on return X and yv are complete, the stores may be
+// in flight.
+template <class Pre, class Late>
 __device__ __forceinline__ int factor_diag_tile(double *__restrict__ T, double *__restrict__ X,
-                                                double *__restrict__ yv, double *__restrict__ rdiag,
-                                                double *__restrict__ pvs, int &sfail, double *__restrict__ A,
-                                                int64_t n, int64_t k0, int nb, double *__restrict__ y,
-                                                double *__restrict__ linv, bool store_L) {
-    const int t = threadIdx.x;
-    const int w = t >> 6;
-    const int i = t & 63;
+                                                double *__restrict__ yv, int &sfail, int64_t k0, int nb,
+                                                double *__restrict__ y, double *__restrict__ linv, Pre pre,
+                                                Late late) {
+    const int w = threadIdx.x >> 6;
+    const int i = threadIdx.x & 63, li = i & 15;
+    d4 s = {0.0, 0.0, 0.0, 0.0};
+    pre(w);
 #pragma unroll 1
     for (int p = 0; p < NPB; p++) {
-        const int c0 = PB * p;
+        const int c0 = PB * p, cp = c0 - PB;   // of this block and of the one before
         if (w == 0) {
-            // row i of the panel (the diagonal blocks are kept in both triangles)
-            double a[PB];
-#pragma unroll
-            for (int k = 0; k < PB; k++) a[k] = T[i * LTS + c0 + k];
-            double bi = yv[i];
-            double pv = bcast(a[0], c0);
-            double s[PB];
-#pragma unroll
-            for (int k = 1; k < PB; k++) s[k] = bcast(a[k], c0);
-            double dn = bcast(a[1], c0 + 1);
-            double bpr = bcast(bi, c0);
-#pragma unroll
-            for (int j = 0; j < PB; j++) {
-                const int pr = c0 + j;
-                const double rj = rsq_refined(pv);
-                double pv_next = 0.0;
-                if (j + 1 < PB) pv_next = fma(-(s[j + 1] * rj) * rj, s[j + 1], dn);
-                const double lij = (i == pr) ? pv * rj : a[j] * rj;
-                const double wv = (i > pr) ? lij * rj : 0.0;
-                a[j] = lij;
-#pragma unroll
-                for (int k = j + 1; k < PB; k++) a[k] = fma(-wv, s[k], a[k]);
-                bi = fma(-wv, bpr, bi);
-                // rows above pr land in the unused upper triangle
-                T[i * LTS + pr] = lij;
-                rdiag[pr] = rj;
-                pvs[pr] = pv;
-                if (j + 1 < PB) {
-#pragma unroll
-                    for (int k = j + 2; k < PB; k++) s[k] = bcast(a[k], pr + 1);
-                    if (j + 2 < PB) dn = bcast(a[j + 2], pr + 2);
-                    bpr = bcast(bi, pr + 1);
-                    pv = pv_next;
+            double b;
+            if (p == 0) {
+                wave_sync();
+                b = yv[li];
+            } else {
+                const d4 L = panel_block(T, X, p, p - 1);
+                b = yv[c0 + li] - panel_rhs(L, yv + cp);
+                trailing_block(T, p, p, L, L);
+                wave_sync();
+            }
+            const int f = factor_block(T, X, yv, p, b);
+            if (f && i == 0) sfail = (int)(k0 + c0 + f);
+        } else if (p == 1) {
+            late(w);
+            wave_sync();
+            // wave 1: (2,1) (2,2) and rows 2 of b; wave 2: (3,1) (3,2); wave 3: (3,3) and rows 3
+            const d4 L3 = panel_block(T, X, w == 1 ? 2 : 3, 0);
+            if (w == 3) {
+                trailing_block(T, 3, 3, L3, L3);
+                keep_panel(T, 3, 0, L3);
+            } else {
+                const d4 L1 = panel_block(T, X, 1, 0);
+                const d4 L2 = w == 1 ? L3 : panel_block(T, X, 2, 0);
+                trailing_block(T, w + 1, 1, L3, L1);
+                trailing_block(T, w + 1, 2, L3, L2);
+                if (w == 1) {
+                    keep_panel(T, 1, 0, L1);
+                    keep_panel(T, 2, 0, L2);
                 }
             }
-            wave_sync();
-            // the panel's pivots checked at once; rows of the panel get
-            // y = residual / L_ii, the rows below keep their residual
-            const double pl = pvs[c0 + (i & 15)];
-            const bool bad = (i < PB) && !(pl >= 2.2250738585072014e-308 && pl <= 1.7976931348623157e308);
-            const unsigned long long bm = __ballot(bad);
-            if (i == 0 && bm) sfail = (int)(k0 + c0 + __builtin_ctzll(bm) + 1);
-            if (i >= c0) yv[i] = (i < c0 + PB) ? bi * rdiag[i] : bi;
-        } else if (w == 1 && p >= 1) {
-            inverse_diag_block(T, X, rdiag, p - 1);
-        } else if (w == 2 && p >= 2) {
-            inverse_off_blocks(T, X, p - 2, 0, p - 2);
-        } else if (w == 3 && p >= 1) {
-            // finished parts go out while the factorization continues: the
-            // columns and right-hand side rows of the previous panel, and the
-            // row block of the inverse completed two panels ago
-            write_panel_L(T, yv, A, y, n, k0, nb, p - 1, i, store_L);
-            if (p >= 3) write_inverse_rows(X, linv, p - 3, i);
+            if (w != 2) {
+                const int r = PB * (w == 1 ? 2 : 3) + li;
+                const double b = yv[r] - panel_rhs(L3, yv);
+                if (i < PB) yv[r] = b;
+            }
+            if (w == 3) write_inverse_rows(X, linv, 0, i);
+        } else if (p == 2) {
+            if (w == 1) {
+                inverse_block(X, 1, 0, inverse_sum(T, X, 1, 0, 1));
+            } else {
+                const d4 L3 = panel_block(T, X, 3, 1);
+                if (w == 2) {
+                    const d4 L2 = panel_block(T, X, 2, 1);
+                    trailing_block(T, 3, 2, L3, L2);
+                    keep_panel(T, 2, 1, L2);
+                } else {
+                    trailing_block(T, 3, 3, L3, L3);
+                    keep_panel(T, 3, 1, L3);
+                    const double b = yv[3 * PB + li] - panel_rhs(L3, yv + PB);
+                    if (i < PB) yv[3 * PB + li] = b;
+                }
+            }
+        } else if (p == 3) {
+            // row block 2, and the sums of row block 3: wave w the column
+            // block w - 1 of both
+            const int j = w - 1;
+            if (j < 2) {
+                inverse_block(X, 2, j, inverse_sum(T, X, 2, j, 2));
+                wave_sync();
+            }
+            s = mma16(panel_block(T, X, 3, 2), block_cols(X + 2 * PB * LTS + PB * j), inverse_sum(T, X, 3, j, 2));
+            if (w == 3) write_inverse_rows(X, linv, 1, i);
         }
-        __syncthreads();
+        lds_barrier();
         if (sfail) return sfail;
-        // rank-16 update of the trailing blocks (I >= J > p) on matrix cores
-        const int nt = NPB - 1 - p;
-        const int nblk = nt * (nt + 1) / 2;
-        for (int b = w; b < nblk; b += 4) {
-            int bi_ = 0;
-            while ((bi_ + 1) * (bi_ + 2) / 2 <= b) bi_++;
-            const int bj = b - bi_ * (bi_ + 1) / 2;
-            const int R = c0 + PB * (1 + bi_), Cc = c0 + PB * (1 + bj);
-            const int li = i & 15, lk = i >> 4;
-            d4 acc0, acc1 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int r = 0; r < 4; r++) acc0[r] = T[(R + lk + 4 * r) * LTS + Cc + li];
-            mma16_nt(T + R * LTS + c0, T + Cc * LTS + c0, -1.0, acc0, acc1);
-            const d4 acc = acc0 + acc1;
-#pragma unroll
-            for (int r = 0; r < 4; r++) T[(R + lk + 4 * r) * LTS + Cc + li] = acc[r];
-        }
-        if (nblk > 0) __syncthreads();
     }
-    // the rest of the inverse: diagonal block 3 (wave 0) and the two
-    // off-diagonal blocks of row block 2 (waves 1, 2), then those of row
-    // block 3, one per wave; wave 3 writes the last panel meanwhile
-    if (w == 0) inverse_diag_block(T, X, rdiag, NPB - 1);
-    else if (w == 1) inverse_off_blocks(T, X, NPB - 2, 1, 2);
-    else if (w == 2) inverse_off_blocks(T, X, NPB - 2, 0, 1);
-    else write_panel_L(T, yv, A, y, n, k0, nb, NPB - 1, i, store_L);
-    __syncthreads();
-    if (w < NPB - 1) inverse_off_blocks(T, X, NPB - 1, w, w + 1);
-    else write_inverse_rows(X, linv, 1, i);
-    __syncthreads();
-    // row blocks 2 and 3 of the inverse (zero above the diagonal blocks)
-#pragma unroll
-    for (int u = 0; u < 2 * PB * TB / 256; u++) {
-        const int e = t + 256 * u;
-        const int r = 2 * PB + (e >> 6), c = e & 63;
-        linv[r * TB + c] = (r / PB >= c / PB) ? X[r * LTS + c] : 0.0;
-    }
+    if (w >= 1) inverse_block(X, 3, w - 1, s);
+    lds_barrier();
+    if (w == 1) write_inverse_rows(X, linv, 2, i);
+    if (w == 2) write_inverse_rows(X, linv, 3, i);
+    if (w == 3 && i < nb) store_through(y + i, yv[i]);
     return 0;
 }
 
@@ -675,8 +717,6 @@ __global__ __launch_bounds__(256) void k_potf2(const DenseDesc *__restrict__ des
     __shared__ __align__(16) double T[TB * LTS];
     __shared__ __align__(16) double X[TB * LTS];
     __shared__ double yv[TB];
-    __shared__ double rdiag[TB];
-    __shared__ double pvs[TB];
     __shared__ int sfail;
     const int m = blockIdx.y;
     const DenseParam pm = prm[m];
@@ -705,8 +745,8 @@ __global__ __launch_bounds__(256) void k_potf2(const DenseDesc *__restrict__ des
     if (t < TB) yv[t] = work[d.v_off + k0 + std::min(t, nb - 1)] * (t < nb ? 1.0 : 0.0);
     if (t == 0) sfail = 0;
     __syncthreads();
-    const int f = factor_diag_tile(T, X, yv, rdiag, pvs, sfail, A, d.n, k0, nb, work + d.v_off + k0,
-                                   work + d.linv_off + (int64_t)step * TB * TB, true);
+    const int f = factor_diag_tile(T, X, yv, sfail, k0, nb, work + d.v_off + k0,
+                                   work + d.linv_off + (int64_t)step * TB * TB, [](int) {}, [](int) {});
     if (f && t == 0 && f <= d.n) prm[m].info = f;
 }
 
@@ -1036,9 +1076,11 @@ __global__ __launch_bounds__(256) void k_backsub_rows(const DenseDesc *__restric
 //    L_j+1,j = P_j+1,j L_jj^-T, with the inverse still in LDS.  Only the
 //    walker's work lies on the critical path, and it never waits for a
 //    launch boundary;
-//  - by column c = 0, 1, ...: tile tasks L_ic = (A_ic - sum_{k<c} L_ik L_ck^T)
-//    L_cc^-T for i >= c + 3, then the two partial sums of row r = c + 2 that
-//    the walker takes at its steps r - 1 and r, each left in place: P_rr with
+//  - by column c = 0, 1, ...: the two partial sums of row r = c + 2 that the
+//    walker takes next (at its steps r - 1 and r; ahead of the column's other
+//    tasks they are in time for it: 6000 rows 4.31 -> 3.95 ms), then the tile
+//    tasks L_ic = (A_ic - sum_{k<c} L_ik L_ck^T) L_cc^-T for i >= c + 3.  The
+//    partial sums are left in place: P_rr with
 //    the right-hand side rows b_r - sum_{k<=c} L_rk y_k, and P_r,r-1 =
 //    A_r,r-1 - sum_{k<=c} L_rk L_r-1,k^T.  Both tasks form L_rc themselves
 //    (the same arithmetic, so the same bits), beside their partial sums and
@@ -1121,7 +1163,7 @@ __device__ __forceinline__ bool flow_poll(glb_i32 *f, glb_i32 *ab, glb_i32 *gab,
 
 // All threads: waits until *f is set; false on abandon or abort.
 __device__ __forceinline__ bool flow_wait(glb_i32 *f, glb_i32 *ab, glb_i32 *gab, int limit, lds_i32 *s_val) {
-    __syncthreads();
+    lds_barrier();
     if (threadIdx.x == 0) {
         *s_val = flow_poll(f, ab, gab, limit) ? 1 : 0;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -1136,7 +1178,7 @@ __device__ __forceinline__ bool flow_wait(glb_i32 *f, glb_i32 *ab, glb_i32 *gab,
 template <int NR>
 __device__ __forceinline__ int flow_wait_cols(const FlowMat &fm, const int (&rows)[NR], int klo, int kend,
                                               glb_i32 *gab, int limit, lds_i32 *s_val) {
-    __syncthreads();
+    lds_barrier();
     if (threadIdx.x == 0) {
         bool ok = true;
         for (int q = 0; q < NR && ok; q++) ok = flow_poll(fm.fl + rows[q] * fm.T + klo, fm.ab, gab, limit);
@@ -1164,26 +1206,20 @@ __device__ __forceinline__ void flow_publish(glb_i32 *f) {
     if (threadIdx.x == 0) flag_set(f, __ATOMIC_RELEASE);
 }
 
-// All threads: waits until *f1 and *f2 are set; false on abandon or abort.
+// All threads: waits until *f1 and *f2 are set; false on abandon or abort.  The
+// caller has a barrier between its uses, so that thread 0 polls at once.
 __device__ __forceinline__ bool flow_wait2(glb_i32 *f1, glb_i32 *f2, glb_i32 *ab, glb_i32 *gab, int limit,
                                            lds_i32 *s_val) {
-    __syncthreads();
     if (threadIdx.x == 0) {
-        *s_val = (flow_poll(f1, ab, gab, limit) && flow_poll(f2, ab, gab, limit)) ? 1 : 0;
+        const int r1 = flag_get(f1), r2 = flag_get(f2);   // both in flight
+        *s_val = (limit >= 0 && r1 && r2) ||
+                         (flow_poll(f1, ab, gab, limit) && flow_poll(f2, ab, gab, limit))
+                     ? 1
+                     : 0;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
     return *s_val != 0;
-}
-
-// flow_publish of two flags behind one fence.
-__device__ __forceinline__ void flow_publish2(glb_i32 *f1, glb_i32 *f2) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        flag_set(f1, __ATOMIC_RELEASE);
-        flag_set(f2, __ATOMIC_RELAXED);
-    }
 }
 
 // Tile M[r0.., c0..] (row stride ld) into LDS S (row stride LTS), zero
@@ -1233,7 +1269,7 @@ __device__ __forceinline__ void acc_to_global(const d4 acc[2][2], double *__rest
 #pragma unroll
             for (int r = 0; r < 4; r++)
                 if ((int)ACC_ROW(rb, r) < nr && (int)ACC_COL(cb) < nc)
-                    M[(r0 + ACC_ROW(rb, r)) * ld + c0 + ACC_COL(cb)] = acc[rb][cb][r];
+                    store_through(M + (r0 + ACC_ROW(rb, r)) * ld + c0 + ACC_COL(cb), acc[rb][cb][r]);
 }
 
 // Into LDS (row stride LTS), rows >= nr cleared.
@@ -1330,17 +1366,18 @@ __device__ __forceinline__ void tile_syrk_y(double *__restrict__ lds, const doub
 }
 
 // ---- the walker's tile products, shaped by their triangular operands
-// A 64 x 64 diagonal tile by its ten lower 16 x 16 blocks (rb >= cb, taken
-// in the order (0,0), (1,0), (1,1), (2,0), ..., (3,3)): wave w holds blocks
-// w, w + 4 and (waves 0, 1) w + 8, each in the v_mfma_f64_16x16x4f64
-// accumulator layout.
+// A 64 x 64 diagonal tile by its ten lower 16 x 16 blocks: wave 0, on the
+// critical chain, holds (0,0); wave w > 0 holds (w,0) and (w,1), which the
+// factor takes first, and of (2,2), (3,2), (3,3) the w-th; each in the
+// v_mfma_f64_16x16x4f64 accumulator layout.
 struct LowTile {
     d4 b[3];
 };
 
-__device__ __forceinline__ void low_block(int q, int &rb, int &cb) {
-    rb = q >= 6 ? 3 : (q >= 3 ? 2 : (q >= 1 ? 1 : 0));
-    cb = q - rb * (rb + 1) / 2;
+__device__ __forceinline__ void low_block(int w, int s, int &rb, int &cb) {
+    rb = s < 2 ? w : min(w + 1, 3);
+    cb = w == 0 ? 0 : (s < 2 ? s : max(w, 2));
+    if (w == 0) rb = 0;
 }
 
 // Loads the lower blocks of tile M[r0.., r0..] (row stride ld), zero outside
@@ -1351,8 +1388,7 @@ __device__ __forceinline__ void low_load(LowTile &D, const double *__restrict__ 
 #pragma unroll
     for (int s = 0; s < 3; s++) {
         int rb, cb;
-        low_block(w + 4 * s, rb, cb);
-        if (s == 2 && w >= 2) rb = cb = 0;
+        low_block(w, s, rb, cb);
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             const int row = 16 * rb + lk + 4 * r, col = 16 * cb + li;
@@ -1362,7 +1398,7 @@ __device__ __forceinline__ void low_load(LowTile &D, const double *__restrict__ 
 #pragma unroll
     for (int s = 0; s < 3; s++) {
         int rb, cb;
-        low_block(w + 4 * s, rb, cb);
+        low_block(w, s, rb, cb);
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             const int row = 16 * rb + lk + 4 * r, col = 16 * cb + li;
@@ -1377,8 +1413,8 @@ __device__ __forceinline__ void low_damp(LowTile &D, double mu, double floor_) {
 #pragma unroll
     for (int s = 0; s < 3; s++) {
         int rb, cb;
-        low_block(w + 4 * s, rb, cb);
-        if (rb != cb || (s == 2 && w >= 2)) continue;
+        low_block(w, s, rb, cb);
+        if (rb != cb || (s > 0 && w == 0)) continue;
 #pragma unroll
         for (int r = 0; r < 4; r++)
             if (lk + 4 * r == li) {
@@ -1388,14 +1424,16 @@ __device__ __forceinline__ void low_damp(LowTile &D, double mu, double floor_) {
     }
 }
 
-// D -= L L^T on the lower blocks, L (64 x 64) in LDS with row stride LTS.
+// D -= L L^T on the lower blocks S0 <= s < S1 of each wave, L (64 x 64) in LDS
+// with row stride LTS.
+template <int S0, int S1>
 __device__ __forceinline__ void low_syrk_sub(LowTile &D, const double *__restrict__ L) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
 #pragma unroll
-    for (int s = 0; s < 3; s++) {
-        if (s == 2 && w >= 2) break;
+    for (int s = S0; s < S1; s++) {
+        if (s > 0 && w == 0) break;
         int rb, cb;
-        low_block(w + 4 * s, rb, cb);
+        low_block(w, s, rb, cb);
         d4 a0 = D.b[s], a1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int kk = 0; kk < TB; kk += 8) {
@@ -1408,15 +1446,16 @@ __device__ __forceinline__ void low_syrk_sub(LowTile &D, const double *__restric
     }
 }
 
-// The lower blocks into the factor's LDS layout (put_diag_elem); the blocks
-// above the diagonal are never read.
+// The lower blocks S0 <= s < S1 of each wave into the factor's LDS layout
+// (put_diag_elem).
+template <int S0, int S1>
 __device__ __forceinline__ void low_put(const LowTile &D, double *__restrict__ T, int nb) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
 #pragma unroll
-    for (int s = 0; s < 3; s++) {
-        if (s == 2 && w >= 2) break;
+    for (int s = S0; s < S1; s++) {
+        if (s > 0 && w == 0) break;
         int rb, cb;
-        low_block(w + 4 * s, rb, cb);
+        low_block(w, s, rb, cb);
 #pragma unroll
         for (int r = 0; r < 4; r++) put_diag_elem(T, 16 * rb + lk + 4 * r, 16 * cb + li, nb, D.b[s][r]);
     }
@@ -1451,7 +1490,7 @@ __device__ __forceinline__ void rows_to_global(const RowTile &L, double *__restr
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             const int row = 16 * w + lk + 4 * r;
-            if (row < nr) M[(r0 + row) * ld + c0 + 16 * cb + li] = L.c[cb][r];
+            if (row < nr) store_through(M + (r0 + row) * ld + c0 + 16 * cb + li, L.c[cb][r]);
         }
 }
 
@@ -1503,7 +1542,7 @@ __device__ __forceinline__ void flow_solve_tile(const d4 raw[2][2], int nr, cons
         for (int cb = 0; cb < 2; cb++) p[rb][cb] = raw[rb][cb] - acc[rb][cb];
     acc_to_lds(p, Pl, nr);
     tile_to_lds(Xl, linv_c, TB, 0, 0, TB, TB);
-    __syncthreads();
+    lds_barrier();
     rows_trsm(Pl, Xl, l);
 }
 
@@ -1542,22 +1581,23 @@ __device__ __noinline__ void flow_pdiag(const DenseDesc d, glb_f64 *gwork, const
     double *Pl = lds, *Xl = lds + TB * LTS, *ys = lds + 2 * TB * LTS;
     RowTile l;
     flow_solve_tile(raw, nr, work + d.linv_off + (int64_t)c * TB * TB, aa, Pl, Xl, l);
-    __syncthreads();
+    lds_barrier();
     rows_to_lds(l, Pl, nr);
     if (threadIdx.x < TB) ys[threadIdx.x] = v[C0 + threadIdx.x];
-    __syncthreads();
+    lds_barrier();
     mma64_nt<false>(Pl, Pl, 1.0, ac);
     q += lds_gemv_part(Pl, ys);
     acc_sub(rrr, ac);
     acc_to_global(rrr, A, n, R0, R0, nr, nr);
     q = row_sum4(q);
-    if ((threadIdx.x & 3) == 0 && row < nr) v[R0 + row] = -graw - q;
+    if ((threadIdx.x & 3) == 0 && row < nr) store_through(v + R0 + row, -graw - q);
     flow_publish(fm.pd + r);
 }
 
 // Off-diagonal partial task of row r = c + 2: L_rc (its sums formed beside
-// those of the partial) and P_r,r-1 with the last term L_rc L_c+1,c^T (the
-// walker's tile of step c), published behind one fence.
+// those of the partial), published as soon as it is formed, since the next
+// row's task takes it, and P_r,r-1 with the last term L_rc L_c+1,c^T (the
+// walker's tile of step c).
 __device__ __noinline__ void flow_poff(const DenseDesc d, glb_f64 *gwork, const FlowRaw rw, const FlowMat fm, int r,
                                       int c, glb_i32 *gab, int limit, lds_f64 *glds, lds_i32 *s_val) {
     double *work = (double *)gwork, *lds = (double *)glds;
@@ -1584,19 +1624,21 @@ __device__ __noinline__ void flow_poff(const DenseDesc d, glb_f64 *gwork, const 
         tile_gemm_nt_acc(lds, lds + TB * LDK, A, n, R0, ka, n, n, A, n, C1, ka, n, n, ab, TB * (khi - klo));
         klo = khi;
     }
-    if (!flow_wait2(fm.dg + c, fm.fl + (c + 1) * fm.T + c, fm.ab, gab, limit, s_val)) return;
+    if (!flow_wait(fm.dg + c, fm.ab, gab, limit, s_val)) return;
     double *Pl = lds, *Xl = lds + TB * LTS, *Ll = lds + 2 * TB * LTS;
-    tile_to_lds(Ll, A, n, C1, C0, TB, TB);   // L_c+1,c, loaded beside the inverse
     RowTile l;
     flow_solve_tile(raw, nr, work + d.linv_off + (int64_t)c * TB * TB, aa, Pl, Xl, l);
-    rows_to_global(l, A, n, R0, C0, nr);    // stored while the last term is formed
-    __syncthreads();
+    rows_to_global(l, A, n, R0, C0, nr);
+    flow_publish(fm.fl + r * fm.T + c);
+    // block c is published ahead of the tile L_c+1,c that the last term takes
+    if (!flow_wait(fm.fl + (c + 1) * fm.T + c, fm.ab, gab, limit, s_val)) return;
     rows_to_lds(l, Pl, nr);
-    __syncthreads();
+    tile_to_lds(Ll, A, n, C1, C0, TB, TB);
+    lds_barrier();
     mma64_nt<false>(Pl, Ll, 1.0, ab);
     acc_sub(rrp, ab);
     acc_to_global(rrp, A, n, R0, C1, nr, TB);
-    flow_publish2(fm.po + r, fm.fl + r * fm.T + c);
+    flow_publish(fm.po + r);
 }
 
 // Tile task: L_ic = (A_ic - sum_{k<c} L_ik L_ck^T) L_cc^-T for i >= c + 3.
@@ -1635,48 +1677,84 @@ __device__ __forceinline__ void flow_abandon(glb_i32 *info, const FlowMat &fm, i
     }
 }
 
+// Waves 1 to 3, each after its stores: the last of them to arrive publishes
+// them (`count` starts at 0 and counts arrivals).  Returns to every lane of
+// that wave whether it is the one.
+__device__ __forceinline__ bool flow_last_wave(lds_i32 *count) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    int old = 0;
+    if ((threadIdx.x & 63) == 0)
+        old = __hip_atomic_fetch_add((int *)count, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return __builtin_amdgcn_readfirstlane(old) % 3 == 2;
+}
+
 // Walker of one matrix (see above).  LDS: the factor's tile and inverse
-// (lds, lds + TB * LTS), its vectors, and ybuf (y of the previous block).
-// Step j factors D_j (held in dacc, b_j in bq), then waits once for both
-// partial sums of block row j + 1, solves L_j+1,j while D_j+1 and b_j+1 load,
-// forms their last terms, and publishes block j and that tile behind one
-// fence.  L_jj itself is not stored.
+// (lds, lds + TB * LTS), the tile L_j,j-1 (lds + 2 * TB * LTS), yv, and ybuf (y
+// of the previous block).  Step j factors D_j, then waits once for both partial
+// sums of block row j + 1, solves L_j+1,j while D_j+1 and b_j+1 load, and forms
+// their last terms.  Wave 0 carries the critical chain: it forms only block
+// (0, 0) of D_j+1 and the first 16 rows of b_j+1 and goes on to factor them,
+// while the other waves form the rest and store and publish: block j (its
+// inverse and y) while wave 0 waits, the tile L_j+1,j during the first block of
+// the next step, when its stores have been acknowledged.  L_jj itself is not stored.  A step took 23.6 us with the
+// last terms and the publishing between the factors, and takes 15.9 us.
 __device__ __noinline__ void flow_walk(const DenseDesc d, glb_i32 *info, glb_f64 *gwork, const FlowRaw rw,
                                       const FlowMat fm, glb_i32 *gab, int limit, lds_f64 *glds, lds_f64 *gyv,
-                                      lds_f64 *grdiag, lds_f64 *gpvs, lds_f64 *gybuf, lds_i32 *gsfail,
-                                      lds_i32 *s_val) {
-    double *work = (double *)gwork, *lds = (double *)glds, *yv = (double *)gyv, *rdiag = (double *)grdiag;
+                                      lds_f64 *gybuf, lds_i32 *gsfail, lds_i32 *s_val, lds_i32 *count) {
+    double *work = (double *)gwork, *lds = (double *)glds, *yv = (double *)gyv;
     const double *H = (const double *)rw.H, *g = (const double *)rw.g;
-    double *pvs = (double *)gpvs, *ybuf = (double *)gybuf;
+    double *ybuf = (double *)gybuf;
     int &sfail = *(int *)gsfail;
     const int64_t n = d.n;
     double *A = work + d.a_off, *v = work + d.v_off;
-    double *Tl = lds, *Xl = lds + TB * LTS;
+    double *Tl = lds, *Xl = lds + TB * LTS, *Ll = lds + 2 * TB * LTS;
     const int t = threadIdx.x, row = t >> 2;
+    if (t == 0) {
+        sfail = 0;
+        *count = 0;
+    }
     // blocks 0 and 1 have no partial sums: raw tiles
     int nb = (int)std::min<int64_t>(TB, n);
     LowTile dt;
     low_load(dt, H, n, 0, nb);
     low_damp(dt, rw.mu, rw.floor_);
     double bq = (row < nb) ? -g[std::min(row, nb - 1)] : 0.0;
+    lds_barrier();
     for (int j = 0; j < fm.T; j++) {
         const int64_t k0 = (int64_t)TB * j;
-        low_put(dt, Tl, nb);
-        if ((t & 3) == 0) yv[row] = bq;
-        if (t == 0) sfail = 0;
-        __syncthreads();
-        const int f = factor_diag_tile(Tl, Xl, yv, rdiag, pvs, sfail, A, n, k0, nb, v + k0,
-                                       work + d.linv_off + (int64_t)j * TB * TB, false);
+        const int f = factor_diag_tile(
+            Tl, Xl, yv, sfail, k0, nb, v + k0, work + d.linv_off + (int64_t)j * TB * TB, [&](int w) {
+                double c[6];
+                if (j > 0 && w > 0) {
+                    // wave 0 stores nothing: its rows of L_j,j-1 from LDS
+#pragma unroll
+                    for (int u = 0; u < 6; u++) c[u] = Ll[min(w - 1 + 3 * u, PB - 1) * LTS + (t & 63)];
+#pragma unroll
+                    for (int u = 0; u < 6; u++) {
+                        const int r = w - 1 + 3 * u;
+                        if (r < std::min(PB, nb)) store_through(A + (k0 + r) * n + k0 - TB + (t & 63), c[u]);
+                    }
+                }
+                if (j > 0) {   // the last terms, with L_j,j-1 in Ll
+                    low_syrk_sub<0, 2>(dt, Ll);
+                    bq -= row_sum4(lds_gemv_part(Ll, ybuf));
+                }
+                low_put<0, 2>(dt, Tl, nb);
+                if ((t & 3) == 0) yv[row] = bq;
+                if (j > 0 && w > 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            },
+            [&](int) {
+                if (j > 0 && t == 192) flag_set(fm.fl + j * fm.T + j - 1, __ATOMIC_RELEASE);
+                if (j > 0) low_syrk_sub<2, 3>(dt, Ll);
+                low_put<2, 3>(dt, Tl, nb);
+            });
         if (f) {
             flow_abandon(info, fm, f);
             return;
         }
-        __syncthreads();
-        if (t < TB) ybuf[t] = yv[t];
-        if (j + 1 >= fm.T) {
-            flow_publish(fm.dg + j);
-            break;
-        }
+        if (t >= 192) ybuf[t - 192] = yv[t - 192];
+        if (t >= 64 && flow_last_wave(count) && (t & 63) == 0) flag_set(fm.dg + j, __ATOMIC_RELEASE);
+        if (j + 1 >= fm.T) break;
         // partial sums of block row j + 1 (raw for j = 0)
         if (j >= 1 && !flow_wait2(fm.po + j + 1, fm.pd + j + 1, fm.ab, gab, limit, s_val)) {
             flow_abandon(info, fm, -1);
@@ -1686,23 +1764,17 @@ __device__ __noinline__ void flow_walk(const DenseDesc d, glb_i32 *info, glb_f64
         const int nr = (int)std::min<int64_t>(TB, n - r0);
         const double *Pj = j == 0 ? H : A;
         tile_to_lds(Tl, Pj, n, r0, k0, nr, TB);
-        __syncthreads();
+        lds_barrier();
         // D_j+1 and b_j+1 are loaded while L_j+1,j = P_j+1,j L_jj^-T is formed
         // with the inverse in LDS
         low_load(dt, Pj, n, r0, nr);
+        if (j == 0) low_damp(dt, rw.mu, rw.floor_);
         bq = (row < nr) ? (j == 0 ? -g[r0 + std::min(row, nr - 1)] : v[r0 + std::min(row, nr - 1)]) : 0.0;
         RowTile l;
         rows_trsm(Tl, Xl, l);
-        rows_to_global(l, A, n, r0, k0, nr);
-        __syncthreads();
-        rows_to_lds(l, Xl, nr);
-        __syncthreads();
-        // the last terms of D_j+1 and b_j+1 (the stores of L_j+1,j complete
-        // meanwhile), then block j and that tile are published
-        if (j == 0) low_damp(dt, rw.mu, rw.floor_);
-        low_syrk_sub(dt, Xl);
-        bq -= row_sum4(lds_gemv_part(Xl, ybuf));
-        flow_publish2(fm.dg + j, fm.fl + (j + 1) * fm.T + j);
+        rows_to_lds(l, Ll, nr);
+        if (t >= 64) rows_to_global(l, A, n, r0, k0, nr);
+        lds_barrier();
         nb = nr;
     }
 }
@@ -1715,8 +1787,8 @@ __global__ __launch_bounds__(256) void k_chol_flow(const DenseDesc *__restrict__
                                                    const int64_t *__restrict__ fo, int *__restrict__ queue,
                                                    int *__restrict__ gab, int limit) {
     __shared__ __align__(16) double lds[3 * TB * LTS];
-    __shared__ double yv[TB], rdiag[TB], pvs[TB], ybuf[TB];
-    __shared__ int s_task, s_val, sfail;
+    __shared__ double yv[TB], ybuf[TB];
+    __shared__ int s_task, s_val, sfail, s_count;
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) s_task = atomicAdd(queue, 1);
@@ -1737,7 +1809,7 @@ __global__ __launch_bounds__(256) void k_chol_flow(const DenseDesc *__restrict__
         lds_i32 *sv = (lds_i32 *)&s_val;
         if (tk.kind == FLOW_WALK)
             flow_walk(d, (glb_i32 *)&prm[tk.m].info, gw, rw, fm, ga, limit, (lds_f64 *)lds, (lds_f64 *)yv,
-                      (lds_f64 *)rdiag, (lds_f64 *)pvs, (lds_f64 *)ybuf, (lds_i32 *)&sfail, sv);
+                      (lds_f64 *)ybuf, (lds_i32 *)&sfail, sv, (lds_i32 *)&s_count);
         else if (tk.kind == FLOW_TILE)
             flow_tile(d, gw, rw, fm, tk.i, tk.c, ga, limit, (lds_f64 *)lds, sv);
         else if (tk.kind == FLOW_PDIAG)
@@ -1755,11 +1827,11 @@ __global__ void k_flow_tasks_one(int32_t T, FlowTask *__restrict__ tasks) {
     if (c >= T) return;
     int64_t o = 1;
     for (int cc = 0; cc < c; cc++) o += std::max(0, T - cc - 3) + (cc + 2 <= T - 1 ? 2 : 0);
-    for (int i = c + 3; i < T; i++) tasks[o++] = FlowTask{0, FLOW_TILE, i, c};
     if (c + 2 <= T - 1) {
-        tasks[o] = FlowTask{0, FLOW_PDIAG, c + 2, c};
-        tasks[o + 1] = FlowTask{0, FLOW_POFF, c + 2, c};
+        tasks[o++] = FlowTask{0, FLOW_PDIAG, c + 2, c};
+        tasks[o++] = FlowTask{0, FLOW_POFF, c + 2, c};
     }
+    for (int i = c + 3; i < T; i++) tasks[o++] = FlowTask{0, FLOW_TILE, i, c};
 }
 
 // ---------------------------------------------------------------- dataflow back substitution
@@ -2315,11 +2387,11 @@ ba_status dense_prepare(Problem *P) {
             for (int32_t c = 0; c < maxT; c++)
                 for (int32_t m = m0; m < m1; m++) {
                     const int32_t T = (desc[m].n + TB - 1) / TB;
-                    for (int32_t i = c + 3; i < T; i++) tasks.push_back(FlowTask{m, FLOW_TILE, i, c});
                     if (c + 2 <= T - 1) {
                         tasks.push_back(FlowTask{m, FLOW_PDIAG, c + 2, c});
                         tasks.push_back(FlowTask{m, FLOW_POFF, c + 2, c});
                     }
+                    for (int32_t i = c + 3; i < T; i++) tasks.push_back(FlowTask{m, FLOW_TILE, i, c});
                 }
             D->flow_count.push_back((int32_t)tasks.size() - D->flow_first.back());
             int64_t work = 0;
