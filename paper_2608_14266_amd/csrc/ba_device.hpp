@@ -2,6 +2,8 @@
 // Wave64 reductions, double-double error-free transforms, small 3x3 algebra.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include "ba_internal.hpp"
 #include <stdint.h>
 
 #define BA_WAVE 64
@@ -565,6 +567,34 @@ __device__ __forceinline__ void pose_plus(const double *T, const double *x, doub
     out[9] = T[9] + x[3];
     out[10] = T[10] + x[4];
     out[11] = T[11] + x[5];
+}
+
+// Component k of pose j's derivatives: its chunks' partial sums in chunk order,
+// stored to g (6) or, both triangles, to H (6x6).
+__device__ __forceinline__ void reduce_pose_value(int j, int k, const int32_t *chunk_ptr, const double *partials,
+                                                  double *g, double *H) {
+    double s = 0.0;
+    const int c0 = chunk_ptr[j], c1 = chunk_ptr[j + 1];
+#pragma unroll 4
+    for (int c = c0; c < c1; c++) s += partials[(int64_t)c * NPART + k];
+    double *h = H + 36LL * j;
+    if (k < 6) {
+        g[6LL * j + k] = s;
+    } else if (k < 12) {
+        const int ii[6] = {0, 0, 0, 1, 1, 2}, jj[6] = {0, 1, 2, 1, 2, 2};
+        const int r = ii[k - 6], c = jj[k - 6];
+        h[6 * r + c] = s;
+        h[6 * c + r] = s;
+    } else if (k < 21) {
+        const int r = (k - 12) / 3, c = (k - 12) % 3;
+        h[6 * r + 3 + c] = s;
+        h[6 * (3 + c) + r] = s;
+    } else {
+        const int ii[6] = {0, 0, 0, 1, 1, 2}, jj[6] = {0, 1, 2, 1, 2, 2};
+        const int r = 3 + ii[k - 21], c = 3 + jj[k - 21];
+        h[6 * r + c] = s;
+        h[6 * c + r] = s;
+    }
 }
 
 // The trial pose of scan j, and in the precision form (pdelta not null) its

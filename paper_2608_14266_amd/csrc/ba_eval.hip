@@ -706,28 +706,7 @@ __global__ __launch_bounds__(DECIDE_THREADS) void k_reduce_partials(
         const LMState &st = lm[pose_window[j]];
         if (st.done || !st.need_eval) return;
     }
-    double s = 0.0;
-    const int c0 = chunk_ptr[j], c1 = chunk_ptr[j + 1];
-#pragma unroll 4
-    for (int c = c0; c < c1; c++) s += partials[(int64_t)c * NPART + k];
-    double *h = H + 36LL * j;
-    if (k < 6) {
-        g[6LL * j + k] = s;
-    } else if (k < 12) {
-        const int ii[6] = {0, 0, 0, 1, 1, 2}, jj[6] = {0, 1, 2, 1, 2, 2};
-        const int r = ii[k - 6], c = jj[k - 6];
-        h[6 * r + c] = s;
-        h[6 * c + r] = s;
-    } else if (k < 21) {
-        const int r = (k - 12) / 3, c = (k - 12) % 3;
-        h[6 * r + 3 + c] = s;
-        h[6 * (3 + c) + r] = s;
-    } else {
-        const int ii[6] = {0, 0, 0, 1, 1, 2}, jj[6] = {0, 1, 2, 1, 2, 2};
-        const int r = 3 + ii[k - 21], c = 3 + jj[k - 21];
-        h[6 * r + c] = s;
-        h[6 * c + r] = s;
-    }
+    reduce_pose_value(j, k, chunk_ptr, partials, g, H);
 }
 
 // One block per window: the window's residual, summed in the order the LM
