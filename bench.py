@@ -216,9 +216,6 @@ def main():
     ba.profile_enable(False)
     vox_ms, vox_n = ba.profile_query("k_vox")
     pose_ms, pose_n = ba.profile_query("k_pose")
-    syrk_ms, syrk_n = ba.profile_query("k_syrk")
-    trsm_ms, trsm_n = ba.profile_query("k_trsm")
-    potf2_ms, potf2_n = ba.profile_query("k_potf2")
     flow_ms, flow_n = ba.profile_query("k_chol_flow")
     bs_ms, bs_n = ba.profile_query("k_backsub_flow")
     ba.profile_reset()
@@ -249,8 +246,7 @@ def main():
             "unit": "GB/s", "frac": round(kern[dom]["gbs"] / HBM_PEAK_GBS, 4), "traffic": traffic,
             "bytes_per_launch": kern[dom]["bytes"], "avg_launch_us": round(kern[dom]["avg_us"], 3)}
     if args.mode == "coupled" and flow_n > 0:
-        # dataflow factorization (one launch per solve, matrices up to 6144
-        # rows): algorithmic flops n^3/3 of one 6N x 6N Cholesky per launch
+        # dataflow factorization (one launch per solve): algorithmic flops n^3/3 of one 6N x 6N Cholesky per launch
         n = 6 * N
         fl = n ** 3 / 3
         tfs = fl * flow_n / (flow_ms * 1e-3) / 1e12
@@ -260,27 +256,6 @@ def main():
         roof = {"kernel": "k_chol_flow", "bound": "mfma", "achieved": round(tfs, 3),
                 "peak": FP64_MFMA_PEAK_TFS, "unit": "TFLOP/s", "frac": round(tfs / FP64_MFMA_PEAK_TFS, 4),
                 "traffic": None, "flops_per_factorization": fl, "avg_launch_us": round(1e3 * flow_ms / flow_n, 3)}
-    elif args.mode == "coupled" and syrk_n > 0:
-        # dense factorization on FP64 matrix cores: algorithmic flops of the
-        # panel solves (rows below x 64 x 64 x 2) and trailing updates
-        # (rows below^2 x 64, lower half) of one 6N x 6N factorization
-        n = 6 * N
-        fl_trsm = fl_syrk = 0
-        for st in range((n + 63) // 64):
-            below = n - 64 * (st + 1)
-            if below > 0:
-                fl_trsm += below * 64 * 64 * 2
-                fl_syrk += below * below * 64
-        n_fact = potf2_n / ((n + 63) // 64)   # one diagonal-block factor per 64-wide step
-        tfs = (fl_trsm + fl_syrk) * n_fact / ((syrk_ms + trsm_ms) * 1e-3) / 1e12
-        kern["k_syrk"] = dict(avg_us=1e3 * syrk_ms / max(syrk_n, 1), launches=syrk_n)
-        kern["k_trsm"] = dict(avg_us=1e3 * trsm_ms / max(trsm_n, 1), launches=trsm_n)
-        kern["k_potf2"] = dict(avg_us=1e3 * potf2_ms / max(potf2_n, 1), launches=potf2_n)
-        kern["factorization"] = dict(count=n_fact, flops=fl_trsm + fl_syrk)
-        roof = {"kernel": "k_syrk+k_trsm", "bound": "mfma", "achieved": round(tfs, 3),
-                "peak": FP64_MFMA_PEAK_TFS, "unit": "TFLOP/s", "frac": round(tfs / FP64_MFMA_PEAK_TFS, 4),
-                "traffic": None, "flops_per_factorization": fl_trsm + fl_syrk,
-                "avg_launch_us": round(1e3 * syrk_ms / max(syrk_n, 1), 3)}
 
     # precision form on the same workload: FP32 voxel-centred clusters, same
     # LM, same number of solves; final poses compared with the FP64 run

@@ -235,10 +235,9 @@ size_t ba_solve_increment_workspace(int32_t mode, int32_t n_scans);
  * scan no voxel constrains would otherwise make singular).
  *   BA_MODE_MM: n_scans independent 6x6 LDL^T factorizations; hess is [N][36].
  *   BA_MODE_COUPLED (or BA_MODE_EXACT): one dense Cholesky of the (6N)^2
- *   row-major hess by 64 x 64 tiles on FP64 matrix cores: up to 6144 rows
- *   in one persistent dataflow launch for the factorization and forward
- *   substitution and one for the back substitution, larger ones blocked
- *   with one launch per step; hess is symmetric and only its lower
+ *   row-major hess by 64 x 64 tiles on FP64 matrix cores, in one persistent
+ *   dataflow launch for the factorization and forward substitution and
+ *   one for the back substitution; hess is symmetric and only its lower
  *   triangle is read.
  * hess, grad: device inputs (unchanged).  dx: device [N][6] output.
  * info: device int32 output, 0, the 1-based index of the first

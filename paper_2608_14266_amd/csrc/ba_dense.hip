@@ -9,13 +9,11 @@
 // each key's contributions in a fixed order and writes that 6x6 block (and
 // its transpose) of the dense per-window matrix.
 //
-// The damped system (H + mu D) dx = -g is solved by a right-looking blocked
-// Cholesky with 64-wide panels (Alg. 2's Solver replaced by a dense one in
-// this coupled form): the diagonal block is factored and inverted in LDS,
-// the panel solve (P L^-T) and the trailing update (C -= P_I P_J^T) run on
-// FP64 matrix cores (v_mfma_f64_16x16x4f64), the forward substitution rides
-// along the panel steps, and the backward substitution sweeps the block
-// rows.  Every kernel is batched over independent windows (blockIdx.y).
+// The damped system (H + mu D) dx = -g is solved by a Cholesky factorization
+// by 64 x 64 tiles (Alg. 2's Solver replaced by a dense one in this coupled
+// form), products on FP64 matrix cores (v_mfma_f64_16x16x4f64): one persistent
+// launch factors the matrices of all windows and forward-substitutes, a second
+// substitutes backwards.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,6 +29,7 @@
 namespace ba {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double v2d __attribute__((ext_vector_type(2)));   // (HIP's double2 arrays stay in memory here)
 
 static constexpr int TB = 64;         // tile / panel width
 static constexpr int LDK = 33;        // LDS row stride of a 32-wide K chunk (padded)
@@ -330,45 +329,11 @@ __device__ __forceinline__ void tile_gemm_nt_acc(double *__restrict__ As, double
     }
 }
 
-// The same product into a cleared accumulator.
-__device__ __forceinline__ void tile_gemm_nt(double *__restrict__ As, double *__restrict__ Bs,
-                                             const double *__restrict__ A, int64_t lda, int64_t ra, int64_t ka,
-                                             int64_t nra, int64_t nca, const double *__restrict__ B, int64_t ldb,
-                                             int64_t rb, int64_t kb, int64_t nrb, int64_t ncb, d4 acc[2][2],
-                                             int kw = 64) {
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-    tile_gemm_nt_acc(As, Bs, A, lda, ra, ka, nra, nca, B, ldb, rb, kb, nrb, ncb, acc, kw);
-}
-
 // element (row, col) of the 64x64 tile held in acc[rb][cb][r] by this lane
 #define ACC_ROW(rb, r) (32 * ((threadIdx.x >> 6) >> 1) + 16 * (rb) + ((threadIdx.x & 63) >> 4) + 4 * (r))
 #define ACC_COL(cb) (32 * ((threadIdx.x >> 6) & 1) + 16 * (cb) + (threadIdx.x & 15))
 
 // ---------------------------------------------------------------- factorization
-// A = H + mu max(diag H, floor) ; v = -g
-__global__ void k_damp_copy(const DenseDesc *__restrict__ desc, const DenseParam *__restrict__ prm,
-                            const double *__restrict__ H, const int64_t *__restrict__ h_off,
-                            const double *__restrict__ g, double *__restrict__ work) {
-    const int m = blockIdx.y;
-    const DenseDesc d = desc[m];
-    const DenseParam p = prm[m];
-    if (!p.active) return;
-    const int64_t nn = (int64_t)d.n * d.n;
-    const double *Hm = H + h_off[m];
-    double *A = work + d.a_off;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nn; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / d.n, c = i % d.n;
-        double v = Hm[i];
-        if (r == c) v += p.mu * (v > p.floor_ ? v : p.floor_);
-        A[i] = v;
-    }
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < d.n) work[d.v_off + t] = -g[6LL * d.pose0 + t];
-}
-
 // Broadcast lane J of every row of 16 lanes to that row.
 template <int J>
 __device__ __forceinline__ double row_bcast(double v) {
@@ -712,362 +677,10 @@ __device__ __forceinline__ int factor_diag_tile(double *__restrict__ T, double *
     return 0;
 }
 
-__global__ __launch_bounds__(256) void k_potf2(const DenseDesc *__restrict__ desc, DenseParam *__restrict__ prm,
-                                               double *__restrict__ work, int step) {
-    __shared__ __align__(16) double T[TB * LTS];
-    __shared__ __align__(16) double X[TB * LTS];
-    __shared__ double yv[TB];
-    __shared__ int sfail;
-    const int m = blockIdx.y;
-    const DenseParam pm = prm[m];
-    const DenseDesc d = desc[m];
-    if (!pm.active || pm.info) return;
-    const int64_t k0 = (int64_t)TB * step;
-    if (k0 >= d.n) return;
-    const int nb = (int)std::min<int64_t>(TB, d.n - k0);
-    double *A = work + d.a_off;
-    const int t = threadIdx.x;
-    const int w = t >> 6;
-    const int i = t & 63;
-    {   // the tile; only its lower triangle is read.  The loads are
-        // unconditional from a clamped in-bounds address so that all of them
-        // are in flight at once.
-        double v[TB / 4];
-        const int ci = std::min(i, nb - 1);
-#pragma unroll
-        for (int u = 0; u < TB / 4; u++) {
-            const int r = std::min(w + 4 * u, nb - 1);
-            v[u] = A[(k0 + r) * d.n + k0 + ci];
-        }
-#pragma unroll
-        for (int u = 0; u < TB / 4; u++) put_diag_elem(T, w + 4 * u, i, nb, v[u]);
-    }
-    if (t < TB) yv[t] = work[d.v_off + k0 + std::min(t, nb - 1)] * (t < nb ? 1.0 : 0.0);
-    if (t == 0) sfail = 0;
-    __syncthreads();
-    const int f = factor_diag_tile(T, X, yv, sfail, k0, nb, work + d.v_off + k0,
-                                   work + d.linv_off + (int64_t)step * TB * TB, [](int) {}, [](int) {});
-    if (f && t == 0 && f <= d.n) prm[m].info = f;
-}
-
-// Panel solve on matrix cores: rows below block `step`:  P <- P L_kk^-T,
-// then b_rows -= P y_k (forward substitution).
-__global__ __launch_bounds__(256) void k_trsm(const DenseDesc *__restrict__ desc, const DenseParam *__restrict__ prm,
-                                              double *__restrict__ work, int step) {
-    // one staging buffer: the two K chunks during the product, then the result tile
-    __shared__ double sm[2 * TB * LDK];
-    __shared__ double yk[TB];
-    double *As = sm, *Bs = sm + TB * LDK;
-    double(*Ts)[TB + 1] = (double(*)[TB + 1])sm;
-    const int m = blockIdx.y;
-    const DenseDesc d = desc[m];
-    if (!prm[m].active || prm[m].info) return;
-    const int64_t k0 = (int64_t)TB * step;
-    const int64_t R0 = k0 + TB + (int64_t)TB * blockIdx.x;
-    if (R0 >= d.n) return;
-    double *A = work + d.a_off;
-    const double *linv = work + d.linv_off + (int64_t)step * TB * TB;
-    d4 acc[2][2];
-    tile_gemm_nt(As, Bs, A, d.n, R0, k0, d.n, k0 + TB, linv, TB, 0, 0, TB, TB, acc);
-    const int64_t nrow = std::min<int64_t>(TB, d.n - R0);
-#pragma unroll
-    for (int rb = 0; rb < 2; rb++)
-#pragma unroll
-        for (int cb = 0; cb < 2; cb++)
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int row = ACC_ROW(rb, r), col = ACC_COL(cb);
-                Ts[row][col] = acc[rb][cb][r];
-                if (row < nrow) A[(R0 + row) * d.n + k0 + col] = acc[rb][cb][r];
-            }
-    if (threadIdx.x < TB) yk[threadIdx.x] = work[d.v_off + k0 + threadIdx.x];
-    __syncthreads();
-    if (threadIdx.x < nrow) {
-        double s = 0.0;
-        for (int c = 0; c < TB; c++) s += Ts[threadIdx.x][c] * yk[c];
-        work[d.v_off + R0 + threadIdx.x] -= s;
-    }
-}
-
-// Trailing update on matrix cores: C_IJ -= P_I P_J^T for tiles I >= J.
-// Symmetric update on matrix cores of the lower tiles of a region:
-// A[r][c] -= sum_k L[r][k] L[c][k] over the K columns [k0, k0 + kw), for
-// rows r >= T0 and columns T0 <= c < Cend (64x64 tiles, I >= J).  A panel
-// step updates only the rest of its panel (narrow column range); the update
-// after a panel covers the whole trailing matrix with the panel's width as K.
-__global__ __launch_bounds__(256) void k_syrk(const DenseDesc *__restrict__ desc, const DenseParam *__restrict__ prm,
-                                              double *__restrict__ work, int kstep, int kw, int tstep, int cend_step) {
-    __shared__ double sm[2 * TB * LDK];
-    double *As = sm, *Bs = sm + TB * LDK;
-    const int m = blockIdx.y;
-    const DenseDesc d = desc[m];
-    if (!prm[m].active || prm[m].info) return;
-    const int64_t k0 = (int64_t)TB * kstep;
-    const int64_t T0 = (int64_t)TB * tstep;
-    if (T0 >= d.n) return;
-    const int64_t cend = std::min<int64_t>((int64_t)TB * cend_step, d.n);
-    const int64_t ntr = (d.n - T0 + TB - 1) / TB;            // tile rows
-    const int64_t ntc = (cend - T0 + TB - 1) / TB;           // tile columns
-    if (ntc <= 0) return;
-    const int64_t idx = blockIdx.x;
-    int64_t I, J;
-    if (ntc == ntr) {   // whole lower triangle: idx = I (I + 1) / 2 + J
-        if (idx >= ntr * (ntr + 1) / 2) return;
-        I = (int64_t)((sqrt(8.0 * (double)idx + 1.0) - 1.0) * 0.5);
-        while (I * (I + 1) / 2 > idx) I--;
-        while ((I + 1) * (I + 2) / 2 <= idx) I++;
-        J = idx - I * (I + 1) / 2;
-    } else {            // a few tile columns: column J holds tile rows J..ntr-1
-        int64_t r = idx;
-        J = 0;
-        while (J < ntc && r >= ntr - J) {
-            r -= ntr - J;
-            J++;
-        }
-        if (J >= ntc) return;
-        I = J + r;
-    }
-    const int64_t ri = T0 + TB * I, rj = T0 + TB * J;
-    const int64_t kend = std::min<int64_t>(k0 + kw, d.n);
-    double *A = work + d.a_off;
-    d4 acc[2][2];
-    tile_gemm_nt(As, Bs, A, d.n, ri, k0, d.n, kend, A, d.n, rj, k0, d.n, kend, acc, kw);
-#pragma unroll
-    for (int rb = 0; rb < 2; rb++)
-#pragma unroll
-        for (int cb = 0; cb < 2; cb++)
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int64_t row = ri + ACC_ROW(rb, r), col = rj + ACC_COL(cb);
-                if (row < d.n && col < cend) A[row * d.n + col] -= acc[rb][cb][r];
-            }
-}
-
-// The same trailing update by 128 x 128 tiles, a 64 x 64 quadrant per wave (16
-// accumulators of v_mfma_f64_16x16x4f64), two blocks per compute unit.  Half
-// the operand bytes per product of the 64 x 64 tiles above; two k stages in
-// LDS, one barrier a stage.  On the first update of 12000 rows (K = 256) the
-// matrix cores are busy 64% of the time against 56%, 50 against 44 TF/s; the
-// factorization's updates together 16.4 -> 14.5 ms.  (32 k values staged once
-// instead of 16 twice: 15.2; squares of 4 x 4 or 8 x 8 tiles per XCD instead
-// of 2 x 2: 14.8, 15.6.)
-typedef double v2d __attribute__((ext_vector_type(2)));   // (HIP's double2 arrays stay in memory here)
-static constexpr int WT = 128;        // tile edge
-static constexpr int WK = 16;         // k values staged at a time
-static constexpr int WLD = WK + 2;    // LDS row stride: 16-byte reads of 16 rows fall into distinct banks
-static constexpr int WSUP = 2;        // tiles are dealt to the XCDs in WSUP x WSUP squares, which share operands in L2
-
-__device__ __forceinline__ void wide_load(v2d (&v)[WK / 4], const double *__restrict__ A, int64_t ld, int64_t r0,
-                                          int64_t k0, int64_t n) {
-#pragma unroll
-    for (int e = 0; e < WK / 4; e++) {
-        const int idx = threadIdx.x + 256 * e;
-        // rows past the end repeat the last one: they only feed elements that are not stored
-        const int64_t row = std::min<int64_t>(r0 + (idx / (WK / 2)), n - 1);
-        v[e] = *reinterpret_cast<const v2d *>(A + row * ld + k0 + 2 * (idx % (WK / 2)));
-    }
-}
-
-__device__ __forceinline__ void wide_store(double *__restrict__ lds, const v2d (&v)[WK / 4]) {
-#pragma unroll
-    for (int e = 0; e < WK / 4; e++) {
-        const int idx = threadIdx.x + 256 * e;
-        *reinterpret_cast<v2d *>(lds + (idx / (WK / 2)) * WLD + 2 * (idx % (WK / 2))) = v[e];
-    }
-}
-
-__global__ __launch_bounds__(256, 2) void k_syrk_wide(const DenseDesc *__restrict__ desc,
-                                                      const DenseParam *__restrict__ prm, double *__restrict__ work,
-                                                      int kstep, int kw, int tstep) {
-    __shared__ __attribute__((aligned(16))) double sm[2][2][WT * WLD];
-    const int m = blockIdx.y;
-    const DenseDesc d = desc[m];
-    if (!prm[m].active || prm[m].info) return;
-    const int64_t k0 = (int64_t)TB * kstep, T0 = (int64_t)TB * tstep;
-    if (T0 >= d.n) return;
-    const int nt = (int)((d.n - T0 + WT - 1) / WT);
-    // block -> (square of the lower triangle, tile in it); a square's tiles go to one XCD
-    const int b = (int)blockIdx.x;
-    constexpr int PER = WSUP * WSUP;
-    const int sq = (b / (8 * PER)) * 8 + (b & 7), in = (b >> 3) % PER;
-    int SI = (int)((sqrt(8.0 * (double)sq + 1.0) - 1.0) * 0.5);
-    while (SI * (SI + 1) / 2 > sq) SI--;
-    while ((SI + 1) * (SI + 2) / 2 <= sq) SI++;
-    const int I = SI * WSUP + in / WSUP, J = (sq - SI * (SI + 1) / 2) * WSUP + in % WSUP;
-    if (I >= nt || J > I) return;
-    const int64_t ri = T0 + (int64_t)WT * I, rj = T0 + (int64_t)WT * J;
-    double *A = work + d.a_off;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int wr = 64 * (w >> 1), wc = 64 * (w & 1);
-    const int li = lane & 15, lk = lane >> 4;
-    d4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-    v2d va[WK / 4], vb[WK / 4];
-    wide_load(va, A, d.n, ri, k0, d.n);
-    wide_load(vb, A, d.n, rj, k0, d.n);
-    const int steps = kw / WK;
-#pragma unroll 1
-    for (int st = 0; st < steps; st++) {
-        double *Sa = sm[st & 1][0], *Sb = sm[st & 1][1];
-        wide_store(Sa, va);
-        wide_store(Sb, vb);
-        __syncthreads();   // one barrier a step: the other stage is rewritten only after the next one
-        // the next step's operands (the last step loads its own again)
-        const int64_t kn = k0 + WK * std::min(st + 1, steps - 1);
-        wide_load(va, A, d.n, ri, kn, d.n);
-        wide_load(vb, A, d.n, rj, kn, d.n);
-        const double *As = Sa + (wr + li) * WLD + 2 * lk, *Bs = Sb + (wc + li) * WLD + 2 * lk;
-#pragma unroll
-        for (int kk = 0; kk < WK; kk += 8) {
-            // lane group lk holds k = kk + 2 lk (first product) and kk + 2 lk + 1 (second)
-            v2d a[4], bb[4];
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                a[i] = *reinterpret_cast<const v2d *>(As + 16 * i * WLD + kk);
-                bb[i] = *reinterpret_cast<const v2d *>(Bs + 16 * i * WLD + kk);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int j = 0; j < 4; j++)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, bb[j].x, acc[i][j], 0, 0, 0);
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int j = 0; j < 4; j++)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, bb[j].y, acc[i][j], 0, 0, 0);
-        }
-    }
-    if (I == J && wc > wr) return;   // the quadrant above the diagonal is not needed
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        double c[4][4];
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int64_t row = ri + wr + 16 * i + lk + 4 * r, col = rj + wc + 16 * j + li;
-                c[j][r] = (row < d.n && col < d.n) ? A[row * d.n + col] : 0.0;
-            }
-#pragma unroll
-        for (int j = 0; j < 4; j++)
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int64_t row = ri + wr + 16 * i + lk + 4 * r, col = rj + wc + 16 * j + li;
-                if (row < d.n && col < d.n) A[row * d.n + col] = c[j][r] - acc[i][j][r];
-            }
-    }
-}
-
-// Backward substitution, R block rows per launch: rows k, k-1, ..., k-R+1
-// (those >= 0 that the matrix has; k = `step`).  Every workgroup forms the
-// rows' solutions in order, x_r = L_rr^-T (y_r - sum of L_r'r^T x_r' over the
-// rows r' above r in the group), and workgroup J below the group applies
-// y_J <- y_J - sum_r L_rJ^T x_r (rows in order); workgroup 0 stores x.  All
-// tiles are loaded before the first product.  Four threads share each
-// 64-term dot product.
-template <int R>
-__global__ __launch_bounds__(256) void k_backsub_rows(const DenseDesc *__restrict__ desc,
-                                                      const DenseParam *__restrict__ prm, double *__restrict__ work,
-                                                      double *__restrict__ x, const int64_t *__restrict__ x_off,
-                                                      int step) {
-    __shared__ double xs[R][TB], ys[R][TB];
-    const int m = blockIdx.y;
-    const DenseDesc d = desc[m];
-    if (!prm[m].active || prm[m].info) return;
-    const int lo = step - R + 1;   // lowest row of the group (may be < 0)
-    if ((int64_t)TB * std::max(lo, 0) >= d.n) return;   // the group lies beyond this (smaller) matrix
-    const int64_t J = blockIdx.x;
-    if (J > 0 && J >= lo) return;
-    const bool upd = J < lo;
-    const int t = threadIdx.x, o = t >> 2, part = t & 3;
-    const double *A = work + d.a_off;
-    int nb[R];
-#pragma unroll
-    for (int i = 0; i < R; i++) {
-        const int64_t r0 = (int64_t)TB * (step - i);
-        nb[i] = (step - i >= 0 && r0 < d.n) ? (int)std::min<int64_t>(TB, d.n - r0) : 0;
-    }
-    double li[R][16], lj[R][16], lc[R > 1 ? R * (R - 1) / 2 : 1][16];
-#pragma unroll
-    for (int i = 0; i < R; i++) {
-        const int64_t r0 = (int64_t)TB * (step - i);
-#pragma unroll
-        for (int q = 0; q < 16; q++) {
-            const int r = part + 4 * q;
-            li[i][q] = nb[i] ? work[d.linv_off + (int64_t)(step - i) * TB * TB + r * TB + o] : 0.0;
-            lj[i][q] = (upd && r < nb[i]) ? A[(r0 + r) * d.n + TB * J + o] : 0.0;
-        }
-    }
-    // lc[p(i, i')]: the tile (row block step - i', column block step - i), i' < i
-#pragma unroll
-    for (int i = 1; i < R; i++)
-#pragma unroll
-        for (int ip = 0; ip < i; ip++) {
-            const int p = i * (i - 1) / 2 + ip;
-            const int64_t r0 = (int64_t)TB * (step - ip), c0 = (int64_t)TB * (step - i);
-#pragma unroll
-            for (int q = 0; q < 16; q++) {
-                const int r = part + 4 * q;
-                lc[p][q] = (nb[i] && r < nb[ip]) ? A[(r0 + r) * d.n + c0 + o] : 0.0;
-            }
-        }
-    if (t < TB) {
-#pragma unroll
-        for (int i = 0; i < R; i++)
-            ys[i][t] = t < nb[i] ? work[d.v_off + (int64_t)TB * (step - i) + t] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < R; i++) {
-        if (i > 0) {   // y_i -= L_i'i^T x_i' for the rows above, in order
-            double yi = ys[i][o];
-#pragma unroll
-            for (int ip = 0; ip < i; ip++) {
-                const int p = i * (i - 1) / 2 + ip;
-                double sum = 0.0;
-#pragma unroll
-                for (int q = 0; q < 16; q++) sum += lc[p][q] * xs[ip][part + 4 * q];
-                sum += __shfl_xor(sum, 1, 64);
-                sum += __shfl_xor(sum, 2, 64);
-                yi -= sum;
-            }
-            __syncthreads();
-            if (part == 0) ys[i][o] = yi;
-            __syncthreads();
-        }
-        double sum = 0.0;   // x_i[o] = sum_c Linv_i[c][o] y_i[c]
-#pragma unroll
-        for (int q = 0; q < 16; q++) sum += li[i][q] * ys[i][part + 4 * q];
-        sum += __shfl_xor(sum, 1, 64);
-        sum += __shfl_xor(sum, 2, 64);
-        if (part == 0) xs[i][o] = sum;
-        __syncthreads();
-        if (J == 0 && t < nb[i]) x[x_off[m] + (int64_t)TB * (step - i) + t] = xs[i][t];
-    }
-    if (!upd) return;
-    double yJ = 0.0;   // y_J[o] <- ((y_J[o] - L_0J^T x_0) - L_1J^T x_1) - ...
-#pragma unroll
-    for (int i = 0; i < R; i++) {
-        double sum = 0.0;
-#pragma unroll
-        for (int q = 0; q < 16; q++) sum += lj[i][q] * xs[i][part + 4 * q];
-        sum += __shfl_xor(sum, 1, 64);
-        sum += __shfl_xor(sum, 2, 64);
-        if (i == 0) yJ = work[d.v_off + TB * J + o];
-        yJ -= sum;
-    }
-    if (part == 0) work[d.v_off + TB * J + o] = yJ;
-}
-
 // ---------------------------------------------------------------- dataflow factorization
 // One persistent launch factors a set of damped matrices and forward-
 // substitutes their right-hand sides (A = L L^T, y = L^-1 b, and L_kk^-1 per
-// diagonal block for the back substitution), with the same 64 x 64 tiles as
-// the launch-per-step path.  Work is taken from one queue by running workgroups
+// diagonal block for the back substitution), by 64 x 64 tiles.  Work is taken from one queue by running workgroups
 // (an atomic ticket), in this order:
 //  - one walker per matrix.  For j = 0, 1, ... it takes the diagonal tile's
 //    partial sum P_jj = A_jj - sum_{k<j-1} L_jk L_jk^T, subtracts the last
@@ -1076,10 +689,11 @@ __global__ __launch_bounds__(256) void k_backsub_rows(const DenseDesc *__restric
 //    L_j+1,j = P_j+1,j L_jj^-T, with the inverse still in LDS.  Only the
 //    walker's work lies on the critical path, and it never waits for a
 //    launch boundary;
-//  - by column c = 0, 1, ...: the two partial sums of row r = c + 2 that the
-//    walker takes next (at its steps r - 1 and r; ahead of the column's other
-//    tasks they are in time for it: 6000 rows 4.31 -> 3.95 ms), then the tile
-//    tasks L_ic = (A_ic - sum_{k<c} L_ik L_ck^T) L_cc^-T for i >= c + 3.  The
+//  - by pair of columns: the two partial sums of row r = c + 2 that the walker
+//    takes next (at its steps r - 1 and r; ahead of the column's other tasks
+//    they are in time for it: 6000 rows 4.31 -> 3.95 ms), then the tiles
+//    L_ic = (A_ic - sum_{k<c} L_ik L_ck^T) L_cc^-T for i >= c + 3, by two rows of
+//    one or two columns (flow_columns), what is left over by single tiles.  The
 //    partial sums are left in place: P_rr with
 //    the right-hand side rows b_r - sum_{k<=c} L_rk y_k, and P_r,r-1 =
 //    A_r,r-1 - sum_{k<=c} L_rk L_r-1,k^T.  Both tasks form L_rc themselves
@@ -1100,13 +714,17 @@ __global__ __launch_bounds__(256) void k_backsub_rows(const DenseDesc *__restric
 // taken only by a running workgroup, so the earliest unfinished task can
 // always proceed.  Every wait is bounded: after `limit` polls the launch is
 // aborted (all waits end, prm.info = -1 for the matrices not finished);
-// a pivot failure abandons the matrix (prm.info as in k_potf2).
+// a pivot failure abandons the matrix (prm.info = the pivot's 1-based row).
 struct FlowTask {
     int32_t m, kind, i, c;
 };
-static constexpr int FLOW_WALK = 0, FLOW_TILE = 1, FLOW_PDIAG = 2, FLOW_POFF = 3;
+// From FLOW_QUAD_T tile rows on a task takes two columns of two rows, below one
+// column of two (k_chol_flow in ms, one / two columns: 4500 rows 1.43 / 1.50,
+// 5700 2.29 / 2.29, 6000 2.53 / 2.44, 9000 6.49 / 6.26, 12000 13.9 / 12.9, 18000
+// 44.9 / 39.7; single tiles: 3000 rows 0.86 against 0.83, 6000 3.62, 12000 20.1).
+static constexpr int FLOW_QUAD_T = 90;
+static constexpr int FLOW_WALK = 0, FLOW_TILE = 1, FLOW_PDIAG = 2, FLOW_POFF = 3, FLOW_PAIR = 4, FLOW_QUAD = 5;
 static constexpr int FLOW_MAX_MATS = 128;     // walkers per launch
-static constexpr int32_t FLOW_MAX_N = 6144;   // larger matrices take the launch-per-step path
 static constexpr int FLOW_SPIN = 1 << 20;     // polls before a wait gives up (each about 1 us)
 
 // Flags of one matrix with T tile rows: T*T tile flags (i, k), T diagonal
@@ -1220,6 +838,16 @@ __device__ __forceinline__ bool flow_wait2(glb_i32 *f1, glb_i32 *f2, glb_i32 *ab
     }
     __syncthreads();
     return *s_val != 0;
+}
+
+// flow_publish of two flags behind one fence.
+__device__ __forceinline__ void flow_publish2(glb_i32 *f1, glb_i32 *f2) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        flag_set(f1, __ATOMIC_RELEASE);
+        flag_set(f2, __ATOMIC_RELAXED);
+    }
 }
 
 // Tile M[r0.., c0..] (row stride ld) into LDS S (row stride LTS), zero
@@ -1669,6 +1297,197 @@ __device__ __noinline__ void flow_tile(const DenseDesc d, glb_f64 *gwork, const 
     flow_publish(fm.fl + i * fm.T + c);
 }
 
+// Larger tasks, which read each tile of L for more products than a single tile's
+// task does: the sums of rows i, i + 1 and of NB columns as one 128 x 64 NB
+// product, the wave's part 32 x 64 (NB = 1) or 64 x 64 (NB = 2).  K values of k
+// at a time, double-buffered in LDS behind one barrier that leaves the next
+// loads in flight.  A tile product takes 1.7 us on a compute unit's matrix cores;
+// the single-tile tasks took 3.5 us for one, waiting for their loads.
+template <int NB>
+struct WidePart {
+    static constexpr int K = NB == 1 ? 32 : 16;      // k values staged at a time
+    static constexpr int LD = K + 2;                 // LDS row stride: 16-byte reads of 16 rows fall into distinct banks
+    static constexpr int ROWS = (2 + NB) * TB;       // staged rows: of the two tile rows, then of the columns' tile rows
+    static constexpr int XB = 2 * NB, YB = 4;        // the wave's 16 x 16 blocks
+    static constexpr int LOADS = ROWS * K / 512;     // 16-byte loads per thread and stage
+    d4 a[XB][YB];
+    // first row and column of the wave's part
+    static __device__ __forceinline__ int r0() {
+        const int w = threadIdx.x >> 6;
+        return NB == 1 ? 32 * w : TB * (w >> 1);
+    }
+    static __device__ __forceinline__ int c0() { return NB == 1 ? 0 : TB * ((threadIdx.x >> 6) & 1); }
+};
+static constexpr int WIDE_LDS = std::max(2 * WidePart<1>::ROWS * WidePart<1>::LD, 2 * WidePart<2>::ROWS * WidePart<2>::LD);
+
+template <int NB>
+__device__ __forceinline__ void part_load(v2d (&v)[WidePart<NB>::LOADS], const double *__restrict__ A, int64_t ld,
+                                          int64_t ra, int64_t rb, int64_t k0, int64_t n) {
+    constexpr int TR = WidePart<NB>::K / 2, STEP = 256 / TR;   // threads per row, rows per load
+#pragma unroll
+    for (int e = 0; e < WidePart<NB>::LOADS; e++) {
+        const int row = (int)threadIdx.x / TR + STEP * e;
+        // rows past the end repeat the last one: they only feed elements that are not stored
+        const int64_t gr = row < 2 * TB ? std::min<int64_t>(ra + row, n - 1) : rb + row - 2 * TB;
+        v[e] = *reinterpret_cast<const v2d *>(A + gr * ld + k0 + 2 * (threadIdx.x % TR));
+    }
+}
+
+template <int NB>
+__device__ __forceinline__ void part_gemm(double *__restrict__ lds, const double *__restrict__ A, int64_t n,
+                                          int64_t ra, int64_t rb, int64_t k0, int kw, WidePart<NB> &acc) {
+    using P = WidePart<NB>;
+    constexpr int TR = P::K / 2, STEP = 256 / TR;
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    v2d v[P::LOADS];
+    part_load<NB>(v, A, n, ra, rb, k0, n);
+#pragma unroll 1
+    for (int kc = 0; kc < kw; kc += P::K) {
+        double *S = lds + ((kc / P::K) & 1) * P::ROWS * P::LD;
+#pragma unroll
+        for (int e = 0; e < P::LOADS; e++)
+            *reinterpret_cast<v2d *>(S + ((int)threadIdx.x / TR + STEP * e) * P::LD + 2 * (threadIdx.x % TR)) = v[e];
+        lds_barrier();   // the other buffer is rewritten only after the next one
+        part_load<NB>(v, A, n, ra, rb, k0 + std::min(kc + P::K, kw - P::K), n);
+        __builtin_amdgcn_sched_barrier(0);   // the loads go out here, not before the stores that take them
+        const double *As = S + (P::r0() + li) * P::LD + 2 * lk, *Bs = S + (2 * TB + P::c0() + li) * P::LD + 2 * lk;
+#pragma unroll
+        for (int kk = 0; kk < P::K; kk += 8) {
+            v2d a[P::XB], b[P::YB];
+#pragma unroll
+            for (int q = 0; q < P::XB; q++) a[q] = *reinterpret_cast<const v2d *>(As + 16 * q * P::LD + kk);
+#pragma unroll
+            for (int q = 0; q < P::YB; q++) b[q] = *reinterpret_cast<const v2d *>(Bs + 16 * q * P::LD + kk);
+#pragma unroll
+            for (int x = 0; x < P::XB; x++)
+#pragma unroll
+                for (int y = 0; y < P::YB; y++)
+                    acc.a[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x].x, b[y].x, acc.a[x][y], 0, 0, 0);
+#pragma unroll
+            for (int x = 0; x < P::XB; x++)
+#pragma unroll
+                for (int y = 0; y < P::YB; y++)
+                    acc.a[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x].y, b[y].y, acc.a[x][y], 0, 0, 0);
+        }
+    }
+}
+
+// acc = H - acc on the wave's part of the 128 x 64 NB block at (R0, C0), of
+// which nr rows exist.
+template <int NB>
+__device__ __forceinline__ void part_from_raw(WidePart<NB> &acc, const double *__restrict__ H, int64_t n, int64_t R0,
+                                              int64_t C0, int nr) {
+    using P = WidePart<NB>;
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+#pragma unroll
+    for (int x = 0; x < P::XB; x++) {
+        d4 raw[P::YB];
+#pragma unroll
+        for (int y = 0; y < P::YB; y++)
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                raw[y][r] = H[(R0 + std::min(P::r0() + 16 * x + lk + 4 * r, nr - 1)) * n + C0 + P::c0() + 16 * y + li];
+#pragma unroll
+        for (int y = 0; y < P::YB; y++) acc.a[x][y] = raw[y] - acc.a[x][y];
+    }
+}
+
+// The wave's part of a 128 x 64 column as the two tiles at S and S + TB * LTS,
+// rows from nr on cleared.
+template <int NB>
+__device__ __forceinline__ void part_to_lds(const WidePart<NB> &acc, double *__restrict__ S, int nr) {
+    using P = WidePart<NB>;
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+#pragma unroll
+    for (int x = 0; x < P::XB; x++)
+#pragma unroll
+        for (int y = 0; y < P::YB; y++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int row = P::r0() + 16 * x + lk + 4 * r;
+                S[row * LTS + 16 * y + li] = row < nr ? acc.a[x][y][r] : 0.0;
+            }
+}
+
+// The tiles (i, c + q) and (i + 1, c + q), q < NB, in one task.  With two
+// columns the first is solved and published, its tiles are the second's last
+// term, and the second follows.
+template <int NB>
+__device__ __forceinline__ void flow_wide(const DenseDesc &d, glb_f64 *gwork, const FlowRaw &rw, const FlowMat &fm,
+                                          int i, int c, glb_i32 *gab, int limit, lds_f64 *glds, lds_i32 *s_val) {
+    double *work = (double *)gwork, *lds = (double *)glds;
+    const double *H = (const double *)rw.H;
+    const int64_t n = d.n;
+    double *A = work + d.a_off;
+    const int64_t R0 = (int64_t)TB * i, C0 = (int64_t)TB * c;
+    const int nr = (int)std::min<int64_t>(2 * TB, n - R0);   // rows of both tiles (the first is whole)
+    WidePart<NB> acc;
+#pragma unroll
+    for (int x = 0; x < WidePart<NB>::XB; x++)
+#pragma unroll
+        for (int y = 0; y < WidePart<NB>::YB; y++) acc.a[x][y] = d4{0.0, 0.0, 0.0, 0.0};
+    const int rows[4] = {i, i + 1, c, NB == 2 ? c + 1 : c};
+    for (int klo = 0; klo < c;) {
+        const int khi = flow_wait_cols<4>(fm, rows, klo, c, gab, limit, s_val);
+        if (khi < 0) return;
+        part_gemm<NB>(lds, A, n, R0, C0, (int64_t)TB * klo, TB * (khi - klo), acc);
+        klo = khi;
+    }
+    double *Xl = lds + 2 * TB * LTS;   // the column's sums in tile layout at lds, then the inverse
+#pragma unroll 1
+    for (int q = 0; q < NB; q++) {
+        const int cq = c + q;
+        const bool own = NB == 1 || WidePart<NB>::c0() == TB * q;   // the wave's part lies in this column
+        if (q == 0) part_from_raw<NB>(acc, H, n, R0, C0, nr);
+        if (!flow_wait(fm.dg + cq, fm.ab, gab, limit, s_val)) return;
+        if (own) part_to_lds<NB>(acc, lds, nr);
+        tile_to_lds(Xl, work + d.linv_off + (int64_t)cq * TB * TB, TB, 0, 0, TB, TB);
+        lds_barrier();
+        RowTile l0, l1;
+        rows_trsm(lds, Xl, l0);
+        rows_to_global(l0, A, n, R0, C0 + TB * q, TB);
+        rows_trsm(lds + TB * LTS, Xl, l1);
+        rows_to_global(l1, A, n, R0 + TB, C0 + TB * q, nr - TB);
+        flow_publish2(fm.fl + i * fm.T + cq, fm.fl + (i + 1) * fm.T + cq);
+        if (NB == 2 && q == 0) {
+            // the second column's last term, L_.c L_c+1,c^T, by the waves that hold it
+            if (!flow_wait(fm.fl + (c + 1) * fm.T + c, fm.ab, gab, limit, s_val)) return;
+            rows_to_lds(l0, lds, TB);
+            rows_to_lds(l1, lds + TB * LTS, nr - TB);
+            tile_to_lds(Xl, A, n, C0 + TB, C0, TB, TB);
+            lds_barrier();
+            if (WidePart<NB>::c0() == TB) {
+                const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+                const double *Ar = lds + (WidePart<NB>::r0() + li) * LTS + lk, *Br = Xl + li * LTS + lk;
+#pragma unroll 2
+                for (int kk = 0; kk < TB; kk += 4) {
+                    double a[4], b[4];
+#pragma unroll
+                    for (int x = 0; x < 4; x++) {
+                        a[x] = -Ar[16 * x * LTS + kk];
+                        b[x] = Br[16 * x * LTS + kk];
+                    }
+#pragma unroll
+                    for (int x = 0; x < WidePart<NB>::XB; x++)
+#pragma unroll
+                        for (int y = 0; y < WidePart<NB>::YB; y++)
+                            acc.a[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], acc.a[x][y], 0, 0, 0);
+                }
+            }
+        }
+    }
+}
+
+__device__ __noinline__ void flow_pair(const DenseDesc d, glb_f64 *gwork, const FlowRaw rw, const FlowMat fm, int i,
+                                      int c, glb_i32 *gab, int limit, lds_f64 *glds, lds_i32 *s_val) {
+    flow_wide<1>(d, gwork, rw, fm, i, c, gab, limit, glds, s_val);
+}
+
+__device__ __noinline__ void flow_quad(const DenseDesc d, glb_f64 *gwork, const FlowRaw rw, const FlowMat fm, int i,
+                                      int c, glb_i32 *gab, int limit, lds_f64 *glds, lds_i32 *s_val) {
+    flow_wide<2>(d, gwork, rw, fm, i, c, gab, limit, glds, s_val);
+}
+
 // Marks the matrix abandoned: a pivot failure (f > 0) or an aborted wait.
 __device__ __forceinline__ void flow_abandon(glb_i32 *info, const FlowMat &fm, int f) {
     if (threadIdx.x == 0) {
@@ -1786,7 +1605,7 @@ __global__ __launch_bounds__(256) void k_chol_flow(const DenseDesc *__restrict__
                                                    int32_t n_tasks, int *__restrict__ flags,
                                                    const int64_t *__restrict__ fo, int *__restrict__ queue,
                                                    int *__restrict__ gab, int limit) {
-    __shared__ __align__(16) double lds[3 * TB * LTS];
+    __shared__ __align__(16) double lds[std::max(3 * TB * LTS, WIDE_LDS)];
     __shared__ double yv[TB], ybuf[TB];
     __shared__ int s_task, s_val, sfail, s_count;
     for (;;) {
@@ -1812,6 +1631,10 @@ __global__ __launch_bounds__(256) void k_chol_flow(const DenseDesc *__restrict__
                       (lds_f64 *)ybuf, (lds_i32 *)&sfail, sv, (lds_i32 *)&s_count);
         else if (tk.kind == FLOW_TILE)
             flow_tile(d, gw, rw, fm, tk.i, tk.c, ga, limit, (lds_f64 *)lds, sv);
+        else if (tk.kind == FLOW_PAIR)
+            flow_pair(d, gw, rw, fm, tk.i, tk.c, ga, limit, (lds_f64 *)lds, sv);
+        else if (tk.kind == FLOW_QUAD)
+            flow_quad(d, gw, rw, fm, tk.i, tk.c, ga, limit, (lds_f64 *)lds, sv);
         else if (tk.kind == FLOW_PDIAG)
             flow_pdiag(d, gw, rw, fm, tk.i, tk.c, ga, limit, (lds_f64 *)lds, sv);
         else
@@ -1819,19 +1642,56 @@ __global__ __launch_bounds__(256) void k_chol_flow(const DenseDesc *__restrict__
     }
 }
 
-// Task list of one matrix with T tile rows (the standalone solve): thread c
-// writes the tasks of column c after the walker.
+// Emits the tasks of columns c and c + 1 (c even) of matrix m with T tile rows
+// through put(FlowTask), in queue order; every task waits only for tasks before
+// it or the walker.
+template <class Put>
+__host__ __device__ inline void flow_columns(int32_t m, int T, int c, Put put) {
+    const bool quad = T >= FLOW_QUAD_T;
+    for (int q = c; q < c + 2; q++) {
+        if (q + 2 <= T - 1) {
+            put(FlowTask{m, FLOW_PDIAG, q + 2, q});
+            put(FlowTask{m, FLOW_POFF, q + 2, q});
+        }
+        if (quad) {
+            if (q == c && c + 3 < T) put(FlowTask{m, FLOW_TILE, c + 3, c});
+            continue;
+        }
+        for (int i = q + 3; i < T; i += 2) put(FlowTask{m, i + 1 < T ? FLOW_PAIR : FLOW_TILE, i, q});
+    }
+    if (quad)
+        for (int i = c + 4; i < T; i += 2) {
+            if (i + 1 < T) {
+                put(FlowTask{m, FLOW_QUAD, i, c});
+            } else {
+                put(FlowTask{m, FLOW_TILE, i, c});
+                put(FlowTask{m, FLOW_TILE, i, c + 1});
+            }
+        }
+}
+
+// Their number.
+__host__ __device__ inline int flow_column_tasks(int T, int c) {
+    int k = 0;
+    for (int q = c; q < c + 2; q++) {
+        if (q + 2 <= T - 1) k += 2;
+        if (T < FLOW_QUAD_T && q + 3 < T) k += (T - q - 2) / 2;
+    }
+    if (T < FLOW_QUAD_T) return k;
+    if (c + 3 < T) k += 1;
+    const int rows = c + 4 < T ? T - c - 4 : 0;
+    return k + rows / 2 + 2 * (rows & 1);
+}
+
+// Task list of one matrix with T tile rows (the standalone solve): thread j
+// writes the tasks of columns 2 j and 2 j + 1 after the walker.
 __global__ void k_flow_tasks_one(int32_t T, FlowTask *__restrict__ tasks) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = 2 * (blockIdx.x * blockDim.x + threadIdx.x);
     if (c == 0) tasks[0] = FlowTask{0, FLOW_WALK, 0, 0};
     if (c >= T) return;
     int64_t o = 1;
-    for (int cc = 0; cc < c; cc++) o += std::max(0, T - cc - 3) + (cc + 2 <= T - 1 ? 2 : 0);
-    if (c + 2 <= T - 1) {
-        tasks[o++] = FlowTask{0, FLOW_PDIAG, c + 2, c};
-        tasks[o++] = FlowTask{0, FLOW_POFF, c + 2, c};
-    }
-    for (int i = c + 3; i < T; i++) tasks[o++] = FlowTask{0, FLOW_TILE, i, c};
+    for (int cc = 0; cc < c; cc += 2) o += flow_column_tasks(T, cc);
+    flow_columns(0, T, c, [&](const FlowTask &k) { tasks[o++] = k; });
 }
 
 // ---------------------------------------------------------------- dataflow back substitution
@@ -1967,7 +1827,11 @@ __global__ void k_fill_i32(int64_t n, int *__restrict__ p, int v) {
         p[i] = v;
 }
 
-static int64_t flow_task_count(int64_t T) { return 1 + (T >= 3 ? (T - 2) * (T - 3) / 2 + 2 * (T - 2) : 0); }
+static int64_t flow_task_count(int64_t T) {
+    int64_t k = 1;
+    for (int64_t c = 0; c < T; c += 2) k += flow_column_tasks((int)T, (int)c);
+    return k;
+}
 
 // ---------------------------------------------------------------- LM glue
 // Per-window damping parameters from the LM state and the dense diagonal.
@@ -2150,7 +2014,7 @@ struct DenseState {
     double *work = nullptr;
     double *hdx = nullptr;
     int32_t max_n = 0;
-    // dataflow factorization (every matrix at most FLOW_MAX_N): task list,
+    // dataflow factorization: task list,
     // per-matrix flags at flow_fo[m], then one queue ticket per launch and the
     // abort flag; launch q takes tasks [flow_first[q], + flow_count[q])
     FlowTask *flow_tasks = nullptr;
@@ -2363,76 +2227,68 @@ ba_status dense_prepare(Problem *P) {
     BA_HIP(hipMemcpy(D->h_off, hoff.data(), sizeof(int64_t) * (W + 1), hipMemcpyHostToDevice));
     BA_HIP(hipMemcpy(D->x_off, xoff.data(), sizeof(int64_t) * W, hipMemcpyHostToDevice));
     BA_HIP(hipMemset(P->dense, 0, sizeof(double) * std::max<int64_t>(h_tot, 1)));
-    if (D->max_n <= FLOW_MAX_N) {
-        // walkers of up to FLOW_MAX_MATS matrices per launch, then their
-        // tasks by column
-        std::vector<FlowTask> tasks;
-        std::vector<int64_t> fo(W);
-        int64_t ints = 0;
-        for (int32_t w = 0; w < W; w++) {
-            fo[w] = ints;
-            ints += flow_flag_ints((desc[w].n + TB - 1) / TB);
-        }
-        // walkers of a launch hold at most half of the compute units, so that
-        // every launch keeps workgroups for its helpers
-        const int32_t per_launch = std::max(1, std::min(FLOW_MAX_MATS, cu_count() / 2));
-        for (int32_t m0 = 0; m0 < W; m0 += per_launch) {
-            const int32_t m1 = std::min<int32_t>(W, m0 + per_launch);
-            D->flow_first.push_back((int32_t)tasks.size());
-            int32_t maxT = 0;
-            for (int32_t m = m0; m < m1; m++) {
-                tasks.push_back(FlowTask{m, FLOW_WALK, 0, 0});
-                maxT = std::max<int32_t>(maxT, (desc[m].n + TB - 1) / TB);
-            }
-            for (int32_t c = 0; c < maxT; c++)
-                for (int32_t m = m0; m < m1; m++) {
-                    const int32_t T = (desc[m].n + TB - 1) / TB;
-                    if (c + 2 <= T - 1) {
-                        tasks.push_back(FlowTask{m, FLOW_PDIAG, c + 2, c});
-                        tasks.push_back(FlowTask{m, FLOW_POFF, c + 2, c});
-                    }
-                    for (int32_t i = c + 3; i < T; i++) tasks.push_back(FlowTask{m, FLOW_TILE, i, c});
-                }
-            D->flow_count.push_back((int32_t)tasks.size() - D->flow_first.back());
-            int64_t work = 0;
-            for (int32_t m = m0; m < m1; m++) {
-                const int64_t T = (desc[m].n + TB - 1) / TB;
-                work += T * T;
-            }
-            D->flow_mats.push_back(m1 - m0);
-            D->flow_work.push_back(work);
-        }
-        D->flow_ints = ints;
-        // back substitution: tasks p-major over the matrices, flags after the
-        // factorization's tickets and abort flag
-        std::vector<BsTask> bs;
-        std::vector<int64_t> bo(W);
-        int64_t bints = ints + (int64_t)D->flow_first.size() + 1;
-        const int64_t bs_base = bints;
-        int32_t maxP = 0;
-        for (int32_t w = 0; w < W; w++) {
-            const int32_t T = (desc[w].n + TB - 1) / TB;
-            bo[w] = bints;
-            bints += T + 1;
-            maxP = std::max(maxP, (T + 1) / 2);
-        }
-        for (int32_t p = 0; p < maxP; p++)
-            for (int32_t w = 0; w < W; w++)
-                if (p < ((desc[w].n + TB - 1) / TB + 1) / 2) bs.push_back(BsTask{w, p});
-        D->bs_ticket = bints;
-        D->bs_ints = bints + 2 - bs_base;
-        D->bs_count = (int32_t)bs.size();
-        BA_TRY(D->mem.alloc(&D->flow_tasks, (int64_t)tasks.size()));
-        BA_TRY(D->mem.alloc(&D->flow_flags, bints + 2));
-        BA_TRY(D->mem.alloc(&D->flow_fo, W));
-        BA_TRY(D->mem.alloc(&D->bs_tasks, std::max<int64_t>(D->bs_count, 1)));
-        BA_TRY(D->mem.alloc(&D->bs_bo, W));
-        BA_HIP(hipMemcpy(D->flow_tasks, tasks.data(), sizeof(FlowTask) * tasks.size(), hipMemcpyHostToDevice));
-        BA_HIP(hipMemcpy(D->flow_fo, fo.data(), sizeof(int64_t) * W, hipMemcpyHostToDevice));
-        if (!bs.empty())
-            BA_HIP(hipMemcpy(D->bs_tasks, bs.data(), sizeof(BsTask) * bs.size(), hipMemcpyHostToDevice));
-        BA_HIP(hipMemcpy(D->bs_bo, bo.data(), sizeof(int64_t) * W, hipMemcpyHostToDevice));
+    // walkers of up to FLOW_MAX_MATS matrices per launch, then their
+    // tasks by column
+    std::vector<FlowTask> tasks;
+    std::vector<int64_t> fo(W);
+    int64_t ints = 0;
+    for (int32_t w = 0; w < W; w++) {
+        fo[w] = ints;
+        ints += flow_flag_ints((desc[w].n + TB - 1) / TB);
     }
+    // walkers of a launch hold at most half of the compute units, so that
+    // every launch keeps workgroups for its helpers
+    const int32_t per_launch = std::max(1, std::min(FLOW_MAX_MATS, cu_count() / 2));
+    for (int32_t m0 = 0; m0 < W; m0 += per_launch) {
+        const int32_t m1 = std::min<int32_t>(W, m0 + per_launch);
+        D->flow_first.push_back((int32_t)tasks.size());
+        int32_t maxT = 0;
+        for (int32_t m = m0; m < m1; m++) {
+            tasks.push_back(FlowTask{m, FLOW_WALK, 0, 0});
+            maxT = std::max<int32_t>(maxT, (desc[m].n + TB - 1) / TB);
+        }
+        for (int32_t c = 0; c < maxT; c += 2)
+            for (int32_t m = m0; m < m1; m++)
+                flow_columns(m, (desc[m].n + TB - 1) / TB, c, [&](const FlowTask &k) { tasks.push_back(k); });
+        D->flow_count.push_back((int32_t)tasks.size() - D->flow_first.back());
+        int64_t work = 0;
+        for (int32_t m = m0; m < m1; m++) {
+            const int64_t T = (desc[m].n + TB - 1) / TB;
+            work += T * T;
+        }
+        D->flow_mats.push_back(m1 - m0);
+        D->flow_work.push_back(work);
+    }
+    D->flow_ints = ints;
+    // back substitution: tasks p-major over the matrices, flags after the
+    // factorization's tickets and abort flag
+    std::vector<BsTask> bs;
+    std::vector<int64_t> bo(W);
+    int64_t bints = ints + (int64_t)D->flow_first.size() + 1;
+    const int64_t bs_base = bints;
+    int32_t maxP = 0;
+    for (int32_t w = 0; w < W; w++) {
+        const int32_t T = (desc[w].n + TB - 1) / TB;
+        bo[w] = bints;
+        bints += T + 1;
+        maxP = std::max(maxP, (T + 1) / 2);
+    }
+    for (int32_t p = 0; p < maxP; p++)
+        for (int32_t w = 0; w < W; w++)
+            if (p < ((desc[w].n + TB - 1) / TB + 1) / 2) bs.push_back(BsTask{w, p});
+    D->bs_ticket = bints;
+    D->bs_ints = bints + 2 - bs_base;
+    D->bs_count = (int32_t)bs.size();
+    BA_TRY(D->mem.alloc(&D->flow_tasks, (int64_t)tasks.size()));
+    BA_TRY(D->mem.alloc(&D->flow_flags, bints + 2));
+    BA_TRY(D->mem.alloc(&D->flow_fo, W));
+    BA_TRY(D->mem.alloc(&D->bs_tasks, std::max<int64_t>(D->bs_count, 1)));
+    BA_TRY(D->mem.alloc(&D->bs_bo, W));
+    BA_HIP(hipMemcpy(D->flow_tasks, tasks.data(), sizeof(FlowTask) * tasks.size(), hipMemcpyHostToDevice));
+    BA_HIP(hipMemcpy(D->flow_fo, fo.data(), sizeof(int64_t) * W, hipMemcpyHostToDevice));
+    if (!bs.empty())
+        BA_HIP(hipMemcpy(D->bs_tasks, bs.data(), sizeof(BsTask) * bs.size(), hipMemcpyHostToDevice));
+    BA_HIP(hipMemcpy(D->bs_bo, bo.data(), sizeof(int64_t) * W, hipMemcpyHostToDevice));
     BA_HIP(hipStreamSynchronize(s));   // the callers' streams need not wait for this one
     D->ready = true;
     return BA_OK;
@@ -2515,96 +2371,17 @@ static void launch_flow_factor(DenseState *D, const double *H, const int64_t *h_
     }
 }
 
-// Blocked right-looking factorization, one launch per step: panels of PANEL
-// 64-wide steps; a step updates the rest of its panel, each panel then the
-// trailing matrix with K = the panel's width (one read and write of the
-// trailing matrix per panel instead of per step).
-// A panel is PANEL tile columns: the trailing matrix is read and written once
-// per panel, so a longer one saves that traffic (the wide update is near it)
-// and costs more small updates inside the panel.  12000 rows: 20.4 ms with 8,
-// 22.0 with 4.  The wide kernel from 256 tiles of its own on (two thirds of
-// them in flight at once); at 6600 rows, where the two meet, both take 6.8 ms.
-// Measured and dropped: the part of an update that the next panel does not
-// need on a second stream beside that panel's factorization (20.2 ms; the
-// panel's kernels then take 1.3 to 2.4 times as long), and the same with that
-// stream held to 192-240 compute units by a mask (27.7-29.3 ms).
-static constexpr int PANEL = 8;
-static constexpr int64_t WIDE_TILES = 256;
-
-// Trailing update by panel [p, pe).
-static void launch_trailing(DenseState *D, int32_t nmat, int nsteps, int p, int pe, hipStream_t s) {
-    const int64_t rest = nsteps - pe;
-    if (rest <= 0) return;
-    const int64_t wide = (rest + 1) / 2;   // 128-wide tile rows
-    ProfScope prof("k_syrk", s);
-    if (wide * (wide + 1) / 2 >= WIDE_TILES) {
-        const int64_t sup = (wide + WSUP - 1) / WSUP, squares = sup * (sup + 1) / 2;
-        hipLaunchKernelGGL(k_syrk_wide, dim3((unsigned)((squares + 7) / 8 * 8 * WSUP * WSUP), nmat), dim3(256), 0, s,
-                           D->desc, D->prm, D->work, p, TB * (pe - p), pe);
-    } else {
-        hipLaunchKernelGGL(k_syrk, dim3((unsigned)(rest * (rest + 1) / 2), nmat), dim3(256), 0, s, D->desc, D->prm,
-                           D->work, p, TB * (pe - p), pe, nsteps);
-    }
-}
-
-static void launch_blocked_factor(DenseState *D, int32_t nmat, int nsteps, hipStream_t s) {
-    for (int p = 0; p < nsteps; p += PANEL) {
-        const int pe = std::min(p + PANEL, nsteps);
-        for (int st = p; st < pe; st++) {
-            {
-                ProfScope prof("k_potf2", s);
-                hipLaunchKernelGGL(k_potf2, dim3(1, nmat), dim3(256), 0, s, D->desc, D->prm, D->work, st);
-            }
-            const int64_t below = nsteps - st - 1;
-            if (below > 0) {
-                {
-                    ProfScope prof("k_trsm", s);
-                    hipLaunchKernelGGL(k_trsm, dim3((unsigned)below, nmat), dim3(256), 0, s, D->desc, D->prm,
-                                       D->work, st);
-                }
-                const int64_t cols = pe - st - 1;   // tile columns left in the panel
-                if (cols > 0) {
-                    const int64_t tiles = cols * below - cols * (cols - 1) / 2;
-                    ProfScope prof("k_syrk", s);
-                    hipLaunchKernelGGL(k_syrk, dim3((unsigned)tiles, nmat), dim3(256), 0, s, D->desc, D->prm,
-                                       D->work, st, TB, st + 1, pe);
-                }
-            }
-        }
-        launch_trailing(D, nmat, nsteps, p, pe, s);
-    }
-}
-
-static void launch_factor_solve(DenseState *D, int32_t nmat, int32_t max_n, const double *H, const int64_t *h_off,
-                                const double *g, double *x, const int64_t *x_off, hipStream_t s) {
-    const int nsteps = (max_n + TB - 1) / TB;
-    const int64_t nn = (int64_t)max_n * max_n;
-    if (D->flow_tasks && max_n <= FLOW_MAX_N) {
-        launch_flow_factor(D, H, h_off, g, s);   // reads H and g directly (and clears both kernels' flags)
-        // back substitution in one launch: tasks of a matrix mostly wait on
-        // each other, so a few per compute unit
-        const int grid = (int)std::min<int64_t>(D->bs_count, 2LL * cu_count());
-        if (grid > 0) {
-            ProfScope prof("k_backsub_flow", s);
-            hipLaunchKernelGGL(k_backsub_flow, dim3((unsigned)grid), dim3(256), 0, s, D->desc, D->prm, D->work, x,
-                               x_off, D->bs_tasks, D->bs_count, D->flow_flags, D->bs_bo,
-                               D->flow_flags + D->bs_ticket, D->flow_flags + D->bs_ticket + 1, flow_spin_limit());
-        }
-        return;
-    } else {
-        hipLaunchKernelGGL(k_damp_copy, dim3((unsigned)std::min<int64_t>(nblk(nn), 4096), nmat), dim3(256), 0, s,
-                           D->desc, D->prm, H, h_off, g, D->work);
-        launch_blocked_factor(D, nmat, nsteps, s);
-    }
-    // launch-per-step path: backward substitution two block rows per launch
-    // (every workgroup loads the rows' inverse and cross tiles: with three rows
-    // its 145 loads per thread need three rounds of outstanding loads, 15 us a
-    // launch)
-    constexpr int BR = 2;
-    for (int st = nsteps - 1; st >= 0; st -= BR) {
-        ProfScope prof("k_backsub_rows", s);
-        hipLaunchKernelGGL(k_backsub_rows<BR>, dim3((unsigned)std::max(st - BR + 1, 1), nmat), dim3(256), 0, s,
-                           D->desc, D->prm, D->work, x, x_off, st);
+static void launch_factor_solve(DenseState *D, const double *H, const int64_t *h_off, const double *g, double *x,
+                                const int64_t *x_off, hipStream_t s) {
+    launch_flow_factor(D, H, h_off, g, s);   // reads H and g directly (and clears both kernels' flags)
+    // back substitution in one launch: tasks of a matrix mostly wait on
+    // each other, so a few per compute unit
+    const int grid = (int)std::min<int64_t>(D->bs_count, 2LL * cu_count());
+    if (grid > 0) {
+        ProfScope prof("k_backsub_flow", s);
+        hipLaunchKernelGGL(k_backsub_flow, dim3((unsigned)grid), dim3(256), 0, s, D->desc, D->prm, D->work, x, x_off,
+                           D->bs_tasks, D->bs_count, D->flow_flags, D->bs_bo, D->flow_flags + D->bs_ticket,
+                           D->flow_flags + D->bs_ticket + 1, flow_spin_limit());
     }
 }
 
@@ -2619,7 +2396,7 @@ ba_status dense_lm_step(Problem *P, const double *poses, double tol_g, hipStream
     const int32_t W = P->n_windows;
     hipLaunchKernelGGL(k_dense_params, dim3(W), dim3(256), 0, s, W, D->desc, P->dense, D->h_off, P->lm, D->prm, tol_g,
                        P->g);
-    launch_factor_solve(D, W, D->max_n, P->dense, D->h_off, P->g, P->dx, D->x_off, s);
+    launch_factor_solve(D, P->dense, D->h_off, P->g, P->dx, D->x_off, s);
     hipLaunchKernelGGL(k_dense_hdx, dim3(nblk((int64_t)D->max_n * 64), W), dim3(256), 0, s, W, D->desc, D->prm,
                        P->dense, D->h_off, P->dx, D->hdx);
     hipLaunchKernelGGL(k_dense_finish, dim3(nblk(P->n_poses)), dim3(256), 0, s, P->n_poses, P->pose_window,
@@ -2642,15 +2419,15 @@ static size_t solve_work_bytes(int64_t n) {
 static int64_t solve_flag_ints(int64_t T) { return flow_flag_ints(T) + 2 + (T + 1) + 2; }
 static size_t solve_flag_bytes(int64_t n) {
     const int64_t T = (n + TB - 1) / TB;
-    return n <= FLOW_MAX_N ? align_up(sizeof(int) * (size_t)solve_flag_ints(T), 256) : 0;
+    return align_up(sizeof(int) * (size_t)solve_flag_ints(T), 256);
 }
 static size_t solve_task_bytes(int64_t n) {
     const int64_t T = (n + TB - 1) / TB;
-    return n <= FLOW_MAX_N ? align_up(sizeof(FlowTask) * (size_t)flow_task_count(T), 256) : 0;
+    return align_up(sizeof(FlowTask) * (size_t)flow_task_count(T), 256);
 }
 size_t dense_solve_workspace(int64_t n) {
     const int64_t T = (n + TB - 1) / TB;
-    const size_t bs = n <= FLOW_MAX_N ? sizeof(BsTask) * (size_t)((T + 1) / 2) : 0;
+    const size_t bs = sizeof(BsTask) * (size_t)((T + 1) / 2);
     return solve_head_bytes() + solve_work_bytes(n) + solve_flag_bytes(n) + solve_task_bytes(n) + bs + 256;
 }
 
@@ -2707,26 +2484,24 @@ ba_status dense_solve(int64_t n, const double *A, const double *g, double mu, do
     tmp.desc = desc;
     tmp.prm = prm;
     tmp.work = work;
-    if (n <= FLOW_MAX_N) {
-        const int64_t T = (n + TB - 1) / TB;
-        tmp.flow_flags = (int *)(p + solve_head_bytes() + solve_work_bytes(n));
-        tmp.flow_tasks = (FlowTask *)(p + solve_head_bytes() + solve_work_bytes(n) + solve_flag_bytes(n));
-        tmp.flow_fo = offs + 2;
-        tmp.flow_ints = flow_flag_ints(T);
-        tmp.flow_first.push_back(0);
-        tmp.flow_count.push_back((int32_t)flow_task_count(T));
-        tmp.flow_mats.push_back(1);
-        tmp.flow_work.push_back(T * T);
-        tmp.bs_tasks = (BsTask *)(p + solve_head_bytes() + solve_work_bytes(n) + solve_flag_bytes(n) +
-                                  solve_task_bytes(n));
-        tmp.bs_count = (int32_t)((T + 1) / 2);
-        tmp.bs_bo = offs + 3;
-        tmp.bs_ticket = flow_flag_ints(T) + 2 + T + 1;
-        tmp.bs_ints = T + 1 + 2;
-        hipLaunchKernelGGL(k_flow_tasks_one, dim3(nblk(T)), dim3(256), 0, s, (int32_t)T, tmp.flow_tasks);
-        hipLaunchKernelGGL(k_bs_tasks_one, dim3(nblk((T + 1) / 2)), dim3(256), 0, s, (int32_t)T, tmp.bs_tasks);
-    }
-    launch_factor_solve(&tmp, 1, (int32_t)n, A, offs, g, dx, offs + 1, s);
+    const int64_t T = (n + TB - 1) / TB;
+    tmp.flow_flags = (int *)(p + solve_head_bytes() + solve_work_bytes(n));
+    tmp.flow_tasks = (FlowTask *)(p + solve_head_bytes() + solve_work_bytes(n) + solve_flag_bytes(n));
+    tmp.flow_fo = offs + 2;
+    tmp.flow_ints = flow_flag_ints(T);
+    tmp.flow_first.push_back(0);
+    tmp.flow_count.push_back((int32_t)flow_task_count(T));
+    tmp.flow_mats.push_back(1);
+    tmp.flow_work.push_back(T * T);
+    tmp.bs_tasks = (BsTask *)(p + solve_head_bytes() + solve_work_bytes(n) + solve_flag_bytes(n) +
+                              solve_task_bytes(n));
+    tmp.bs_count = (int32_t)((T + 1) / 2);
+    tmp.bs_bo = offs + 3;
+    tmp.bs_ticket = flow_flag_ints(T) + 2 + T + 1;
+    tmp.bs_ints = T + 1 + 2;
+    hipLaunchKernelGGL(k_flow_tasks_one, dim3(nblk(T)), dim3(256), 0, s, (int32_t)T, tmp.flow_tasks);
+    hipLaunchKernelGGL(k_bs_tasks_one, dim3(nblk((T + 1) / 2)), dim3(256), 0, s, (int32_t)T, tmp.bs_tasks);
+    launch_factor_solve(&tmp, A, offs, g, dx, offs + 1, s);
     hipLaunchKernelGGL(k_solve_final, dim3(nblk(n)), dim3(256), 0, s, n, prm, dx, info);
     BA_HIP(hipGetLastError());
     return BA_OK;

@@ -1,6 +1,6 @@
-"""The trailing update by 128 x 128 tiles (dense systems over 6144 rows) at
-its edges: an odd number of 64-row tiles under a panel, a last tile of a few
-rows, and the sizes where the update passes from wide to narrow tiles."""
+"""Dense systems over 6144 rows, whose factorization takes its tiles by two rows
+and two columns, at its edges: odd numbers of 64-row tiles, which leave a row of
+single tiles, and last tiles of a few rows."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ pytestmark = [pytest.mark.gpu, pytest.mark.timeout(300)]
 @pytest.mark.parametrize("n", [6150, 6336, 6402, 7170])
 def test_wide_updates_against_lapack(n):
     """Backward error within 16 times LAPACK's own on the same system; a
-    non-positive pivot under a wide update is reported at its place."""
+    non-positive pivot far down is reported at its place."""
     import torch
     import paper_2608_14266_amd as ba
     dev = torch.device("cuda:0")
