@@ -305,6 +305,22 @@ __device__ __forceinline__ void store_chunk(double *__restrict__ lds, const doub
     }
 }
 
+// A task's sums over k are kept in two levels, so that their rounding does not
+// grow with the matrix: every FOLD_K values (counted from the first column,
+// whatever the schedule) the running sum goes to the total and starts again.
+// Backward error of 9000 rows 0.20 eps with one level, 0.05 eps with two.
+static constexpr int FOLD_K = 8 * TB;
+
+__device__ __forceinline__ void acc_fold(d4 tot[2][2], d4 acc[2][2]) {
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+            tot[i][j] += acc[i][j];
+            acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        }
+}
+
 // acc += A(rows ra.., cols ka..ka+kw-1) * B(rows rb.., cols kb..kb+kw-1)^T for
 // a 64 x 64 tile (kw a multiple of 32).  The next K chunk is loaded into
 // registers while the matrix cores work on the current one.
@@ -312,7 +328,7 @@ __device__ __forceinline__ void tile_gemm_nt_acc(double *__restrict__ As, double
                                                  const double *__restrict__ A, int64_t lda, int64_t ra, int64_t ka,
                                                  int64_t nra, int64_t nca, const double *__restrict__ B, int64_t ldb,
                                                  int64_t rb, int64_t kb, int64_t nrb, int64_t ncb, d4 acc[2][2],
-                                                 int kw) {
+                                                 int kw, d4 tot[2][2]) {
     double va[8], vb[8];
     load_chunk(va, A, lda, ra, ka, nra, nca);
     load_chunk(vb, B, ldb, rb, kb, nrb, ncb);
@@ -325,6 +341,7 @@ __device__ __forceinline__ void tile_gemm_nt_acc(double *__restrict__ As, double
             load_chunk(vb, B, ldb, rb, kb + kc + 32, nrb, ncb);
         }
         mma_chunk(As, Bs, acc);
+        if ((ka + kc + 32) % FOLD_K == 0) acc_fold(tot, acc);
         __syncthreads();
     }
 }
@@ -719,10 +736,11 @@ struct FlowTask {
     int32_t m, kind, i, c;
 };
 // From FLOW_QUAD_T tile rows on a task takes two columns of two rows, below one
-// column of two (k_chol_flow in ms, one / two columns: 4500 rows 1.43 / 1.50,
-// 5700 2.29 / 2.29, 6000 2.53 / 2.44, 9000 6.49 / 6.26, 12000 13.9 / 12.9, 18000
-// 44.9 / 39.7; single tiles: 3000 rows 0.86 against 0.83, 6000 3.62, 12000 20.1).
-static constexpr int FLOW_QUAD_T = 90;
+// column of two (k_chol_flow in ms, one / two columns: 3840 rows 1.07 / 1.20,
+// 4800 1.58 / 1.63, 5100 1.81 / 1.78, 6000 2.57 / 2.40, 9000 6.6 / 6.1, 12000 14.3 /
+// 12.6, 18000 46.2 / 38.7; single tiles: 3000 rows 0.86 against 0.83, 6000 3.62,
+// 12000 20.1).
+static constexpr int FLOW_QUAD_T = 80;
 static constexpr int FLOW_WALK = 0, FLOW_TILE = 1, FLOW_PDIAG = 2, FLOW_POFF = 3, FLOW_PAIR = 4, FLOW_QUAD = 5;
 static constexpr int FLOW_MAX_MATS = 128;     // walkers per launch
 static constexpr int FLOW_SPIN = 1 << 20;     // polls before a wait gives up (each about 1 us)
@@ -972,7 +990,7 @@ __device__ __forceinline__ double row_sum4(double s) {
 // is used.
 __device__ __forceinline__ void tile_syrk_y(double *__restrict__ lds, const double *__restrict__ A, int64_t n,
                                             int64_t ra, int64_t ka, int kw, const double *__restrict__ y,
-                                            d4 acc[2][2], double &q) {
+                                            d4 acc[2][2], double &q, d4 tot[2][2], double &tq) {
     double *As = lds, *ys = lds + TB * LDK;
     const int t = threadIdx.x, row = t >> 2, part = t & 3;
     double va[8], vy = 0.0;
@@ -989,6 +1007,11 @@ __device__ __forceinline__ void tile_syrk_y(double *__restrict__ lds, const doub
         mma_chunk(As, As, acc);
 #pragma unroll
         for (int e = 0; e < 8; e++) q = fma(As[row * LDK + part + 4 * e], ys[part + 4 * e], q);
+        if ((ka + kc + 32) % FOLD_K == 0) {
+            acc_fold(tot, acc);
+            tq += q;
+            q = 0.0;
+        }
         __syncthreads();
     }
 }
@@ -1192,30 +1215,35 @@ __device__ __noinline__ void flow_pdiag(const DenseDesc d, glb_f64 *gwork, const
     const int row = threadIdx.x >> 2;
     const double graw = g[R0 + std::min(row, nr - 1)];
     flow_publish(fm.ra + r);   // the raw tile (r, c) is read
-    d4 aa[2][2], ac[2][2];
+    d4 aa[2][2], ac[2][2], ta[2][2], tc[2][2];
     acc_zero(aa);
     acc_zero(ac);
-    double q = 0.0;
+    acc_zero(ta);
+    acc_zero(tc);
+    double q = 0.0, tq = 0.0;
     const int rows[2] = {r, c};
     for (int klo = 0; klo < c;) {
         const int khi = flow_wait_cols<2>(fm, rows, klo, c, gab, limit, s_val);
         if (khi < 0) return;
         const int64_t ka = (int64_t)TB * klo;
-        tile_gemm_nt_acc(lds, lds + TB * LDK, A, n, R0, ka, n, n, A, n, C0, ka, n, n, aa, TB * (khi - klo));
-        tile_syrk_y(lds, A, n, R0, ka, TB * (khi - klo), v, ac, q);
+        tile_gemm_nt_acc(lds, lds + TB * LDK, A, n, R0, ka, n, n, A, n, C0, ka, n, n, aa, TB * (khi - klo), ta);
+        tile_syrk_y(lds, A, n, R0, ka, TB * (khi - klo), v, ac, q, tc, tq);
         klo = khi;
     }
+    acc_fold(ta, aa);
     if (!flow_wait(fm.dg + c, fm.ab, gab, limit, s_val)) return;
     double *Pl = lds, *Xl = lds + TB * LTS, *ys = lds + 2 * TB * LTS;
     RowTile l;
-    flow_solve_tile(raw, nr, work + d.linv_off + (int64_t)c * TB * TB, aa, Pl, Xl, l);
+    flow_solve_tile(raw, nr, work + d.linv_off + (int64_t)c * TB * TB, ta, Pl, Xl, l);
     lds_barrier();
     rows_to_lds(l, Pl, nr);
     if (threadIdx.x < TB) ys[threadIdx.x] = v[C0 + threadIdx.x];
     lds_barrier();
     mma64_nt<false>(Pl, Pl, 1.0, ac);
     q += lds_gemv_part(Pl, ys);
-    acc_sub(rrr, ac);
+    q += tq;
+    acc_fold(tc, ac);
+    acc_sub(rrr, tc);
     acc_to_global(rrr, A, n, R0, R0, nr, nr);
     q = row_sum4(q);
     if ((threadIdx.x & 3) == 0 && row < nr) store_through(v + R0 + row, -graw - q);
@@ -1240,22 +1268,25 @@ __device__ __noinline__ void flow_poff(const DenseDesc d, glb_f64 *gwork, const 
     // L_rc goes to the tile (r, c) in place: first the diagonal task (earlier
     // in the queue) must have read the raw tile
     if (!flow_wait(fm.ra + r, fm.ab, gab, limit, s_val)) return;
-    d4 aa[2][2], ab[2][2];
+    d4 aa[2][2], ab[2][2], ta[2][2], tb[2][2];
     acc_zero(aa);
     acc_zero(ab);
+    acc_zero(ta);
+    acc_zero(tb);
     const int rows[3] = {r, c, c + 1};
     for (int klo = 0; klo < c;) {
         const int khi = flow_wait_cols<3>(fm, rows, klo, c, gab, limit, s_val);
         if (khi < 0) return;
         const int64_t ka = (int64_t)TB * klo;
-        tile_gemm_nt_acc(lds, lds + TB * LDK, A, n, R0, ka, n, n, A, n, C0, ka, n, n, aa, TB * (khi - klo));
-        tile_gemm_nt_acc(lds, lds + TB * LDK, A, n, R0, ka, n, n, A, n, C1, ka, n, n, ab, TB * (khi - klo));
+        tile_gemm_nt_acc(lds, lds + TB * LDK, A, n, R0, ka, n, n, A, n, C0, ka, n, n, aa, TB * (khi - klo), ta);
+        tile_gemm_nt_acc(lds, lds + TB * LDK, A, n, R0, ka, n, n, A, n, C1, ka, n, n, ab, TB * (khi - klo), tb);
         klo = khi;
     }
+    acc_fold(ta, aa);
     if (!flow_wait(fm.dg + c, fm.ab, gab, limit, s_val)) return;
     double *Pl = lds, *Xl = lds + TB * LTS, *Ll = lds + 2 * TB * LTS;
     RowTile l;
-    flow_solve_tile(raw, nr, work + d.linv_off + (int64_t)c * TB * TB, aa, Pl, Xl, l);
+    flow_solve_tile(raw, nr, work + d.linv_off + (int64_t)c * TB * TB, ta, Pl, Xl, l);
     rows_to_global(l, A, n, R0, C0, nr);
     flow_publish(fm.fl + r * fm.T + c);
     // block c is published ahead of the tile L_c+1,c that the last term takes
@@ -1264,7 +1295,8 @@ __device__ __noinline__ void flow_poff(const DenseDesc d, glb_f64 *gwork, const 
     tile_to_lds(Ll, A, n, C1, C0, TB, TB);
     lds_barrier();
     mma64_nt<false>(Pl, Ll, 1.0, ab);
-    acc_sub(rrp, ab);
+    acc_fold(tb, ab);
+    acc_sub(rrp, tb);
     acc_to_global(rrp, A, n, R0, C1, nr, TB);
     flow_publish(fm.po + r);
 }
@@ -1278,21 +1310,23 @@ __device__ __noinline__ void flow_tile(const DenseDesc d, glb_f64 *gwork, const 
     double *A = work + d.a_off;
     const int64_t R0 = (int64_t)TB * i, C0 = (int64_t)TB * c;
     const int nr = (int)std::min<int64_t>(TB, n - R0);
-    d4 acc[2][2];
+    d4 acc[2][2], tot[2][2];
     acc_zero(acc);
+    acc_zero(tot);
     const int rows[2] = {i, c};
     for (int klo = 0; klo < c;) {
         const int khi = flow_wait_cols<2>(fm, rows, klo, c, gab, limit, s_val);
         if (khi < 0) return;
         const int64_t ka = (int64_t)TB * klo;
-        tile_gemm_nt_acc(lds, lds + TB * LDK, A, n, R0, ka, n, n, A, n, C0, ka, n, n, acc, TB * (khi - klo));
+        tile_gemm_nt_acc(lds, lds + TB * LDK, A, n, R0, ka, n, n, A, n, C0, ka, n, n, acc, TB * (khi - klo), tot);
         klo = khi;
     }
+    acc_fold(tot, acc);
     d4 raw[2][2];
     tile_to_acc(raw, H, n, R0, C0, nr, TB);
     if (!flow_wait(fm.dg + c, fm.ab, gab, limit, s_val)) return;
     RowTile l;
-    flow_solve_tile(raw, nr, work + d.linv_off + (int64_t)c * TB * TB, acc, lds, lds + TB * LTS, l);
+    flow_solve_tile(raw, nr, work + d.linv_off + (int64_t)c * TB * TB, tot, lds, lds + TB * LTS, l);
     rows_to_global(l, A, n, R0, C0, nr);
     flow_publish(fm.fl + i * fm.T + c);
 }
@@ -1306,11 +1340,17 @@ __device__ __noinline__ void flow_tile(const DenseDesc d, glb_f64 *gwork, const 
 template <int NB>
 struct WidePart {
     static constexpr int K = NB == 1 ? 32 : 16;      // k values staged at a time
-    static constexpr int LD = K + 2;                 // LDS row stride: 16-byte reads of 16 rows fall into distinct banks
-    static constexpr int ROWS = (2 + NB) * TB;       // staged rows: of the two tile rows, then of the columns' tile rows
+    static constexpr int LD = K + 2;                 // LDS row stride: 16 rows' reads fall into distinct banks
+    static constexpr int ROWS = (2 + NB) * TB;       // staged rows: the two tile rows', then the columns'
     static constexpr int XB = 2 * NB, YB = 4;        // the wave's 16 x 16 blocks
     static constexpr int LOADS = ROWS * K / 512;     // 16-byte loads per thread and stage
     d4 a[XB][YB];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int x = 0; x < XB; x++)
+#pragma unroll
+            for (int y = 0; y < YB; y++) a[x][y] = d4{0.0, 0.0, 0.0, 0.0};
+    }
     // first row and column of the wave's part
     static __device__ __forceinline__ int r0() {
         const int w = threadIdx.x >> 6;
@@ -1318,7 +1358,8 @@ struct WidePart {
     }
     static __device__ __forceinline__ int c0() { return NB == 1 ? 0 : TB * ((threadIdx.x >> 6) & 1); }
 };
-static constexpr int WIDE_LDS = std::max(2 * WidePart<1>::ROWS * WidePart<1>::LD, 2 * WidePart<2>::ROWS * WidePart<2>::LD);
+static constexpr int WIDE_LDS =
+    2 * std::max(WidePart<1>::ROWS * WidePart<1>::LD, WidePart<2>::ROWS * WidePart<2>::LD);
 
 template <int NB>
 __device__ __forceinline__ void part_load(v2d (&v)[WidePart<NB>::LOADS], const double *__restrict__ A, int64_t ld,
@@ -1334,41 +1375,57 @@ __device__ __forceinline__ void part_load(v2d (&v)[WidePart<NB>::LOADS], const d
 }
 
 template <int NB>
+__device__ __forceinline__ void part_fold(WidePart<NB> &tot, WidePart<NB> &sum) {
+#pragma unroll
+    for (int x = 0; x < WidePart<NB>::XB; x++)
+#pragma unroll
+        for (int y = 0; y < WidePart<NB>::YB; y++) tot.a[x][y] += sum.a[x][y];
+    sum.clear();
+}
+
+template <int NB>
 __device__ __forceinline__ void part_gemm(double *__restrict__ lds, const double *__restrict__ A, int64_t n,
-                                          int64_t ra, int64_t rb, int64_t k0, int kw, WidePart<NB> &acc) {
+                                          int64_t ra, int64_t rb, int64_t k0, int kw, WidePart<NB> &acc,
+                                          WidePart<NB> &tot) {
     using P = WidePart<NB>;
     constexpr int TR = P::K / 2, STEP = 256 / TR;
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
     v2d v[P::LOADS];
     part_load<NB>(v, A, n, ra, rb, k0, n);
 #pragma unroll 1
-    for (int kc = 0; kc < kw; kc += P::K) {
-        double *S = lds + ((kc / P::K) & 1) * P::ROWS * P::LD;
+    for (int kc = 0; kc < kw;) {
+        const int ke = std::min(kw, kc + FOLD_K - (int)((k0 + kc) % FOLD_K));
+        // no fold in the inner loop: as a branch there it cost 12000 rows 13.9 ms against 12.6
+#pragma unroll 1
+        for (; kc < ke; kc += P::K) {
+            double *S = lds + ((kc / P::K) & 1) * P::ROWS * P::LD;
 #pragma unroll
-        for (int e = 0; e < P::LOADS; e++)
-            *reinterpret_cast<v2d *>(S + ((int)threadIdx.x / TR + STEP * e) * P::LD + 2 * (threadIdx.x % TR)) = v[e];
-        lds_barrier();   // the other buffer is rewritten only after the next one
-        part_load<NB>(v, A, n, ra, rb, k0 + std::min(kc + P::K, kw - P::K), n);
-        __builtin_amdgcn_sched_barrier(0);   // the loads go out here, not before the stores that take them
-        const double *As = S + (P::r0() + li) * P::LD + 2 * lk, *Bs = S + (2 * TB + P::c0() + li) * P::LD + 2 * lk;
+            for (int e = 0; e < P::LOADS; e++)
+                *reinterpret_cast<v2d *>(S + (threadIdx.x / TR + STEP * e) * P::LD + 2 * (threadIdx.x % TR)) = v[e];
+            lds_barrier();   // the other buffer is rewritten only after the next one
+            part_load<NB>(v, A, n, ra, rb, k0 + std::min(kc + P::K, kw - P::K), n);
+            __builtin_amdgcn_sched_barrier(0);   // the loads go out here, not before the stores that take them
+            const double *As = S + (P::r0() + li) * P::LD + 2 * lk, *Bs = S + (2 * TB + P::c0() + li) * P::LD + 2 * lk;
 #pragma unroll
-        for (int kk = 0; kk < P::K; kk += 8) {
-            v2d a[P::XB], b[P::YB];
+            for (int kk = 0; kk < P::K; kk += 8) {
+                v2d a[P::XB], b[P::YB];
 #pragma unroll
-            for (int q = 0; q < P::XB; q++) a[q] = *reinterpret_cast<const v2d *>(As + 16 * q * P::LD + kk);
+                for (int q = 0; q < P::XB; q++) a[q] = *reinterpret_cast<const v2d *>(As + 16 * q * P::LD + kk);
 #pragma unroll
-            for (int q = 0; q < P::YB; q++) b[q] = *reinterpret_cast<const v2d *>(Bs + 16 * q * P::LD + kk);
+                for (int q = 0; q < P::YB; q++) b[q] = *reinterpret_cast<const v2d *>(Bs + 16 * q * P::LD + kk);
 #pragma unroll
-            for (int x = 0; x < P::XB; x++)
+                for (int x = 0; x < P::XB; x++)
 #pragma unroll
-                for (int y = 0; y < P::YB; y++)
-                    acc.a[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x].x, b[y].x, acc.a[x][y], 0, 0, 0);
+                    for (int y = 0; y < P::YB; y++)
+                        acc.a[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x].x, b[y].x, acc.a[x][y], 0, 0, 0);
 #pragma unroll
-            for (int x = 0; x < P::XB; x++)
+                for (int x = 0; x < P::XB; x++)
 #pragma unroll
-                for (int y = 0; y < P::YB; y++)
-                    acc.a[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x].y, b[y].y, acc.a[x][y], 0, 0, 0);
+                    for (int y = 0; y < P::YB; y++)
+                        acc.a[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x].y, b[y].y, acc.a[x][y], 0, 0, 0);
+            }
         }
+        if ((k0 + kc) % FOLD_K == 0) part_fold<NB>(tot, acc);
     }
 }
 
@@ -1421,18 +1478,17 @@ __device__ __forceinline__ void flow_wide(const DenseDesc &d, glb_f64 *gwork, co
     double *A = work + d.a_off;
     const int64_t R0 = (int64_t)TB * i, C0 = (int64_t)TB * c;
     const int nr = (int)std::min<int64_t>(2 * TB, n - R0);   // rows of both tiles (the first is whole)
-    WidePart<NB> acc;
-#pragma unroll
-    for (int x = 0; x < WidePart<NB>::XB; x++)
-#pragma unroll
-        for (int y = 0; y < WidePart<NB>::YB; y++) acc.a[x][y] = d4{0.0, 0.0, 0.0, 0.0};
+    WidePart<NB> sum, acc;   // the running sum, the total
+    sum.clear();
+    acc.clear();
     const int rows[4] = {i, i + 1, c, NB == 2 ? c + 1 : c};
     for (int klo = 0; klo < c;) {
         const int khi = flow_wait_cols<4>(fm, rows, klo, c, gab, limit, s_val);
         if (khi < 0) return;
-        part_gemm<NB>(lds, A, n, R0, C0, (int64_t)TB * klo, TB * (khi - klo), acc);
+        part_gemm<NB>(lds, A, n, R0, C0, (int64_t)TB * klo, TB * (khi - klo), sum, acc);
         klo = khi;
     }
+    part_fold<NB>(acc, sum);
     double *Xl = lds + 2 * TB * LTS;   // the column's sums in tile layout at lds, then the inverse
 #pragma unroll 1
     for (int q = 0; q < NB; q++) {
