@@ -500,8 +500,8 @@ ba_status ba_release_cached_memory(void);
  * Kernel timing (instrumentation, not part of the method): when enabled,
  * later calls record a pair of HIP events on their stream around each launch
  * of the residual kernel ("k_vox"), the derivative kernel ("k_pose"), the
- * diagonal-block factor ("k_potf2"), the matrix-core factorization kernels
- * ("k_trsm", "k_syrk"), the per-window MM increment solve ("k_window_solve_mm")
+ * dense factorization and back substitution ("k_chol_flow",
+ * "k_backsub_flow"), the per-window MM increment solve ("k_window_solve_mm")
  * and the LM decision ("k_decide"); ba_iterate then
  * runs its launches eagerly instead of replaying a captured graph.
  * ba_profile_query waits for the recorded events and returns the summed

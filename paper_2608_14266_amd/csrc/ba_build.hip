@@ -11,7 +11,8 @@
 //     are packed 64 to a wave group, cluster k of lane l at cbase + 64 k + l,
 //     so the residual pass reads fully coalesced with no divergence;
 //   * a pose-major copy cut into chunks of one pose, so the derivative pass
-//     reduces per pose in registers without scatter or atomics.
+//     reduces per pose in registers without scatter or atomics;
+// both in tiles of 64 clusters (Tile<T>).  The plan is formed on the device.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

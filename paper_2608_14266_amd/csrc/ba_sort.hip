@@ -3,8 +3,9 @@
 //   * exclusive prefix scan of int64 (reduce-then-scan, three launches);
 //   * stable LSD radix sort of (uint64 key, uint32 value) pairs with 8-bit
 //     digits: per-tile digit histograms, a scan of the (digit, tile) counts
-//     and a stable scatter whose within-tile ranks come from wave ballots
-//     and per-wave digit counts, so equal keys keep their input order.
+//     and a stable scatter in which every wave ranks its own keys against a
+//     digit table of its own, so equal keys keep their input order;
+//   * runs of equal keys (count and starts).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

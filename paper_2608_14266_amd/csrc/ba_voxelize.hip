@@ -10,7 +10,7 @@
 //   k_vx_bbox         one block: bounding box and flags of the whole cloud
 //   k_vx_keys_points  packed (cell offsets, scan) key per point
 //   k_vx_keys_up      packed key of the parent cell per cluster
-//   (stable LSD radix sort of the keys, head flags, exclusive scan)
+//   (stable LSD radix sort of the keys, runs of equal keys)
 //   k_vx_sum_points   8 lanes per level-1 cluster: raw sums of its points
 //   k_vx_sum_clusters thread per level-k cluster: sums of its child clusters
 //   k_vx_select       thread per cell: voxel covariance, eigenvalues, decision
