@@ -550,9 +550,11 @@ ba_status replan_chunks(Problem *P, int32_t chunk_len, hipStream_t s) {
     const int32_t N = P->n_poses;
     std::vector<int32_t> chunk_ptr(N + 1, 0);
     int64_t n = 0;
+    bool one = true;
     for (int32_t j = 0; j < N; j++) {
         chunk_ptr[j] = (int32_t)n;
         n += (P->h_pose_start[j + 1] - P->h_pose_start[j] + chunk_len - 1) / chunk_len;
+        one = one && n == j + 1;
     }
     chunk_ptr[N] = (int32_t)n;
     if (n > P->chunk_cap) {
@@ -565,6 +567,7 @@ ba_status replan_chunks(Problem *P, int32_t chunk_len, hipStream_t s) {
     BA_HIP(hipGetLastError());
     BA_HIP(hipStreamSynchronize(s));
     P->n_chunks = (int32_t)n;
+    P->one_chunk = one && N > 0;
     P->chunk_len = chunk_len;
     P->tune.chunk_len = chunk_len;
     return BA_OK;

@@ -26,6 +26,31 @@ __device__ __forceinline__ double window_cost_sum(int g0, int g1, const double *
     return block_sum<DECIDE_THREADS / 64>(window_cost_part(g0, g1, group_cost), red);
 }
 
+// The same sum by a block of B threads, thread t playing threads t, t + B, ...
+template <int B>
+__device__ __forceinline__ double window_cost_ordered(int g0, int g1, const double *__restrict__ group_cost,
+                                                      double *red) {
+    constexpr int V = DECIDE_THREADS / B, NWB = B / 64;
+    double c[V];
+#pragma unroll
+    for (int v = 0; v < V; v++) c[v] = 0.0;
+    for (int i = g0 + threadIdx.x; i < g1; i += DECIDE_THREADS) {
+#pragma unroll
+        for (int v = 0; v < V; v++)
+            if (i + v * B < g1) c[v] += group_cost[i + v * B];
+    }
+#pragma unroll
+    for (int v = 0; v < V; v++) {
+        const double s = wave_sum(c[v]);
+        if ((threadIdx.x & 63) == 0) red[v * NWB + (threadIdx.x >> 6)] = s;
+    }
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < DECIDE_THREADS / 64; i++) s += red[i];
+    return s;
+}
+
 // Copy of a window's 12 * n pose values, eight loads in flight per thread
 // before their stores (the two arrays never overlap).
 __device__ __forceinline__ void copy_window_poses(const double *__restrict__ src, double *__restrict__ dst,

@@ -569,14 +569,8 @@ __device__ __forceinline__ void pose_plus(const double *T, const double *x, doub
     out[11] = T[11] + x[5];
 }
 
-// Component k of pose j's derivatives: its chunks' partial sums in chunk order,
-// stored to g (6) or, both triangles, to H (6x6).
-__device__ __forceinline__ void reduce_pose_value(int j, int k, const int32_t *chunk_ptr, const double *partials,
-                                                  double *g, double *H) {
-    double s = 0.0;
-    const int c0 = chunk_ptr[j], c1 = chunk_ptr[j + 1];
-#pragma unroll 4
-    for (int c = c0; c < c1; c++) s += partials[(int64_t)c * NPART + k];
+// Component k of pose j's derivatives to g (6) or, both triangles, to H (6x6).
+__device__ __forceinline__ void store_pose_value(int j, int k, double s, double *g, double *H) {
     double *h = H + 36LL * j;
     if (k < 6) {
         g[6LL * j + k] = s;
@@ -595,6 +589,16 @@ __device__ __forceinline__ void reduce_pose_value(int j, int k, const int32_t *c
         h[6 * r + c] = s;
         h[6 * c + r] = s;
     }
+}
+
+// The same from the partial sums of the pose's chunks, in chunk order.
+__device__ __forceinline__ void reduce_pose_value(int j, int k, const int32_t *chunk_ptr, const double *partials,
+                                                  double *g, double *H) {
+    double s = 0.0;
+    const int c0 = chunk_ptr[j], c1 = chunk_ptr[j + 1];
+#pragma unroll 4
+    for (int c = c0; c < c1; c++) s += partials[(int64_t)c * NPART + k];
+    store_pose_value(j, k, s, g, H);
 }
 
 // The trial pose of scan j, and in the precision form (pdelta not null) its

@@ -114,6 +114,7 @@ struct Problem {
     int32_t n_groups = 0;
     int64_t c_pad = 0;          // clusters incl. padding in the K_vox layout
     int32_t n_chunks = 0;
+    bool one_chunk = false;     // every pose has exactly one chunk
     int32_t chunk_len = 0;      // max clusters per pose chunk
     int32_t max_m = 0;
     int32_t prec = BA_PREC_F64;   // storage of the two iteration copies

@@ -14,6 +14,8 @@ void launch_pose_chunks(Problem *P, const double *poses, bool use_lm, hipStream_
 // cost: NULL, or the windows' residuals at the same poses, summed in the same launch
 void launch_pose_derivs(Problem *P, const double *poses, bool use_lm, double *g, double *H, hipStream_t s,
                         bool hess64 = false, double *cost = nullptr);
+// whether launch_pose_derivs is one launch without a reduction (every pose one chunk)
+bool pose_direct(const Problem *P);
 void launch_voxel_eig(Problem *P, double *out, hipStream_t s);
 
 // LM (ba_lm.hip)

@@ -316,7 +316,7 @@ static int32_t widest_window(const Problem *P) {
     return widest;
 }
 
-bool fold_reduce(const Problem *P) { return widest_window(P) <= FOLD_POSES; }
+bool fold_reduce(const Problem *P) { return !pose_direct(P) && widest_window(P) <= FOLD_POSES; }
 
 void launch_window_solve_mm(Problem *P, const double *poses, double tol_g, hipStream_t s) {
     const int32_t widest = widest_window(P);
@@ -335,7 +335,7 @@ void launch_window_solve_mm(Problem *P, const double *poses, double tol_g, hipSt
                        0, s, P->n_windows,                                                                         \
                        P->win_pose_ptr, P->lm, P->g, P->H, P->chunk_ptr, P->partials, poses, P->dx, P->pose_q,      \
                        P->pose_info, P->poses_trial, tol_g, P->ref_poses, P->pdelta)
-    if (widest <= FOLD_POSES) BA_WSOLVE(true);
+    if (fold_reduce(P)) BA_WSOLVE(true);
     else BA_WSOLVE(false);
 #undef BA_WSOLVE
 }
