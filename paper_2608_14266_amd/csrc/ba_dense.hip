@@ -1076,7 +1076,9 @@ __device__ __forceinline__ void low_damp(LowTile &D, double mu, double floor_) {
 }
 
 // D -= L L^T on the lower blocks S0 <= s < S1 of each wave, L (64 x 64) in LDS
-// with row stride LTS.
+// with row stride LTS.  The products are summed from zero: started from D, each
+// of them would round at D's size (error of a solution, 2-norm, 150 to 12000
+// rows: 1.1-1.9e-15 from D, 0.7-1.1e-15 from zero).
 template <int S0, int S1>
 __device__ __forceinline__ void low_syrk_sub(LowTile &D, const double *__restrict__ L) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
@@ -1085,7 +1087,7 @@ __device__ __forceinline__ void low_syrk_sub(LowTile &D, const double *__restric
         if (s > 0 && w == 0) break;
         int rb, cb;
         low_block(w, s, rb, cb);
-        d4 a0 = D.b[s], a1 = {0.0, 0.0, 0.0, 0.0};
+        d4 a0 = {0.0, 0.0, 0.0, 0.0}, a1 = a0;
 #pragma unroll
         for (int kk = 0; kk < TB; kk += 8) {
             const double x0 = -L[(16 * rb + li) * LTS + kk + lk], y0 = L[(16 * cb + li) * LTS + kk + lk];
@@ -1093,7 +1095,7 @@ __device__ __forceinline__ void low_syrk_sub(LowTile &D, const double *__restric
             a0 = __builtin_amdgcn_mfma_f64_16x16x4f64(x0, y0, a0, 0, 0, 0);
             a1 = __builtin_amdgcn_mfma_f64_16x16x4f64(x1, y1, a1, 0, 0, 0);
         }
-        D.b[s] = a0 + a1;
+        D.b[s] += a0 + a1;
     }
 }
 
