@@ -596,7 +596,10 @@ __device__ __forceinline__ void put_diag_elem(double *__restrict__ T, int r, int
 // mirrored in LDS and kept in both triangles by the trailing updates.
 // The block is held in T (layout of put_diag_elem; the blocks above the
 // diagonal are work space) with the right-hand side slice in yv; X and sfail
-// are LDS work space (sfail zero on entry).  `pre` is run by each wave first:
+// are LDS work space (sfail zero on entry; block p's failure goes to sfail[p],
+// which the waves read behind block p's barrier: with one word for all blocks a
+// wave late at its read could find block p + 1's and leave a barrier early).
+// `pre` is run by each wave first:
 // wave 0 fills block (0, 0) and yv[0..16), the others the rest but blocks (2, 2),
 // (3, 2) and (3, 3), which `late` fills in waves 1, 2 and 3 a block later (or
 // the caller has filled all and synchronised).  Writes y to y[0..nb) and L^-1
@@ -609,7 +612,7 @@ __device__ __forceinline__ void put_diag_elem(double *__restrict__ T, int r, int
 // in flight.
 template <class Pre, class Late>
 __device__ __forceinline__ int factor_diag_tile(double *__restrict__ T, double *__restrict__ X,
-                                                double *__restrict__ yv, int &sfail, int64_t k0, int nb,
+                                                double *__restrict__ yv, int *sfail, int64_t k0, int nb,
                                                 double *__restrict__ y, double *__restrict__ linv, Pre pre,
                                                 Late late) {
     const int w = threadIdx.x >> 6;
@@ -631,7 +634,7 @@ __device__ __forceinline__ int factor_diag_tile(double *__restrict__ T, double *
                 wave_sync();
             }
             const int f = factor_block(T, X, yv, p, b);
-            if (f && i == 0) sfail = (int)(k0 + c0 + f);
+            if (f && i == 0) sfail[p] = (int)(k0 + c0 + f);
         } else if (p == 1) {
             late(w);
             wave_sync();
@@ -684,7 +687,7 @@ __device__ __forceinline__ int factor_diag_tile(double *__restrict__ T, double *
             if (w == 3) write_inverse_rows(X, linv, 1, i);
         }
         lds_barrier();
-        if (sfail) return sfail;
+        if (const int f = sfail[p]) return f;
     }
     if (w >= 1) inverse_block(X, 3, w - 1, s);
     lds_barrier();
@@ -1581,15 +1584,13 @@ __device__ __noinline__ void flow_walk(const DenseDesc d, glb_i32 *info, glb_f64
     double *work = (double *)gwork, *lds = (double *)glds, *yv = (double *)gyv;
     const double *H = (const double *)rw.H, *g = (const double *)rw.g;
     double *ybuf = (double *)gybuf;
-    int &sfail = *(int *)gsfail;
+    int *sfail = (int *)gsfail;
     const int64_t n = d.n;
     double *A = work + d.a_off, *v = work + d.v_off;
     double *Tl = lds, *Xl = lds + TB * LTS, *Ll = lds + 2 * TB * LTS;
     const int t = threadIdx.x, row = t >> 2;
-    if (t == 0) {
-        sfail = 0;
-        *count = 0;
-    }
+    if (t < NPB) sfail[t] = 0;
+    if (t == 0) *count = 0;
     // blocks 0 and 1 have no partial sums: raw tiles
     int nb = (int)std::min<int64_t>(TB, n);
     LowTile dt;
@@ -1665,7 +1666,7 @@ __global__ __launch_bounds__(256) void k_chol_flow(const DenseDesc *__restrict__
                                                    int *__restrict__ gab, int limit) {
     __shared__ __align__(16) double lds[std::max(3 * TB * LTS, WIDE_LDS)];
     __shared__ double yv[TB], ybuf[TB];
-    __shared__ int s_task, s_val, sfail, s_count;
+    __shared__ int s_task, s_val, sfail[NPB], s_count;
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) s_task = atomicAdd(queue, 1);
@@ -1686,7 +1687,7 @@ __global__ __launch_bounds__(256) void k_chol_flow(const DenseDesc *__restrict__
         lds_i32 *sv = (lds_i32 *)&s_val;
         if (tk.kind == FLOW_WALK)
             flow_walk(d, (glb_i32 *)&prm[tk.m].info, gw, rw, fm, ga, limit, (lds_f64 *)lds, (lds_f64 *)yv,
-                      (lds_f64 *)ybuf, (lds_i32 *)&sfail, sv, (lds_i32 *)&s_count);
+                      (lds_f64 *)ybuf, (lds_i32 *)sfail, sv, (lds_i32 *)&s_count);
         else if (tk.kind == FLOW_TILE)
             flow_tile(d, gw, rw, fm, tk.i, tk.c, ga, limit, (lds_f64 *)lds, sv);
         else if (tk.kind == FLOW_PAIR)
