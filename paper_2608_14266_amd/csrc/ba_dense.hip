@@ -2054,7 +2054,6 @@ static int flow_spin_limit() {
 // captured graph), then one persistent launch per group of matrices.
 struct DenseState {
     DevArena mem;
-    bool ready = false;
     // pairs
     int32_t n_seg = 0;
     PairSeg *segs = nullptr;
@@ -2174,11 +2173,9 @@ int64_t dense_device_bytes(const Problem *P) {
     return D ? (int64_t)D->mem.bytes : 0;
 }
 
-ba_status dense_prepare(Problem *P) {
-    if (P->dense_state) return BA_OK;
+static ba_status dense_form(Problem *P) {
     hipStream_t s = 0;
-    DenseState *D = new DenseState();
-    P->dense_state = D;
+    DenseState *D = dense_state(P);
     const int64_t C = P->n_clusters;
     const int32_t W = P->n_windows;
     // voxel runs of the voxel-major clusters and their pair counts (host),
@@ -2349,8 +2346,22 @@ ba_status dense_prepare(Problem *P) {
         BA_HIP(hipMemcpy(D->bs_tasks, bs.data(), sizeof(BsTask) * bs.size(), hipMemcpyHostToDevice));
     BA_HIP(hipMemcpy(D->bs_bo, bo.data(), sizeof(int64_t) * W, hipMemcpyHostToDevice));
     BA_HIP(hipStreamSynchronize(s));   // the callers' streams need not wait for this one
-    D->ready = true;
     return BA_OK;
+}
+
+// The coupled form's plan and buffers, formed by the first call that needs
+// them.  After a failure (most likely of an allocation) nothing is kept, so
+// that the next call fails or succeeds by itself.
+ba_status dense_prepare(Problem *P) {
+    if (P->dense_state) return BA_OK;
+    P->dense_state = new DenseState();
+    const ba_status st = dense_form(P);
+    if (st != BA_OK) {
+        P->dense = nullptr;
+        P->dense_total = 0;
+        dense_release(P);
+    }
+    return st;
 }
 
 // Coupled Hessian at `poses` into hess_out (one window, standalone) or into
