@@ -52,6 +52,7 @@ ba_status dense_lm_step(Problem *P, const double *poses, double tol_g, hipStream
 void launch_dense_gnorm(Problem *P, hipStream_t s, double tol_g = 0.0);
 void dense_release(Problem *P);
 ba_status dense_prepare(Problem *P);
+ba_status dense_prepare_exact(Problem *P);
 
 // ---------------------------------------------------------------- profiling
 // Event pairs recorded around kernel launches (eager launches only: a call
@@ -449,7 +450,7 @@ ba_status ba_iterate(ba_problem *p, double *poses_inout, const ba_lm_options *op
         if (!P->lm_init) BA_TRY(P->mem.alloc(&P->lm_init, 4LL * W));
         BA_HIP(hipMemcpyAsync(P->lm_init, opt->resume, sizeof(double) * 4 * W, hipMemcpyHostToDevice, stream));
     }
-    if (opt->mode == BA_MODE_COUPLED) BA_TRY(dense_prepare(P));
+    if (opt->mode == BA_MODE_COUPLED) BA_TRY(opt->exact_below > 0.0 ? dense_prepare_exact(P) : dense_prepare(P));
     double *dtrace = nullptr;
     if (trace && iters > 0) {
         if (P->trace_cap < iters) {

@@ -2364,6 +2364,14 @@ ba_status dense_prepare(Problem *P) {
     return st;
 }
 
+// The exact form's vectors, before any capture: an allocation cannot be captured.
+ba_status dense_prepare_exact(Problem *P) {
+    BA_TRY(dense_prepare(P));
+    DenseState *D = dense_state(P);
+    if (!D->ev) BA_TRY(D->mem.alloc(&D->ev, 18 * std::max<int64_t>(P->n_clusters, 1)));
+    return BA_OK;
+}
+
 // Coupled Hessian at `poses` into hess_out (one window, standalone) or into
 // the problem's per-window dense buffers (LM).
 ba_status dense_assemble(Problem *P, const double *poses, double *hess_out, bool use_lm, hipStream_t s) {
@@ -2395,13 +2403,12 @@ ba_status dense_assemble(Problem *P, const double *poses, double *hess_out, bool
 // norm is below exact_below.
 ba_status dense_assemble_exact(Problem *P, const double *poses, double *hess_out, bool use_lm, double exact_below,
                                hipStream_t s) {
-    BA_TRY(dense_prepare(P));
-    DenseState *D = dense_state(P);
     if (P->prec != BA_PREC_F64) {
         set_error("the exact Hessian is built for FP64 problems only");
         return BA_E_UNSUPPORTED;
     }
-    if (!D->ev) BA_TRY(D->mem.alloc(&D->ev, 18 * std::max<int64_t>(P->n_clusters, 1)));
+    BA_TRY(dense_prepare_exact(P));
+    DenseState *D = dense_state(P);
     double *dst = hess_out ? hess_out : P->dense;
     const LMState *lm = use_lm ? P->lm : nullptr;
     hipLaunchKernelGGL(k_exact_vecs, dim3(nblk(D->n_vx)), dim3(256), 0, s, D->n_vx, D->vptr, P->c_rec,
