@@ -117,8 +117,11 @@ hipError_t pool_alloc(void **p, size_t nb, size_t *bytes) {
     if ((*p = take(want, dev, bytes))) return hipSuccess;
     *bytes = want;
     e = hipMalloc(p, want);
-    if (e == hipSuccess) return e;
-    // out of memory: without what is kept, and without the rounding
+    // Only a lack of memory is a reason to give up what is kept: another error
+    // (inside a stream capture this thread may neither allocate nor release)
+    // would meet the releases too.
+    if (e != hipErrorOutOfMemory) return e;
+    // once more without what is kept, and without the rounding
     (void)hipGetLastError();
     pool_trim();
     *bytes = nb;

@@ -1,0 +1,106 @@
+// The pool of kept memory (csrc/ba_mem.hip) on the host, over stand-ins of the
+// HIP calls it makes that can be told to fail.  One scenario per run, named by
+// the first argument; exit status 0 if it holds.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include <hip/hip_runtime.h>
+
+#include "ba.h"
+#include "ba_host.hpp"
+
+// ---------------------------------------------------------------- stand-ins
+static std::map<void *, size_t> g_dev, g_pinned;   // what the "driver" holds
+static size_t g_total = (size_t)256 << 30, g_used = 0;
+static hipError_t g_malloc_error = hipSuccess, g_free_error = hipSuccess, g_host_error = hipSuccess;
+static uintptr_t g_next = (uintptr_t)1 << 40;
+
+static hipError_t take(std::map<void *, size_t> &m, void **p, size_t nb) {
+    if (g_used + nb > g_total) return hipErrorOutOfMemory;
+    *p = (void *)g_next;
+    g_next += nb + 4096;
+    m[*p] = nb;
+    g_used += nb;
+    return hipSuccess;
+}
+static hipError_t drop(std::map<void *, size_t> &m, void *p) {
+    if (!m.count(p)) return hipErrorInvalidValue;
+    g_used -= m[p];
+    m.erase(p);
+    return hipSuccess;
+}
+
+extern "C" {
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipMemGetInfo(size_t *f, size_t *t) {
+    *f = g_total - g_used;
+    *t = g_total;
+    return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t nb) { return g_malloc_error != hipSuccess ? g_malloc_error : take(g_dev, p, nb); }
+hipError_t hipFree(void *p) { return g_free_error != hipSuccess ? g_free_error : drop(g_dev, p); }
+hipError_t hipHostMalloc(void **p, size_t nb, unsigned) {
+    return g_host_error != hipSuccess ? g_host_error : take(g_pinned, p, nb);
+}
+hipError_t hipHostFree(void *p) { return g_free_error != hipSuccess ? g_free_error : drop(g_pinned, p); }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = nullptr; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+}
+
+namespace ba {
+void set_error(const char *, ...) {}
+thread_local SlotArena *tl_slot_arena = nullptr;
+}
+
+// ---------------------------------------------------------------- scenarios
+#define CHECK(c)                                                                        \
+    do {                                                                                \
+        if (!(c)) {                                                                     \
+            std::fprintf(stderr, "%s:%d: %s does not hold\n", __FILE__, __LINE__, #c); \
+            std::exit(1);                                                               \
+        }                                                                               \
+    } while (0)
+
+static constexpr size_t MB = (size_t)1 << 20;
+
+// Leaves n kept blocks of 40 MB and returns their bytes.
+static size_t keep(int n) {
+    ba::DevArena a;
+    for (int i = 0; i < n; i++) {
+        char *p;
+        CHECK(a.alloc(&p, 40 * (int64_t)MB) == BA_OK);
+    }
+    a.release();
+    return g_used;
+}
+
+// An allocation refused for another reason than a lack of memory, as inside a
+// stream capture, where releases are refused too: what is kept stays kept.
+static void refused() {
+    const size_t kept = keep(3);
+    CHECK(kept >= 120 * MB);
+    g_malloc_error = g_free_error = hipErrorStreamCaptureUnsupported;
+    ba::DevArena a;
+    char *p;
+    CHECK(a.alloc(&p, 500 * (int64_t)MB) == BA_E_NOMEM);
+    g_malloc_error = g_free_error = hipSuccess;
+    CHECK(g_used == kept);
+    CHECK(a.alloc(&p, 40 * (int64_t)MB) == BA_OK && g_used == kept);   // from the list
+    a.release();
+    CHECK(ba_release_cached_memory() == BA_OK && g_used == 0);
+}
+
+int main(int argc, char **argv) {
+    const std::string s = argc > 1 ? argv[1] : "";
+    if (s == "refused") refused();
+    else return 2;
+    return 0;
+}
