@@ -61,20 +61,32 @@ static size_t rounded(size_t nb) {
     return (nb + step - 1) / step * step;
 }
 
+static hipError_t release_block(const PoolBlock &b) {
+    if (b.device < 0) return hipHostFree(b.p);
+    (void)hipSetDevice(b.device);
+    return hipFree(b.p);
+}
+
+// Returns blocks to the driver.  One that it refuses (inside a stream capture
+// of this thread) goes back to the list, so that it is not lost.
 static void give_back(std::list<PoolBlock> &out) {
     if (out.empty()) return;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    for (PoolBlock &b : out) {
-        if (b.device < 0) {
-            (void)hipHostFree(b.p);
+    for (auto it = out.begin(); it != out.end();) {
+        if (release_block(*it) == hipSuccess) {
+            it = out.erase(it);
         } else {
-            (void)hipSetDevice(b.device);
-            (void)hipFree(b.p);
+            (void)hipGetLastError();
+            ++it;
         }
     }
     (void)hipSetDevice(dev);
-    out.clear();
+    if (out.empty()) return;
+    Pool &P = pool();
+    std::lock_guard<std::mutex> lk(P.mu);
+    for (const PoolBlock &b : out) (b.device < 0 ? P.pinned_bytes : P.dev_bytes) += b.bytes;
+    P.kept.splice(P.kept.begin(), out);
 }
 
 // Takes the smallest kept block of at least nb bytes and at most a quarter

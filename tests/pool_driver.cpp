@@ -98,9 +98,30 @@ static void refused() {
     CHECK(ba_release_cached_memory() == BA_OK && g_used == 0);
 }
 
+// Releases refused by the driver, on request and past the bound: the blocks
+// stay on the list, serve later calls and go back once releases work.
+static void unreleased() {
+    const size_t kept = keep(3);
+    g_free_error = hipErrorStreamCaptureUnsupported;
+    CHECK(ba_release_cached_memory() == BA_OK && g_used == kept);
+    ba::DevArena a;
+    char *p;
+    CHECK(a.alloc(&p, 40 * (int64_t)MB) == BA_OK && g_used == kept);   // from the list
+    const size_t big = g_total / 64 + MB;   // two of them pass the bound of 1/32
+    for (int i = 0; i < 3; i++) CHECK(a.alloc(&p, (int64_t)big) == BA_OK);
+    a.release();
+    size_t bytes = 0;
+    void *q = nullptr;
+    CHECK(ba::pinned_alloc(&q, 200 * MB, &bytes) == hipSuccess);   // above the bound of pinned memory
+    ba::pinned_free(q, bytes);
+    g_free_error = hipSuccess;
+    CHECK(ba_release_cached_memory() == BA_OK && g_used == 0);
+}
+
 int main(int argc, char **argv) {
     const std::string s = argc > 1 ? argv[1] : "";
     if (s == "refused") refused();
+    else if (s == "unreleased") unreleased();
     else return 2;
     return 0;
 }
