@@ -490,8 +490,10 @@ ba_status ba_voxel_map_destroy(ba_voxel_map *m);
  * maps return their device memory to a list that later calls take from (a
  * release and a new allocation of such sizes cost this driver milliseconds,
  * at times far more).  At most 1/32 of the device's memory is kept, nothing
- * while less than 1/8 of it is free, and all of it is returned when an
- * allocation of the library fails.  This call returns it to the driver now
+ * while less than 1/8 of it is free, and all of it is returned, and the
+ * allocation tried again, when an allocation of the library finds too little
+ * memory.  Memory of other allocators in the process is not looked at in
+ * between.  This call returns it to the driver now
  * (e.g. before another library needs the memory).  Any thread.
  */
 ba_status ba_release_cached_memory(void);

@@ -37,7 +37,7 @@ struct ProfScope {
 // A slot-owned block of device memory that allocations of the calling thread
 // are carved from (bump allocation, 256-byte aligned) while it is installed in
 // tl_slot_arena; the owner resets `off` when the work that used it is done.
-// Allocations that do not fit fall through to hipMalloc.
+// Allocations that do not fit fall through to the kept blocks.
 struct SlotArena {
     char *base = nullptr;
     size_t cap = 0;
@@ -51,6 +51,7 @@ struct DevBlock {
     size_t bytes;
     int device;
 };
+hipError_t device_alloc(void **p, size_t nb);   // for hipFree, not for the list
 hipError_t pool_alloc(void **p, size_t nb, size_t *bytes);
 void pool_free(const std::vector<DevBlock> &blocks);
 hipError_t pinned_alloc(void **p, size_t nb, size_t *bytes);

@@ -121,6 +121,15 @@ void pool_trim() {
     for (auto &s : streams) (void)hipStreamDestroy(s.first);
 }
 
+// hipMalloc, and for a lack of memory once more without what is kept.
+hipError_t device_alloc(void **p, size_t nb) {
+    const hipError_t e = hipMalloc(p, nb);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    pool_trim();
+    return hipMalloc(p, nb);
+}
+
 hipError_t pool_alloc(void **p, size_t nb, size_t *bytes) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -177,6 +186,10 @@ hipError_t pinned_alloc(void **p, size_t nb, size_t *bytes) {
     const size_t want = rounded(nb);
     if ((*p = take(want, -1, bytes))) return hipSuccess;
     *bytes = want;
+    const hipError_t e = hipHostMalloc(p, want, hipHostMallocDefault);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    pool_trim();
     return hipHostMalloc(p, want, hipHostMallocDefault);
 }
 

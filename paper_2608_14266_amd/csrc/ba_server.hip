@@ -212,7 +212,7 @@ static void arena_reserve(Server *S, SlotArena &a, int64_t need) {
     a.base = nullptr;
     a.cap = 0;
     void *q = nullptr;
-    if (hipMalloc(&q, (size_t)need) == hipSuccess) {
+    if (device_alloc(&q, (size_t)need) == hipSuccess) {
         a.base = (char *)q;
         a.cap = (size_t)need;
     } else {

@@ -118,10 +118,33 @@ static void unreleased() {
     CHECK(ba_release_cached_memory() == BA_OK && g_used == 0);
 }
 
+// A lack of memory while blocks are kept: every allocation of the library is
+// tried again without them.
+static void lack() {
+    const size_t room = g_total;
+    void *q = nullptr;
+    size_t bytes = 0;
+    g_total = keep(3) + MB;
+    CHECK(ba::device_alloc(&q, 100 * MB) == hipSuccess && g_used == 100 * MB);
+    CHECK(hipFree(q) == hipSuccess);
+    g_total = room;
+    g_total = keep(3) + MB;
+    CHECK(ba::pinned_alloc(&q, 100 * MB, &bytes) == hipSuccess && g_used == bytes);
+    ba::pinned_free(q, bytes);
+    CHECK(ba_release_cached_memory() == BA_OK && g_used == 0);
+    g_total = room;
+    g_total = keep(3) + MB;
+    ba::DevArena a;
+    char *p;
+    CHECK(a.alloc(&p, 100 * (int64_t)MB) == BA_OK && g_used == 100 * MB);
+    CHECK(a.alloc(&p, 100 * (int64_t)MB) == BA_E_NOMEM);
+}
+
 int main(int argc, char **argv) {
     const std::string s = argc > 1 ? argv[1] : "";
     if (s == "refused") refused();
     else if (s == "unreleased") unreleased();
+    else if (s == "lack") lack();
     else return 2;
     return 0;
 }
