@@ -18,6 +18,7 @@
 
 #include <list>
 #include <mutex>
+#include <new>
 #include <utility>
 
 #include "ba.h"
@@ -65,6 +66,19 @@ static hipError_t release_block(const PoolBlock &b) {
     if (b.device < 0) return hipHostFree(b.p);
     (void)hipSetDevice(b.device);
     return hipFree(b.p);
+}
+
+// Puts a block on a list, or returns it to the driver where the list cannot
+// grow: blocks are released by destructors, which must not throw.
+static void list_block(std::list<PoolBlock> &l, const PoolBlock &b) {
+    try {
+        l.push_back(b);
+    } catch (const std::bad_alloc &) {
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        (void)release_block(b);
+        (void)hipSetDevice(dev);
+    }
 }
 
 // Returns blocks to the driver.  One that it refuses (inside a stream capture
@@ -156,17 +170,18 @@ void pool_free(const std::vector<DevBlock> &blocks) {
     size_t fr = 0, total = 0;
     const bool known = hipGetDevice(&dev) == hipSuccess && hipMemGetInfo(&fr, &total) == hipSuccess;
     Pool &P = pool();
-    std::list<PoolBlock> out;
+    std::list<PoolBlock> in, out;
+    for (const DevBlock &b : blocks) list_block(in, PoolBlock{b.p, b.bytes, b.device});
     {
         std::lock_guard<std::mutex> lk(P.mu);
-        for (const DevBlock &b : blocks) {
-            PoolBlock k{b.p, b.bytes, b.device};
-            if (!known || b.device != dev || fr < total / LOW_SHARE || b.bytes > total / POOL_SHARE) {
-                out.push_back(k);
+        while (!in.empty()) {
+            const PoolBlock &k = in.front();
+            if (!known || k.device != dev || fr < total / LOW_SHARE || k.bytes > total / POOL_SHARE) {
+                out.splice(out.end(), in, in.begin());
                 continue;
             }
-            P.kept.push_back(k);
             P.dev_bytes += k.bytes;
+            P.kept.splice(P.kept.end(), in, in.begin());
         }
         const size_t bound = known && fr >= total / LOW_SHARE ? total / POOL_SHARE : 0;
         for (auto it = P.kept.begin(); it != P.kept.end() && P.dev_bytes > bound;) {
@@ -175,8 +190,7 @@ void pool_free(const std::vector<DevBlock> &blocks) {
                 continue;
             }
             P.dev_bytes -= it->bytes;
-            out.push_back(*it);
-            it = P.kept.erase(it);
+            out.splice(out.end(), P.kept, it++);
         }
     }
     give_back(out);
@@ -197,13 +211,13 @@ void pinned_free(void *p, size_t bytes) {
     if (!p) return;
     Pool &P = pool();
     std::list<PoolBlock> out;
+    list_block(out, PoolBlock{p, bytes, -1});
+    if (out.empty()) return;
     {
         std::lock_guard<std::mutex> lk(P.mu);
         if (P.pinned_bytes + bytes <= POOL_PINNED) {
-            P.kept.push_back(PoolBlock{p, bytes, -1});
             P.pinned_bytes += bytes;
-        } else {
-            out.push_back(PoolBlock{p, bytes, -1});
+            P.kept.splice(P.kept.end(), out);
         }
     }
     give_back(out);
@@ -229,8 +243,11 @@ void stream_put(hipStream_t s, int device) {
     {
         std::lock_guard<std::mutex> lk(P.mu);
         if (P.streams.size() < POOL_STREAMS) {
-            P.streams.emplace_back(s, device);
-            return;
+            try {
+                P.streams.emplace_back(s, device);
+                return;
+            } catch (const std::bad_alloc &) {
+            }
         }
     }
     (void)hipStreamDestroy(s);
@@ -262,6 +279,12 @@ void DevArena::release() {
 
 ba_status DevArena::alloc_block(void **p, size_t nb) {
     DevBlock b{nullptr, 0, 0};
+    try {
+        ptrs.reserve(ptrs.size() + 1);   // no block without a place to note it
+    } catch (const std::bad_alloc &) {
+        set_error("host allocation failed");
+        return BA_E_NOMEM;
+    }
     (void)hipGetDevice(&b.device);
     hipError_t e = pool_alloc(&b.p, nb, &b.bytes);
     if (e != hipSuccess) {

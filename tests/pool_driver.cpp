@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -18,6 +19,16 @@ static std::map<void *, size_t> g_dev, g_pinned;   // what the "driver" holds
 static size_t g_total = (size_t)256 << 30, g_used = 0;
 static hipError_t g_malloc_error = hipSuccess, g_free_error = hipSuccess, g_host_error = hipSuccess;
 static uintptr_t g_next = (uintptr_t)1 << 40;
+
+// ordinary allocations of the host, refused on request
+static bool g_no_new = false;
+void *operator new(size_t n) {
+    void *p = g_no_new ? nullptr : std::malloc(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 static hipError_t take(std::map<void *, size_t> &m, void **p, size_t nb) {
     if (g_used + nb > g_total) return hipErrorOutOfMemory;
@@ -140,11 +151,35 @@ static void lack() {
     CHECK(a.alloc(&p, 100 * (int64_t)MB) == BA_E_NOMEM);
 }
 
+// No host memory left while blocks are released (by destructors, as a rule):
+// they go back to the driver, and nothing throws.
+static void no_host_memory() {
+    size_t bytes = 0;
+    void *q = nullptr;
+    {
+        ba::DevArena a;
+        char *p;
+        for (int i = 0; i < 3; i++) CHECK(a.alloc(&p, 40 * (int64_t)MB) == BA_OK);
+        CHECK(ba::pinned_alloc(&q, MB, &bytes) == hipSuccess);
+        g_no_new = true;
+        ba::pinned_free(q, bytes);
+    }
+    g_no_new = false;
+    CHECK(g_dev.empty() && g_pinned.empty() && g_used == 0);
+    ba::DevArena a;
+    char *p;
+    g_no_new = true;
+    const ba_status st = a.alloc(&p, 40 * (int64_t)MB);
+    g_no_new = false;
+    CHECK(st == BA_E_NOMEM && g_used == 0);
+}
+
 int main(int argc, char **argv) {
     const std::string s = argc > 1 ? argv[1] : "";
     if (s == "refused") refused();
     else if (s == "unreleased") unreleased();
     else if (s == "lack") lack();
+    else if (s == "no_host_memory") no_host_memory();
     else return 2;
     return 0;
 }
