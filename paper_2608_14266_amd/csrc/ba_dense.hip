@@ -52,8 +52,8 @@ struct DenseParam {
 };
 
 __global__ void k_fill(int64_t n, double *__restrict__ p, double v) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        p[i] = v;
 }
 
 struct PairSeg {
@@ -2272,9 +2272,6 @@ static ba_status dense_form(Problem *P) {
     BA_TRY(D->mem.alloc(&D->hdx, 6LL * P->n_poses));
     BA_TRY(D->mem.alloc(&P->dense, std::max<int64_t>(h_tot, 1)));
     P->dense_total = h_tot;
-    // zero once: an assembly rewrites the same pair blocks and nothing else
-    hipLaunchKernelGGL(k_fill, dim3(nblk(std::max<int64_t>(h_tot, 1))), dim3(256), 0, s, std::max<int64_t>(h_tot, 1),
-                       P->dense, 0.0);
     for (int32_t w = 0; w < W; w++) {
         desc[w].linv_off += a_tot;
         desc[w].v_off += a_tot + l_tot;
@@ -2282,6 +2279,7 @@ static ba_status dense_form(Problem *P) {
     BA_HIP(hipMemcpy(D->desc, desc.data(), sizeof(DenseDesc) * W, hipMemcpyHostToDevice));
     BA_HIP(hipMemcpy(D->h_off, hoff.data(), sizeof(int64_t) * (W + 1), hipMemcpyHostToDevice));
     BA_HIP(hipMemcpy(D->x_off, xoff.data(), sizeof(int64_t) * W, hipMemcpyHostToDevice));
+    // zero once: an assembly rewrites the same pair blocks and nothing else
     BA_HIP(hipMemset(P->dense, 0, sizeof(double) * std::max<int64_t>(h_tot, 1)));
     // walkers of up to FLOW_MAX_MATS matrices per launch, then their
     // tasks by column
@@ -2388,7 +2386,7 @@ ba_status dense_assemble(Problem *P, const double *poses, double *hess_out, bool
     // 26 us of 1390 us an iteration at 500 poses.
     if (!use_lm) {
         const int64_t tot = P->dense_total;
-        hipLaunchKernelGGL(k_fill, dim3(nblk(tot)), dim3(256), 0, s, tot, dst, 0.0);
+        hipLaunchKernelGGL(k_fill, dim3(stride_blocks(tot)), dim3(256), 0, s, tot, dst, 0.0);
     }
     if (D->n_seg)
         hipLaunchKernelGGL(k_pairs, dim3(nblk((int64_t)D->n_seg * 64)), dim3(256), 0, s, D->n_seg, D->segs, D->pa,
@@ -2415,7 +2413,7 @@ ba_status dense_assemble_exact(Problem *P, const double *poses, double *hess_out
                        P->c_scan, D->qc, poses, D->ev);
     if (!use_lm) {
         const int64_t tot = P->dense_total;
-        hipLaunchKernelGGL(k_fill, dim3(nblk(tot)), dim3(256), 0, s, tot, dst, 0.0);
+        hipLaunchKernelGGL(k_fill, dim3(stride_blocks(tot)), dim3(256), 0, s, tot, dst, 0.0);
     }
     if (D->n_seg)
         hipLaunchKernelGGL(k_pairs_x, dim3(nblk((int64_t)D->n_seg * 64)), dim3(256), 0, s, D->n_seg, D->segs, D->pa,

@@ -14,6 +14,12 @@ namespace ba {
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Blocks of 256 threads for a kernel that walks n items by the stride of its
+// grid: a thread per item up to 2^30 of them.  A launch holds fewer than 2^32
+// threads; of a larger one the runtime drops the excess, with an error only
+// where nothing is left.
+static inline unsigned stride_blocks(int64_t n) { return (unsigned)(n < (1LL << 30) ? (n + 255) / 256 : 1 << 22); }
+
 // One K_vox wave group: up to 64 voxels with the same cluster count m, one
 // voxel per lane; cluster k of lane l lives at cbase + 64 k + l.
 struct GroupDesc {
