@@ -333,23 +333,24 @@ __global__ void k_gather_pose(int64_t C, const uint32_t *__restrict__ order, con
 
 __global__ void k_export_records(int64_t C, const double *__restrict__ crec, double *__restrict__ count,
                                  double *__restrict__ mu, double *__restrict__ S) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= CREC * C) return;
-    const int64_t c = t / CREC;
-    const int e = (int)(t - CREC * c);
-    const double v = crec[t];
-    if (e == 0) {
-        if (count) count[c] = v;
-    } else if (e < 4) {
-        if (mu) mu[3 * c + e - 1] = v;
-    } else if (S) {
-        S[6 * c + e - 4] = v;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < CREC * C;
+         t += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t c = t / CREC;
+        const int e = (int)(t - CREC * c);
+        const double v = crec[t];
+        if (e == 0) {
+            if (count) count[c] = v;
+        } else if (e < 4) {
+            if (mu) mu[3 * c + e - 1] = v;
+        } else if (S) {
+            S[6 * c + e - 4] = v;
+        }
     }
 }
 
 hipError_t export_records(const Problem *P, double *count, double *mu, double *S, hipStream_t s) {
     const int64_t C = P->n_clusters;
-    hipLaunchKernelGGL(k_export_records, dim3(nblk(CREC * C)), dim3(256), 0, s, C, P->c_rec, count, mu, S);
+    hipLaunchKernelGGL(k_export_records, dim3(stride_blocks(CREC * C)), dim3(256), 0, s, C, P->c_rec, count, mu, S);
     return hipGetLastError();
 }
 
