@@ -1032,9 +1032,12 @@ ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, P
     BA_TRY(keep.alloc(&P->c_rec, CREC * C));
     BA_TRY(keep.alloc(&P->c_vox, C));
     BA_TRY(keep.alloc(&P->c_scan, C));
-    hipLaunchKernelGGL(k_cluster_stats, dim3(nblk(C * 64)), dim3(256), 0, s, C, starts, b.vals, pts->x, pts->y,
-                       pts->z, b.keys, sbits, P->c_rec, P->c_vox, P->c_scan);
-    BA_HIP(hipGetLastError());
+    for (int64_t c = 0, k; c < C; c += k) {
+        k = std::min(C - c, launch_items(64));
+        hipLaunchKernelGGL(k_cluster_stats, dim3(nblk(k * 64)), dim3(256), 0, s, k, starts + c, b.vals, pts->x, pts->y,
+                           pts->z, b.keys, sbits, P->c_rec + CREC * c, P->c_vox + c, P->c_scan + c);
+        BA_HIP(hipGetLastError());
+    }
     BA_TRY(finish_build(P, keep, opt, b, s));
     tmp.drained = true;   // the plan's last step waits for the stream
     return BA_OK;

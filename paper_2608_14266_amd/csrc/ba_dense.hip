@@ -2388,9 +2388,11 @@ ba_status dense_assemble(Problem *P, const double *poses, double *hess_out, bool
         const int64_t tot = P->dense_total;
         hipLaunchKernelGGL(k_fill, dim3(stride_blocks(tot)), dim3(256), 0, s, tot, dst, 0.0);
     }
-    if (D->n_seg)
-        hipLaunchKernelGGL(k_pairs, dim3(nblk((int64_t)D->n_seg * 64)), dim3(256), 0, s, D->n_seg, D->segs, D->pa,
-                           D->pb, D->h, P->H, P->pose_window, P->win_pose_ptr, D->h_off, lm, dst);
+    for (int64_t i = 0, k; i < D->n_seg; i += k) {
+        k = std::min(D->n_seg - i, launch_items(64));
+        hipLaunchKernelGGL(k_pairs, dim3(nblk(k * 64)), dim3(256), 0, s, (int32_t)k, D->segs + i, D->pa, D->pb,
+                           D->h, P->H, P->pose_window, P->win_pose_ptr, D->h_off, lm, dst);
+    }
     BA_HIP(hipGetLastError());
     return BA_OK;
 }
@@ -2415,9 +2417,11 @@ ba_status dense_assemble_exact(Problem *P, const double *poses, double *hess_out
         const int64_t tot = P->dense_total;
         hipLaunchKernelGGL(k_fill, dim3(stride_blocks(tot)), dim3(256), 0, s, tot, dst, 0.0);
     }
-    if (D->n_seg)
-        hipLaunchKernelGGL(k_pairs_x, dim3(nblk((int64_t)D->n_seg * 64)), dim3(256), 0, s, D->n_seg, D->segs, D->pa,
-                           D->pb, D->ev, P->H, P->pose_window, P->win_pose_ptr, D->h_off, lm, exact_below, dst);
+    for (int64_t i = 0, k; i < D->n_seg; i += k) {
+        k = std::min(D->n_seg - i, launch_items(64));
+        hipLaunchKernelGGL(k_pairs_x, dim3(nblk(k * 64)), dim3(256), 0, s, (int32_t)k, D->segs + i, D->pa, D->pb,
+                           D->ev, P->H, P->pose_window, P->win_pose_ptr, D->h_off, lm, exact_below, dst);
+    }
     BA_HIP(hipGetLastError());
     return BA_OK;
 }

@@ -19,6 +19,9 @@ static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; 
 // threads; of a larger one the runtime drops the excess, with an error only
 // where nothing is left.
 static inline unsigned stride_blocks(int64_t n) { return (unsigned)(n < (1LL << 30) ? (n + 255) / 256 : 1 << 22); }
+// Items of a launch that gives each of them `threads` threads, for the same
+// reason: longer lists go in several launches.
+static constexpr int64_t launch_items(int64_t threads) { return (1LL << 31) / threads; }
 
 // One K_vox wave group: up to 64 voxels with the same cluster count m, one
 // voxel per lane; cluster k of lane l lives at cbase + 64 k + l.

@@ -485,12 +485,17 @@ static ba_status vx_form_level(DevArena &tmp, SortBuf &w, int64_t m, bool by_sca
     BA_TRY(tmp.alloc(&cur.count, cur.C));
     BA_TRY(tmp.alloc(&cur.s1, 3 * cur.C));
     BA_TRY(tmp.alloc(&cur.s2, 6 * cur.C));
-    if (x)
-        hipLaunchKernelGGL(k_vx_sum_points, dim3(vx_nblk(cur.C * VX_SUM_LANES)), dim3(VX_THREADS), 0, s, cur.C, starts, w.keys, w.vals,
-                           x, y, z, cur.ckey, cur.count, cur.s1, cur.s2);
-    else
+    if (x) {
+        for (int64_t c = 0, k; c < cur.C; c += k) {
+            k = std::min(cur.C - c, launch_items(VX_SUM_LANES));
+            hipLaunchKernelGGL(k_vx_sum_points, dim3(vx_nblk(k * VX_SUM_LANES)), dim3(VX_THREADS), 0, s, k, starts + c,
+                               w.keys, w.vals, x, y, z, cur.ckey + c, cur.count + c, cur.s1 + 3 * c, cur.s2 + 6 * c);
+            BA_HIP(hipGetLastError());
+        }
+    } else {
         hipLaunchKernelGGL(k_vx_sum_clusters, dim3(vx_nblk(cur.C)), dim3(VX_THREADS), 0, s, cur.C, starts, w.keys,
                            w.vals, ccount, cs1, cs2, cur.ckey, cur.count, cur.s1, cur.s2);
+    }
     BA_HIP(hipGetLastError());
     return BA_OK;
 }
