@@ -601,7 +601,9 @@ __global__ __launch_bounds__(256) void k_plan_check(int32_t V, const int64_t *__
     if (threadIdx.x == 0) atomicMax(max_m, m);
 }
 
-// Sort key (window, m, first observing scan) of every voxel.
+// Sort key (window, m, first observing scan) of every voxel.  Where these take
+// more than 64 bits the voxels are sorted by the scan (k_plan_scans) and then,
+// stably, by (window, m) (k_plan_windows).
 __global__ void k_plan_keys(int32_t V, const int64_t *__restrict__ vstart, const int32_t *__restrict__ cscan,
                             const int32_t *__restrict__ pose_window, int mbits, int sbits,
                             uint64_t *__restrict__ keys) {
@@ -610,6 +612,21 @@ __global__ void k_plan_keys(int32_t V, const int64_t *__restrict__ vstart, const
     const int64_t a = vstart[v];
     const uint64_t m = (uint64_t)(vstart[v + 1] - a), j = (uint64_t)cscan[a];
     keys[v] = (((uint64_t)pose_window[j] << mbits | m) << sbits) | j;
+}
+
+__global__ void k_plan_scans(int32_t V, const int64_t *__restrict__ vstart, const int32_t *__restrict__ cscan,
+                             uint64_t *__restrict__ keys) {
+    const int32_t v = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (v < V) keys[v] = (uint64_t)cscan[vstart[v]];
+}
+
+__global__ void k_plan_windows(int32_t V, const uint32_t *__restrict__ order, const int64_t *__restrict__ vstart,
+                               const int32_t *__restrict__ pose_window, int mbits, uint64_t *__restrict__ keys) {
+    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i >= V) return;
+    const int64_t v = order[i];
+    const uint64_t m = (uint64_t)(vstart[v + 1] - vstart[v]);
+    keys[i] = (uint64_t)pose_window[keys[i]] << mbits | m;   // the key is the first scan
 }
 
 __global__ void k_run_keys(int64_t R, const int64_t *__restrict__ starts, const uint64_t *__restrict__ keys,
@@ -792,11 +809,22 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     // voxel order: (window, m, first observing scan, voxel id), a stable sort;
     // then its runs of one window and one m
     const int sbits = bit_length((uint64_t)(N - 1)), mbits = bit_length((uint64_t)P->max_m);
-    hipLaunchKernelGGL(k_plan_keys, dim3(nblk(V)), dim3(256), 0, s, V, vstart, P->c_scan, P->pose_window, mbits,
-                       sbits, bw.keys);
-    BA_HIP(radix_sort_pairs(bw, V, 0, sbits + mbits + bit_length((uint64_t)(W - 1)), true, s));
+    const int wbits = bit_length((uint64_t)(W - 1));
+    const bool one_key = wbits + mbits + sbits <= 64;
+    const int shift = one_key ? sbits : 0;   // of a key's (window, m)
+    if (one_key) {
+        hipLaunchKernelGGL(k_plan_keys, dim3(nblk(V)), dim3(256), 0, s, V, vstart, P->c_scan, P->pose_window, mbits,
+                           sbits, bw.keys);
+        BA_HIP(radix_sort_pairs(bw, V, 0, sbits + mbits + wbits, true, s));
+    } else {
+        hipLaunchKernelGGL(k_plan_scans, dim3(nblk(V)), dim3(256), 0, s, V, vstart, P->c_scan, bw.keys);
+        BA_HIP(radix_sort_pairs(bw, V, 0, sbits, true, s));
+        hipLaunchKernelGGL(k_plan_windows, dim3(nblk(V)), dim3(256), 0, s, V, bw.vals, vstart, P->pose_window, mbits,
+                           bw.keys);
+        BA_HIP(radix_sort_pairs(bw, V, 0, mbits + wbits, false, s));
+    }
     int64_t R = 0;
-    BA_HIP(segment_count((const uint64_t *)bw.keys, (int64_t)V, sbits, bw.total, bw.ws, s));
+    BA_HIP(segment_count((const uint64_t *)bw.keys, (int64_t)V, shift, bw.total, bw.ws, s));
     BA_TRY(read_count(&R, bw.total, s));
     int64_t *d_rs;
     uint64_t *d_rk;
@@ -806,8 +834,8 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     BA_TRY(tmp.alloc(&d_rk, R));
     BA_TRY(tmp.alloc(&order, V));
     BA_TRY(tmp.alloc(&d_runs, R));
-    BA_HIP(segment_write((const uint64_t *)bw.keys, (int64_t)V, sbits, R, d_rs, bw.ws, s));
-    hipLaunchKernelGGL(k_run_keys, dim3(nblk(R)), dim3(256), 0, s, R, d_rs, bw.keys, sbits, d_rk);
+    BA_HIP(segment_write((const uint64_t *)bw.keys, (int64_t)V, shift, R, d_rs, bw.ws, s));
+    hipLaunchKernelGGL(k_run_keys, dim3(nblk(R)), dim3(256), 0, s, R, d_rs, bw.keys, shift, d_rk);
     BA_HIP(hipGetLastError());
     BA_HIP(hipMemcpyAsync(order, bw.vals, sizeof(uint32_t) * V, hipMemcpyDeviceToDevice, s));
     std::vector<int64_t> rs(R + 1);
