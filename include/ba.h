@@ -103,7 +103,7 @@ typedef struct ba_problem_info {
     int32_t n_scans;
     int32_t n_windows;
     int32_t max_m;          /* largest number of scans observing one voxel */
-    int64_t device_bytes;   /* device memory held by the problem */
+    int64_t device_bytes;   /* device memory held by the problem (whole blocks, up to a quarter more than its arrays) */
     int32_t n_wave_groups;  /* residual-pass wave groups (64 voxels of equal cluster count each) */
     int32_t n_pose_chunks;  /* derivative-pass chunks (clusters of one scan each) */
     int64_t padded_clusters; /* cluster slots of the wave-interleaved layout, incl. padding */

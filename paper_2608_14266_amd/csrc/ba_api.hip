@@ -329,7 +329,7 @@ ba_status ba_problem_get_info(const ba_problem *p, ba_problem_info *info) {
     info->n_scans = P.n_poses;
     info->n_windows = P.n_windows;
     info->max_m = P.max_m;
-    info->device_bytes = (int64_t)P.mem.bytes + dense_device_bytes(&P);
+    info->device_bytes = (int64_t)P.mem.used() + dense_device_bytes(&P);
     info->n_wave_groups = P.n_groups;
     info->n_pose_chunks = P.n_chunks;
     info->padded_clusters = P.c_pad;

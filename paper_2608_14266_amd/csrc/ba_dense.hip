@@ -2170,7 +2170,7 @@ __global__ void k_seg_count(int64_t n_seg, int64_t E, PairSeg *__restrict__ segs
 
 int64_t dense_device_bytes(const Problem *P) {
     const DenseState *D = (const DenseState *)P->dense_state;
-    return D ? (int64_t)D->mem.bytes : 0;
+    return D ? (int64_t)D->mem.used() : 0;
 }
 
 static ba_status dense_form(Problem *P) {

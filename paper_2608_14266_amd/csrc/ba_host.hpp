@@ -70,7 +70,7 @@ struct DevArena {
     std::vector<DevBlock> ptrs;
     char *slab = nullptr;
     size_t slab_left = 0;
-    size_t bytes = 0;
+    size_t bytes = 0;       // of the blocks held (a block from the list may be a quarter larger than asked for)
     bool drained = false;
     DevArena() = default;
     DevArena(const DevArena &) = delete;
@@ -78,6 +78,7 @@ struct DevArena {
     ~DevArena() { release(); }
     void release();
     ba_status alloc_block(void **p, size_t nb);
+    size_t used() const { return bytes - slab_left; }   // the blocks without the last slab's free end
     template <class T>
     ba_status alloc(T **p, int64_t count) {
         const size_t nb = sizeof(T) * (size_t)(count > 0 ? count : 1);
@@ -86,7 +87,7 @@ struct DevArena {
             if (a->off + nba <= a->cap) {
                 *p = (T *)(a->base + a->off);
                 a->off += nba;
-                bytes += nb;
+                bytes += nba;
                 return BA_OK;
             }
         }
@@ -104,7 +105,6 @@ struct DevArena {
         } else {
             BA_TRY(alloc_block(&q, nb));
         }
-        bytes += nb;
         *p = (T *)q;
         return BA_OK;
     }

@@ -293,6 +293,7 @@ ba_status DevArena::alloc_block(void **p, size_t nb) {
         return BA_E_NOMEM;
     }
     ptrs.push_back(b);
+    bytes += b.bytes;
     *p = b.p;
     return BA_OK;
 }

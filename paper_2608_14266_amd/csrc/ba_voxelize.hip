@@ -946,7 +946,7 @@ ba_status ba_voxel_map_get_info(const ba_voxel_map *m, ba_voxel_map_info *info) 
         info->level_kept_voxels[k] = m->lv[k][2];
         info->level_kept_clusters[k] = m->lv[k][3];
     }
-    info->device_bytes = (int64_t)m->mem.bytes;
+    info->device_bytes = (int64_t)m->mem.used();
     return BA_OK;
 }
 

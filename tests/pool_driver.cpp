@@ -174,12 +174,29 @@ static void no_host_memory() {
     CHECK(st == BA_E_NOMEM && g_used == 0);
 }
 
+// An arena counts the blocks it holds, not the bytes it asked for.
+static void held() {
+    keep(1);
+    ba::DevArena a;
+    char *p;
+    CHECK(a.alloc(&p, 33 * (int64_t)MB) == BA_OK);   // the kept block of 40 MB
+    CHECK(a.used() == 40 * MB && g_used == 40 * MB);
+    for (int i = 1; i <= 600; i++) {   // small ones share slabs, by pages
+        CHECK(a.alloc(&p, 5000) == BA_OK);
+        CHECK(a.used() >= 40 * MB + (size_t)i * 8192 && a.used() <= g_used);
+    }
+    CHECK(g_used - a.used() < 2 * MB);
+    a.release();
+    CHECK(a.used() == 0);
+}
+
 int main(int argc, char **argv) {
     const std::string s = argc > 1 ? argv[1] : "";
     if (s == "refused") refused();
     else if (s == "unreleased") unreleased();
     else if (s == "lack") lack();
     else if (s == "no_host_memory") no_host_memory();
+    else if (s == "held") held();
     else return 2;
     return 0;
 }

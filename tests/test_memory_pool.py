@@ -24,7 +24,7 @@ def driver(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["refused", "unreleased", "lack", "no_host_memory"])
+@pytest.mark.parametrize("scenario", ["refused", "unreleased", "lack", "no_host_memory", "held"])
 def test_pool(driver, scenario):
     r = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
