@@ -299,7 +299,8 @@ ba_status ba_problem_set_tuning(ba_problem *p, const ba_tuning *t);
 /*
  * ba_autotune — grid search over the launch choices on this problem: every
  * (vox_split, vox_grid) pair of the residual pass and every (chunk_len,
- * pose_grid) pair of the derivative pass is timed with HIP events over
+ * pose_grid) pair of the derivative pass (with its reduction where the pair
+ * leads to one) is timed with HIP events over
  * `reps` evaluations at `poses` (device [n_scans][12]); the fastest of each
  * pass is applied to the problem and returned in *best (host, may be NULL).
  * Overwrites the problem's voxel state (as an evaluation does).  Synchronous.
@@ -501,11 +502,12 @@ ba_status ba_release_cached_memory(void);
 /*
  * Kernel timing (instrumentation, not part of the method): when enabled,
  * later calls record a pair of HIP events on their stream around each launch
- * of the residual kernel ("k_vox"), the derivative kernel ("k_pose"), the
- * dense factorization and back substitution ("k_chol_flow",
- * "k_backsub_flow"), the per-window MM increment solve ("k_window_solve_mm")
- * and the LM decision ("k_decide"); ba_iterate then
- * runs its launches eagerly instead of replaying a captured graph.
+ * of the residual kernel ("k_vox"), the derivative kernel ("k_pose") and the
+ * reduction of its partial sums ("k_reduce_partials"), the dense
+ * factorization and back substitution ("k_chol_flow", "k_backsub_flow"), the
+ * per-window MM increment solve ("k_window_solve_mm") and the LM decision
+ * ("k_decide"); ba_iterate then runs its launches eagerly instead of replaying
+ * a captured graph.
  * ba_profile_query waits for the recorded events and returns the summed
  * elapsed time and the launch count of one kernel; ba_profile_reset drops
  * the records.  Process-wide, guarded by a mutex.

@@ -566,7 +566,10 @@ static ba_tuning export_tuning(const Problem *P) {
     return t;
 }
 
-// Mean time of `reps` launches of one pass (after one untimed launch).
+// Mean time of `reps` launches of one pass (after one untimed launch).  The
+// derivative pass is timed in the form that the choices under test lead to:
+// stored directly where every pose has one chunk and the grid is not
+// persistent, else with the reduction of its partial sums.
 static ba_status time_pass(Problem *P, const double *poses, bool vox, int reps, hipStream_t s, float *ms) {
     hipEvent_t a, b;
     BA_HIP(hipEventCreate(&a));
@@ -575,7 +578,7 @@ static ba_status time_pass(Problem *P, const double *poses, bool vox, int reps, 
         if (vox)
             launch_vox(P, poses, false, false, s);
         else
-            launch_pose_chunks(P, poses, false, s);
+            launch_pose_derivs(P, poses, false, P->g, P->H, s);
     };
     launch();
     hipError_t e = hipEventRecord(a, s);

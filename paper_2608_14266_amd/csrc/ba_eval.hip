@@ -892,6 +892,7 @@ void launch_pose_derivs(Problem *P, const double *poses, bool use_lm, double *g,
         return;
     }
     launch_pose_chunks(P, poses, use_lm, s, hess64);
+    ProfScope prof("k_reduce_partials", s);
     // blocks of 256 threads unless the window sums ride along, which take the
     // decision kernel's block (in the LM loop the larger ones took 1 us longer)
     const int t = cost ? DECIDE_THREADS : 256;
