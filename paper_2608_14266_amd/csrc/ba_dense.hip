@@ -718,8 +718,8 @@ __device__ __forceinline__ int factor_diag_tile(double *__restrict__ T, double *
 //    the right-hand side rows b_r - sum_{k<=c} L_rk y_k, and P_r,r-1 =
 //    A_r,r-1 - sum_{k<=c} L_rk L_r-1,k^T.  Both tasks form L_rc themselves
 //    (the same arithmetic, so the same bits), beside their partial sums and
-//    from the raw tile (r, c) they load first; the off-diagonal task stores
-//    and publishes it once the diagonal task has read the raw tile.
+//    from the raw tile (r, c) of H; the off-diagonal task stores and publishes
+//    it.
 // The raw tiles come straight from the undamped matrix H (damped on the
 // diagonal as they are loaded, A = H + mu max(diag H, floor)) and the raw
 // right-hand side from g (b = -g): each is read once, by the task that first
@@ -749,8 +749,8 @@ static constexpr int FLOW_MAX_MATS = 128;     // walkers per launch
 static constexpr int FLOW_SPIN = 1 << 20;     // polls before a wait gives up (each about 1 us)
 
 // Flags of one matrix with T tile rows: T*T tile flags (i, k), T diagonal
-// flags, 3 T flags of the partial-sum tasks and one "abandoned" flag.
-__host__ __device__ static inline int64_t flow_flag_ints(int64_t T) { return T * T + 4 * T + 1; }
+// flags, 2 T flags of the partial-sum tasks and one "abandoned" flag.
+__host__ __device__ static inline int64_t flow_flag_ints(int64_t T) { return T * T + 3 * T + 1; }
 
 // Pointers with their address space spelled out: the task bodies below are
 // compiled out of line (each with its own register allocation), and their
@@ -765,7 +765,6 @@ struct FlowMat {
     glb_i32 *dg;   // dg[k]: diagonal block k factored; its inverse and y rows final
     glb_i32 *po;   // po[r]: partial sum of tile (r, r - 1) in place
     glb_i32 *pd;   // pd[r]: partial sums of tile (r, r) and of rows r of b in place
-    glb_i32 *ra;   // ra[r]: raw tile (r, r - 2) read by the diagonal task
     glb_i32 *ab;   // matrix abandoned
     int T;
 };
@@ -1219,7 +1218,6 @@ __device__ __noinline__ void flow_pdiag(const DenseDesc d, glb_f64 *gwork, const
     damp_diag_tile(rrr, rw);
     const int row = threadIdx.x >> 2;
     const double graw = g[R0 + std::min(row, nr - 1)];
-    flow_publish(fm.ra + r);   // the raw tile (r, c) is read
     d4 aa[2][2], ac[2][2], ta[2][2], tc[2][2];
     acc_zero(aa);
     acc_zero(ac);
@@ -1270,9 +1268,6 @@ __device__ __noinline__ void flow_poff(const DenseDesc d, glb_f64 *gwork, const 
     d4 raw[2][2], rrp[2][2];
     tile_to_acc(raw, H, n, R0, C0, nr, TB);
     tile_to_acc(rrp, H, n, R0, C1, nr, TB);
-    // L_rc goes to the tile (r, c) in place: first the diagonal task (earlier
-    // in the queue) must have read the raw tile
-    if (!flow_wait(fm.ra + r, fm.ab, gab, limit, s_val)) return;
     d4 aa[2][2], ab[2][2], ta[2][2], tb[2][2];
     acc_zero(aa);
     acc_zero(ab);
@@ -1680,7 +1675,7 @@ __global__ __launch_bounds__(256) void k_chol_flow(const DenseDesc *__restrict__
         const int T = (d.n + TB - 1) / TB;
         glb_i32 *fb = (glb_i32 *)(flags + fo[tk.m]);
         glb_i32 *fs = fb + T * T;
-        const FlowMat fm{fb, fs, fs + T, fs + 2 * T, fs + 3 * T, fs + 4 * T, T};
+        const FlowMat fm{fb, fs, fs + T, fs + 2 * T, fs + 3 * T, T};
         glb_f64 *gw = (glb_f64 *)work;
         const FlowRaw rw{(glb_f64 *)(H + h_off[tk.m]), (glb_f64 *)(g + 6LL * d.pose0), pm.mu, pm.floor_};
         glb_i32 *ga = (glb_i32 *)gab;
