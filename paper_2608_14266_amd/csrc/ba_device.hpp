@@ -591,6 +591,30 @@ __device__ __forceinline__ void store_pose_value(int j, int k, double s, double 
     }
 }
 
+// Which component of a pose's sums (g[6] + Hpp[6] + Hpt[9] + Htt[6]) entry t of
+// its row of H (t < 36, row-major) or of g (36 + i) is.
+__device__ __forceinline__ int pose_component(int t) {
+    if (t >= 36) return t - 36;
+    const int r = t / 6, c = t - 6 * r, a = min(r, c), b = max(r, c);
+    if (a < 3 && b >= 3) return 12 + 3 * a + b - 3;
+    const int o = a < 3 ? 0 : 3, i = a - o;
+    return (a < 3 ? 6 : 21) + (i == 0 ? 0 : 2 * i + 1) + (b - a);   // 00 01 02 11 12 22
+}
+
+// Pose j's derivatives from one wave that holds component k in lane 2 k: the
+// entries of H and g are gathered from the lanes and stored in rows of 288 and
+// 48 bytes.  Out of line, so that the derivative pass's loop compiles as it does
+// without this epilogue: inlined, the FP64 loop loaded a cluster's slot last and
+// waited for all its values before the voxel's row (4000 poses of 200 clusters
+// 24.9 us against 20.1; with each component stored by its own lane, in four
+// divergent branches, 27.0; the form with partial sums 19.5 and a reduction of
+// 4.6 behind it).
+__device__ __noinline__ void store_pose_row(int j, double v, int lane, double *g, double *H) {
+    const double e = __shfl(v, 2 * pose_component(min(lane, 41)), BA_WAVE);
+    if (lane < 36) H[36LL * j + lane] = e;
+    else if (lane < 42) g[6LL * j + lane - 36] = e;
+}
+
 // The same from the partial sums of the pose's chunks, in chunk order.
 __device__ __forceinline__ void reduce_pose_value(int j, int k, const int32_t *chunk_ptr, const double *partials,
                                                   double *g, double *H) {

@@ -700,10 +700,8 @@ __global__ __launch_bounds__(256) void k_pose(const ChunkDesc *__restrict__ chun
 #pragma unroll
         for (int q = 0; q < 32; q++) red[q] = (q < NPART) ? acc[q] : 0.0;
         const double v = wave_reduce_scatter32(red, lane);
-        if ((lane & 1) == 0 && (lane >> 1) < NPART) {
-            if constexpr (DIRECT) store_pose_value(ch.pose, lane >> 1, v, out.g, out.H);
-            else partials[(int64_t)wave * NPART + (lane >> 1)] = v;
-        }
+        if constexpr (DIRECT) store_pose_row(ch.pose, v, lane, out.g, out.H);
+        else if ((lane & 1) == 0 && (lane >> 1) < NPART) partials[(int64_t)wave * NPART + (lane >> 1)] = v;
     }
 }
 
