@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <vector>
 
 #include "ba.h"
@@ -112,19 +113,72 @@ __device__ __forceinline__ double dd_div_int(double hi, double lo, double n) {
 // points: 363 us; 421 us keeping 8 points a lane (5 waves per SIMD instead of
 // 6), 469 us with 16 lanes per cluster, 632 us with a gathered copy of the
 // points in between, read by both passes.
+// Clusters of more than STATS_LONG points are only listed (see k_long_stats).
 static constexpr int STATS_KEEP = 4;
+static constexpr int64_t STATS_LONG = 32768;
+
+struct PointSums {
+    double hx = 0, lx = 0, hy = 0, ly = 0, hz = 0, lz = 0;
+    __device__ __forceinline__ void add(double x, double y, double z) {
+        dd_add(hx, lx, x);
+        dd_add(hy, ly, y);
+        dd_add(hz, lz, z);
+    }
+    // the wave's centroid of n points
+    __device__ __forceinline__ void mean(double n, double (&m)[3]) {
+        wave_dd_sum(hx, lx);
+        wave_dd_sum(hy, ly);
+        wave_dd_sum(hz, lz);
+        m[0] = dd_div_int(hx, lx, n);
+        m[1] = dd_div_int(hy, ly, n);
+        m[2] = dd_div_int(hz, lz, n);
+    }
+};
+
+struct PointScatter {
+    double xx = 0, xy = 0, xz = 0, yy = 0, yz = 0, zz = 0;
+    __device__ __forceinline__ void add(const double (&m)[3], double qx, double qy, double qz) {
+        const double dx = qx - m[0], dy = qy - m[1], dz = qz - m[2];
+        xx = fma(dx, dx, xx); xy = fma(dx, dy, xy); xz = fma(dx, dz, xz);
+        yy = fma(dy, dy, yy); yz = fma(dy, dz, yz); zz = fma(dz, dz, zz);
+    }
+    // the wave's record of cluster c
+    __device__ __forceinline__ void store(int64_t c, int lane, double n, const double (&m)[3],
+                                          double *__restrict__ crec) {
+        xx = wave_sum(xx); xy = wave_sum(xy); xz = wave_sum(xz);
+        yy = wave_sum(yy); yz = wave_sum(yz); zz = wave_sum(zz);
+        if (lane != 0) return;
+        double2 *o = reinterpret_cast<double2 *>(crec + CREC * c);
+        o[0] = {n, m[0]};
+        o[1] = {m[1], m[2]};
+        o[2] = {xx, xy};
+        o[3] = {xz, yy};
+        o[4] = {yz, zz};
+    }
+};
+
 __global__ __launch_bounds__(256) void k_cluster_stats(int64_t C, const int64_t *__restrict__ starts,
                                                        const uint32_t *__restrict__ idx,
                                                        const double *__restrict__ x, const double *__restrict__ y,
                                                        const double *__restrict__ z,
                                                        const uint64_t *__restrict__ skeys, int sbits,
                                                        double *__restrict__ crec, int32_t *__restrict__ cvox,
-                                                       int32_t *__restrict__ cscan) {
+                                                       int32_t *__restrict__ cscan, int64_t c_first,
+                                                       unsigned long long *__restrict__ n_long,
+                                                       uint32_t *__restrict__ longs) {
     int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     int lane = threadIdx.x & 63;
     if (c >= C) return;
     int64_t a = starts[c], b = starts[c + 1];
     const uint64_t key = skeys[a];
+    if (lane == 0) {
+        cvox[c] = (int32_t)(key >> sbits);
+        cscan[c] = (int32_t)(key & (((uint64_t)1 << sbits) - 1));
+    }
+    if (b - a > STATS_LONG) {
+        if (lane == 0) longs[atomicAdd(n_long, 1ull)] = (uint32_t)(c_first + c);
+        return;
+    }
     double px[STATS_KEEP], py[STATS_KEEP], pz[STATS_KEEP];
 #pragma unroll
     for (int k = 0; k < STATS_KEEP; k++) {
@@ -136,49 +190,72 @@ __global__ __launch_bounds__(256) void k_cluster_stats(int64_t C, const int64_t 
             pz[k] = z[j];
         }
     }
-    double hx = 0, lx = 0, hy = 0, ly = 0, hz = 0, lz = 0;
+    PointSums sum;
 #pragma unroll
     for (int k = 0; k < STATS_KEEP; k++)
-        if (a + 64 * k + lane < b) {
-            dd_add(hx, lx, px[k]);
-            dd_add(hy, ly, py[k]);
-            dd_add(hz, lz, pz[k]);
+        if (a + 64 * k + lane < b) sum.add(px[k], py[k], pz[k]);
+    for (int64_t i = a + 64 * STATS_KEEP + lane; i < b; i += 64) {
+        const uint32_t j = idx[i];
+        sum.add(x[j], y[j], z[j]);
+    }
+    const double n = (double)(b - a);
+    double m[3];
+    sum.mean(n, m);
+    PointScatter sc;
+#pragma unroll
+    for (int k = 0; k < STATS_KEEP; k++)
+        if (a + 64 * k + lane < b) sc.add(m, px[k], py[k], pz[k]);
+    for (int64_t i = a + 64 * STATS_KEEP + lane; i < b; i += 64) {
+        const uint32_t j = idx[i];
+        sc.add(m, x[j], y[j], z[j]);
+    }
+    sc.store(c, lane, n, m, crec);
+}
+
+// The listed long clusters, one wave each in the same order of sums, with
+// LONG_ROWS of its rows of 64 points in flight: alone on a chip a wave is bound
+// by the two dependent loads of every row.  10M points in one cluster: a build
+// of 90 ms against 247 in the kernel above and 132 with the points gathered
+// first; in eight 12.8 against 34 and 22.
+static constexpr int LONG_ROWS = 8;
+
+template <class Take>
+__device__ __forceinline__ void long_points(int64_t a, int64_t b, int lane, const uint32_t *__restrict__ idx,
+                                            const double *__restrict__ x, const double *__restrict__ y,
+                                            const double *__restrict__ z, Take take) {
+    for (int64_t i = a + lane; i < b; i += 64 * LONG_ROWS) {
+        uint32_t j[LONG_ROWS];
+        double px[LONG_ROWS], py[LONG_ROWS], pz[LONG_ROWS];
+#pragma unroll
+        for (int r = 0; r < LONG_ROWS; r++) j[r] = idx[min(i + 64 * r, b - 1)];
+#pragma unroll
+        for (int r = 0; r < LONG_ROWS; r++) {
+            px[r] = x[j[r]];
+            py[r] = y[j[r]];
+            pz[r] = z[j[r]];
         }
-    for (int64_t i = a + 64 * STATS_KEEP + lane; i < b; i += 64) {
-        const uint32_t j = idx[i];
-        dd_add(hx, lx, x[j]);
-        dd_add(hy, ly, y[j]);
-        dd_add(hz, lz, z[j]);
-    }
-    wave_dd_sum(hx, lx);
-    wave_dd_sum(hy, ly);
-    wave_dd_sum(hz, lz);
-    double n = (double)(b - a);
-    double mx = dd_div_int(hx, lx, n), my = dd_div_int(hy, ly, n), mz = dd_div_int(hz, lz, n);
-    double sxx = 0, sxy = 0, sxz = 0, syy = 0, syz = 0, szz = 0;
-    auto add = [&](double qx, double qy, double qz) {
-        double dx = qx - mx, dy = qy - my, dz = qz - mz;
-        sxx = fma(dx, dx, sxx); sxy = fma(dx, dy, sxy); sxz = fma(dx, dz, sxz);
-        syy = fma(dy, dy, syy); syz = fma(dy, dz, syz); szz = fma(dz, dz, szz);
-    };
 #pragma unroll
-    for (int k = 0; k < STATS_KEEP; k++)
-        if (a + 64 * k + lane < b) add(px[k], py[k], pz[k]);
-    for (int64_t i = a + 64 * STATS_KEEP + lane; i < b; i += 64) {
-        const uint32_t j = idx[i];
-        add(x[j], y[j], z[j]);
+        for (int r = 0; r < LONG_ROWS; r++)
+            if (i + 64 * r < b) take(px[r], py[r], pz[r]);
     }
-    sxx = wave_sum(sxx); sxy = wave_sum(sxy); sxz = wave_sum(sxz);
-    syy = wave_sum(syy); syz = wave_sum(syz); szz = wave_sum(szz);
-    if (lane == 0) {
-        double2 *o = reinterpret_cast<double2 *>(crec + CREC * c);
-        o[0] = {n, mx};
-        o[1] = {my, mz};
-        o[2] = {sxx, sxy};
-        o[3] = {sxz, syy};
-        o[4] = {syz, szz};
-        cvox[c] = (int32_t)(key >> sbits);
-        cscan[c] = (int32_t)(key & (((uint64_t)1 << sbits) - 1));
+}
+
+__global__ __launch_bounds__(64) void k_long_stats(int64_t n_long, const uint32_t *__restrict__ longs,
+                                                   const int64_t *__restrict__ starts,
+                                                   const uint32_t *__restrict__ idx, const double *__restrict__ x,
+                                                   const double *__restrict__ y, const double *__restrict__ z,
+                                                   double *__restrict__ crec) {
+    const int lane = threadIdx.x;
+    for (int64_t e = blockIdx.x; e < n_long; e += gridDim.x) {
+        const int64_t c = longs[e], a = starts[c], b = starts[c + 1];
+        PointSums sum;
+        long_points(a, b, lane, idx, x, y, z, [&](double qx, double qy, double qz) { sum.add(qx, qy, qz); });
+        const double n = (double)(b - a);
+        double m[3];
+        sum.mean(n, m);
+        PointScatter sc;
+        long_points(a, b, lane, idx, x, y, z, [&](double qx, double qy, double qz) { sc.add(m, qx, qy, qz); });
+        sc.store(c, lane, n, m, crec);
     }
 }
 
@@ -529,6 +606,14 @@ static ba_status read_count(int64_t *dst, const int64_t *src, hipStream_t s) {
     return BA_OK;
 }
 
+// What a build reads back first, in one allocation cleared by one fill: error
+// flags and the order's two, a count of the caller's and, right behind it, the
+// count of a list of runs.
+struct BuildHead {
+    int32_t err, order[2], pad;
+    int64_t pending, total;
+};
+
 static int bit_length(uint64_t v) {
     int b = 0;
     while (v) { b++; v >>= 1; }
@@ -778,8 +863,13 @@ __global__ void k_pose_starts(int64_t C, int32_t N, const uint64_t *__restrict__
     start[j] = lo;
 }
 
+// pending: what the caller's kernels have counted since its last look (device,
+// beside bw.total); seen(count) is called where the plan first waits for the
+// device, ahead of its kernels that read the centred clusters.
+using Seen = std::function<ba_status(int64_t)>;
+
 static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, SortBuf &bw, DevArena &keep,
-                           hipStream_t s) {
+                           const int64_t *pending, const Seen &seen, hipStream_t s) {
     const int64_t C = P->n_clusters;
     const int32_t N = P->n_poses;
     const int32_t W = P->n_windows;
@@ -796,10 +886,12 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     std::memcpy(P->h_win_pose_ptr, win_pose_ptr.data(), sizeof(int32_t) * (W + 1));
 
     // voxels
-    int64_t V64 = 0;
+    int64_t first[2] = {0, 0};   // pending, voxels
     BA_HIP(segment_count(P->c_vox, C, 0, bw.total, bw.ws, s));
-    BA_TRY(read_count(&V64, bw.total, s));
-    const int32_t V = (int32_t)V64;
+    BA_HIP(hipMemcpyAsync(first, pending, sizeof(first), hipMemcpyDeviceToHost, s));
+    BA_HIP(hipStreamSynchronize(s));
+    BA_TRY(seen(first[0]));
+    const int32_t V = (int32_t)first[1];
     P->n_vox = V;
     int64_t *vstart;
     int32_t *d_chk;
@@ -997,7 +1089,7 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
 }
 
 static ba_status finish_build(Problem *P, DevArena &keep, const ba_build_options *opt, SortBuf &bw,
-                              hipStream_t s) {
+                              const int64_t *pending, const Seen &seen, hipStream_t s) {
     std::vector<int32_t> scan_window(P->n_poses, 0);
     int32_t W = 1;
     if (opt && opt->n_windows > 1) {
@@ -1044,7 +1136,7 @@ static ba_status finish_build(Problem *P, DevArena &keep, const ba_build_options
             return BA_E_ARG;
         }
     }
-    return make_plan(P, scan_window, bw, keep, s);
+    return make_plan(P, scan_window, bw, keep, pending, seen, s);
 }
 
 ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, Problem *P, DevArena &keep,
@@ -1062,17 +1154,18 @@ ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, P
     P->n_voxels_in = pts->n_voxels;
     P->chunk_len = (opt && opt->chunk_len > 0) ? opt->chunk_len : 256;
     DevArena tmp;
-    int32_t *err;
+    BuildHead *head;
     SortBuf b;
-    BA_TRY(tmp.alloc(&err, 3));   // error flags, then the order's two
+    BA_TRY(tmp.alloc(&head, 1));
     BA_TRY(b.alloc(tmp, n));
-    BA_HIP(hipMemsetAsync(err, 0, 3 * sizeof(int32_t), s));
+    b.total = &head->total;
+    BA_HIP(hipMemsetAsync(head, 0, sizeof(BuildHead), s));
     const int sbits = bit_length((uint64_t)(pts->n_scans - 1)), vbits = bit_length((uint64_t)(pts->n_voxels - 1));
     hipLaunchKernelGGL(k_point_keys, dim3(std::min(nblk(n), KEY_BLOCKS)), dim3(256), 0, s, n, pts->x, pts->y, pts->z, pts->scan, pts->voxel,
-                       pts->n_scans, pts->n_voxels, sbits, b.keys, err);
+                       pts->n_scans, pts->n_voxels, sbits, b.keys, &head->err);
     BA_HIP(hipGetLastError());
     int32_t flags[3] = {0, 0, 0};
-    BA_HIP(hipMemcpyAsync(flags, err, sizeof(flags), hipMemcpyDeviceToHost, s));
+    BA_HIP(hipMemcpyAsync(flags, &head->err, sizeof(flags), hipMemcpyDeviceToHost, s));
     BA_HIP(hipStreamSynchronize(s));
     if (flags[0]) {
         set_error("invalid points (flags 0x%x: 1 non-finite, 2 scan out of range, 4 voxel out of range)", flags[0]);
@@ -1084,7 +1177,9 @@ ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, P
     BA_TRY(read_count(&C, b.total, s));
     P->n_clusters = C;
     int64_t *starts;
+    uint32_t *longs;
     BA_TRY(tmp.alloc(&starts, C + 1));
+    BA_TRY(tmp.alloc(&longs, n / STATS_LONG + 1));
     BA_HIP(segment_write((const uint64_t *)b.keys, n, 0, C, starts, b.ws, s));
     BA_TRY(keep.alloc(&P->c_rec, CREC * C));
     BA_TRY(keep.alloc(&P->c_vox, C));
@@ -1092,10 +1187,17 @@ ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, P
     for (int64_t c = 0, k; c < C; c += k) {
         k = std::min(C - c, launch_items(64));
         hipLaunchKernelGGL(k_cluster_stats, dim3(nblk(k * 64)), dim3(256), 0, s, k, starts + c, b.vals, pts->x, pts->y,
-                           pts->z, b.keys, sbits, P->c_rec + CREC * c, P->c_vox + c, P->c_scan + c);
+                           pts->z, b.keys, sbits, P->c_rec + CREC * c, P->c_vox + c, P->c_scan + c, c,
+                           (unsigned long long *)&head->pending, longs);
         BA_HIP(hipGetLastError());
     }
-    BA_TRY(finish_build(P, keep, opt, b, s));
+    BA_TRY(finish_build(P, keep, opt, b, &head->pending, [&](int64_t n_long) -> ba_status {
+        if (n_long > 0)
+            hipLaunchKernelGGL(k_long_stats, dim3((unsigned)std::min<int64_t>(n_long, 1 << 20)), dim3(64), 0, s, n_long,
+                               longs, starts, b.vals, pts->x, pts->y, pts->z, P->c_rec);
+        BA_HIP(hipGetLastError());
+        return BA_OK;
+    }, s));
     tmp.drained = true;   // the plan's last step waits for the stream
     return BA_OK;
 }
@@ -1115,11 +1217,13 @@ ba_status build_from_sums(const ba_cluster_sums *cs, const ba_build_options *opt
     P->n_voxels_in = cs->n_voxels;
     P->chunk_len = (opt && opt->chunk_len > 0) ? opt->chunk_len : 256;
     DevArena tmp;
-    int32_t *err;
+    BuildHead *head;
     SortBuf b;
-    BA_TRY(tmp.alloc(&err, 3));   // error flags, then the order's two
+    BA_TRY(tmp.alloc(&head, 1));
     BA_TRY(b.alloc(tmp, n));
-    BA_HIP(hipMemsetAsync(err, 0, 3 * sizeof(int32_t), s));
+    b.total = &head->total;
+    BA_HIP(hipMemsetAsync(head, 0, sizeof(BuildHead), s));
+    int32_t *err = &head->err;
     const int sbits = bit_length((uint64_t)(cs->n_scans - 1)), vbits = bit_length((uint64_t)(cs->n_voxels - 1));
     hipLaunchKernelGGL(k_validate_sums, dim3(nblk(n)), dim3(256), 0, s, n, cs->voxel, cs->scan, cs->count, cs->sum,
                        cs->sumsq, cs->n_scans, cs->n_voxels, err);
@@ -1146,7 +1250,7 @@ ba_status build_from_sums(const ba_cluster_sums *cs, const ba_build_options *opt
     hipLaunchKernelGGL(k_center_sums, dim3(nblk(n)), dim3(256), 0, s, n, b.vals, b.keys, cs->count, cs->sum, cs->sumsq,
                        sbits, P->c_rec, P->c_vox, P->c_scan);
     BA_HIP(hipGetLastError());
-    BA_TRY(finish_build(P, keep, opt, b, s));
+    BA_TRY(finish_build(P, keep, opt, b, &head->pending, [](int64_t) { return BA_OK; }, s));
     tmp.drained = true;   // the plan's last step waits for the stream
     return BA_OK;
 }
