@@ -606,12 +606,14 @@ static ba_status read_count(int64_t *dst, const int64_t *src, hipStream_t s) {
     return BA_OK;
 }
 
-// What a build reads back first, in one allocation cleared by one fill: error
-// flags and the order's two, a count of the caller's and, right behind it, the
-// count of a list of runs.
+// What a build reads back, in one allocation cleared by one fill: error flags
+// and the order's two; then, where the plan first waits for the device, a count
+// of the caller's, the number of voxels, an error of the reference poses, and
+// what k_plan_check finds.
 struct BuildHead {
-    int32_t err, order[2], pad;
+    int32_t err, order[2], bad_poses;
     int64_t pending, total;
+    int32_t max_m, bad_voxel;
 };
 
 static int bit_length(uint64_t v) {
@@ -679,18 +681,20 @@ ba_status replan_chunks(Problem *P, int32_t chunk_len, hipStream_t s) {
 // takes 2.7 ms.)
 
 // The largest cluster count of a voxel (one atomic per block: blocks walk the
-// voxels), and the first voxel that
-// is observed from more than one window (err, or INT32_MAX).
-__global__ __launch_bounds__(256) void k_plan_check(int32_t V, const int64_t *__restrict__ vstart,
+// voxels), and the first voxel that is observed from more than one window
+// (kept as INT32_MAX less the voxel, so that zero means none).
+__global__ __launch_bounds__(256) void k_plan_check(const int64_t *__restrict__ n_vox,
+                                                    const int64_t *__restrict__ vstart,
                                                     const int32_t *__restrict__ cscan,
                                                     const int32_t *__restrict__ pose_window, int32_t W,
                                                     int32_t *__restrict__ max_m, int32_t *__restrict__ err) {
+    const int64_t V = *n_vox;
     int32_t m = 0;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += (int64_t)gridDim.x * blockDim.x) {
         const int64_t a = vstart[v], b = vstart[v + 1];
         m = max(m, (int32_t)(b - a));
         // the scans rise, and so do their windows
-        if (W > 1 && pose_window[cscan[b - 1]] != pose_window[cscan[a]]) atomicMin(err, (int32_t)v);
+        if (W > 1 && pose_window[cscan[b - 1]] != pose_window[cscan[a]]) atomicMax(err, INT32_MAX - (int32_t)v);
     }
     __shared__ int red[4];
     m = -block_min_i<4>(-m, red);
@@ -725,10 +729,19 @@ __global__ void k_plan_windows(int32_t V, const uint32_t *__restrict__ order, co
     keys[i] = (uint64_t)pose_window[keys[i]] << mbits | m;   // the key is the first scan
 }
 
-__global__ void k_run_keys(int64_t R, const int64_t *__restrict__ starts, const uint64_t *__restrict__ keys,
-                           int shift, uint64_t *__restrict__ out) {
+// First position and (window, m) of every run, behind the number of runs: the
+// host takes the first RUNS_AHEAD with their number, and the rest by itself.
+struct RunHead {
+    int64_t first;
+    uint64_t key;
+};
+static constexpr int64_t RUNS_AHEAD = 2048;
+__global__ void k_run_list(const int64_t *__restrict__ n_runs, const int64_t *__restrict__ starts,
+                           const uint64_t *__restrict__ keys, int shift, RunHead *__restrict__ out) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < R) out[r] = keys[starts[r]] >> shift;
+    const int64_t R = *n_runs;
+    if (r == 0) out[0] = RunHead{R, 0};
+    if (r < R) out[1 + r] = RunHead{starts[r], keys[starts[r]] >> shift};
 }
 
 // A run of voxels (in plan order) of one window and one cluster count m.
@@ -863,13 +876,12 @@ __global__ void k_pose_starts(int64_t C, int32_t N, const uint64_t *__restrict__
     start[j] = lo;
 }
 
-// pending: what the caller's kernels have counted since its last look (device,
-// beside bw.total); seen(count) is called where the plan first waits for the
+// seen(count) is called with head->pending where the plan first waits for the
 // device, ahead of its kernels that read the centred clusters.
 using Seen = std::function<ba_status(int64_t)>;
 
 static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, SortBuf &bw, DevArena &keep,
-                           const int64_t *pending, const Seen &seen, hipStream_t s) {
+                           BuildHead *head, const Seen &seen, hipStream_t s) {
     const int64_t C = P->n_clusters;
     const int32_t N = P->n_poses;
     const int32_t W = P->n_windows;
@@ -885,36 +897,34 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     P->h_win_pose_ptr = new int32_t[W + 1];
     std::memcpy(P->h_win_pose_ptr, win_pose_ptr.data(), sizeof(int32_t) * (W + 1));
 
-    // voxels
-    int64_t first[2] = {0, 0};   // pending, voxels
-    BA_HIP(segment_count(P->c_vox, C, 0, bw.total, bw.ws, s));
-    BA_HIP(hipMemcpyAsync(first, pending, sizeof(first), hipMemcpyDeviceToHost, s));
-    BA_HIP(hipStreamSynchronize(s));
-    BA_TRY(seen(first[0]));
-    const int32_t V = (int32_t)first[1];
-    P->n_vox = V;
+    // voxels (their number stays on the device until they have been checked)
+    const int64_t v_max = std::min<int64_t>(C, P->n_voxels_in);
     int64_t *vstart;
-    int32_t *d_chk;
-    BA_TRY(tmp.alloc(&vstart, (int64_t)V + 1));
-    BA_TRY(tmp.alloc(&d_chk, 2));
-    BA_HIP(segment_write(P->c_vox, C, 0, (int64_t)V, vstart, bw.ws, s));
-    int32_t chk[2] = {0, INT32_MAX};   // largest m, first offending voxel
-    BA_HIP(hipMemcpyAsync(d_chk, chk, sizeof(chk), hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_plan_check, dim3(std::min(nblk(V), 512u)), dim3(256), 0, s, V, vstart, P->c_scan, P->pose_window, W, d_chk,
-                       d_chk + 1);
+    BA_TRY(tmp.alloc(&vstart, v_max + 1));
+    BA_HIP(segments(P->c_vox, C, 0, bw.total, vstart, bw.ws, s));
+    hipLaunchKernelGGL(k_plan_check, dim3(std::min(nblk(v_max), 512u)), dim3(256), 0, s, bw.total, vstart, P->c_scan,
+                       P->pose_window, W, &head->max_m, &head->bad_voxel);
     BA_HIP(hipGetLastError());
-    BA_HIP(hipMemcpyAsync(chk, d_chk, sizeof(chk), hipMemcpyDeviceToHost, s));
+    BuildHead h;
+    BA_HIP(hipMemcpyAsync(&h, head, sizeof(h), hipMemcpyDeviceToHost, s));
     BA_HIP(hipStreamSynchronize(s));
-    if (chk[1] != INT32_MAX) {
+    BA_TRY(seen(h.pending));
+    if (h.bad_poses) {
+        set_error("ref_poses holds non-finite values");
+        return BA_E_ARG;
+    }
+    if (h.bad_voxel) {
         int64_t a = 0;
         int32_t id = 0;
-        BA_TRY(read_count(&a, vstart + chk[1], s));
+        BA_TRY(read_count(&a, vstart + (INT32_MAX - h.bad_voxel), s));
         BA_HIP(hipMemcpyAsync(&id, P->c_vox + a, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         BA_HIP(hipStreamSynchronize(s));
         set_error("voxel %d is observed by scans of different windows", id);
         return BA_E_ARG;
     }
-    P->max_m = chk[0];
+    const int32_t V = (int32_t)h.total;
+    P->n_vox = V;
+    P->max_m = h.max_m;
 
     // voxel order: (window, m, first observing scan, voxel id), a stable sort;
     // then its runs of one window and one m
@@ -933,26 +943,26 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
                            bw.keys);
         BA_HIP(radix_sort_pairs(bw, V, 0, mbits + wbits, false, s));
     }
-    int64_t R = 0;
-    BA_HIP(segment_count((const uint64_t *)bw.keys, (int64_t)V, shift, bw.total, bw.ws, s));
-    BA_TRY(read_count(&R, bw.total, s));
     int64_t *d_rs;
-    uint64_t *d_rk;
-    uint32_t *order;
+    RunHead *d_rl;
     PlanRun *d_runs;
-    BA_TRY(tmp.alloc(&d_rs, R + 1));
-    BA_TRY(tmp.alloc(&d_rk, R));
-    BA_TRY(tmp.alloc(&order, V));
-    BA_TRY(tmp.alloc(&d_runs, R));
-    BA_HIP(segment_write((const uint64_t *)bw.keys, (int64_t)V, shift, R, d_rs, bw.ws, s));
-    hipLaunchKernelGGL(k_run_keys, dim3(nblk(R)), dim3(256), 0, s, R, d_rs, bw.keys, shift, d_rk);
+    BA_TRY(tmp.alloc(&d_rs, (int64_t)V + 1));
+    BA_TRY(tmp.alloc(&d_rl, (int64_t)V + 1));
+    BA_HIP(segments((const uint64_t *)bw.keys, (int64_t)V, shift, bw.total, d_rs, bw.ws, s));
+    hipLaunchKernelGGL(k_run_list, dim3(nblk(V)), dim3(256), 0, s, bw.total, d_rs, bw.keys, shift, d_rl);
     BA_HIP(hipGetLastError());
-    BA_HIP(hipMemcpyAsync(order, bw.vals, sizeof(uint32_t) * V, hipMemcpyDeviceToDevice, s));
-    std::vector<int64_t> rs(R + 1);
-    std::vector<uint64_t> rk(R);
-    BA_HIP(hipMemcpyAsync(rs.data(), d_rs, sizeof(int64_t) * (R + 1), hipMemcpyDeviceToHost, s));
-    BA_HIP(hipMemcpyAsync(rk.data(), d_rk, sizeof(uint64_t) * R, hipMemcpyDeviceToHost, s));
+    std::vector<RunHead> rl(1 + std::min<int64_t>(V, RUNS_AHEAD));
+    BA_HIP(hipMemcpyAsync(rl.data(), d_rl, sizeof(RunHead) * rl.size(), hipMemcpyDeviceToHost, s));
     BA_HIP(hipStreamSynchronize(s));
+    const int64_t R = rl[0].first, ahead = (int64_t)rl.size();
+    rl.resize(R + 2);
+    if (R >= ahead) {
+        BA_HIP(hipMemcpyAsync(rl.data() + ahead, d_rl + ahead, sizeof(RunHead) * (R + 1 - ahead),
+                              hipMemcpyDeviceToHost, s));
+        BA_HIP(hipStreamSynchronize(s));
+    }
+    rl[R + 1].first = V;
+    BA_TRY(tmp.alloc(&d_runs, R));
     std::vector<PlanRun> runs(R);
     std::vector<int32_t> win_group_ptr(W + 1, 0);
     std::vector<PlanMix> mix(W);
@@ -960,10 +970,10 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     int64_t cbase = 0, ubase = 0, G = 0;
     for (int64_t r = 0; r < R; r++) {
         PlanRun &q = runs[r];
-        q.first = rs[r];
-        q.len = rs[r + 1] - rs[r];
-        q.m = (int32_t)(rk[r] & (((uint64_t)1 << mbits) - 1));
-        q.window = (int32_t)(rk[r] >> mbits);
+        q.first = rl[1 + r].first;
+        q.len = rl[2 + r].first - q.first;
+        q.m = (int32_t)(rl[1 + r].key & (((uint64_t)1 << mbits) - 1));
+        q.window = (int32_t)(rl[1 + r].key >> mbits);
         q.gbase = (int32_t)G;
         q.cbase = cbase;
         q.ubase = ubase;
@@ -1036,9 +1046,11 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
     BA_HIP(hipMemcpyAsync(d_runs, runs.data(), sizeof(PlanRun) * R, hipMemcpyHostToDevice, s));
     BA_HIP(hipMemcpyAsync(d_mix, mix.data(), sizeof(PlanMix) * W, hipMemcpyHostToDevice, s));
     BA_HIP(hipMemsetAsync(P->vstate, 0, sizeof(double) * 2 * std::max<int64_t>(NS, 1) * VSTATE, s));
-    hipLaunchKernelGGL(k_plan_groups, dim3(nblk(NS)), dim3(256), 0, s, P->n_groups, (int32_t)R, d_runs, order, vstart,
-                       P->c_vox, P->c_scan, P->win_group_ptr, P->groups, P->vblocks, P->slot_vox, slot_start,
-                       P->c_slot, bw.keys, bw.vals);
+    hipLaunchKernelGGL(k_plan_groups, dim3(nblk(NS)), dim3(256), 0, s, P->n_groups, (int32_t)R, d_runs, bw.vals,
+                       vstart, P->c_vox, P->c_scan, P->win_group_ptr, P->groups, P->vblocks, P->slot_vox, slot_start,
+                       P->c_slot, bw.keys2, bw.vals2);
+    std::swap(bw.keys, bw.keys2);
+    std::swap(bw.vals, bw.vals2);
     hipLaunchKernelGGL(k_plan_mix, dim3(nblk(n_mix)), dim3(256), 0, s, n_mix, W, d_mix, P->vblocks_mix);
     // pose-major order (scan, slot): a stable sort by scan of that list (a
     // voxel's clusters have distinct scans)
@@ -1089,7 +1101,7 @@ static ba_status make_plan(Problem *P, const std::vector<int32_t> &scan_window, 
 }
 
 static ba_status finish_build(Problem *P, DevArena &keep, const ba_build_options *opt, SortBuf &bw,
-                              const int64_t *pending, const Seen &seen, hipStream_t s) {
+                              BuildHead *head, const Seen &seen, hipStream_t s) {
     std::vector<int32_t> scan_window(P->n_poses, 0);
     int32_t W = 1;
     if (opt && opt->n_windows > 1) {
@@ -1121,22 +1133,10 @@ static ba_status finish_build(Problem *P, DevArena &keep, const ba_build_options
         const int64_t np = 12LL * P->n_poses;
         BA_TRY(keep.alloc(&P->ref_poses, np));
         BA_HIP(hipMemcpyAsync(P->ref_poses, opt->ref_poses, sizeof(double) * np, hipMemcpyDeviceToDevice, s));
-        DevArena tmp;
-        int32_t *d_err;
-        BA_TRY(tmp.alloc(&d_err, 1));
-        BA_HIP(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
-        hipLaunchKernelGGL(k_validate_poses, dim3(nblk(np)), dim3(256), 0, s, np, P->ref_poses, d_err);
+        hipLaunchKernelGGL(k_validate_poses, dim3(nblk(np)), dim3(256), 0, s, np, P->ref_poses, &head->bad_poses);
         BA_HIP(hipGetLastError());
-        int32_t herr = 0;
-        BA_HIP(hipMemcpyAsync(&herr, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        BA_HIP(hipStreamSynchronize(s));
-        tmp.drained = true;
-        if (herr) {
-            set_error("ref_poses holds non-finite values");
-            return BA_E_ARG;
-        }
     }
-    return make_plan(P, scan_window, bw, keep, pending, seen, s);
+    return make_plan(P, scan_window, bw, keep, head, seen, s);
 }
 
 ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, Problem *P, DevArena &keep,
@@ -1180,7 +1180,7 @@ ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, P
     uint32_t *longs;
     BA_TRY(tmp.alloc(&starts, C + 1));
     BA_TRY(tmp.alloc(&longs, n / STATS_LONG + 1));
-    BA_HIP(segment_write((const uint64_t *)b.keys, n, 0, C, starts, b.ws, s));
+    BA_HIP(segment_write((const uint64_t *)b.keys, n, 0, b.total, starts, b.ws, s));
     BA_TRY(keep.alloc(&P->c_rec, CREC * C));
     BA_TRY(keep.alloc(&P->c_vox, C));
     BA_TRY(keep.alloc(&P->c_scan, C));
@@ -1191,7 +1191,7 @@ ba_status build_from_points(const ba_points *pts, const ba_build_options *opt, P
                            (unsigned long long *)&head->pending, longs);
         BA_HIP(hipGetLastError());
     }
-    BA_TRY(finish_build(P, keep, opt, b, &head->pending, [&](int64_t n_long) -> ba_status {
+    BA_TRY(finish_build(P, keep, opt, b, head, [&](int64_t n_long) -> ba_status {
         if (n_long > 0)
             hipLaunchKernelGGL(k_long_stats, dim3((unsigned)std::min<int64_t>(n_long, 1 << 20)), dim3(64), 0, s, n_long,
                                longs, starts, b.vals, pts->x, pts->y, pts->z, P->c_rec);
@@ -1229,19 +1229,21 @@ ba_status build_from_sums(const ba_cluster_sums *cs, const ba_build_options *opt
                        cs->sumsq, cs->n_scans, cs->n_voxels, err);
     hipLaunchKernelGGL(k_sum_keys, dim3(std::min(nblk(n), KEY_BLOCKS)), dim3(256), 0, s, n, cs->scan, cs->voxel, sbits, b.keys, err + 1);
     BA_HIP(hipGetLastError());
-    int32_t lacks[2] = {0, 0};
-    BA_HIP(hipMemcpyAsync(lacks, err + 1, sizeof(lacks), hipMemcpyDeviceToHost, s));
+    int32_t flags[3] = {0, 0, 0};
+    BA_HIP(hipMemcpyAsync(flags, err, sizeof(flags), hipMemcpyDeviceToHost, s));
     BA_HIP(hipStreamSynchronize(s));
-    BA_HIP(sort_keys(b, n, vbits, sbits, lacks, s));
-    hipLaunchKernelGGL(k_dup_keys, dim3(nblk(n)), dim3(256), 0, s, n, b.keys, err);
+    BA_HIP(sort_keys(b, n, vbits, sbits, flags + 1, s));
+    // duplicates are known where the plan first waits, or here if the input is invalid anyway
+    hipLaunchKernelGGL(k_dup_keys, dim3(nblk(n)), dim3(256), 0, s, n, b.keys, (int32_t *)&head->pending);
     BA_HIP(hipGetLastError());
-    int32_t herr = 0;
-    BA_HIP(hipMemcpyAsync(&herr, err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    BA_HIP(hipStreamSynchronize(s));
-    if (herr) {
-        set_error("invalid clusters (flags 0x%x: 1 non-finite, 2 scan, 4 voxel, 8 count < 1, 16 duplicate pair)",
-                  herr);
+    auto refuse = [](int32_t e) {
+        set_error("invalid clusters (flags 0x%x: 1 non-finite, 2 scan, 4 voxel, 8 count < 1, 16 duplicate pair)", e);
         return BA_E_ARG;
+    };
+    if (flags[0]) {
+        int64_t dup = 0;
+        BA_TRY(read_count(&dup, &head->pending, s));
+        return refuse(flags[0] | (int32_t)dup);
     }
     P->n_clusters = n;
     BA_TRY(keep.alloc(&P->c_rec, CREC * n));
@@ -1250,7 +1252,8 @@ ba_status build_from_sums(const ba_cluster_sums *cs, const ba_build_options *opt
     hipLaunchKernelGGL(k_center_sums, dim3(nblk(n)), dim3(256), 0, s, n, b.vals, b.keys, cs->count, cs->sum, cs->sumsq,
                        sbits, P->c_rec, P->c_vox, P->c_scan);
     BA_HIP(hipGetLastError());
-    BA_TRY(finish_build(P, keep, opt, b, &head->pending, [](int64_t) { return BA_OK; }, s));
+    BA_TRY(finish_build(P, keep, opt, b, head,
+                        [&](int64_t dup) -> ba_status { return dup ? refuse((int32_t)dup) : BA_OK; }, s));
     tmp.drained = true;   // the plan's last step waits for the stream
     return BA_OK;
 }

@@ -204,8 +204,10 @@ hipError_t exclusive_scan_i64(const int64_t *in, int64_t *out, int64_t n, int64_
 template <class K>
 hipError_t segment_count(const K *keys, int64_t n, int shift, int64_t *total, void *ws, hipStream_t s);
 template <class K>
-hipError_t segment_write(const K *keys, int64_t n, int shift, int64_t n_seg, int64_t *starts, void *ws,
+hipError_t segment_write(const K *keys, int64_t n, int shift, int64_t *total, int64_t *starts, void *ws,
                          hipStream_t s);
+template <class K>
+hipError_t segments(const K *keys, int64_t n, int shift, int64_t *total, int64_t *starts, void *ws, hipStream_t s);
 size_t radix_sort_workspace_bytes(int64_t n);
 // Buffers of the radix sort (and of scans of up to cap values, in ws).
 struct SortBuf {

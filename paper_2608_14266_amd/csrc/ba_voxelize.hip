@@ -458,7 +458,7 @@ static ba_status vx_segments(DevArena &tmp, SortBuf &w, const uint64_t *keys, in
     BA_HIP(segment_count(keys, n, shift, w.total, w.ws, s));
     BA_TRY(sync_read(n_seg, w.total, sizeof(int64_t), s));
     BA_TRY(tmp.alloc(starts, *n_seg + 1));
-    BA_HIP(segment_write(keys, n, shift, *n_seg, *starts, w.ws, s));
+    BA_HIP(segment_write(keys, n, shift, w.total, *starts, w.ws, s));
     return BA_OK;
 }
 
