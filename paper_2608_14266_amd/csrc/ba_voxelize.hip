@@ -653,8 +653,11 @@ struct VxBatch {
 // and queue every piece's transfer as soon as it is filled, beside the thread
 // that queues the previous batch's device work.  The pinned memory (32 MB) and
 // the stream are kept between calls.  With that and the kept device blocks a
-// pass over 9.5M pageable points in four batches takes 9.0 ms (29 GB/s of
+// pass over 9.5M pageable points in four batches takes 8.6 ms (31 GB/s of
 // input) against 42-60 ms with batch-sized buffers allocated by each call.
+// A batch takes a thread per piece's worth of bytes, and one of less than two
+// pieces is staged by the caller: starting threads costs more than it saves
+// there (5000 points in three batches 1.3 ms, with eight threads 1.9-2.0).
 static constexpr int STAGE_THREADS = 8;
 static constexpr size_t STAGE_PIECE = (size_t)2 << 20;
 
@@ -671,15 +674,16 @@ struct HostStream {
     hipEvent_t filled[2 * STAGE_THREADS] = {};
     void *pinned = nullptr;
     size_t pinned_bytes = 0;
+    int n_threads = 1;             // that stage a batch; 1: the caller does
     std::vector<HostPiece> pieces;
     std::vector<std::thread> threads;
     hipError_t err[STAGE_THREADS] = {};
 
-    // pieces t, t + STAGE_THREADS, ... of the batch
+    // pieces t, t + n_threads, ... of the batch
     void fill(int t) {
         hipError_t e = hipSetDevice(device);
         int k = 0;
-        for (size_t i = (size_t)t; i < pieces.size() && e == hipSuccess; i += STAGE_THREADS, k ^= 1) {
+        for (size_t i = (size_t)t; i < pieces.size() && e == hipSuccess; i += n_threads, k ^= 1) {
             char *buf = (char *)pinned + STAGE_PIECE * (size_t)(2 * t + k);
             e = hipEventSynchronize(filled[2 * t + k]);   // the piece's previous transfer has finished
             if (e != hipSuccess) break;
@@ -690,19 +694,23 @@ struct HostStream {
         err[t] = e;
     }
     void start() {
-        for (int t = 0; t < STAGE_THREADS; t++) err[t] = hipSuccess;
+        for (int t = 0; t < n_threads; t++) err[t] = hipSuccess;
+        if (n_threads == 1) {
+            fill(0);
+            return;
+        }
         int t = 0;
         try {
-            threads.reserve(STAGE_THREADS);
-            for (; t < STAGE_THREADS; t++) threads.emplace_back([this, t] { fill(t); });
+            threads.reserve(n_threads);
+            for (; t < n_threads; t++) threads.emplace_back([this, t] { fill(t); });
         } catch (...) {
-            for (; t < STAGE_THREADS; t++) fill(t);   // no more threads: this one copies
+            for (; t < n_threads; t++) fill(t);   // no more threads: this one copies
         }
     }
     hipError_t join() {
         for (auto &t : threads) t.join();
         threads.clear();
-        for (int t = 0; t < STAGE_THREADS; t++)
+        for (int t = 0; t < n_threads; t++)
             if (err[t] != hipSuccess) return err[t];
         return hipSuccess;
     }
@@ -743,8 +751,10 @@ static ba_status voxelize_host(const double *hx, const double *hy, const double 
         BA_HIP(hipEventCreateWithFlags(&hs.consumed[k], hipEventDisableTiming));
     }
     if (!pinned_in) {
-        BA_HIP(pinned_alloc(&hs.pinned, 2 * STAGE_THREADS * STAGE_PIECE, &hs.pinned_bytes));
-        for (hipEvent_t &e : hs.filled) BA_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        hs.n_threads = (int)std::max<size_t>(1, std::min<size_t>(STAGE_THREADS, (size_t)B * 28 / STAGE_PIECE));
+        BA_HIP(pinned_alloc(&hs.pinned, 2 * hs.n_threads * STAGE_PIECE, &hs.pinned_bytes));
+        for (int k = 0; k < 2 * hs.n_threads; k++)
+            BA_HIP(hipEventCreateWithFlags(&hs.filled[k], hipEventDisableTiming));
     }
     double *dx[2], *dy[2], *dz[2];
     int32_t *ds[2], *cell;
