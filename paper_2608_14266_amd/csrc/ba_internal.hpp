@@ -41,7 +41,7 @@ struct GroupDesc {
 // pose-major one).  A wave reads 64 consecutive clusters, so one trip touches
 // one contiguous run of BYTES instead of eleven arrays far apart, and the
 // loads share one address.  Measured with the two passes' loads made
-// unconditional (see k_pose), against eleven arrays: one evaluation of 6.4M
+// unconditional (see k_pose), against eleven arrays: one evaluation of 4.0M
 // clusters in FP32 184.6 -> 180.3 us, ten LM iterations of 256 windows (37M
 // clusters, FP32) 13.96 -> 13.75 ms, an evaluation of 785k clusters in FP64
 // 59.5 -> 58.8 us.

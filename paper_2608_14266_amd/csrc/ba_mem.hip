@@ -4,12 +4,14 @@
 // them back before it returns.  On this driver that costs more than the work:
 // a release of 128 MB or more takes 0.25-0.3 ms when it goes well, and after
 // some tens of rounds of such calls single allocations and releases stall for
-// 50 ms to 2 s.  Measured with blocks kept: a build from 29.6M points 47 ->
-// 5.5 ms, the voxelization of 117M points 97-140 -> 18.4 ms a call.  So
+// 50 ms to 2 s.  Measured when blocks were first kept, with nothing else
+// changed: a build from 29.6M points 26-48 (by how long the process had run)
+// -> 5.5 ms, the voxelization of 117M points 97-140 -> 18.4 ms a call.  So
 // released blocks stay in a list per device and later calls take them again.
 // What is kept is bounded (POOL_SHARE of the device's memory, POOL_PINNED of
-// host memory), and it is given back when the device runs low, when an
-// allocation fails, when the bound is passed (oldest blocks first) and by
+// host memory), and it is given back when the device runs low (looked at when
+// something is released), when an allocation of the library finds too little
+// memory, when the bound is passed (oldest blocks first) and by
 // ba_release_cached_memory.
 //
 // A block enters the list only after all device work that may use it has
